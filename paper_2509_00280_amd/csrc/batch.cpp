@@ -384,7 +384,7 @@ spt_status BatchEngine::rebuild() {
         for (Member *m : act)
             if (m->t->nmodes > n) {
                 rmax = std::max(rmax, m->R);
-                vec4 = vec4 && (m->R % 4 == 0);
+                vec4 = vec4 && m->R >= 4;
             }
         const int ld = rmax;
         const int rw = rmax > 0 ? apply_rows_per_launch_block(rmax) : 1;
@@ -679,7 +679,7 @@ spt_status spt_mttkrp_batched(const spt_tensor *ts, int count, const float *cons
         rmax = std::max(rmax, ranks[b]);
         nmax = std::max(nmax, t->nmodes);
         nmin = std::min(nmin, t->nmodes);
-        vec4 = vec4 && ranks[b] % 4 == 0;
+        vec4 = vec4 && ranks[b] >= 4;
     }
     if (tv.empty()) return SPT_OK;
     if (!seg_batch_fits(nmax, tile)) return fail(SPT_E_INVALID_ARG, "mttkrp_batched: too many modes");

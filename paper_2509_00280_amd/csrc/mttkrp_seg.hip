@@ -220,8 +220,7 @@ __device__ __forceinline__ void seg_stage(const MttkrpArgs &a, int64_t tile, con
 // Walk the staged tile: every piece (nonzeros [p0, p1) of the row-grouped
 // tile, one output row) becomes one record of ld floats (columns R..ld-1
 // zero) at the position the piece source gives, with row row_base + its row.
-// EXACT: the lane groups cover exactly R columns (no column mask).
-// With at most 4 modes every nonzero slot of an unrolled step reads all its
+// With at most 5 modes every nonzero slot of an unrolled step reads all its
 // coordinates from LDS first, then issues every factor-row gather, then waits
 // once; with more modes the gathers go mode by mode.  NFIX > 0: the tensor has
 // exactly NFIX modes (no run-time mode test between the gathers, which would
@@ -231,17 +230,19 @@ __device__ __forceinline__ void seg_stage(const MttkrpArgs &a, int64_t tile, con
 // the LDS row cache (at most lim, the offset of the cache's last row) or, with
 // kDictMiss set, a global row.  Every lane reads its step's rows from LDS
 // first, then the lanes whose row is global load it over the LDS value.
-template <int NT, int T, int G, int VEC, int NB, int NMAX, int NFIX, bool EXACT, class Pieces, bool DICT = false>
+template <int NT, int T, int VEC, int NMAX, int NFIX, class Pieces, bool DICT = false>
 __device__ __forceinline__ void seg_walk(const MttkrpArgs &a, const uint32_t *__restrict__ crdg,
                                          const float *__restrict__ valg, int npieces, const Pieces &pieces,
                                          uint64_t *__restrict__ rec_row, float *__restrict__ rec_val, int ld,
                                          int64_t row_base, const char *__restrict__ ldsb = nullptr, uint32_t lim = 0) {
     constexpr int UB = DICT ? kUnrollDict : kUnroll;
     constexpr int NO = NMAX - 1;  // non-output modes at most
-    const int j = threadIdx.x % G;
     static_assert(NFIX == 0 || NFIX == NMAX, "a fixed mode count is the maximum");
     static_assert(!DICT || NMAX <= 4, "the row cache serves at most 3 non-output modes");
     const int R = a.rank, mode = a.mode, no = NFIX ? NFIX - 1 : a.nmodes - 1;
+    const LaneGroup lg = lane_group<VEC>(R);
+    if (npieces <= 0 || !lg.on) return;
+    const int c = lg.col;
     // factor of the o-th non-output mode as a row buffer
     spt_i4 fb[NO];
 #pragma unroll
@@ -249,11 +250,10 @@ __device__ __forceinline__ void seg_walk(const MttkrpArgs &a, const uint32_t *__
         const int k = o + (o >= mode);
         fb[o] = o < no ? row_rsrc(a.f[k], R, a.frows[k]) : row_rsrc(nullptr, R, 0u);
     }
-    constexpr int NG = NT / G;
-    if (npieces <= 0) return;
+    const int NG = NT / 64 * lg.per_wave;
     // pieces are dealt in snake order (round r: group g, then NG - 1 - g),
     // which balances the groups when the plan lists the pieces longest first
-    const int g = threadIdx.x / G;
+    const int g = lg.g;
     const int nr = (npieces + NG - 1) / NG;
     auto kof = [&](int r) { return min(r * NG + ((r & 1) ? NG - 1 - g : g), npieces - 1); };
     typename Pieces::Raw cur = pieces.fetch(kof(0));
@@ -267,11 +267,9 @@ __device__ __forceinline__ void seg_walk(const MttkrpArgs &a, const uint32_t *__
         const bool live = k < npieces && pieces.decode(k, cur, p0, p1, prow, pos);
         cur = nxt;
         if (!live) continue;
-        float acc[NB][VEC];
+        float acc[VEC];
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[b][v] = 0.f;
+        for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
         for (int q = p0; q < p1; q += UB) {
             int pp[UB];
             float x[UB];
@@ -282,21 +280,19 @@ __device__ __forceinline__ void seg_walk(const MttkrpArgs &a, const uint32_t *__
                 const float v = valg[pp[u]];
                 x[u] = ok ? v : 0.f;
             }
-            float p[UB][NB][VEC];
+            float p[UB][VEC];
 #pragma unroll
             for (int u = 0; u < UB; ++u)
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) p[u][b][v] = x[u];
-            if constexpr (NO <= 3) {
+                for (int v = 0; v < VEC; ++v) p[u][v] = x[u];
+            if constexpr (NO <= 4) {
                 uint32_t row[NO][UB];
 #pragma unroll
                 for (int o = 0; o < NO; ++o)
                     if (o < no)
 #pragma unroll
                         for (int u = 0; u < UB; ++u) row[o][u] = crdg[o * T + pp[u]];
-                float xv[NO][UB][NB][VEC];
+                float xv[NO][UB][VEC];
                 if constexpr (DICT) {
                     // every index read of the step is issued before anything
                     // waits for one (the scheduler may not hoist a use between them)
@@ -312,63 +308,26 @@ __device__ __forceinline__ void seg_walk(const MttkrpArgs &a, const uint32_t *__
 #pragma unroll
                         for (int u = 0; u < UB; ++u) {
                             const uint32_t off = min(row[o][u], lim);
-#pragma unroll
-                            for (int b = 0; b < NB; ++b) {
-                                const int c = (b * G + j) * VEC;
-                                if (o < no && (EXACT || c < R)) {
-                                    const float *cp = reinterpret_cast<const float *>(ldsb + off) + c;
-                                    if constexpr (VEC == 4) {
-                                        const float4 t4 = *reinterpret_cast<const float4 *>(cp);
-                                        xv[o][u][b][0] = t4.x;
-                                        xv[o][u][b][1] = t4.y;
-                                        xv[o][u][b][2] = t4.z;
-                                        xv[o][u][b][3] = t4.w;
-                                    } else {
-#pragma unroll
-                                        for (int v = 0; v < VEC; ++v) xv[o][u][b][v] = cp[v];
-                                    }
-                                }
+                            if (o < no) {
+                                const float *cp = reinterpret_cast<const float *>(ldsb + off) + lg.j * VEC;
+                                load_vec<VEC>(cp, xv[o][u]);
                             }
                         }
                     }
 #pragma unroll
-                    for (int o = 0; o < NO; ++o) {
-                        if (o < no) {
+                    for (int o = 0; o < NO; ++o)
+                        if (o < no)
 #pragma unroll
                             for (int u = 0; u < UB; ++u) {
                                 const uint32_t rv = row[o][u];
-#pragma unroll
-                                for (int b = 0; b < NB; ++b) {
-                                    const int c = (b * G + j) * VEC;
-                                    if (EXACT || c < R) {
-                                        if (rv & kDictMiss) load_row_vec<VEC>(fb[o], rv & ~kDictMiss, c, xv[o][u][b]);
-                                    } else {
-#pragma unroll
-                                        for (int v = 0; v < VEC; ++v) xv[o][u][b][v] = 0.f;
-                                    }
-                                }
+                                if (rv & kDictMiss) load_row_vec<VEC>(fb[o], rv & ~kDictMiss, c, xv[o][u]);
                             }
-                        }
-                    }
                 } else {
 #pragma unroll
-                    for (int o = 0; o < NO; ++o) {
-                        if (o < no) {
+                    for (int o = 0; o < NO; ++o)
+                        if (o < no)
 #pragma unroll
-                            for (int u = 0; u < UB; ++u) {
-#pragma unroll
-                                for (int b = 0; b < NB; ++b) {
-                                    const int c = (b * G + j) * VEC;
-                                    if (EXACT || c < R) {
-                                        load_row_vec<VEC>(fb[o], row[o][u], c, xv[o][u][b]);
-                                    } else {
-#pragma unroll
-                                        for (int v = 0; v < VEC; ++v) xv[o][u][b][v] = 0.f;
-                                    }
-                                }
-                            }
-                        }
-                    }
+                            for (int u = 0; u < UB; ++u) load_row_vec<VEC>(fb[o], row[o][u], c, xv[o][u]);
                 }
 #pragma unroll
                 for (int o = 0; o < NO; ++o)
@@ -376,59 +335,30 @@ __device__ __forceinline__ void seg_walk(const MttkrpArgs &a, const uint32_t *__
 #pragma unroll
                         for (int u = 0; u < UB; ++u)
 #pragma unroll
-                            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                                for (int v = 0; v < VEC; ++v) p[u][b][v] *= xv[o][u][b][v];
+                            for (int v = 0; v < VEC; ++v) p[u][v] *= xv[o][u][v];
             } else {
 #pragma unroll
                 for (int o = 0; o < NO; ++o) {
                     if (o < no) {
-                        float xv[UB][NB][VEC];
+                        float xv[UB][VEC];
 #pragma unroll
-                        for (int u = 0; u < UB; ++u) {
-                            const uint32_t rw = crdg[o * T + pp[u]];
-#pragma unroll
-                            for (int b = 0; b < NB; ++b) {
-                                const int c = (b * G + j) * VEC;
-                                if (EXACT || c < R) {
-                                    load_row_vec<VEC>(fb[o], rw, c, xv[u][b]);
-                                } else {
-#pragma unroll
-                                    for (int v = 0; v < VEC; ++v) xv[u][b][v] = 0.f;
-                                }
-                            }
-                        }
+                        for (int u = 0; u < UB; ++u) load_row_vec<VEC>(fb[o], crdg[o * T + pp[u]], c, xv[u]);
 #pragma unroll
                         for (int u = 0; u < UB; ++u)
 #pragma unroll
-                            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                                for (int v = 0; v < VEC; ++v) p[u][b][v] *= xv[u][b][v];
+                            for (int v = 0; v < VEC; ++v) p[u][v] *= xv[u][v];
                     }
                 }
             }
 #pragma unroll
             for (int u = 0; u < UB; ++u)
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[b][v] += p[u][b][v];
+                for (int v = 0; v < VEC; ++v) acc[v] += p[u][v];
         }
-        if (j == 0) rec_row[pos] = (uint64_t)(row_base + prow);
+        if (lg.j == 0) rec_row[pos] = (uint64_t)(row_base + prow);
         float *o = rec_val + pos * ld;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int c = (b * G + j) * VEC;
-            if (EXACT || c < ld) {
-                if constexpr (VEC == 4) {
-                    // columns at or beyond R were loaded as zero factors, so acc is 0 there
-                    *reinterpret_cast<float4 *>(o + c) = make_float4(acc[b][0], acc[b][1], acc[b][2], acc[b][3]);
-                } else {
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) o[c + v] = acc[b][v];
-                }
-            }
-        }
+        store_vec<VEC>(o + c, acc);
+        for (int z = R + lg.j; z < ld; z += lg.G) o[z] = 0.f;
     }
 }
 
@@ -476,7 +406,7 @@ struct PackedPieces {
 // PACKED: the pieces come from a.pl_piece (one tensor, records from 0);
 // otherwise from a.pl_desc / pl_row / pl_dest with records from rec_base
 // (a batched member).
-template <int NT, int T, int G, int VEC, int NB, int NMAX, int NFIX, bool EXACT, bool PACKED>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool PACKED>
 __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, char *lds, uint64_t *__restrict__ rec_row,
                                           float *__restrict__ rec_val, int ld, int64_t rec_base, int64_t row_base) {
     constexpr int PER = T / NT;  // nonzeros staged per thread
@@ -544,21 +474,21 @@ __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, cha
         if (tid + u * NT < cnt) valg[ps[u]] = v[u];
     __syncthreads();
     if constexpr (PACKED)
-        seg_walk<NT, T, G, VEC, NB, NMAX, NFIX, EXACT>(
+        seg_walk<NT, T, VEC, NMAX, NFIX>(
             a, crdg, valg, npieces, PackedPieces<T>{reinterpret_cast<const spt_u4 *>(a.pl_piece), k0, a.rec_cap},
             rec_row, rec_val, ld, row_base);
     else
-        seg_walk<NT, T, G, VEC, NB, NMAX, NFIX, EXACT>(
+        seg_walk<NT, T, VEC, NMAX, NFIX>(
             a, crdg, valg, npieces, PlanPieces<T>{a.pl_desc, a.pl_row, a.pl_dest, k0, a.rec_cap, rec_base}, rec_row,
             rec_val, ld, row_base);
 }
 
-template <int NT, int T, int G, int VEC, int NB, int NMAX, int NFIX, bool EXACT>
+template <int NT, int T, int VEC, int NMAX, int NFIX>
 __global__ __launch_bounds__(NT) void k_mttkrp_segp(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segp_tile<NT, T, G, VEC, NB, NMAX, NFIX, EXACT, true>(a, tile, lds, a.rec_row, a.rec_val, a.rank, 0, 0);
+    segp_tile<NT, T, VEC, NMAX, NFIX, true>(a, tile, lds, a.rec_row, a.rec_val, a.rank, 0, 0);
 }
 
 // ---------------------------------------------------------------- row cache
@@ -658,10 +588,14 @@ __global__ __launch_bounds__(NT) void k_emit_dict(MttkrpArgs a, const int64_t *_
     }
 }
 
+// Floats of one cached row: a slot for every lane of a group (see LaneGroup),
+// so that each lane reads its columns as one aligned vector at any rank.
+__host__ __device__ inline int cached_row_floats(int R) { return R < 4 ? R : (R + 3) & ~3; }
+
 // LDS of the row-cached kernel: crdg[nm - 1][T], valg[T], then the cache of
-// cap rows of R floats per non-output mode.
+// cap rows per non-output mode.
 __host__ __device__ inline size_t segd_lds_bytes(int T, int nmodes, int cap, int R) {
-    return segp_lds_bytes(T, nmodes) + (size_t)(nmodes - 1) * cap * R * 4;
+    return segp_lds_bytes(T, nmodes) + (size_t)(nmodes - 1) * cap * cached_row_floats(R) * 4;
 }
 
 // Row-cached form of segp_tile (tiles of kDictTile nonzeros).  Staging reads
@@ -670,7 +604,7 @@ __host__ __device__ inline size_t segd_lds_bytes(int T, int nmodes, int cap, int
 // tile dictionary are copied to LDS; a nonzero whose index is below cap
 // reads its factor row there, any other reads it from HBM/L2 by its global
 // row.
-template <int NT, int T, int G, int VEC, int NB, int NMAX, int NFIX, bool EXACT>
+template <int NT, int T, int VEC, int NMAX, int NFIX>
 __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, char *lds) {
     constexpr int PER = T / NT;
     constexpr int NO = NMAX - 1;
@@ -751,32 +685,18 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, cha
             dlast[o] = (int)max<int64_t>(d - 1, 0);
         }
     }
-    if ((R & 3) == 0) {
-        const int r4 = R >> 2;
+    const int RS = cached_row_floats(R), slots = RS / VEC;
 #pragma unroll
-        for (int o = 0; o < NO; ++o) {
-            if (o < no) {
-                const float *f = a.f[o + (o >= mode)];
-                const uint32_t *dr = a.d_row[o] + dbase[o];
-                float *cb = cache + (size_t)o * cap * R;
-                for (int i = tid; i < dn[o] * r4; i += NT) {
-                    const int sidx = i / r4, c = i - sidx * r4;
-                    const float4 x = *reinterpret_cast<const float4 *>(f + (size_t)dr[sidx] * R + 4 * c);
-                    *reinterpret_cast<float4 *>(cb + (size_t)sidx * R + 4 * c) = x;
-                }
-            }
-        }
-    } else {
-#pragma unroll
-        for (int o = 0; o < NO; ++o) {
-            if (o < no) {
-                const float *f = a.f[o + (o >= mode)];
-                const uint32_t *dr = a.d_row[o] + dbase[o];
-                float *cb = cache + (size_t)o * cap * R;
-                for (int i = tid; i < dn[o] * R; i += NT) {
-                    const int sidx = i / R, c = i - sidx * R;
-                    cb[(size_t)sidx * R + c] = f[(size_t)dr[sidx] * R + c];
-                }
+    for (int o = 0; o < NO; ++o) {
+        if (o < no) {
+            const float *f = a.f[o + (o >= mode)];
+            const uint32_t *dr = a.d_row[o] + dbase[o];
+            float *cb = cache + (size_t)o * cap * RS;
+            for (int i = tid; i < dn[o] * slots; i += NT) {
+                const int sidx = i / slots, jj = i - sidx * slots;
+                float x[VEC];
+                load_vec_any<VEC>(f + (size_t)dr[sidx] * R + (VEC == 4 ? min(4 * jj, R - 4) : jj), x);
+                store_vec<VEC>(cb + (size_t)sidx * RS + VEC * jj, x);
             }
         }
     }
@@ -801,7 +721,7 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, cha
             for (int o = 0; o < NO; ++o) {
                 if (o < no) {
                     const uint32_t si = min(sl[o][u], (uint32_t)dlast[o]);
-                    crdg[o * T + q[u]] = (int)si < dn[o] ? cache_off + ((uint32_t)(o * cap) + si) * (uint32_t)(R * 4)
+                    crdg[o * T + q[u]] = (int)si < dn[o] ? cache_off + ((uint32_t)(o * cap) + si) * (uint32_t)(RS * 4)
                                                          : (grow[o][u] | kDictMiss);
                 }
             }
@@ -809,18 +729,18 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, cha
     }
     __syncthreads();
     // the largest entry a cached row can have: the last slot of the last mode
-    const uint32_t lim = cache_off + ((uint32_t)(no * cap) - 1u) * (uint32_t)(R * 4);
-    seg_walk<NT, T, G, VEC, NB, NMAX, NFIX, EXACT, PackedPieces<T>, true>(
+    const uint32_t lim = cache_off + ((uint32_t)(no * cap) - 1u) * (uint32_t)(RS * 4);
+    seg_walk<NT, T, VEC, NMAX, NFIX, PackedPieces<T>, true>(
         a, crdg, valg, (int)(k1 - k0), PackedPieces<T>{reinterpret_cast<const spt_u4 *>(a.pl_piece), k0, a.rec_cap},
         a.rec_row, a.rec_val, a.rank, 0, lds, lim);
 }
 
-template <int NT, int T, int G, int VEC, int NB, int NMAX, int NFIX, bool EXACT>
+template <int NT, int T, int VEC, int NMAX, int NFIX>
 __global__ __launch_bounds__(NT) void k_mttkrp_segd(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segd_tile<NT, T, G, VEC, NB, NMAX, NFIX, EXACT>(a, tile, lds);
+    segd_tile<NT, T, VEC, NMAX, NFIX>(a, tile, lds);
 }
 
 // Batched: tile `it` of the whole batch belongs to the last item whose
@@ -843,7 +763,7 @@ __device__ __forceinline__ int seg_item_of(const SegItem *__restrict__ items, in
 // *next_tile, zero at launch, until the counter passes total_tiles.  A
 // workgroup's tiles only increase, so it finds each tile's tensor by moving
 // forward from the last one.
-template <int NT, int G, int VEC, int NB, int NMAX, int NFIX>
+template <int NT, int VEC, int NMAX, int NFIX>
 __global__ __launch_bounds__(NT) void k_mttkrp_segp_batched(const SegItem *__restrict__ items, int count,
                                                             int64_t total_tiles, uint64_t *__restrict__ rec_row,
                                                             float *__restrict__ rec_val, int ld,
@@ -859,8 +779,8 @@ __global__ __launch_bounds__(NT) void k_mttkrp_segp_batched(const SegItem *__res
         if (it >= total_tiles) break;
         while (b + 1 < count && items[b + 1].first_tile <= it) ++b;
         const SegItem &item = items[b];
-        segp_tile<NT, 4 * NT, G, VEC, NB, NMAX, NFIX, false, false>(item.a, it - item.first_tile, lds, rec_row, rec_val,
-                                                                    ld, item.rec_base, item.row_base);
+        segp_tile<NT, 4 * NT, VEC, NMAX, NFIX, false>(item.a, it - item.first_tile, lds, rec_row, rec_val, ld,
+                                                      item.rec_base, item.row_base);
     }
 }
 
@@ -1056,49 +976,26 @@ __global__ __launch_bounds__(NT) void k_count_pieces_batched(const SegItem *__re
     if (threadIdx.x == 0) out[it] = c;
 }
 
-template <int NT, int T, int NMAX, int NFIX, int G, int VEC, int NB>
+template <int NT, int T, int NMAX, int NFIX, int VEC>
 spt_status launch_seg_k(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
     if constexpr (T == kDictTile && NMAX <= 4) {
         if (a.d_cap > 0) {
             const size_t lds = segd_lds_bytes(T, a.nmodes, a.d_cap, a.rank);
-            if (a.rank == G * VEC * NB)
-                hipLaunchKernelGGL((k_mttkrp_segd<NT, T, G, VEC, NB, NMAX, NFIX, true>), dim3((unsigned)ntiles),
-                                   dim3(NT), lds, s, a, ntiles);
-            else
-                hipLaunchKernelGGL((k_mttkrp_segd<NT, T, G, VEC, NB, NMAX, NFIX, false>), dim3((unsigned)ntiles),
-                                   dim3(NT), lds, s, a, ntiles);
+            hipLaunchKernelGGL((k_mttkrp_segd<NT, T, VEC, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a,
+                               ntiles);
             SPT_HIP(hipGetLastError());
             return SPT_OK;
         }
     }
     const size_t lds = segp_lds_bytes(T, a.nmodes);
-    if (a.rank == G * VEC * NB)
-        hipLaunchKernelGGL((k_mttkrp_segp<NT, T, G, VEC, NB, NMAX, NFIX, true>), dim3((unsigned)ntiles), dim3(NT), lds, s,
-                           a, ntiles);
-    else
-        hipLaunchKernelGGL((k_mttkrp_segp<NT, T, G, VEC, NB, NMAX, NFIX, false>), dim3((unsigned)ntiles), dim3(NT), lds,
-                           s, a, ntiles);
+    hipLaunchKernelGGL((k_mttkrp_segp<NT, T, VEC, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, ntiles);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
 template <int NT, int T, int NMAX, int NFIX>
 spt_status launch_seg_nt(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
-    const int R = a.rank;
-    if ((R & 3) == 0) {
-        const int r4 = R >> 2;
-        if (r4 <= 1) return launch_seg_k<NT, T, NMAX, NFIX, 1, 4, 1>(a, ntiles, s);
-        if (r4 <= 2) return launch_seg_k<NT, T, NMAX, NFIX, 2, 4, 1>(a, ntiles, s);
-        if (r4 <= 4) return launch_seg_k<NT, T, NMAX, NFIX, 4, 4, 1>(a, ntiles, s);
-        if (r4 <= 8) return launch_seg_k<NT, T, NMAX, NFIX, 8, 4, 1>(a, ntiles, s);
-        if (r4 <= 16) return launch_seg_k<NT, T, NMAX, NFIX, 16, 4, 1>(a, ntiles, s);
-        if (r4 <= 32) return launch_seg_k<NT, T, NMAX, NFIX, 32, 4, 1>(a, ntiles, s);
-        return launch_seg_k<NT, T, NMAX, NFIX, 64, 4, 1>(a, ntiles, s);
-    }
-    if (R <= 64) return launch_seg_k<NT, T, NMAX, NFIX, 64, 1, 1>(a, ntiles, s);
-    if (R <= 128) return launch_seg_k<NT, T, NMAX, NFIX, 64, 1, 2>(a, ntiles, s);
-    if (R <= 192) return launch_seg_k<NT, T, NMAX, NFIX, 64, 1, 3>(a, ntiles, s);
-    return launch_seg_k<NT, T, NMAX, NFIX, 64, 1, 4>(a, ntiles, s);
+    return a.rank >= 4 ? launch_seg_k<NT, T, NMAX, NFIX, 4>(a, ntiles, s) : launch_seg_k<NT, T, NMAX, NFIX, 1>(a, ntiles, s);
 }
 
 template <int NT>
@@ -1162,12 +1059,13 @@ spt_status launch_count_pieces(const MttkrpArgs &a, int64_t *counts, hipStream_t
 }
 
 namespace {
-// 3 and 4 modes get a kernel with the mode count fixed; others the general one
+// 3, 4 and 5 modes get a kernel with the mode count fixed; others the general one
 template <int NT, int T>
 spt_status launch_seg_tile(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
     const int nm = a.nmodes;
     if (nm == 3) return launch_seg_nt<NT, T, 3, 3>(a, ntiles, s);
     if (nm == 4) return launch_seg_nt<NT, T, 4, 4>(a, ntiles, s);
+    if (nm == 5) return launch_seg_nt<NT, T, 5, 5>(a, ntiles, s);
     return nm < 3 ? launch_seg_nt<NT, T, 3, 0>(a, ntiles, s) : launch_seg_nt<NT, T, 8, 0>(a, ntiles, s);
 }
 }  // namespace
@@ -1186,7 +1084,7 @@ int dict_cap(int nmodes, int rank) {
     if (nmodes < 2 || nmodes > 4) return 0;
     const size_t fixed = segp_lds_bytes(kDictTile, nmodes);
     if (fixed >= kDictLdsBudget) return 0;
-    const size_t cap = (kDictLdsBudget - fixed) / ((size_t)(nmodes - 1) * rank * 4);
+    const size_t cap = (kDictLdsBudget - fixed) / ((size_t)(nmodes - 1) * cached_row_floats(rank) * 4);
     return cap >= (size_t)kDictMinCap ? (int)std::min<size_t>(cap, kDictTile) : 0;
 }
 
@@ -1201,7 +1099,7 @@ spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s) {
 }
 
 namespace {
-template <int NT, int NMAX, int NFIX, int G, int VEC, int NB>
+template <int NT, int NMAX, int NFIX, int VEC>
 spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, uint64_t *rec_row, float *rec_val,
                          int ld, unsigned long long *next_tile, hipStream_t s) {
     const size_t lds = segp_lds_bytes(4 * NT, NMAX);
@@ -1209,7 +1107,7 @@ spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, u
     int pc = per_cu.load(std::memory_order_relaxed);
     if (pc == 0) {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &pc, reinterpret_cast<const void *>(&k_mttkrp_segp_batched<NT, G, VEC, NB, NMAX, NFIX>), NT, lds) !=
+                &pc, reinterpret_cast<const void *>(&k_mttkrp_segp_batched<NT, VEC, NMAX, NFIX>), NT, lds) !=
                 hipSuccess ||
             pc < 1) {
             (void)hipGetLastError();  // not a failure of this call: one resident workgroup per CU is assumed
@@ -1220,7 +1118,7 @@ spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, u
     const int64_t grid = std::min<int64_t>(total_tiles, (int64_t)pc * device_cus());
     spt_status st = launch_fill_zero(reinterpret_cast<float *>(next_tile), 2, s);  // the tile counter
     if (st != SPT_OK) return st;
-    hipLaunchKernelGGL((k_mttkrp_segp_batched<NT, G, VEC, NB, NMAX, NFIX>), dim3((unsigned)grid), dim3(NT), lds, s, items,
+    hipLaunchKernelGGL((k_mttkrp_segp_batched<NT, VEC, NMAX, NFIX>), dim3((unsigned)grid), dim3(NT), lds, s, items,
                        count, total_tiles, rec_row, rec_val, ld, next_tile);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
@@ -1229,15 +1127,8 @@ spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, u
 template <int NT, int NMAX, int NFIX>
 spt_status launch_segb_n(const SegItem *items, int count, int64_t total_tiles, uint64_t *rec_row, float *rec_val,
                          int ld, bool vec4, unsigned long long *next_tile, hipStream_t s) {
-    if (vec4) {
-        const int r4 = ld >> 2;
-        if (r4 <= 1) return launch_segb_k<NT, NMAX, NFIX, 1, 4, 1>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, s);
-        if (r4 <= 2) return launch_segb_k<NT, NMAX, NFIX, 2, 4, 1>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, s);
-        if (r4 <= 4) return launch_segb_k<NT, NMAX, NFIX, 4, 4, 1>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, s);
-        if (r4 <= 8) return launch_segb_k<NT, NMAX, NFIX, 8, 4, 1>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, s);
-        return launch_segb_k<NT, NMAX, NFIX, 16, 4, 1>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, s);
-    }
-    return launch_segb_k<NT, NMAX, NFIX, 64, 1, 1>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, s);
+    return vec4 ? launch_segb_k<NT, NMAX, NFIX, 4>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, s)
+                : launch_segb_k<NT, NMAX, NFIX, 1>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, s);
 }
 
 template <int NT>
@@ -1316,7 +1207,7 @@ spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t to
                                      int nmodes_max, int tile, int ld, bool vec4, uint64_t *rec_row, float *rec_val,
                                      unsigned long long *next_tile, hipStream_t s) {
     if (total_tiles == 0) return SPT_OK;
-    if (ld > 64 || (vec4 && (ld & 3))) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: rank above 64");
+    if (ld > 64) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: rank above 64");
     if (!seg_batch_fits(nmodes_max, tile)) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: tile does not fit LDS");
     if (!next_tile) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: no tile counter");
     if (tile == 1024)

@@ -394,60 +394,50 @@ __global__ __launch_bounds__(256) void k_reduce_priv(const float *__restrict__ p
 #define SPT_RED_CHUNK 512
 #endif
 
-template <int G, int VEC, int NB>
+template <int VEC>
 __global__ __launch_bounds__(256) void k_reduce_records(const uint64_t *__restrict__ srow,
                                                         const uint32_t *__restrict__ sidx,
                                                         const float *__restrict__ rec_val, int64_t P, int R,
                                                         int chunk, int64_t rows, float *__restrict__ out) {
-    constexpr int GROUPS = 256 / G;
     constexpr int UB = SPT_RED_UB;
-    const int g = threadIdx.x / G, j = threadIdx.x % G;
-    const int64_t c0 = ((int64_t)blockIdx.x * GROUPS + g) * chunk;
+    const LaneGroup lg = lane_group<VEC>(R);
+    if (!lg.on) return;
+    const int c = lg.col;
+    const int64_t c0 = ((int64_t)blockIdx.x * (4 * lg.per_wave) + lg.g) * chunk;
     if (c0 >= P) return;
     const int64_t c1 = min(c0 + chunk, P);
     const uint64_t before = c0 > 0 ? srow[c0 - 1] : ~0ull;
     const uint64_t after = c1 < P ? srow[c1] : ~0ull;
     uint64_t cur = srow[c0];
     bool starts_here = cur != before;
-    float acc[NB][VEC];
+    float acc[VEC];
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[b][v] = 0.f;
+    for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
     auto emit = [&](uint64_t r, bool whole) {
         if (r >= (uint64_t)rows) return;  // sentinel records of unused slots
-        float *o = out + (int64_t)r * R;
+        float *o = out + (int64_t)r * R + c;
+        if (whole) {
+            store_vec<VEC>(o, acc);
+        } else {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int c = (b * G + j) * VEC;
-            if (c < R) {
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    if (whole) o[c + v] = acc[b][v];
-                    else unsafeAtomicAdd(o + c + v, acc[b][v]);
-                }
-            }
+            for (int v = 0; v < VEC; ++v)
+                if (c + v >= VEC * lg.j) unsafeAtomicAdd(o + v, acc[v]);  // not the columns repeated from the neighbour
         }
     };
     for (int64_t q = c0; q < c1; q += UB) {
         uint64_t r[UB];
-        float x[UB][NB][VEC];
+        float x[UB][VEC];
 #pragma unroll
         for (int u = 0; u < UB; ++u) {
             const bool ok = q + u < c1;
             r[u] = ok ? srow[q + u] : ~0ull;
             // sidx null: the records are already grouped by row (identity order)
             const int64_t ri = ok ? (sidx ? (int64_t)sidx[q + u] : q + u) : 0;
-            const float *src = rec_val + ri * R;
+            if (ok) {
+                load_vec_any<VEC>(rec_val + ri * R + c, x[u]);
+            } else {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int c = (b * G + j) * VEC;
-                if (ok && c < R) {
-                    load_vec<VEC>(src + c, x[u][b]);
-                } else {
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) x[u][b][v] = 0.f;
-                }
+                for (int v = 0; v < VEC; ++v) x[u][v] = 0.f;
             }
         }
 #pragma unroll
@@ -458,14 +448,10 @@ __global__ __launch_bounds__(256) void k_reduce_records(const uint64_t *__restri
                     cur = r[u];
                     starts_here = true;
 #pragma unroll
-                    for (int b = 0; b < NB; ++b)
-#pragma unroll
-                        for (int v = 0; v < VEC; ++v) acc[b][v] = x[u][b][v];
+                    for (int v = 0; v < VEC; ++v) acc[v] = x[u][v];
                 } else {
 #pragma unroll
-                    for (int b = 0; b < NB; ++b)
-#pragma unroll
-                        for (int v = 0; v < VEC; ++v) acc[b][v] += x[u][b][v];
+                    for (int v = 0; v < VEC; ++v) acc[v] += x[u][v];
                 }
             }
         }
@@ -546,27 +532,17 @@ spt_status launch_reduce_records(const uint64_t *srow, const uint32_t *sidx, con
     // SPT_RED_CHUNK) that still leaves 4096 lane groups, at least 64 records.
     int chunk = SPT_RED_CHUNK;
     while (chunk > 64 && P / chunk < 4096) chunk >>= 1;
-    auto go = [&](auto kern, int G) -> spt_status {
-        const int groups = 256 / G;
-        const int64_t blocks = (P + (int64_t)groups * chunk - 1) / ((int64_t)groups * chunk);
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, srow, sidx, rec_val, P, R, chunk, rows, out);
-        SPT_HIP(hipGetLastError());
-        return SPT_OK;
-    };
-    if ((R & 3) == 0) {
-        const int r4 = R >> 2;
-        if (r4 <= 1) return go(k_reduce_records<1, 4, 1>, 1);
-        if (r4 <= 2) return go(k_reduce_records<2, 4, 1>, 2);
-        if (r4 <= 4) return go(k_reduce_records<4, 4, 1>, 4);
-        if (r4 <= 8) return go(k_reduce_records<8, 4, 1>, 8);
-        if (r4 <= 16) return go(k_reduce_records<16, 4, 1>, 16);
-        if (r4 <= 32) return go(k_reduce_records<32, 4, 1>, 32);
-        return go(k_reduce_records<64, 4, 1>, 64);
-    }
-    if (R <= 64) return go(k_reduce_records<64, 1, 1>, 64);
-    if (R <= 128) return go(k_reduce_records<64, 1, 2>, 64);
-    if (R <= 192) return go(k_reduce_records<64, 1, 3>, 64);
-    return go(k_reduce_records<64, 1, 4>, 64);
+    const int G = R >= 4 ? (R + 3) / 4 : R;  // lanes of a group (LaneGroup)
+    const int64_t per_block = 4 * (64 / G) * (int64_t)chunk;
+    const int64_t blocks = (P + per_block - 1) / per_block;
+    if (R >= 4)
+        hipLaunchKernelGGL(k_reduce_records<4>, dim3((unsigned)blocks), dim3(256), 0, s, srow, sidx, rec_val, P, R, chunk,
+                           rows, out);
+    else
+        hipLaunchKernelGGL(k_reduce_records<1>, dim3((unsigned)blocks), dim3(256), 0, s, srow, sidx, rec_val, P, R, chunk,
+                           rows, out);
+    SPT_HIP(hipGetLastError());
+    return SPT_OK;
 }
 
 }  // namespace spt

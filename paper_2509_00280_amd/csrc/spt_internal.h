@@ -255,7 +255,8 @@ spt_status launch_emit_plan_batched(const SegItem *items, int count, int64_t tot
                                     uint32_t *psub, uint64_t *pair_key, uint32_t *pair_np, hipStream_t s);
 spt_status launch_piece_dest_batched(const SegItem *items, int count, const int64_t *piece_base, const uint32_t *ppair,
                                      const uint32_t *psub, const uint32_t *pair_first, int64_t n, hipStream_t s);
-// next_tile: a device counter (8 bytes) the launch zeroes and the workgroups pull tiles from
+// next_tile: a device counter (8 bytes) the launch zeroes and the workgroups pull tiles from;
+// vec4: every member's rank is at least 4
 spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t total_tiles, int nmodes_min,
                                      int nmodes_max, int tile, int ld, bool vec4, uint64_t *rec_row, float *rec_val,
                                      unsigned long long *next_tile, hipStream_t s);

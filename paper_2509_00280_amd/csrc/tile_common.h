@@ -34,6 +34,66 @@ __device__ __forceinline__ void load_vec(const float *p, float (&x)[VEC]) {
     }
 }
 
+// Four floats at any 4-byte boundary (a row of a rank that is no multiple of
+// 4): global memory takes them as one 16-byte access all the same.
+typedef float spt_f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int VEC>
+__device__ __forceinline__ void load_vec_any(const float *p, float (&x)[VEC]) {
+    if constexpr (VEC == 4) {
+        const spt_f4u t = *reinterpret_cast<const spt_f4u *>(p);
+        x[0] = t.x;
+        x[1] = t.y;
+        x[2] = t.z;
+        x[3] = t.w;
+    } else {
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) x[q] = p[q];
+    }
+}
+
+template <int VEC>
+__device__ __forceinline__ void store_vec(float *p, const float (&x)[VEC]) {
+    if constexpr (VEC == 4) {
+        const spt_f4u t = {x[0], x[1], x[2], x[3]};
+        *reinterpret_cast<spt_f4u *>(p) = t;
+    } else {
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) p[q] = x[q];
+    }
+}
+
+// Lane groups of the walk: a record's R columns are owned by G consecutive
+// lanes of one wave, 64 / G groups to a wave (the lanes left over sit the walk
+// out).  VEC 4 (R >= 4): G = ceil(R / 4) lanes of 4 columns each; the last
+// lane takes the row's last 4 columns, so at a rank that is no multiple of 4
+// it repeats up to 3 columns of its neighbour with the same values instead of
+// idling or masking.  VEC 1 (R < 4): one column a lane.
+// Packing by ceil(R / 4) and not by the next power of two (and, at ranks that
+// are no multiple of 4, instead of one column a lane over the whole wave) puts
+// more nonzeros in flight per wave for the same row bytes.  All-mode sweeps,
+// before and after: rank 25, 5 modes, 5M nonzeros 6.97 / 0.88 ms (with the
+// 5-mode walk that issues all gathers of a step at once); rank 10, 4 modes, 3M
+// nonzeros 2.78 / 1.11 ms; ranks 32 and 64, where the groups are the same
+// lanes as before, 4.53 / 4.55 and 13.65 / 13.62 ms.
+struct LaneGroup {
+    int G, per_wave, j, col;  // lanes per group, groups per wave, lane in the group, first column
+    int g;                    // group in the workgroup
+    bool on;
+};
+template <int VEC>
+__device__ __forceinline__ LaneGroup lane_group(int R) {
+    LaneGroup q;
+    q.G = VEC == 4 ? (R + 3) >> 2 : R;
+    q.per_wave = 64 / q.G;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, gl = lane / q.G;
+    q.j = lane - gl * q.G;
+    q.col = VEC == 4 ? min(4 * q.j, R - 4) : q.j;
+    q.g = w * q.per_wave + gl;
+    q.on = gl < q.per_wave;
+    return q;
+}
+
 // A factor matrix seen as a structured buffer whose records are its rows
 // (stride R floats): a gather passes the row index and the column's byte
 // offset straight to the load, with no address arithmetic, and rows past
