@@ -233,9 +233,11 @@ spt_status run_mttkrp_batched_mode(const SegItem *d_items, int count, int64_t to
     unsigned long long *counter = (unsigned long long *)ws.counter.get(256, s);
     if (!rrow || !rval || !counter) return fail(SPT_E_OOM, "batch: record workspace");
     // the batch's records come out grouped by row: no sort
+    const int64_t n = rows * (int64_t)ld;
+    const bool fill = !zero_on_the_way(n, total_tiles);
     spt_status st = launch_mttkrp_seg_batched(d_items, count, total_tiles, nmodes_min, nmodes_max, tile, ld, vec4, rrow,
-                                              rval, counter, s);
-    if (st == SPT_OK) st = launch_fill_zero(M_all, rows * (int64_t)ld, s);
+                                              rval, counter, fill ? nullptr : M_all, n, s);
+    if (st == SPT_OK && fill) st = launch_fill_zero(M_all, n, s);
     if (st == SPT_OK) st = launch_reduce_records(rrow, nullptr, rval, records, ld, rows, M_all, s);
     return st;
 }

@@ -398,6 +398,13 @@ struct PackedPieces {
     }
 };
 
+// The part of the output that a tile's workgroup zeroes for the record
+// reduction that follows: slice i of `of` of n floats.
+struct ZeroSlice {
+    float *p;
+    int64_t n, i, of;
+};
+
 // Planned SEGMENT kernel.  The plan holds, per nonzero, its position in the
 // tile's row-grouped order (u16) and, per piece, (start | length << 16, row,
 // record), with the records of one row contiguous.  A tile is staged by one
@@ -408,7 +415,8 @@ struct PackedPieces {
 // (a batched member).
 template <int NT, int T, int VEC, int NMAX, int NFIX, bool PACKED>
 __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, char *lds, uint64_t *__restrict__ rec_row,
-                                          float *__restrict__ rec_val, int ld, int64_t rec_base, int64_t row_base) {
+                                          float *__restrict__ rec_val, int ld, int64_t rec_base, int64_t row_base,
+                                          const ZeroSlice &zero) {
     constexpr int PER = T / NT;  // nonzeros staged per thread
     static_assert(PER * NT == T && PER >= 1 && PER <= 8, "tile must be 1..8 nonzeros per thread");
     const int nm = NFIX ? NFIX : a.nmodes, mode = a.mode, tid = threadIdx.x;
@@ -443,6 +451,7 @@ __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, cha
         v[u] = x;
         ps[u] = q;
     }
+    zero_slice(zero.p, zero.n, zero.i, zero.of);  // while the loads above are in flight
     // decode the non-output coordinates and scatter them with the values
 #pragma unroll
     for (int k = 0; k < NMAX; ++k) {
@@ -483,12 +492,16 @@ __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, cha
             rec_val, ld, row_base);
 }
 
+__device__ __forceinline__ ZeroSlice out_slice(const MttkrpArgs &a, int64_t tile, int64_t ntiles) {
+    return ZeroSlice{a.out, (int64_t)a.frows[a.mode] * a.rank, tile, ntiles};
+}
+
 template <int NT, int T, int VEC, int NMAX, int NFIX>
 __global__ __launch_bounds__(NT) void k_mttkrp_segp(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segp_tile<NT, T, VEC, NMAX, NFIX, true>(a, tile, lds, a.rec_row, a.rec_val, a.rank, 0, 0);
+    segp_tile<NT, T, VEC, NMAX, NFIX, true>(a, tile, lds, a.rec_row, a.rec_val, a.rank, 0, 0, out_slice(a, tile, ntiles));
 }
 
 // ---------------------------------------------------------------- row cache
@@ -605,7 +618,7 @@ __host__ __device__ inline size_t segd_lds_bytes(int T, int nmodes, int cap, int
 // reads its factor row there, any other reads it from HBM/L2 by its global
 // row.
 template <int NT, int T, int VEC, int NMAX, int NFIX>
-__device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, char *lds) {
+__device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int64_t ntiles, char *lds) {
     constexpr int PER = T / NT;
     constexpr int NO = NMAX - 1;
     static_assert(PER * NT == T && NMAX <= 4, "row cache: 4 modes at most");
@@ -670,6 +683,10 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, cha
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u) q[u] &= (uint32_t)(T - 1);  // a position inside the tile
+    {
+        const ZeroSlice z = out_slice(a, tile, ntiles);
+        zero_slice(z.p, z.n, z.i, z.of);  // while the loads above are in flight
+    }
     // copy the cached rows: the first min(distinct, cap) of each dictionary
     int64_t dbase[NO];
     int dn[NO], dlast[NO];
@@ -740,7 +757,7 @@ __global__ __launch_bounds__(NT) void k_mttkrp_segd(MttkrpArgs a, int64_t ntiles
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segd_tile<NT, T, VEC, NMAX, NFIX>(a, tile, lds);
+    segd_tile<NT, T, VEC, NMAX, NFIX>(a, tile, ntiles, lds);
 }
 
 // Batched: tile `it` of the whole batch belongs to the last item whose
@@ -767,7 +784,8 @@ template <int NT, int VEC, int NMAX, int NFIX>
 __global__ __launch_bounds__(NT) void k_mttkrp_segp_batched(const SegItem *__restrict__ items, int count,
                                                             int64_t total_tiles, uint64_t *__restrict__ rec_row,
                                                             float *__restrict__ rec_val, int ld,
-                                                            unsigned long long *__restrict__ next_tile) {
+                                                            unsigned long long *__restrict__ next_tile,
+                                                            float *__restrict__ out, int64_t out_floats) {
     extern __shared__ __align__(16) char lds[];
     __shared__ int64_t s_tile;
     int b = 0;
@@ -780,7 +798,8 @@ __global__ __launch_bounds__(NT) void k_mttkrp_segp_batched(const SegItem *__res
         while (b + 1 < count && items[b + 1].first_tile <= it) ++b;
         const SegItem &item = items[b];
         segp_tile<NT, 4 * NT, VEC, NMAX, NFIX, false>(item.a, it - item.first_tile, lds, rec_row, rec_val, ld,
-                                                      item.rec_base, item.row_base);
+                                                      item.rec_base, item.row_base,
+                                                      ZeroSlice{out, out_floats, it, total_tiles});
     }
 }
 
@@ -1101,7 +1120,7 @@ spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s) {
 namespace {
 template <int NT, int NMAX, int NFIX, int VEC>
 spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, uint64_t *rec_row, float *rec_val,
-                         int ld, unsigned long long *next_tile, hipStream_t s) {
+                         int ld, unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
     const size_t lds = segp_lds_bytes(4 * NT, NMAX);
     static std::atomic<int> per_cu{0};  // resident workgroups per CU (fixed per instantiation: its LDS is)
     int pc = per_cu.load(std::memory_order_relaxed);
@@ -1119,25 +1138,26 @@ spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, u
     spt_status st = launch_fill_zero(reinterpret_cast<float *>(next_tile), 2, s);  // the tile counter
     if (st != SPT_OK) return st;
     hipLaunchKernelGGL((k_mttkrp_segp_batched<NT, VEC, NMAX, NFIX>), dim3((unsigned)grid), dim3(NT), lds, s, items,
-                       count, total_tiles, rec_row, rec_val, ld, next_tile);
+                       count, total_tiles, rec_row, rec_val, ld, next_tile, out, out_floats);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
 template <int NT, int NMAX, int NFIX>
 spt_status launch_segb_n(const SegItem *items, int count, int64_t total_tiles, uint64_t *rec_row, float *rec_val,
-                         int ld, bool vec4, unsigned long long *next_tile, hipStream_t s) {
-    return vec4 ? launch_segb_k<NT, NMAX, NFIX, 4>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, s)
-                : launch_segb_k<NT, NMAX, NFIX, 1>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, s);
+                         int ld, bool vec4, unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
+    return vec4 ? launch_segb_k<NT, NMAX, NFIX, 4>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, out, out_floats, s)
+                : launch_segb_k<NT, NMAX, NFIX, 1>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, out, out_floats, s);
 }
 
 template <int NT>
 spt_status launch_segb_t(const SegItem *items, int count, int64_t total_tiles, int nmodes_min, int nmodes_max, int ld,
-                         bool vec4, uint64_t *rec_row, float *rec_val, unsigned long long *next_tile, hipStream_t s) {
+                         bool vec4, uint64_t *rec_row, float *rec_val, unsigned long long *next_tile, float *out,
+                         int64_t out_floats, hipStream_t s) {
     if (nmodes_min == 3 && nmodes_max == 3)
-        return launch_segb_n<NT, 3, 3>(items, count, total_tiles, rec_row, rec_val, ld, vec4, next_tile, s);
-    if (nmodes_max <= 4) return launch_segb_n<NT, 4, 0>(items, count, total_tiles, rec_row, rec_val, ld, vec4, next_tile, s);
-    return launch_segb_n<NT, 8, 0>(items, count, total_tiles, rec_row, rec_val, ld, vec4, next_tile, s);
+        return launch_segb_n<NT, 3, 3>(items, count, total_tiles, rec_row, rec_val, ld, vec4, next_tile, out, out_floats, s);
+    if (nmodes_max <= 4) return launch_segb_n<NT, 4, 0>(items, count, total_tiles, rec_row, rec_val, ld, vec4, next_tile, out, out_floats, s);
+    return launch_segb_n<NT, 8, 0>(items, count, total_tiles, rec_row, rec_val, ld, vec4, next_tile, out, out_floats, s);
 }
 
 template <int NT>
@@ -1205,16 +1225,16 @@ spt_status launch_count_pieces_batched(const SegItem *items, int count, int64_t 
 
 spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t total_tiles, int nmodes_min,
                                      int nmodes_max, int tile, int ld, bool vec4, uint64_t *rec_row, float *rec_val,
-                                     unsigned long long *next_tile, hipStream_t s) {
+                                     unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
     if (total_tiles == 0) return SPT_OK;
     if (ld > 64) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: rank above 64");
     if (!seg_batch_fits(nmodes_max, tile)) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: tile does not fit LDS");
     if (!next_tile) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: no tile counter");
     if (tile == 1024)
-        return launch_segb_t<256>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_row, rec_val, next_tile, s);
+        return launch_segb_t<256>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_row, rec_val, next_tile, out, out_floats, s);
     if (tile == 2048)
-        return launch_segb_t<512>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_row, rec_val, next_tile, s);
-    return launch_segb_t<1024>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_row, rec_val, next_tile, s);
+        return launch_segb_t<512>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_row, rec_val, next_tile, out, out_floats, s);
+    return launch_segb_t<1024>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_row, rec_val, next_tile, out, out_floats, s);
 }
 
 }  // namespace spt

@@ -449,6 +449,23 @@ spt_status profile_read(double *ms, int64_t *launches) {
     return SPT_OK;
 }
 
+// The SEGMENT kernel, with `out` zeroed for the record reduction that follows:
+// by its workgroups on the way, or by a launch of its own where that is too
+// much for one of them (zero_on_the_way) or where out shares memory with a
+// factor that they read.
+static spt_status launch_seg_zeroing(MttkrpArgs a, float *out, hipStream_t s) {
+    const int64_t n = (int64_t)a.frows[a.mode] * a.rank;
+    a.out = zero_on_the_way(n, (a.nnz + a.tile - 1) / a.tile) ? out : nullptr;
+    for (int k = 0; k < a.nmodes; ++k) {
+        const uintptr_t f = (uintptr_t)a.f[k], o = (uintptr_t)out;
+        if (k != a.mode && o < f + sizeof(float) * (size_t)a.frows[k] * a.rank && f < o + sizeof(float) * (size_t)n)
+            a.out = nullptr;
+    }
+    spt_status st = launch_mttkrp_seg(a, s);
+    if (st == SPT_OK && !a.out) st = launch_fill_zero(out, n, s);
+    return st;
+}
+
 // Records path shared by SEGMENT and TABLE: the main kernel writes P
 // records (row, R floats) and the reducer sums them per row into out.
 // SEGMENT records come out grouped by row (the plan laid them out); TABLE
@@ -479,8 +496,7 @@ spt_status reduce_via_records(Tensor *t, MttkrpArgs &a, int64_t P, int rank, int
     if (segment) {
         a.rec_row = rrow;
         a.rec_val = rval;
-        st = launch_mttkrp_seg(a, s);
-        if (st == SPT_OK) st = launch_fill_zero(out, rows * (int64_t)rank, s);
+        st = launch_seg_zeroing(a, out, s);
         if (st == SPT_OK) st = launch_reduce_records(rrow, nullptr, rval, P, rank, rows, out, s);
         release();
         return st;
@@ -694,8 +710,7 @@ spt_status run_mttkrp_noalloc(Tensor *t, const float *const *factors, int rank, 
     // reduction reads it, so the array needs no clearing between calls
     a.rec_row = (uint64_t *)base;
     a.rec_val = (float *)((char *)base + row_bytes);
-    st = launch_mttkrp_seg(a, s);
-    if (st == SPT_OK) st = launch_fill_zero(out, rows * (int64_t)rank, s);
+    st = launch_seg_zeroing(a, out, s);
     if (st == SPT_OK) st = launch_reduce_records(a.rec_row, nullptr, a.rec_val, P, rank, rows, out, s);
     return st;
 }

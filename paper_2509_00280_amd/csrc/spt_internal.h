@@ -217,6 +217,13 @@ spt_status launch_emit_plan(const MttkrpArgs &a, const PlanOut &o, hipStream_t s
 // packed[k] = {desc[k], prow[k], first record of piece k's pair + its index, 0}
 spt_status launch_piece_pack(const uint32_t *ppair, const uint32_t *psub, const uint32_t *pair_first,
                              const uint32_t *desc, const uint32_t *prow, uint32_t *packed, int64_t n, hipStream_t s);
+// Whether a launch of `wgs` workgroups clears n floats of output on its way.
+// It saves the fill launch (rank 64, 150M nonzeros, 14 KB a workgroup: 25 us of
+// 3.4 ms a call) but is at the mercy of the few workgroups of a small or very
+// sparse tensor: at 1 MB each (2.6M rows of rank 32, 1.3M nonzeros) a call
+// took 262 us against 247 with a fill of its own, at 5 MB 112 against 76.
+inline bool zero_on_the_way(int64_t n, int64_t wgs) { return n <= wgs * (64 * 1024 / 4); }
+// the SEGMENT kernel on a's plan: records to a.rec_row / a.rec_val, a.out (if any) zeroed
 spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s);
 // mttkrp_f64.hip
 bool f64_tile_ok(int tile, int nmodes);
@@ -256,10 +263,10 @@ spt_status launch_emit_plan_batched(const SegItem *items, int count, int64_t tot
 spt_status launch_piece_dest_batched(const SegItem *items, int count, const int64_t *piece_base, const uint32_t *ppair,
                                      const uint32_t *psub, const uint32_t *pair_first, int64_t n, hipStream_t s);
 // next_tile: a device counter (8 bytes) the launch zeroes and the workgroups pull tiles from;
-// vec4: every member's rank is at least 4
+// vec4: every member's rank is at least 4; out: out_floats that the launch also zeroes
 spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t total_tiles, int nmodes_min,
                                      int nmodes_max, int tile, int ld, bool vec4, uint64_t *rec_row, float *rec_val,
-                                     unsigned long long *next_tile, hipStream_t s);
+                                     unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s);
 
 // Batched dense steps (dense.hip): one workgroup per item, except apply
 // (a grid over the items' row blocks).

@@ -34,6 +34,7 @@ __device__ __forceinline__ void load_vec(const float *p, float (&x)[VEC]) {
     }
 }
 
+typedef float spt_f4 __attribute__((ext_vector_type(4)));
 // Four floats at any 4-byte boundary (a row of a rank that is no multiple of
 // 4): global memory takes them as one 16-byte access all the same.
 typedef float spt_f4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -94,12 +95,28 @@ __device__ __forceinline__ LaneGroup lane_group(int R) {
     return q;
 }
 
+// Zeroes slice `i` of `of` of an array of n floats (16-byte aligned, or null): a kernel
+// whose workgroups wait on other things clears the output of the kernel that
+// follows it on the way, which costs that launch and not its bytes.
+__device__ __forceinline__ void zero_slice(float *__restrict__ p, int64_t n, int64_t i, int64_t of) {
+    if (!p) return;
+    const int64_t per = ((n + of - 1) / of + 3) & ~int64_t(3);
+    const int64_t a = i * per, b = min(a + per, n);
+    const spt_f4 z = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t e = a + 4 * (int64_t)threadIdx.x; e < b; e += 4 * (int64_t)blockDim.x) {
+        if (e + 4 <= b) {
+            __builtin_nontemporal_store(z, reinterpret_cast<spt_f4 *>(p + e));
+        } else {
+            for (int64_t k = e; k < b; ++k) p[k] = 0.f;
+        }
+    }
+}
+
 // A factor matrix seen as a structured buffer whose records are its rows
 // (stride R floats): a gather passes the row index and the column's byte
 // offset straight to the load, with no address arithmetic, and rows past
 // `rows` read as zero.  The descriptor is wave-uniform (SGPRs); R <= 4095.
 typedef int spt_i4 __attribute__((ext_vector_type(4)));
-typedef float spt_f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t spt_u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t spt_u4 __attribute__((ext_vector_type(4)));
 __device__ spt_f4 spt_row_load4(spt_i4 rsrc, int vindex, int voffset, int soffset, int aux) __asm(
