@@ -11,6 +11,7 @@
 //               fit's inner product sum M .* C * lambda fused in.
 //   fit         |Xhat|^2 = lambda^T (Hadamard of all Grams) lambda and the fit.
 #include <algorithm>
+#include <utility>
 
 #include "spt_internal.h"
 
@@ -227,167 +228,212 @@ __global__ __launch_bounds__(kThreads) void k_gram_reduce2(const double *__restr
 }
 
 // ------------------------------------------------------------------ solve preparation
-// One workgroup; R <= 64.  LDS: three R x R FP64 matrices.  W = V^-1 from
-// the Cholesky factor: a right-looking factorisation V = L L^T and, in the
-// same sweep, a right-looking forward substitution X = L^-1 (step j of the
-// substitution needs only column j of L, which step j of the factorisation
-// forms), then W = X^T X.  Every thread updates the same matrix elements in
-// place at every step; the only values a step reads from other threads (the
-// pivot column, the pivot row of X) are staged in double-buffered vectors by
-// their owners during the step before: one barrier per step.  The pivot's
-// reciprocal square root comes from the hardware estimate and two Newton
-// steps, which gives l, 1/l and 1/l^2 without a square root or a divide.
-// One 16 x 16 tile (ti, tj) of X^T Y for R x R row-major LDS matrices (R <=
-// 64) on v_mfma_f64_16x16x4_f64 (A[m][k] from lane m + 16 k, B[k][n] from
-// lane n + 16 k; D[m][n] in lane n + 16 (m % 4), element m / 4).  Indices at
-// or beyond R read as 0.  Every lane of the wave must be active.
-__device__ __forceinline__ double4_t solve_mfma_tile(const double *X, const double *Y, int R, int ti, int tj,
-                                                     int lane) {
-    double4_t acc = {0.0, 0.0, 0.0, 0.0};
-    const int kq = lane >> 4, row = ti * 16 + (lane & 15), col = tj * 16 + (lane & 15);
-    for (int k0 = 0; k0 < R; k0 += 4) {
-        const int k = k0 + kq;
-        const double a = (k < R && row < R) ? X[k * R + row] : 0.0;
-        const double b = (k < R && col < R) ? Y[k * R + col] : 0.0;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+// One workgroup; R <= 64, padded to RP = 16 nb by an identity block (V) and
+// zeros (Gm).  W = V^-1 from the Cholesky factor V = L L^T, in 16 x 16 blocks.
+// What bounds it is one serial chain: R pivots, each a reciprocal square root
+// that the next one waits for.  So that chain alone runs in one wave, in
+// registers (a diagonal block factored and inverted at once, 16 pivots, no
+// barrier), and everything else is FP64 MFMA tiles of other waves beside it:
+// per block column k two barriers, the first behind the diagonal block (X_kk =
+// L_kk^-1) and the sums that do not need it, the second behind what does:
+//   T_ki = V_ki - sum_{p<k} L_kp L_ip^T,   L_ik^T = X_kk T_ki      (i > k)
+//   D_kj = sum_{j<=p<k} L_kp X_pj,         X_kj   = -X_kk D_kj     (j < k)
+// with X = L^-1, then W = X^T X.  An MFMA result D[m][n] sits in lane n + 16
+// (m % 4), element m / 4, which is where the next product wants it as its
+// right operand: no result moves between the two.
+// One element sweep with a barrier per pivot, as it was, took 84 / 51 / 31 / 16
+// us at rank 64 / 48 / 32 / 16.
+constexpr int kSolveThreads = 512;
+constexpr int kSolveLd = 66;  // doubles: rows 4 banks apart, so that 16 rows of one column do not collide
+
+__device__ __forceinline__ double lane_f64(double x, int lane) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
+    return __hiloint2double(hi, lo);
+}
+
+// lane J of each row of 16 lanes to the whole row
+template <int J>
+__device__ __forceinline__ double row_bcast_f64(double x) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), 0x150 + J, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), 0x150 + J, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Pivot J of a 16 x 16 block held by one wave in MFMA result layout (lane n +
+// 16 q: column n, rows 4 e + q): b the symmetric block, x the inverse of its
+// factor so far (identity at first).  c = column J as it is: rows i > J lose
+// c_i c_n / d from b and c_i x[J][n] / d from x, row J of x is scaled by 1 / l.
+// The pivot's reciprocal square root is the hardware estimate and two Newton
+// steps, which gives 1 / l and 1 / d without a square root or a divide.
+template <int J>
+__device__ __forceinline__ void solve_pivot(double (&b)[4], double (&x)[4], int n, int q, bool &ok) {
+    constexpr int E = J / 4, Q = J % 4;
+    const double d = lane_f64(b[E], J + 16 * Q);
+    ok = ok && d > 0.0 && isfinite(d);
+    double r = __builtin_amdgcn_rsq(d);
+    r = r * (1.5 - 0.5 * d * r * r);
+    r = r * (1.5 - 0.5 * d * r * r);
+    const double id = r * r;
+    double c[4];
+    c[0] = row_bcast_f64<J>(b[0]);
+    c[1] = row_bcast_f64<J>(b[1]);
+    c[2] = row_bcast_f64<J>(b[2]);
+    c[3] = row_bcast_f64<J>(b[3]);
+    const double cn = __shfl(b[E], n + 16 * Q, 64);  // b is symmetric: its row J is its column J
+    const double xn = __shfl(x[E], n + 16 * Q, 64);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double ci = 4 * e + q > J ? c[e] : 0.0;
+        b[e] -= ci * cn * id;
+        x[e] -= ci * xn * id;
     }
+    if (q == Q) x[E] *= r;
+}
+
+template <int... J>
+__device__ __forceinline__ void solve_pivots(double (&b)[4], double (&x)[4], int n, int q, bool &ok,
+                                             std::integer_sequence<int, J...>) {
+    (solve_pivot<J>(b, x, n, q, ok), ...);
+}
+
+// acc + sign * X Y^T over 16 columns, X and Y 16 x 16 blocks of row-major LDS matrices
+__device__ __forceinline__ double4_t mfma_abt(const double *X, const double *Y, double4_t acc, int lane) {
+    const int r = lane & 15, kq = lane >> 4;
+#pragma unroll
+    for (int k = 0; k < 16; k += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[r * kSolveLd + k + kq], Y[r * kSolveLd + k + kq], acc, 0, 0, 0);
     return acc;
 }
 
-constexpr int kSolveThreads = 1024;  // 16 waves: 4 matrix elements per thread at R = 64
+// acc + X Y over 16 columns of X
+__device__ __forceinline__ double4_t mfma_ab(const double *X, const double *Y, double4_t acc, int lane) {
+    const int r = lane & 15, kq = lane >> 4;
+#pragma unroll
+    for (int k = 0; k < 16; k += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[r * kSolveLd + k + kq], Y[(k + kq) * kSolveLd + r], acc, 0, 0, 0);
+    return acc;
+}
+
+// X^T Y over the rows [k0, k1) of two row-major LDS matrices (16-column blocks at X and Y)
+__device__ __forceinline__ double4_t mfma_atb(const double *X, const double *Y, int k0, int k1, int lane) {
+    double4_t acc = {0.0, 0.0, 0.0, 0.0};
+    const int r = lane & 15, kq = lane >> 4;
+    for (int k = k0; k < k1; k += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[(k + kq) * kSolveLd + r], Y[(k + kq) * kSolveLd + r], acc, 0, 0, 0);
+    return acc;
+}
+
 __device__ __forceinline__ void solve_prep_body(const double *__restrict__ grams, int nmodes, int mode, int R,
                                                 const double *__restrict__ gram_m, double *__restrict__ S,
                                                 double *__restrict__ lambda, int *__restrict__ status,
                                                 double *__restrict__ gram_new) {
-    __shared__ double A[64 * 64];
-    __shared__ double B[64 * 64];
-    __shared__ double Xs[64 * 64];
-    __shared__ double vec[2][64];   // staged pivot column of the factorisation
-    __shared__ double vecx[2][64];  // staged pivot row of X
-    const int tid = threadIdx.x;
-    const int RR = R * R;
+    constexpr int LD = kSolveLd;
+    __shared__ double A[64 * LD];
+    __shared__ double B[64 * LD];
+    __shared__ double Xs[64 * LD];
+    __shared__ double lam_s[64];
+    __shared__ int failed;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int nb = (R + 15) / 16, RP = nb * 16, RR = R * R;
+    const int n = lane & 15, q = lane >> 4;
     // V = Hadamard product of the Grams of every mode except `mode` -> A
-    for (int e = tid; e < RR; e += kSolveThreads) {
-        double v = 1.0;
-        for (int k = 0; k < nmodes; ++k)
-            if (k != mode) v *= grams[(size_t)k * RR + e];
-        A[e] = v;
+    for (int e = tid; e < RP * RP; e += kSolveThreads) {
+        const int i = e / RP, j = e - i * RP;
+        double v = i == j ? 1.0 : 0.0;
+        if (i < R && j < R) {
+            v = 1.0;
+            for (int k = 0; k < nmodes; ++k)
+                if (k != mode) v *= grams[(size_t)k * RR + i * R + j];
+        }
+        A[i * LD + j] = v;
     }
+    if (tid == 0) failed = 0;
     __syncthreads();
-    double trace = 0.0;
-    for (int i = 0; i < R; ++i) trace += A[i * R + i];
-    const double ridge0 = 1e-12 * trace / R;
-    // The sweep below changes only lower triangles (of the working matrix and
-    // of X): each thread owns up to PT of their R (R + 1) / 2 elements, the
-    // t-th in row i = largest with i (i + 1) / 2 <= t, column t - i (i + 1) / 2.
-    constexpr int PT = (64 * 65 / 2 + kSolveThreads - 1) / kSolveThreads;
-    const int RT = R * (R + 1) / 2;
-    int ei[PT], ek[PT];  // row and column of each owned element (t < RT)
-#pragma unroll
-    for (int m = 0; m < PT; ++m) {
-        const int t = tid + m * kSolveThreads;
-        int i = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
-        while ((i + 1) * (i + 2) / 2 <= t) ++i;
-        while (i > 0 && i * (i + 1) / 2 > t) --i;
-        ei[m] = i;
-        ek[m] = t - i * (i + 1) / 2;
-    }
     int attempt = 0;
     for (; attempt < 4; ++attempt) {
-        const double ridge = attempt == 0 ? 0.0 : ridge0 * pow(1e3, (double)(attempt - 1));
-        for (int e = tid; e < RR; e += kSolveThreads) {
-            const int i = e / R, j = e % R;
-            B[e] = A[e] + (i == j ? ridge : 0.0);
-            Xs[e] = i == j ? 1.0 : 0.0;
-            if (j == 0) vec[0][i] = B[e];
-            if (i == 0) vecx[0][j] = Xs[e];
+        double ridge = 0.0;
+        if (attempt > 0) {
+            double trace = 0.0;
+            for (int i = 0; i < R; ++i) trace += A[i * LD + i];
+            ridge = 1e-12 * trace / R * pow(1e3, (double)(attempt - 1));
         }
-        __syncthreads();
-        // Step j: with column j of the working matrix as it was before the
-        // step (cj) and l = L[j][j], the factorisation scales column j and
-        // updates the trailing matrix (lower triangle of B), and the
-        // substitution scales row j of X and subtracts L[i][j] X[j][:] / l
-        // (= cj[i] X[j][:] / d) from the rows below, X[j][:] as it was before
-        // the step (rj).  The owners of column j + 1 and of row j + 1 of X
-        // stage them for the next step.  All threads read the same pivot, so
-        // they leave the loop together.
-        bool ok = true;
-        for (int j = 0; j < R; ++j) {
-            const double *cj = vec[j & 1];
-            double *cn = vec[(j + 1) & 1];
-            const double *rj = vecx[j & 1];
-            double *rn = vecx[(j + 1) & 1];
-            const double d = cj[j];
-            if (!(d > 0.0) || !isfinite(d)) {
-                ok = false;
-                break;
-            }
-            double r = __builtin_amdgcn_rsq(d);
-            r = r * (1.5 - 0.5 * d * r * r);
-            r = r * (1.5 - 0.5 * d * r * r);
-            const double l = d * r, il = r, id = r * r;
+        // the ridge goes on the diagonal blocks only, as they are read
+        for (int k = 0; k < nb; ++k) {
+            double4_t acc = {0.0, 0.0, 0.0, 0.0};
+            const int panel = nb - 1 - k;                    // tiles i > k
+            const bool is_panel = wave >= 1 && wave <= panel;
+            const bool is_inv = wave > panel && wave < nb;   // tiles j < k
+            const int t = is_panel ? k + wave : wave - 1 - panel;  // i or j
+            if (wave == 0) {
+                for (int p = 0; p < k; ++p) acc = mfma_abt(B + k * 16 * LD + p * 16, B + k * 16 * LD + p * 16, acc, lane);
+                double b[4], x[4];
 #pragma unroll
-            for (int m = 0; m < PT; ++m) {
-                // rows above the pivot are final in both matrices
-                if (tid + m * kSolveThreads < RT && ei[m] >= j) {
-                    const int i = ei[m], k = ek[m], e = i * R + k;
-                    double x = B[e];
-                    if (k == j) {
-                        x = i == j ? l : (i > j ? x * il : x);
-                        B[e] = x;
-                    } else if (i > j && k > j && k <= i) {
-                        x -= cj[i] * cj[k] * id;
-                        B[e] = x;
-                    }
-                    if (k == j + 1 && i > j) cn[i] = x;
-                    double y = Xs[e];
-                    if (i == j) {
-                        y *= il;
-                        Xs[e] = y;
-                    } else if (i > j && k <= j) {
-                        y -= cj[i] * rj[k] * id;
-                        Xs[e] = y;
-                    }
-                    if (i == j + 1) rn[k] = y;
+                for (int e = 0; e < 4; ++e) {
+                    const int i = 4 * e + q, gi = k * 16 + i;
+                    double v = A[gi * LD + k * 16 + n];
+                    if (i == n && gi < R) v += ridge;
+                    b[e] = v - acc[e];
+                    x[e] = i == n ? 1.0 : 0.0;
+                }
+                bool ok = true;
+                solve_pivots(b, x, n, q, ok, std::make_integer_sequence<int, 16>{});
+                if (!ok && lane == 0) failed = 1;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) Xs[(k * 16 + 4 * e + q) * LD + k * 16 + n] = x[e];
+            } else if (is_panel) {
+                for (int p = 0; p < k; ++p) acc = mfma_abt(B + k * 16 * LD + p * 16, B + t * 16 * LD + p * 16, acc, lane);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] = A[(k * 16 + 4 * e + q) * LD + t * 16 + n] - acc[e];
+            } else if (is_inv) {
+                for (int p = t; p < k; ++p) acc = mfma_ab(B + k * 16 * LD + p * 16, Xs + p * 16 * LD + t * 16, acc, lane);
+            }
+            __syncthreads();
+            if (failed) break;
+            if (is_panel || is_inv) {
+                double4_t r = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    r = __builtin_amdgcn_mfma_f64_16x16x4f64(Xs[(k * 16 + n) * LD + k * 16 + 4 * s + q], acc[s], r, 0, 0, 0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (is_panel) B[(t * 16 + n) * LD + k * 16 + 4 * e + q] = r[e];  // L_ik, transposed back
+                    else Xs[(k * 16 + 4 * e + q) * LD + t * 16 + n] = -r[e];
                 }
             }
             __syncthreads();
         }
-        if (ok) break;
+        if (!failed) break;
+        __syncthreads();  // every wave has read the flag
+        if (tid == 0) failed = 0;
         __syncthreads();
     }
     if (attempt == 4) {
         if (tid == 0) *status = -1;
         return;
     }
-    // The three R x R products below run on FP64 MFMA, one 16 x 16 output
-    // tile per wave.  Every left operand is read transposed (X^T, and the
-    // symmetric Gm and W), so a wave's reads of either operand run along a
-    // row of LDS.
-    const int wave = tid >> 6, lane = tid & 63, nt = (R + 15) / 16;
-    const bool tile_wave = wave < nt * nt;
-    const int ti = tile_wave ? wave / nt : 0, tj = tile_wave ? wave % nt : 0;
-    auto store_tile = [&](const double4_t &acc, double *dst) {
+    // Gm over V (which no wave reads any more); W = X^T X = V^-1 into B
+    for (int e = tid; e < RP * RP; e += kSolveThreads) {
+        const int i = e / RP, j = e - i * RP;
+        A[i * LD + j] = i < R && j < R ? gram_m[i * R + j] : 0.0;
+    }
+    auto tiles = [&](auto product, double *dst) {
+        for (int t = wave; t < nb * nb; t += kSolveThreads / 64) {
+            const int ti = t / nb, tj = t - ti * nb;
+            const double4_t acc = product(ti, tj);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int r = ti * 16 + 4 * e + (lane >> 4), c = tj * 16 + (lane & 15);
-            if (r < R && c < R) dst[r * R + c] = acc[e];
+            for (int e = 0; e < 4; ++e) dst[(ti * 16 + 4 * e + q) * LD + tj * 16 + n] = acc[e];
         }
+        __syncthreads();
     };
-    // W = X^T X = V^-1 into B (L is no longer needed)
-    if (tile_wave) store_tile(solve_mfma_tile(Xs, Xs, R, ti, tj, lane), B);
-    for (int e = tid; e < RR; e += kSolveThreads) A[e] = gram_m[e];
-    __syncthreads();
-    // Tm = Gm W into Xs
-    if (tile_wave) store_tile(solve_mfma_tile(A, B, R, ti, tj, lane), Xs);
-    __syncthreads();
-    // P = W Tm = W Gm W into A (every read of Gm is done)
-    if (tile_wave) store_tile(solve_mfma_tile(B, Xs, R, ti, tj, lane), A);
-    __syncthreads();
+    // X is lower triangular: its blocks above the diagonal were never written
+    tiles([&](int ti, int tj) { return mfma_atb(Xs + ti * 16, Xs + tj * 16, max(ti, tj) * 16, RP, lane); }, B);
+    // Tm = Gm W into Xs, then P = W Tm = W Gm W into A (Gm and W are symmetric)
+    tiles([&](int ti, int tj) { return mfma_atb(A + ti * 16, B + tj * 16, 0, RP, lane); }, Xs);
+    tiles([&](int ti, int tj) { return mfma_atb(B + ti * 16, Xs + tj * 16, 0, RP, lane); }, A);
     // lambda_r^2 = P[r][r]
-    __shared__ double lam_s[64];
     for (int r = tid; r < R; r += kSolveThreads) {
-        const double s2 = A[r * R + r];
+        const double s2 = A[r * LD + r];
         const double l = s2 > 0.0 ? sqrt(s2) : 0.0;
         lam_s[r] = l > 0.0 ? l : 1.0;
         lambda[r] = lam_s[r];
@@ -398,9 +444,11 @@ __device__ __forceinline__ void solve_prep_body(const double *__restrict__ grams
     // P[p][q] / (lambda_p lambda_q).  FP64 throughout, so it is the Gram of
     // the exact product rather than of C rounded to FP32.  Only the other
     // modes' Grams were read above, so the slot of `mode` may be overwritten.
-    if (gram_new)
-        for (int e = tid; e < RR; e += kSolveThreads) gram_new[e] = A[e] / (lam_s[e / R] * lam_s[e % R]);
-    for (int e = tid; e < RR; e += kSolveThreads) S[e] = B[e] / lam_s[e % R];
+    for (int e = tid; e < RR; e += kSolveThreads) {
+        const int i = e / R, j = e - i * R;
+        if (gram_new) gram_new[e] = A[i * LD + j] / (lam_s[i] * lam_s[j]);
+        S[e] = B[i * LD + j] / lam_s[j];
+    }
     if (tid == 0) *status = attempt;
 }
 
