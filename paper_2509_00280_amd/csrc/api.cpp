@@ -608,7 +608,7 @@ spt_status spt_cp_als(spt_tensor t, int rank, int max_iters, double tol, float *
         maxI = std::max(maxI, t->dims[n]);
         gw = std::max(gw, gram_work_bytes(t->dims[n], R));
     }
-    const int inner_parts = apply_blocks(t->dims[N - 1], R);
+    const int inner_parts = apply_blocks(t->dims[N - 1]);
     const int64_t resid_tiles = (t->nnz + 1023) / 1024;
     float *M = (float *)dev_alloc(sizeof(float) * maxI * R, s);
     double *grams = (double *)dev_alloc(sizeof(double) * N * R * R, s);
@@ -654,16 +654,17 @@ spt_status spt_cp_als(spt_tensor t, int rank, int max_iters, double tol, float *
             return st__;         \
         }                        \
     } while (0)
-    for (int k = 0; k < N; ++k) CK(launch_gram(F[k], t->dims[k], R, grams + (size_t)k * R * R, gwork, gw, s));
+    for (int k = 0; k < N; ++k) CK(launch_gram(F[k], t->dims[k], R, grams + (size_t)k * R * R, gwork, gw, nullptr, s));
     double fit = 0.0, fit_prev = 0.0;
     int it = 0;
     while (it < max_iters) {
         for (int n = 0; n < N; ++n) {
             const int64_t In = t->dims[n];
             CK(run_mttkrp(t, (const float *const *)F, R, n, M, s, &ws));
-            CK(launch_gram(M, In, R, gram_m, gwork, gw, s));
-            CK(launch_solve_prep(grams, N, n, R, gram_m, S, lam, status + n, grams + (size_t)n * R * R, s));
-            CK(launch_apply(M, In, R, S, F[n], lam, n == N - 1 ? inner : nullptr, nullptr, s));
+            GramRef gm{};
+            CK(launch_gram(M, In, R, gram_m, gwork, gw, &gm, s));
+            CK(launch_solve_prep(grams, N, n, R, gm, S, lam, status + n, grams + (size_t)n * R * R, s));
+            CK(launch_apply(M, In, R, S, F[n], lam, n == N - 1 ? inner : nullptr, s));
         }
         CK(launch_fit(grams, N, R, lam, inner, inner_parts, t->norm_x2, fitd, s));
         double hf[4];
@@ -743,9 +744,10 @@ spt_status spt_als_update(const double *grams, int nmodes, int mode, int rank, c
         return fail(SPT_E_OOM, "als_update: workspace allocation failed");
     }
     spt_status st = SPT_OK;
-    if (rows > 0) st = launch_gram(M, rows, R, gram_m, gwork, gw, s);
+    GramRef gm{gram_m, 0};
+    if (rows > 0) st = launch_gram(M, rows, R, gram_m, gwork, gw, &gm, s);
     else st = launch_fill_zero((float *)gram_m, 2 * (int64_t)R * R, s);  // FP64 zeros are all-zero bits
-    if (st == SPT_OK) st = launch_solve_prep(grams, nmodes, mode, R, gram_m, S, lam, status, nullptr, s);
+    if (st == SPT_OK) st = launch_solve_prep(grams, nmodes, mode, R, gm, S, lam, status, nullptr, s);
     int hs = 0;
     if (st == SPT_OK && (hipMemcpyAsync(&hs, status, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
                          hipStreamSynchronize(s) != hipSuccess))
@@ -753,7 +755,7 @@ spt_status spt_als_update(const double *grams, int nmodes, int mode, int rank, c
     if (st == SPT_OK && hs < 0)
         st = fail(SPT_E_NOT_SPD, "als_update: normal-equation matrix not positive definite after ridge retries");
     // outputs are written only once the solve is known to have succeeded
-    if (st == SPT_OK && rows > 0) st = launch_apply(M, rows, R, S, C, lam, nullptr, nullptr, s);
+    if (st == SPT_OK && rows > 0) st = launch_apply(M, rows, R, S, C, lam, nullptr, s);
     if (st == SPT_OK &&
         hipMemcpyAsync(lambda, lam, sizeof(double) * R, hipMemcpyDeviceToDevice, s) != hipSuccess)
         st = hip_fail(hipGetLastError(), "als_update: lambda copy");

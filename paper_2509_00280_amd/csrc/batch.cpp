@@ -389,7 +389,7 @@ spt_status BatchEngine::rebuild() {
                 vec4 = vec4 && m->R >= 4;
             }
         const int ld = rmax;
-        const int rw = rmax > 0 ? apply_rows_per_launch_block(rmax) : 1;
+        const int rw = apply_batch_rows();
         int64_t tiles = 0, recs = 0, rows = 0, blocks = 0;
         for (int i = 0; i < A; ++i) {
             Member *m = act[i];

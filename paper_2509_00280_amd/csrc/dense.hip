@@ -7,8 +7,8 @@
 //               Cholesky V = L L^T with a ridge retry, W = V^-1, column norms of
 //               M W from the quadratic form lambda_r^2 = (W (M^T M) W)_rr,
 //               S = W diag(1/lambda).
-//   apply       C = fp32(M S) row block by row block (FP64 FMAs), with the
-//               fit's inner product sum M .* C * lambda fused in.
+//   apply       C = fp32(M S) by 16-row tiles (FP64 MFMA), with the fit's inner
+//               product sum M .* C * lambda fused in.
 //   fit         |Xhat|^2 = lambda^T (Hadamard of all Grams) lambda and the fit.
 #include <algorithm>
 #include <utility>
@@ -20,100 +20,114 @@ namespace spt {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kGramSliceRows1 = 512;   // rows of a Gram slice (one workgroup, 8 waves)
-constexpr int kGramSThreads = 512;
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
 int gram_nb(int R) { return (R + 15) / 16; }
-// row slices (workgroups, one partial each) of the Gram kernel
-int gram_chunks(int64_t rows, int R) {
-    const int ld = gram_nb(R) * 16;
-    int64_t slices = (rows + kGramSliceRows1 - 1) / kGramSliceRows1;
-    const int64_t cap = std::max<int64_t>(4, (int64_t)(32u << 20) / ((int64_t)ld * ld * 8));  // ~32 MB of partials
-    slices = std::min<int64_t>(slices, cap);
-    return (int)std::max<int64_t>(1, slices);
+// 16 x 16 tiles of the upper block triangle; a partial Gram is that many tiles of 256 doubles, row-major inside
+__host__ __device__ constexpr int gram_tiles(int nb) { return nb * (nb + 1) / 2; }
+
+// Row slices (workgroups, one partial each) of the Gram kernel: 256 rows each,
+// two rounds of rows for each of its 8 waves at rank 64, up to the number of
+// workgroups that are resident at once (80 KB of LDS at rank 64: 2 per CU).
+constexpr int kGramRows = 256;
+constexpr int kGramMaxSlices = 512;
+// A Gram of at most this many slices is left to its reader to add up.
+constexpr int kGramDirect = 4;
+int gram_slices_single(int64_t rows) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>((rows + kGramRows - 1) / kGramRows, kGramMaxSlices));
 }
 
-// Partial Grams of row slices, one slice per workgroup of 8 waves (so
-// enough waves keep the row loads in flight while the number of partials
-// stays bounded).  Wave w takes the slice's row groups of 4 rows
-// w UNR + 8 UNR j, ..., accumulates every 16x16 block tile (pb <= qb) of R
-// with FP64 MFMA into independent accumulators, and the waves add their
-// tiles in LDS in wave order (deterministic).  Lane layout of
-// v_mfma_f64_16x16x4_f64: A[m][k] from lane m + 16k, B[k][n] from lane
-// n + 16k, D[m][n] in lane n + 16*(m%4), element m/4.
-template <int NB, int UNR>
-__global__ __launch_bounds__(kGramSThreads) void k_gram_partial(const float *__restrict__ C, int64_t rows, int R,
-                                                                double *__restrict__ work) {
-    constexpr int NT = NB * (NB + 1) / 2, LDP = NB * 16, NWAVE = kGramSThreads / 64;
-    __shared__ double red[LDP * LDP];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t slice = blockIdx.x;
-    const int64_t nslices = gridDim.x;
-    const int64_t r_per = ((rows + nslices - 1) / nslices + 3) / 4 * 4;
-    const int64_t r0 = slice * r_per;
-    const int64_t r1 = min(r0 + r_per, rows);
-    const int kr = lane >> 4, cc = lane & 15;
+// Partial Gram of the rows [r0, r1) (r0 a multiple of 4) of a row-major FP32
+// matrix, by a workgroup of 8 waves.  Wave w takes row groups of 4 rows w, w +
+// 8, ..., UNR of them at a time, and accumulates every upper tile with FP64
+// MFMA (A[m][k] from lane m + 16 k, B[k][n] from lane n + 16 k, D[m][n] in
+// lane n + 16 (m % 4), element m / 4).  The waves' tiles are added in a fixed
+// order in three steps of LDS.  Bound by load latency before the matrix cores
+// (one v_mfma_f64_16x16x4 a tile and 4 rows, 10 tiles at rank 64), so the next
+// UNR groups are loaded, as FP32, while the present ones are multiplied.
+// With one group in flight and one wave after the other adding its tiles, 100k
+// rows at rank 64 took 29 us, and 20 to add up the partials (5 now).
+constexpr int kGramThreads = 512;
+template <int NB>
+constexpr int gram_unr() { return NB <= 2 ? 4 : 2; }
+
+template <int NB>
+__device__ __forceinline__ void gram_slice(const float *__restrict__ C, int ld, int R, int64_t r0, int64_t r1,
+                                           double *__restrict__ out) {
+    constexpr int NT = gram_tiles(NB), NWAVE = kGramThreads / 64, UNR = gram_unr<NB>();
+    __shared__ double red[NWAVE / 2][NT * 256];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
     double4_t acc[NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i) acc[i] = (double4_t){0.0, 0.0, 0.0, 0.0};
-    for (int64_t g0 = r0 / 4 + (int64_t)wave * UNR; g0 * 4 < r1; g0 += (int64_t)NWAVE * UNR) {
-        double v[UNR][NB];
+    float cur[UNR][NB], nxt[UNR][NB];
+    auto load = [&](float (&x)[UNR][NB], int64_t row0) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            const int64_t row = (g0 + u) * 4 + kr;
-            const bool rok = row < r1;
-            const float *rp = C + row * R;
+            const int64_t row = row0 + (int64_t)u * 4 * NWAVE + kr;
+            const float *rp = C + row * ld;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const int c = b * 16 + cc;
-                v[u][b] = (rok && c < R) ? (double)rp[c] : 0.0;
+                x[u][b] = (row < r1 && c < R) ? rp[c] : 0.f;
             }
         }
+    };
+    constexpr int64_t step = (int64_t)4 * NWAVE * UNR;
+    int64_t row0 = r0 + 4 * wave;
+    load(cur, row0);
+    for (; row0 < r1; row0 += step) {
+        load(nxt, row0 + step);
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
+            double v[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) v[b] = (double)cur[u][b];
             int t = 0;
 #pragma unroll
             for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
                 for (int qb = pb; qb < NB; ++qb, ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[u][pb], v[u][qb], acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[pb], v[qb], acc[t], 0, 0, 0);
         }
+#pragma unroll
+        for (int u = 0; u < UNR; ++u)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) cur[u][b] = nxt[u][b];
     }
-    for (int w = 0; w < NWAVE; ++w) {
-        if (wave == w) {
-            int t = 0;
+    if (wave >= NWAVE / 2) {
 #pragma unroll
-            for (int pb = 0; pb < NB; ++pb)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int qb = pb; qb < NB; ++qb, ++t)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int m = 4 * e + (lane >> 4), n = lane & 15;
-                        double &d = red[(pb * 16 + m) * LDP + qb * 16 + n];
-                        d = (w == 0) ? acc[t][e] : d + acc[t][e];
-                    }
-        }
-        __syncthreads();
+            for (int e = 0; e < 4; ++e) red[wave - NWAVE / 2][t * 256 + e * 64 + lane] = acc[t][e];
     }
-    double *wb = work + (size_t)slice * LDP * LDP;
-    for (int e = threadIdx.x; e < LDP * LDP; e += kGramSThreads) wb[e] = red[e];
+    __syncthreads();
+    if (wave < NWAVE / 2) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                double &d = red[wave][t * 256 + e * 64 + lane];
+                d = acc[t][e] + d;
+            }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < NT * 256; e += kGramThreads) out[e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
 }
 
-// Batched Gram in two launches.  (1) One workgroup of 8 waves per row slice
-// of kGramSliceRows rows of an item: wave w takes row groups of 4 rows
-// [4 (w UNR + 8 UNR j), ...) of the slice, accumulates every 16x16 block tile
-// (pb <= qb) with FP64 MFMA, the waves add their tiles in LDS in wave order,
-// and the slice's partial goes to work[first_slice + slice].  (2) One
-// workgroup per item sums its slices in order (deterministic).  Columns at or
-// beyond the item's rank read as 0.
-constexpr int kGramBThreads = 512;
-template <int NB, int UNR>
-__global__ __launch_bounds__(kGramBThreads) void k_gram_batched_partial(const GramItem *__restrict__ items, int count,
-                                                                       double *__restrict__ work) {
-    constexpr int NT = NB * (NB + 1) / 2, LDP = NB * 16, NWAVE = kGramBThreads / 64;
-    __shared__ double red[LDP * LDP];
+template <int NB>
+__global__ __launch_bounds__(kGramThreads) void k_gram_partial(const float *__restrict__ C, int64_t rows, int R,
+                                                               double *__restrict__ work) {
+    const int64_t per = ((rows + gridDim.x - 1) / gridDim.x + 3) / 4 * 4;
+    const int64_t r0 = blockIdx.x * per;
+    gram_slice<NB>(C, R, R, r0, min(r0 + per, rows), work + (size_t)blockIdx.x * gram_tiles(NB) * 256);
+}
+
+// Batched: slice gs of the launch belongs to the last item whose first_slice <= gs.
+template <int NB>
+__global__ __launch_bounds__(kGramThreads) void k_gram_batched_partial(const GramItem *__restrict__ items, int count,
+                                                                      double *__restrict__ work) {
     const int64_t gs = blockIdx.x;
     int lo = 0, hi = count - 1;
     while (lo < hi) {
@@ -122,109 +136,72 @@ __global__ __launch_bounds__(kGramBThreads) void k_gram_batched_partial(const Gr
         else hi = mid - 1;
     }
     const GramItem &it = items[__builtin_amdgcn_readfirstlane(lo)];
-    const float *__restrict__ C = it.C;
     const int64_t r0 = (gs - it.first_slice) * kGramSliceRows;
-    const int64_t rows = min(it.rows, r0 + kGramSliceRows);
-    const int ld = it.ld, R = it.rank;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int kr = lane >> 4, cc = lane & 15;
-    double4_t acc[NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i) acc[i] = (double4_t){0.0, 0.0, 0.0, 0.0};
-    for (int64_t g0 = r0 / 4 + (int64_t)wave * UNR; g0 * 4 < rows; g0 += (int64_t)NWAVE * UNR) {
-        double v[UNR][NB];
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const int64_t row = (g0 + u) * 4 + kr;
-            const bool rok = row < rows;
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int c = b * 16 + cc;
-                v[u][b] = (rok && c < R) ? (double)C[row * ld + c] : 0.0;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            int t = 0;
-#pragma unroll
-            for (int pb = 0; pb < NB; ++pb)
-#pragma unroll
-                for (int qb = pb; qb < NB; ++qb, ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[u][pb], v[u][qb], acc[t], 0, 0, 0);
-        }
-    }
-    for (int w = 0; w < NWAVE; ++w) {
-        if (wave == w) {
-            int t = 0;
-#pragma unroll
-            for (int pb = 0; pb < NB; ++pb)
-#pragma unroll
-                for (int qb = pb; qb < NB; ++qb, ++t)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int m = 4 * e + (lane >> 4), n = lane & 15;
-                        double &d = red[(pb * 16 + m) * LDP + qb * 16 + n];
-                        d = (w == 0) ? acc[t][e] : d + acc[t][e];
-                    }
-        }
-        __syncthreads();
-    }
-    double *wb = work + (size_t)gs * LDP * LDP;
-    for (int e = threadIdx.x; e < LDP * LDP; e += kGramBThreads) wb[e] = red[e];
+    gram_slice<NB>(it.C, it.ld, it.rank, r0, min(it.rows, r0 + kGramSliceRows),
+                   work + (size_t)gs * gram_tiles(NB) * 256);
 }
 
-template <int NB>
-__global__ __launch_bounds__(256) void k_gram_batched_reduce(const GramItem *__restrict__ items,
-                                                             const double *__restrict__ work) {
-    constexpr int LDP = NB * 16;
-    const GramItem &it = items[blockIdx.x];
-    const int R = it.rank;
-    for (int e = threadIdx.x; e < R * R; e += 256) {
-        const int p = e / R, q = e % R;
-        const int a = (p / 16 <= q / 16) ? p : q, b = (p / 16 <= q / 16) ? q : p;
-        double s = 0.0;
-        for (int64_t k = 0; k < it.nslices; ++k) s += work[(size_t)(it.first_slice + k) * LDP * LDP + a * LDP + b];
-        it.G[e] = s;
-    }
-}
-
-// G[p][q] = sum over slices (upper block triangle mirrored), in two
-// deterministic stages: kGramSplit groups of slices, then the groups.
-constexpr int kGramSplit = 64;
-
-__device__ __forceinline__ size_t gram_upper(int e, int R, int ld) {
-    const int p = e / R, q = e % R;
-    const int a = (p / 16 <= q / 16) ? p : q, b = (p / 16 <= q / 16) ? q : p;
-    return (size_t)a * ld + b;
-}
-
-__global__ __launch_bounds__(kThreads) void k_gram_reduce1(const double *__restrict__ work, int nslices, int R,
-                                                           double *__restrict__ w2) {
-    const int nb = (R + 15) / 16, ld = nb * 16;
-    const int e = blockIdx.x * kThreads + threadIdx.x;
-    if (e >= R * R) return;
-    const int y = blockIdx.y, S = gridDim.y;
-    const int c0 = (int)((int64_t)nslices * y / S), c1 = (int)((int64_t)nslices * (y + 1) / S);
-    const size_t off = gram_upper(e, R, ld), stride = (size_t)ld * ld;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int c = c0;
-    for (; c + 4 <= c1; c += 4) {
-        s0 += work[(size_t)c * stride + off];
-        s1 += work[(size_t)(c + 1) * stride + off];
-        s2 += work[(size_t)(c + 2) * stride + off];
-        s3 += work[(size_t)(c + 3) * stride + off];
-    }
-    for (; c < c1; ++c) s0 += work[(size_t)c * stride + off];
-    w2[(size_t)y * R * R + e] = (s0 + s1) + (s2 + s3);
-}
-
-__global__ __launch_bounds__(kThreads) void k_gram_reduce2(const double *__restrict__ w2, int S, int R,
-                                                           double *__restrict__ G) {
-    const int e = blockIdx.x * kThreads + threadIdx.x;
-    if (e >= R * R) return;
+// G = the sum of a Gram's slices, mirrored: a workgroup adds 32 of their
+// elements, 8 threads to an element (every 8th slice each, then in order).
+constexpr int kGramSumElems = 32;
+__device__ __forceinline__ void gram_sum(const double *__restrict__ work, int64_t nslices, int nb, int R,
+                                         double *__restrict__ G) {
+    constexpr int W = kThreads / kGramSumElems;
+    __shared__ double red[W][kGramSumElems];
+    const int stride = gram_tiles(nb) * 256;
+    const int x = threadIdx.x % kGramSumElems, y = threadIdx.x / kGramSumElems;
+    const int e = blockIdx.x * kGramSumElems + x;
     double s = 0.0;
-    for (int y = 0; y < S; ++y) s += w2[(size_t)y * R * R + e];
-    G[e] = s;
+    if (e < stride) {
+        int64_t k = y;
+        for (; k + 7 * W < nslices; k += 8 * W) {
+            double v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = work[(size_t)(k + i * W) * stride + e];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s += v[i];
+        }
+        for (; k < nslices; k += W) s += work[(size_t)k * stride + e];
+    }
+    red[y][x] = s;
+    __syncthreads();
+    if (y == 0 && e < stride) {
+#pragma unroll
+        for (int i = 1; i < W; ++i) s += red[i][x];
+        int t = e >> 8, pb = 0;
+        while (t >= nb - pb) t -= nb - pb, ++pb;
+        const int p = pb * 16 + ((e >> 4) & 15), q = (pb + t) * 16 + (e & 15);
+        if (p < R && q < R) {
+            G[p * R + q] = s;
+            if (t > 0) G[q * R + p] = s;
+        }
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k_gram_sum(const double *__restrict__ work, int nslices, int nb, int R,
+                                                       double *__restrict__ G) {
+    gram_sum(work, nslices, nb, R, G);
+}
+
+__global__ __launch_bounds__(kThreads) void k_gram_sum_batched(const GramItem *__restrict__ items, int nb,
+                                                               const double *__restrict__ work) {
+    const GramItem &it = items[blockIdx.y];
+    gram_sum(work + (size_t)it.first_slice * gram_tiles(nb) * 256, it.nslices, nb, it.rank, it.G);
+}
+
+// Element (i, j) of the Gram that the solve reads: whole, or still in a few slices.
+__device__ __forceinline__ double gram_at(const GramRef &g, int nb, int R, int i, int j) {
+    if (g.slices == 0) return g.p[i * R + j];
+    if (i / 16 > j / 16) {
+        const int x = i;
+        i = j;
+        j = x;
+    }
+    const int pb = i / 16, stride = gram_tiles(nb) * 256;
+    const double *p = g.p + (pb * nb - pb * (pb - 1) / 2 + j / 16 - pb) * 256 + (i & 15) * 16 + (j & 15);
+    double s = 0.0;
+    for (int k = 0; k < g.slices; ++k) s += p[(size_t)k * stride];
+    return s;
 }
 
 // ------------------------------------------------------------------ solve preparation
@@ -325,7 +302,7 @@ __device__ __forceinline__ double4_t mfma_atb(const double *X, const double *Y, 
 }
 
 __device__ __forceinline__ void solve_prep_body(const double *__restrict__ grams, int nmodes, int mode, int R,
-                                                const double *__restrict__ gram_m, double *__restrict__ S,
+                                                const GramRef &gram_m, double *__restrict__ S,
                                                 double *__restrict__ lambda, int *__restrict__ status,
                                                 double *__restrict__ gram_new) {
     constexpr int LD = kSolveLd;
@@ -415,7 +392,7 @@ __device__ __forceinline__ void solve_prep_body(const double *__restrict__ grams
     // Gm over V (which no wave reads any more); W = X^T X = V^-1 into B
     for (int e = tid; e < RP * RP; e += kSolveThreads) {
         const int i = e / RP, j = e - i * RP;
-        A[i * LD + j] = i < R && j < R ? gram_m[i * R + j] : 0.0;
+        A[i * LD + j] = i < R && j < R ? gram_at(gram_m, nb, R, i, j) : 0.0;
     }
     auto tiles = [&](auto product, double *dst) {
         for (int t = wave; t < nb * nb; t += kSolveThreads / 64) {
@@ -453,139 +430,84 @@ __device__ __forceinline__ void solve_prep_body(const double *__restrict__ grams
 }
 
 __global__ __launch_bounds__(kSolveThreads) void k_solve_prep(const double *__restrict__ grams, int nmodes, int mode, int R,
-                                                         const double *__restrict__ gram_m, double *__restrict__ S,
-                                                         double *__restrict__ lambda, int *__restrict__ status,
-                                                         double *__restrict__ gram_new) {
+                                                              GramRef gram_m, double *__restrict__ S,
+                                                              double *__restrict__ lambda, int *__restrict__ status,
+                                                              double *__restrict__ gram_new) {
     solve_prep_body(grams, nmodes, mode, R, gram_m, S, lambda, status, gram_new);
 }
 
 __global__ __launch_bounds__(kSolveThreads) void k_solve_prep_batched(const SolveItem *__restrict__ items, int mode) {
     const SolveItem &it = items[blockIdx.x];
-    solve_prep_body(it.grams, it.nmodes, mode, it.rank, it.gram_m, it.S, it.lambda, it.status + mode,
+    solve_prep_body(it.grams, it.nmodes, mode, it.rank, GramRef{it.gram_m, 0}, it.S, it.lambda, it.status + mode,
                     it.gram_new);
 }
 
 // ------------------------------------------------------------------ apply
-// RP = R padded to 16/32/64; CG = RP/4 column groups of 4; RG = 256/CG row groups of 4 rows.
-template <int RP>
-__device__ __forceinline__ void apply_body(const float *__restrict__ M, int ldm, int64_t rows, int R,
-                                           const double *__restrict__ S, float *__restrict__ C,
-                                           const double *__restrict__ lambda, double *__restrict__ inner_partials,
-                                           int64_t blk) {
-    constexpr int CG = RP / 4, RG = kThreads / CG, RW = RG * 4;
-    __shared__ double sS[RP * RP];
-    __shared__ float sM[RW * RP];
-    __shared__ double red[4];
-    const int tid = threadIdx.x;
-    for (int e = tid; e < RP * RP; e += kThreads) {
-        const int p = e / RP, q = e % RP;
-        sS[e] = (p < R && q < R) ? S[p * R + q] : 0.0;
-    }
-    const int64_t row0 = blk * RW;
-    for (int e = tid; e < RW * RP; e += kThreads) {
-        const int r = e / RP, c = e % RP;
-        const int64_t row = row0 + r;
-        sM[e] = (row < rows && c < R) ? M[row * ldm + c] : 0.f;
-    }
-    __syncthreads();
-    const int cg = tid % CG, rg = tid / CG;
-    const int c0 = cg * 4, rl = rg * 4;
-    double acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[i][q] = 0.0;
-    for (int k = 0; k < R; ++k) {
-        double m[4], s[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) m[i] = (double)sM[(rl + i) * RP + k];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) s[q] = sS[k * RP + c0 + q];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[i][q] = fma(m[i], s[q], acc[i][q]);
-    }
-    double inner = 0.0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t row = row0 + rl + i;
-        if (row < rows) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int c = c0 + q;
-                if (c < R) {
-                    const float v = (float)acc[i][q];
-                    C[row * R + c] = v;
-                    if (inner_partials) inner += (double)sM[(rl + i) * RP + c] * (double)v * lambda[c];
-                }
-            }
-        }
-    }
-    if (inner_partials) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) inner += __shfl_down(inner, off, 64);
-        if ((tid & 63) == 0) red[tid >> 6] = inner;
-        __syncthreads();
-        if (tid == 0) inner_partials[blk] = red[0] + red[1] + red[2] + red[3];
-    }
-}
-
-
-// Single-tensor apply on FP64 MFMA: C = M S for 16-row tiles, one tile per
-// wave at a time (tiles strided over the grid), S (RP x RP) in LDS.  The k
-// index of v_mfma_f64_16x16x4_f64 is only summed over, so step j takes
-// columns kq KS + j (KS = RP / 4) for lane quarter kq: every lane then holds
-// 16 (or RP / 4) contiguous values of its row of M, loaded once per tile.
-// Also the fit's inner product sum_rc M[r][c] C[r][c] lambda[c] per block.
+// C = M S on FP64 MFMA for 16-row tiles t = t0, t0 + dt, ... < t1, one at a
+// time per wave, S (RP x RP) in LDS.  The k index of v_mfma_f64_16x16x4_f64 is
+// only summed over, so step j takes columns kq KS + j (KS = RP / 4) for lane
+// quarter kq: every lane holds KS contiguous values of its row of M, and the
+// next tile's are loaded while this one is multiplied.  Bound by the matrix
+// cores and by bringing S to LDS, which several tiles of a wave share.  Rows
+// of S in LDS lie so that the four quarters' rows fall on both halves of the
+// banks.  Also the fit's inner product sum_rc M[r][c] C[r][c] lambda[c].
+// 100k rows at rank 64: 38 us with a workgroup for every 4 tiles, rank 48
+// padded to 64 and all four quarters on the same banks.
 template <int NB>
-__global__ __launch_bounds__(kThreads) void k_apply_mfma(const float *__restrict__ M, int64_t rows, int R,
-                                                         const double *__restrict__ S, float *__restrict__ C,
-                                                         const double *__restrict__ lambda,
-                                                         double *__restrict__ inner_partials) {
-    constexpr int RP = NB * 16, KS = RP / 4;
-    __shared__ double sS[RP * RP];
+struct ApplyShape {
+    static constexpr int RP = NB * 16, KS = RP / 4;
+    static constexpr int LD = NB == 1 ? 20 : NB == 2 ? 34 : NB == 3 ? 52 : 65;  // LD KS = 16 (mod 32)
+};
+
+template <int NB>
+__device__ __forceinline__ void apply_tiles(const float *__restrict__ M, int ldm, int64_t rows, int R,
+                                            const double *__restrict__ S, float *__restrict__ C,
+                                            const double *__restrict__ lambda, double *__restrict__ inner_out,
+                                            int64_t t0, int64_t dt, int64_t t1) {
+    constexpr int RP = ApplyShape<NB>::RP, KS = ApplyShape<NB>::KS, LD = ApplyShape<NB>::LD;
+    __shared__ double sS[RP * LD];
     __shared__ double red[kThreads / 64];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    for (int e = tid; e < RP * RP; e += kThreads) {
-        const int p = e / RP, q = e % RP;
-        sS[e] = (p < R && q < R) ? S[p * R + q] : 0.0;
-    }
-    __syncthreads();
     const int mrow = lane & 15, kq = lane >> 4;
-    const int64_t ntile = (rows + 15) / 16;
-    const bool vec_ok = R == RP && ((uintptr_t)M & 15u) == 0;
-    double inner = 0.0;
-    for (int64_t t = (int64_t)blockIdx.x * (kThreads / 64) + wave; t < ntile;
-         t += (int64_t)gridDim.x * (kThreads / 64)) {
-        const int64_t r0 = t * 16;
-        const int64_t arow = r0 + mrow;
-        float a[KS];
-        if (vec_ok && arow < rows) {
+    const bool vec_ok = R == RP && (ldm & 3) == 0 && ((uintptr_t)M & 15u) == 0;
+    auto load = [&](float (&a)[KS], int64_t t) {
+        const int64_t row = t * 16 + mrow;
+        if (vec_ok && t < t1 && row < rows) {
             // the lane's KS values are contiguous and 16-byte aligned: vector loads
-            const float4 *mp = reinterpret_cast<const float4 *>(M + arow * R + kq * KS);
+            const float4 *mp = reinterpret_cast<const float4 *>(M + row * ldm + kq * KS);
 #pragma unroll
-            for (int j4 = 0; j4 < KS / 4; ++j4) {
-                const float4 v = mp[j4];
-                a[4 * j4] = v.x;
-                a[4 * j4 + 1] = v.y;
-                a[4 * j4 + 2] = v.z;
-                a[4 * j4 + 3] = v.w;
+            for (int j = 0; j < KS / 4; ++j) {
+                const float4 v = mp[j];
+                a[4 * j] = v.x;
+                a[4 * j + 1] = v.y;
+                a[4 * j + 2] = v.z;
+                a[4 * j + 3] = v.w;
             }
         } else {
 #pragma unroll
             for (int j = 0; j < KS; ++j) {
                 const int c = kq * KS + j;
-                a[j] = (arow < rows && c < R) ? M[arow * R + c] : 0.f;
+                a[j] = (t < t1 && row < rows && c < R) ? M[row * ldm + c] : 0.f;
             }
         }
+    };
+    float a[KS], nxt[KS];
+    load(a, t0);
+    for (int e = tid; e < RP * RP; e += kThreads) {
+        const int p = e / RP, q = e % RP;
+        sS[p * LD + q] = (p < R && q < R) ? S[p * R + q] : 0.0;
+    }
+    __syncthreads();
+    double inner = 0.0;
+    for (int64_t t = t0; t < t1; t += dt) {
+        load(nxt, t + dt);
         double4_t acc[NB];
 #pragma unroll
         for (int cb = 0; cb < NB; ++cb) acc[cb] = (double4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int j = 0; j < KS; ++j) {
             const double av = (double)a[j];
-            const double *srow = sS + (kq * KS + j) * RP + mrow;  // B[k][n] = S[k][cb 16 + n], n = lane & 15
+            const double *srow = sS + (kq * KS + j) * LD + mrow;  // B[k][n] = S[k][cb 16 + n], n = lane & 15
 #pragma unroll
             for (int cb = 0; cb < NB; ++cb)
                 acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, srow[cb * 16], acc[cb], 0, 0, 0);
@@ -594,18 +516,19 @@ __global__ __launch_bounds__(kThreads) void k_apply_mfma(const float *__restrict
         for (int cb = 0; cb < NB; ++cb) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int m = 4 * e + (lane >> 4), n = lane & 15;
-                const int64_t row = r0 + m;
-                const int c = cb * 16 + n;
+                const int64_t row = t * 16 + 4 * e + kq;
+                const int c = cb * 16 + mrow;
                 if (row < rows && c < R) {
                     const float v = (float)acc[cb][e];
                     C[row * R + c] = v;
-                    if (inner_partials) inner += (double)M[row * R + c] * (double)v * lambda[c];
+                    if (inner_out) inner += (double)M[row * ldm + c] * (double)v * lambda[c];
                 }
             }
         }
+#pragma unroll
+        for (int j = 0; j < KS; ++j) a[j] = nxt[j];
     }
-    if (inner_partials) {
+    if (inner_out) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) inner += __shfl_down(inner, off, 64);
         if (lane == 0) red[wave] = inner;
@@ -613,13 +536,24 @@ __global__ __launch_bounds__(kThreads) void k_apply_mfma(const float *__restrict
         if (tid == 0) {
             double sum = 0.0;
             for (int w = 0; w < kThreads / 64; ++w) sum += red[w];
-            inner_partials[blockIdx.x] = sum;
+            *inner_out = sum;
         }
     }
 }
 
-// Batched: block `g` belongs to the last item whose first_block <= g.
-template <int RP>
+template <int NB>
+__global__ __launch_bounds__(kThreads) void k_apply(const float *__restrict__ M, int64_t rows, int R,
+                                                    const double *__restrict__ S, float *__restrict__ C,
+                                                    const double *__restrict__ lambda,
+                                                    double *__restrict__ inner_partials) {
+    apply_tiles<NB>(M, R, rows, R, S, C, lambda, inner_partials ? inner_partials + blockIdx.x : nullptr,
+                    (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6), (int64_t)gridDim.x * (kThreads / 64),
+                    (rows + 15) / 16);
+}
+
+// Batched: block `g` belongs to the last item whose first_block <= g and takes kApplyBatchRows rows of it.
+constexpr int kApplyBatchRows = 128;
+template <int NB>
 __global__ __launch_bounds__(kThreads) void k_apply_batched(const ApplyItem *__restrict__ items, int count) {
     const int64_t g = blockIdx.x;
     int lo = 0, hi = count - 1;
@@ -629,30 +563,30 @@ __global__ __launch_bounds__(kThreads) void k_apply_batched(const ApplyItem *__r
         else hi = mid - 1;
     }
     const ApplyItem &it = items[__builtin_amdgcn_readfirstlane(lo)];
-    apply_body<RP>(it.M, it.ldm, it.rows, it.rank, it.S, it.C, it.lambda, it.inner, g - it.first_block);
+    const int64_t b = g - it.first_block;
+    apply_tiles<NB>(it.M, it.ldm, it.rows, it.rank, it.S, it.C, it.lambda, it.inner ? it.inner + b : nullptr,
+                    b * (kApplyBatchRows / 16) + (threadIdx.x >> 6), kThreads / 64,
+                    min((b + 1) * (kApplyBatchRows / 16), (it.rows + 15) / 16));
 }
 
-template <int RP>
-int apply_rows_per_block() { return (kThreads / (RP / 4)) * 4; }
-
-int apply_rp(int R) { return R <= 16 ? 16 : (R <= 32 ? 32 : 64); }
-
 // ------------------------------------------------------------------ fit
+// One workgroup: R^2 products and up to 1024 partial sums, so as wide as it gets.
+constexpr int kFitThreads = 1024;
 __device__ __forceinline__ void fit_body(const double *__restrict__ grams, int nmodes, int R,
                                          const double *__restrict__ lambda,
                                          const double *__restrict__ inner_partials, int nparts, double norm_x2,
                                          double *__restrict__ out) {
-    __shared__ double red[2][4];
+    __shared__ double red[2][kFitThreads / 64];
     const int tid = threadIdx.x;
     const int RR = R * R;
     double xh = 0.0;
-    for (int e = tid; e < RR; e += kThreads) {
+    for (int e = tid; e < RR; e += kFitThreads) {
         double v = 1.0;
         for (int k = 0; k < nmodes; ++k) v *= grams[(size_t)k * RR + e];
         xh += lambda[e / R] * v * lambda[e % R];
     }
     double in = 0.0;
-    for (int i = tid; i < nparts; i += kThreads) in += inner_partials[i];
+    for (int i = tid; i < nparts; i += kFitThreads) in += inner_partials[i];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         xh += __shfl_down(xh, off, 64);
@@ -664,8 +598,11 @@ __device__ __forceinline__ void fit_body(const double *__restrict__ grams, int n
     }
     __syncthreads();
     if (tid == 0) {
-        const double nxh = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-        const double inner = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+        double nxh = 0.0, inner = 0.0;
+        for (int w = 0; w < kFitThreads / 64; ++w) {
+            nxh += red[0][w];
+            inner += red[1][w];
+        }
         double r2 = norm_x2 + nxh - 2.0 * inner;
         if (r2 < 0.0) r2 = 0.0;
         out[0] = 1.0 - sqrt(r2) / sqrt(norm_x2);
@@ -674,14 +611,14 @@ __device__ __forceinline__ void fit_body(const double *__restrict__ grams, int n
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_fit(const double *__restrict__ grams, int nmodes, int R,
+__global__ __launch_bounds__(kFitThreads) void k_fit(const double *__restrict__ grams, int nmodes, int R,
                                                   const double *__restrict__ lambda,
                                                   const double *__restrict__ inner_partials, int nparts,
                                                   double norm_x2, double *__restrict__ out) {
     fit_body(grams, nmodes, R, lambda, inner_partials, nparts, norm_x2, out);
 }
 
-__global__ __launch_bounds__(kThreads) void k_fit_batched(const FitItem *__restrict__ items) {
+__global__ __launch_bounds__(kFitThreads) void k_fit_batched(const FitItem *__restrict__ items) {
     const FitItem &it = items[blockIdx.x];
     fit_body(it.grams, it.nmodes, it.rank, it.lambda, it.inner, it.nparts, it.norm_x2, it.out);
 }
@@ -730,32 +667,31 @@ __global__ __launch_bounds__(kThreads) void k_fit_direct_batched(const FitDirect
 }  // namespace
 
 size_t gram_work_bytes(int64_t rows, int rank) {
-    const int ld = gram_nb(rank) * 16;
-    return (size_t)gram_chunks(rows, rank) * ld * ld * sizeof(double) + (size_t)kGramSplit * rank * rank * sizeof(double);
+    return (size_t)gram_slices_single(rows) * gram_tiles(gram_nb(rank)) * 256 * sizeof(double);
 }
 
 spt_status launch_gram(const float *C, int64_t rows, int rank, double *G, double *work, size_t work_bytes,
-                       hipStream_t s) {
+                       GramRef *ref, hipStream_t s) {
     if (rank > 64) return fail(SPT_E_INVALID_ARG, "gram: rank above 64");
-    const int chunks = gram_chunks(rows, rank);
     if (gram_work_bytes(rows, rank) > work_bytes) return fail(SPT_E_INVALID_ARG, "gram: workspace too small");
-    const int nb = gram_nb(rank), ld = nb * 16;
-    const dim3 g((unsigned)chunks), b(kGramSThreads);
-    if (nb == 1) hipLaunchKernelGGL((k_gram_partial<1, 4>), g, b, 0, s, C, rows, rank, work);
-    else if (nb == 2) hipLaunchKernelGGL((k_gram_partial<2, 4>), g, b, 0, s, C, rows, rank, work);
-    else if (nb == 3) hipLaunchKernelGGL((k_gram_partial<3, 2>), g, b, 0, s, C, rows, rank, work);
-    else hipLaunchKernelGGL((k_gram_partial<4, 1>), g, b, 0, s, C, rows, rank, work);
-    const int nslices = chunks;
-    const int S = std::min(kGramSplit, nslices);
-    double *w2 = work + (size_t)nslices * ld * ld;
-    const int rb = (rank * rank + kThreads - 1) / kThreads;
-    hipLaunchKernelGGL(k_gram_reduce1, dim3(rb, S), dim3(kThreads), 0, s, work, nslices, rank, w2);
-    hipLaunchKernelGGL(k_gram_reduce2, dim3(rb), dim3(kThreads), 0, s, w2, S, rank, G);
+    const int nb = gram_nb(rank), slices = gram_slices_single(rows);
+    const dim3 g((unsigned)slices), b(kGramThreads);
+    if (nb == 1) hipLaunchKernelGGL(k_gram_partial<1>, g, b, 0, s, C, rows, rank, work);
+    else if (nb == 2) hipLaunchKernelGGL(k_gram_partial<2>, g, b, 0, s, C, rows, rank, work);
+    else if (nb == 3) hipLaunchKernelGGL(k_gram_partial<3>, g, b, 0, s, C, rows, rank, work);
+    else hipLaunchKernelGGL(k_gram_partial<4>, g, b, 0, s, C, rows, rank, work);
+    if (ref && slices <= kGramDirect) {
+        *ref = GramRef{work, slices};
+    } else {
+        hipLaunchKernelGGL(k_gram_sum, dim3(gram_tiles(nb) * 256 / kGramSumElems), dim3(kThreads), 0, s, work, slices, nb,
+                           rank, G);
+        if (ref) *ref = GramRef{G, 0};
+    }
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
-spt_status launch_solve_prep(const double *grams, int nmodes, int mode, int rank, const double *gram_m, double *S,
+spt_status launch_solve_prep(const double *grams, int nmodes, int mode, int rank, const GramRef &gram_m, double *S,
                              double *lambda, int *status_out, double *gram_new, hipStream_t s) {
     if (rank > 64) return fail(SPT_E_INVALID_ARG, "solve: rank above 64");
     hipLaunchKernelGGL(k_solve_prep, dim3(1), dim3(kSolveThreads), 0, s, grams, nmodes, mode, rank, gram_m, S, lambda,
@@ -764,35 +700,30 @@ spt_status launch_solve_prep(const double *grams, int nmodes, int mode, int rank
     return SPT_OK;
 }
 
-constexpr int64_t kApplyMaxBlocks = 2048;
-int apply_blocks(int64_t rows, int rank) {
-    (void)rank;
-    const int64_t tiles = (rows + 15) / 16;  // 16-row MFMA tiles, 4 per block at a time
-    return (int)std::max<int64_t>(1, std::min<int64_t>((tiles + 3) / 4, kApplyMaxBlocks));
+// 4 waves of 16-row tiles a block; from 1024 blocks on (4 per CU at rank 64's
+// 33 KB of LDS) every wave takes the same number of tiles.
+constexpr int64_t kApplyMaxBlocks = 1024;
+int apply_blocks(int64_t rows) {
+    const int64_t quads = ((rows + 15) / 16 + 3) / 4;
+    const int64_t each = std::max<int64_t>(1, (quads + kApplyMaxBlocks - 1) / kApplyMaxBlocks);
+    return (int)std::max<int64_t>(1, (quads + each - 1) / each);
 }
 
-
 spt_status launch_apply(const float *M, int64_t rows, int rank, const double *S, float *C, const double *lambda,
-                        double *inner_partials, int *nparts_out, hipStream_t s) {
-    const int blocks = apply_blocks(rows, rank);
-    const int rp = apply_rp(rank);
-    if (rp == 16)
-        hipLaunchKernelGGL(k_apply_mfma<1>, dim3(blocks), dim3(kThreads), 0, s, M, rows, rank, S, C, lambda,
-                           inner_partials);
-    else if (rp == 32)
-        hipLaunchKernelGGL(k_apply_mfma<2>, dim3(blocks), dim3(kThreads), 0, s, M, rows, rank, S, C, lambda,
-                           inner_partials);
-    else
-        hipLaunchKernelGGL(k_apply_mfma<4>, dim3(blocks), dim3(kThreads), 0, s, M, rows, rank, S, C, lambda,
-                           inner_partials);
+                        double *inner_partials, hipStream_t s) {
+    const dim3 g((unsigned)apply_blocks(rows)), b(kThreads);
+    const int nb = gram_nb(rank);
+    if (nb == 1) hipLaunchKernelGGL(k_apply<1>, g, b, 0, s, M, rows, rank, S, C, lambda, inner_partials);
+    else if (nb == 2) hipLaunchKernelGGL(k_apply<2>, g, b, 0, s, M, rows, rank, S, C, lambda, inner_partials);
+    else if (nb == 3) hipLaunchKernelGGL(k_apply<3>, g, b, 0, s, M, rows, rank, S, C, lambda, inner_partials);
+    else hipLaunchKernelGGL(k_apply<4>, g, b, 0, s, M, rows, rank, S, C, lambda, inner_partials);
     SPT_HIP(hipGetLastError());
-    if (nparts_out) *nparts_out = blocks;
     return SPT_OK;
 }
 
 spt_status launch_fit(const double *grams, int nmodes, int rank, const double *lambda, const double *inner_partials,
                       int nparts, double norm_x2, double *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_fit, dim3(1), dim3(kThreads), 0, s, grams, nmodes, rank, lambda, inner_partials, nparts, norm_x2,
+    hipLaunchKernelGGL(k_fit, dim3(1), dim3(kFitThreads), 0, s, grams, nmodes, rank, lambda, inner_partials, nparts, norm_x2,
                        out);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
@@ -814,8 +745,7 @@ spt_status launch_fit_direct(const double *resid_partials, int nparts, double no
 int64_t gram_slices(int64_t rows) { return std::max<int64_t>(1, (rows + kGramSliceRows - 1) / kGramSliceRows); }
 
 size_t gram_batched_ws_bytes(int64_t total_slices, int rmax) {
-    const size_t ldp = (size_t)gram_nb(rmax) * 16;
-    return (size_t)std::max<int64_t>(total_slices, 1) * ldp * ldp * sizeof(double);
+    return (size_t)std::max<int64_t>(total_slices, 1) * gram_tiles(gram_nb(rmax)) * 256 * sizeof(double);
 }
 
 spt_status launch_gram_batched(const GramItem *items, int count, int64_t total_slices, int rmax, double *work,
@@ -823,19 +753,15 @@ spt_status launch_gram_batched(const GramItem *items, int count, int64_t total_s
     if (count == 0 || total_slices == 0) return SPT_OK;
     if (rmax > 64) return fail(SPT_E_INVALID_ARG, "gram: rank above 64");
     const int nb = gram_nb(rmax);
-    const dim3 g((unsigned)total_slices), b(kGramBThreads);
-    if (nb == 1) {
-        hipLaunchKernelGGL((k_gram_batched_partial<1, 4>), g, b, 0, s, items, count, work);
-        hipLaunchKernelGGL(k_gram_batched_reduce<1>, dim3(count), dim3(256), 0, s, items, work);
-    } else if (nb == 2) {
-        hipLaunchKernelGGL((k_gram_batched_partial<2, 4>), g, b, 0, s, items, count, work);
-        hipLaunchKernelGGL(k_gram_batched_reduce<2>, dim3(count), dim3(256), 0, s, items, work);
-    } else if (nb == 3) {
-        hipLaunchKernelGGL((k_gram_batched_partial<3, 2>), g, b, 0, s, items, count, work);
-        hipLaunchKernelGGL(k_gram_batched_reduce<3>, dim3(count), dim3(256), 0, s, items, work);
-    } else {
-        hipLaunchKernelGGL((k_gram_batched_partial<4, 2>), g, b, 0, s, items, count, work);
-        hipLaunchKernelGGL(k_gram_batched_reduce<4>, dim3(count), dim3(256), 0, s, items, work);
+    const dim3 g((unsigned)total_slices), b(kGramThreads);
+    if (nb == 1) hipLaunchKernelGGL(k_gram_batched_partial<1>, g, b, 0, s, items, count, work);
+    else if (nb == 2) hipLaunchKernelGGL(k_gram_batched_partial<2>, g, b, 0, s, items, count, work);
+    else if (nb == 3) hipLaunchKernelGGL(k_gram_batched_partial<3>, g, b, 0, s, items, count, work);
+    else hipLaunchKernelGGL(k_gram_batched_partial<4>, g, b, 0, s, items, count, work);
+    for (int c0 = 0; c0 < count; c0 += 65535) {  // grid rows
+        const int c = std::min(count - c0, 65535);
+        hipLaunchKernelGGL(k_gram_sum_batched, dim3(gram_tiles(nb) * 256 / kGramSumElems, c), dim3(kThreads), 0, s,
+                           items + c0, nb, work);
     }
     SPT_HIP(hipGetLastError());
     return SPT_OK;
@@ -848,24 +774,23 @@ spt_status launch_solve_prep_batched(const SolveItem *items, int count, int mode
     return SPT_OK;
 }
 
-int apply_rows_per_launch_block(int rmax) {
-    const int rp = apply_rp(rmax);
-    return rp == 16 ? apply_rows_per_block<16>() : (rp == 32 ? apply_rows_per_block<32>() : apply_rows_per_block<64>());
-}
+int apply_batch_rows() { return kApplyBatchRows; }
 
 spt_status launch_apply_batched(const ApplyItem *items, int count, int64_t total_blocks, int rmax, hipStream_t s) {
     if (total_blocks == 0) return SPT_OK;
-    const int rp = apply_rp(rmax);
-    if (rp == 16) hipLaunchKernelGGL(k_apply_batched<16>, dim3((unsigned)total_blocks), dim3(kThreads), 0, s, items, count);
-    else if (rp == 32) hipLaunchKernelGGL(k_apply_batched<32>, dim3((unsigned)total_blocks), dim3(kThreads), 0, s, items, count);
-    else hipLaunchKernelGGL(k_apply_batched<64>, dim3((unsigned)total_blocks), dim3(kThreads), 0, s, items, count);
+    const dim3 g((unsigned)total_blocks), b(kThreads);
+    const int nb = gram_nb(rmax);
+    if (nb == 1) hipLaunchKernelGGL(k_apply_batched<1>, g, b, 0, s, items, count);
+    else if (nb == 2) hipLaunchKernelGGL(k_apply_batched<2>, g, b, 0, s, items, count);
+    else if (nb == 3) hipLaunchKernelGGL(k_apply_batched<3>, g, b, 0, s, items, count);
+    else hipLaunchKernelGGL(k_apply_batched<4>, g, b, 0, s, items, count);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
 spt_status launch_fit_batched(const FitItem *items, int count, hipStream_t s) {
     if (count == 0) return SPT_OK;
-    hipLaunchKernelGGL(k_fit_batched, dim3(count), dim3(kThreads), 0, s, items);
+    hipLaunchKernelGGL(k_fit_batched, dim3(count), dim3(kFitThreads), 0, s, items);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }

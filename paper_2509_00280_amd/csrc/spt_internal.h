@@ -270,7 +270,7 @@ spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t to
 
 // Batched dense steps (dense.hip): one workgroup per item, except apply
 // (a grid over the items' row blocks).
-constexpr int kGramSliceRows = 2048;  // rows per workgroup of the batched Gram
+constexpr int kGramSliceRows = 512;  // rows per workgroup of the batched Gram
 struct GramItem {
     const float *C;   // rows x rank, leading dimension ld
     int64_t rows;
@@ -306,7 +306,7 @@ struct FitItem {
 spt_status launch_gram_batched(const GramItem *items, int count, int64_t total_slices, int rmax, double *work,
                                hipStream_t s);
 spt_status launch_solve_prep_batched(const SolveItem *items, int count, int mode, hipStream_t s);
-int apply_rows_per_launch_block(int rmax);
+int apply_batch_rows();  // rows per block of launch_apply_batched
 spt_status launch_apply_batched(const ApplyItem *items, int count, int64_t total_blocks, int rmax, hipStream_t s);
 spt_status launch_fit_batched(const FitItem *items, int count, hipStream_t s);
 
@@ -477,18 +477,26 @@ struct FitDirectItem {
 spt_status launch_fit_direct_batched(const FitDirectItem *items, int count, hipStream_t s);
 
 // dense.hip
+// A Gram for the solve: rank x rank (slices 0), or the launch's few partial
+// Grams that the solve adds up itself.
+struct GramRef {
+    const double *p;
+    int slices;
+};
+// G = C^T C.  With `ref` the result is *ref, which may leave G unwritten and
+// point into work.
 spt_status launch_gram(const float *C, int64_t rows, int rank, double *G, double *work, size_t work_bytes,
-                       hipStream_t s);
+                       GramRef *ref, hipStream_t s);
 size_t gram_work_bytes(int64_t rows, int rank);
 // solve preparation: V = Hadamard of grams[k != mode]; Cholesky with ridge; W = V^-1;
 // lambda_r = sqrt((W Gm W)_rr) (1 if 0); S = W diag(1/lambda).  status_out: 0 ok, >0 ridge retries, <0 failure.
 // gram_new (or null): the Gram S^T Gm S of the updated factor M S, in FP64 (may be grams + mode * rank^2).
-spt_status launch_solve_prep(const double *grams, int nmodes, int mode, int rank, const double *gram_m,
+spt_status launch_solve_prep(const double *grams, int nmodes, int mode, int rank, const GramRef &gram_m,
                              double *S, double *lambda, int *status_out, double *gram_new, hipStream_t s);
 // C = fp32(M S) row by row; optional fused inner-product partials sum_{i,r} M C lambda.
 spt_status launch_apply(const float *M, int64_t rows, int rank, const double *S, float *C,
-                        const double *lambda, double *inner_partials, int *nparts_out, hipStream_t s);
-int apply_blocks(int64_t rows, int rank);
+                        const double *lambda, double *inner_partials, hipStream_t s);
+int apply_blocks(int64_t rows);  // blocks of launch_apply: one inner-product partial each
 // fit: out[0] = fit (shortcut), out[1] = |Xhat|^2; reads inner partials
 spt_status launch_fit(const double *grams, int nmodes, int rank, const double *lambda,
                       const double *inner_partials, int nparts, double norm_x2, double *out, hipStream_t s);
