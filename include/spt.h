@@ -85,11 +85,11 @@ typedef struct {
 #define SPT_STRATEGY_AUTO 4     /* SEGMENT (measured fastest for small and large output modes);
                                    the autotuner also tries PRIV where it fits */
 #define SPT_STRATEGY_SEGMENT 5  /* each tile regrouped by output row (the plan: positions of every
-                                   nonzero, pieces of at most 64 nonzeros of one row); every piece
-                                   becomes a record written with plain stores at a slot that keeps the
-                                   records grouped by row; records are summed per row (no atomics
-                                   except for rows split between two reducer chunks).  The plan is
-                                   built by spt_tensor_prepare: 2 B per nonzero plus 16 B per piece */
+                                   nonzero and where the rows' runs begin); every run becomes a
+                                   record written with plain stores at a slot that keeps the records
+                                   grouped by row; records are summed per row (no atomics except for
+                                   rows split between two reducer workgroups).  The plan is built by
+                                   spt_tensor_prepare: 2.25 B per nonzero plus 12 B per run */
 typedef struct {
     int tile[SPT_MAX_MODES];      /* nonzeros per workgroup tile: 256..1024 for DIRECT/REGROUP (larger
                                      values act as 1024), 1024/2048/4096 for SEGMENT (smaller values,
@@ -213,7 +213,7 @@ spt_status spt_tensor_set_plan(spt_tensor t, const spt_plan *plan, void *stream)
 /*
  * Build the per-mode state MTTKRP needs under the tensor's plan, for every
  * mode: the SEGMENT plan (a counting pass and one emission pass over the
- * nonzeros: 2 B per nonzero plus 16 B per piece), the tile dictionaries of
+ * nonzeros: 2.25 B per nonzero plus 12 B per run), the tile dictionaries of
  * the row cache (2 B per nonzero per mode plus 4 B per distinct (tile, row)
  * pair) and, under the TABLE strategy, that strategy's plan for `rank`
  * (the only rank-dependent plan).  `what` is a mask of SPT_PREPARE_*.  It is
@@ -261,8 +261,8 @@ spt_status spt_mttkrp(spt_tensor t, const float *const *factors, int rank, int m
  * memory taken from the allocator.  It calls no allocating routine.  The
  * tensor must be prepared (SPT_PREPARE_SINGLE) and its plan for `mode` must
  * be SEGMENT (or AUTO), DIRECT or REGROUP; a workspace above the maximum
- * (records x (8 + 4 rank) bytes, about 0.1 records per nonzero) is rejected
- * with SPT_E_INVALID_ARG.  Every call on one GPU shares the array: calls that
+ * (records x (8 + 4 rank) bytes, counting a record for every 64 nonzeros of a
+ * run, about 0.1 records per nonzero) is rejected with SPT_E_INVALID_ARG.  Every call on one GPU shares the array: calls that
  * overlap on one GPU (on different streams or threads) race, so the caller
  * orders them.  Asynchronous, free of synchronisation.
  */

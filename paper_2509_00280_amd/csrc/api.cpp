@@ -621,9 +621,7 @@ spt_status spt_cp_als(spt_tensor t, int rank, int max_iters, double tol, float *
     double *lam = (double *)dev_alloc(sizeof(double) * R, s);
     // one record workspace for every mode's MTTKRP (the largest plan's records)
     RecordWs ws;
-    ws.records = std::max<int64_t>(max_plan_records(t), 1);
-    ws.val_floats = ws.records * R;
-    ws.row = (uint64_t *)dev_alloc(sizeof(uint64_t) * ws.records, s);
+    ws.val_floats = std::max<int64_t>(max_plan_records(t), 1) * R;
     ws.val = (float *)dev_alloc(sizeof(float) * ws.val_floats, s);
     // the iterations run on copies: the caller's factors and lambda are
     // written only when the call succeeds
@@ -633,10 +631,10 @@ spt_status spt_cp_als(spt_tensor t, int rank, int max_iters, double tol, float *
     auto cleanup = [&]() {
         dev_free(M, s); dev_free(grams, s); dev_free(gram_m, s); dev_free(S, s); dev_free(gwork, s);
         dev_free(inner, s); dev_free(resid, s); dev_free(fitd, s); dev_free(lam, s);
-        dev_free(ws.row, s); dev_free(ws.val, s);
+        dev_free(ws.val, s);
         for (int k = 0; k < N; ++k) dev_free(F[k], s);
     };
-    if (!M || !grams || !gram_m || !S || !gwork || !inner || !resid || !fitd || !lam || !ws.row || !ws.val || !fok) {
+    if (!M || !grams || !gram_m || !S || !gwork || !inner || !resid || !fitd || !lam || !ws.val || !fok) {
         cleanup();
         return fail(SPT_E_OOM, "cp_als: workspace allocation failed");
     }

@@ -52,9 +52,9 @@ int64_t assign_slices(std::vector<GramItem> &v) {
 void set_batch_plan_args(MttkrpArgs &a, const ModePlan &p) {
     a.pl_off = p.pl_off;
     a.pl_pos = p.pl_pos;
-    a.pl_desc = p.pl_desc;
-    a.pl_row = p.pl_row;
-    a.pl_dest = p.pl_dest;
+    a.pl_start = p.pl_start;
+    a.pl_rec = p.pl_rec;
+    a.pl_rec_row = p.rec_row;
     a.rec_cap = p.records;
 }
 
@@ -63,8 +63,7 @@ void set_batch_plan_args(MttkrpArgs &a, const ModePlan &p) {
 // Builds the batched SEGMENT plan of `mode` for every tensor that lacks it,
 // for all of them at once: one counting launch and readback, one emission
 // launch, one sort of all distinct (tile, row) pairs by row of the
-// concatenated output (tensors in order, tile order kept within a row), one
-// scan of their piece counts.  Each tensor's records come out grouped by row,
+// concatenated output (tensors in order, tile order kept within a row).  Each tensor's records come out grouped by row,
 // numbered from 0 within the tensor.
 int batch_tile_of(const Tensor *t) {
     const int b = t->plan.batch_tile;
@@ -111,27 +110,25 @@ spt_status ensure_batch_plans(const std::vector<Tensor *> &ts, int mode, int til
         d_cnt.release(s);
         return st;
     }
-    // offsets: per tensor (local pieces per tile) and batch-wide (pieces, pairs)
+    // offsets: per tensor (local runs per tile) and batch-wide
     std::vector<std::vector<int64_t>> loff(n);
-    std::vector<int64_t> gpiece(tiles), gpair(tiles), piece_base(n + 1, 0);
+    std::vector<int64_t> gpair(tiles);
     int64_t G = 0, Q = 0;
     for (int i = 0; i < n; ++i) {
         const int64_t nt = (need[i]->nnz + tile - 1) / tile;
         loff[i].assign(nt + 1, 0);
-        piece_base[i] = G;
+        items[i].rec_base = Q;
         int64_t local = 0;
         for (int64_t k = 0; k < nt; ++k) {
             const int64_t it = items[i].first_tile + k, c = h[it];
             loff[i][k] = local;
-            gpiece[it] = G + local;
-            gpair[it] = Q;
-            local += c & 0xFFFFFFFFll;
-            Q += c >> 32;
+            gpair[it] = Q + local;
+            G += c & 0xFFFFFFFFll;
+            local += c >> 32;
         }
         loff[i][nt] = local;
-        G += local;
+        Q += local;
     }
-    piece_base[n] = G;
     if (G >= (int64_t(1) << 32)) {
         d_items.release(s);
         d_cnt.release(s);
@@ -141,13 +138,13 @@ spt_status ensure_batch_plans(const std::vector<Tensor *> &ts, int mode, int til
     for (int i = 0; i < n; ++i) {
         Tensor *t = need[i];
         ModePlan &p = t->bplan[mode];
-        const int64_t nt = (int64_t)loff[i].size() - 1, P = loff[i][nt];
+        const int64_t nt = (int64_t)loff[i].size() - 1, P = loff[i][nt], P1 = std::max<int64_t>(P, 1);
         p.pl_off = (int64_t *)dev_alloc(sizeof(int64_t) * (nt + 1), s);
         p.pl_pos = (uint16_t *)dev_alloc(sizeof(uint16_t) * std::max<int64_t>(t->nnz, 1), s);
-        p.pl_desc = (uint32_t *)dev_alloc(sizeof(uint32_t) * std::max<int64_t>(P, 1), s);
-        p.pl_row = (uint32_t *)dev_alloc(sizeof(uint32_t) * std::max<int64_t>(P, 1), s);
-        p.pl_dest = (uint32_t *)dev_alloc(sizeof(uint32_t) * std::max<int64_t>(P, 1), s);
-        if (!p.pl_off || !p.pl_pos || !p.pl_desc || !p.pl_row || !p.pl_dest) {
+        p.pl_start = (spt_u2 *)dev_alloc(sizeof(spt_u2) * std::max<int64_t>(nt, 1) * (tile / 32), s);
+        p.pl_rec = (uint32_t *)dev_alloc(sizeof(uint32_t) * P1, s);
+        p.rec_row = (uint64_t *)dev_alloc(sizeof(uint64_t) * P1, s);
+        if (!p.pl_off || !p.pl_pos || !p.pl_start || !p.pl_rec || !p.rec_row) {
             (void)hipStreamSynchronize(s);  // copies from host vectors may be in flight
             for (int k = 0; k <= i; ++k) release_batch_plan(need[k], mode, s);
             d_items.release(s);
@@ -159,55 +156,33 @@ spt_status ensure_batch_plans(const std::vector<Tensor *> &ts, int mode, int til
         p.records = P;
         p.strategy = SPT_STRATEGY_SEGMENT;
         p.valid = 1;
-        SegItem &it = items[i];
-        it.a.pl_off = p.pl_off;
-        it.a.pl_pos = p.pl_pos;
-        it.a.pl_desc = p.pl_desc;
-        it.a.pl_row = p.pl_row;
-        it.a.pl_dest = p.pl_dest;
-        it.a.rec_cap = P;
+        set_batch_plan_args(items[i].a, p);
     }
     SPT_HIP(hipMemcpyAsync(d_items.p, items.data(), sizeof(SegItem) * n, hipMemcpyHostToDevice, s));
-    const size_t g1 = (size_t)std::max<int64_t>(G, 1), q1 = (size_t)std::max<int64_t>(Q, 1);
-    DevBuf d_gpiece, d_gpair, d_base, ppair, psub, keys, keys2, np, ia, ib, cnt;
-    if (!d_gpiece.get(sizeof(int64_t) * tiles, s) || !d_gpair.get(sizeof(int64_t) * tiles, s) ||
-        !d_base.get(sizeof(int64_t) * (n + 1), s) || !ppair.get(sizeof(uint32_t) * g1, s) ||
-        !psub.get(sizeof(uint32_t) * g1, s) || !keys.get(sizeof(uint64_t) * q1, s) ||
-        !keys2.get(sizeof(uint64_t) * q1, s) || !np.get(sizeof(uint32_t) * q1, s) || !ia.get(sizeof(uint32_t) * q1, s) ||
-        !ib.get(sizeof(uint32_t) * q1, s) ||
-        !cnt.get(sizeof(uint32_t) * std::max(sort_ws_counts(Q), exclusive_scan_ws(Q)), s)) {
+    const size_t q1 = (size_t)std::max<int64_t>(Q, 1);
+    DevBuf d_gpair, keys, keys2, ia, ib, cnt;
+    if (!d_gpair.get(sizeof(int64_t) * tiles, s) || !keys.get(sizeof(uint64_t) * q1, s) ||
+        !keys2.get(sizeof(uint64_t) * q1, s) || !ia.get(sizeof(uint32_t) * q1, s) ||
+        !ib.get(sizeof(uint32_t) * q1, s) || !cnt.get(sizeof(uint32_t) * sort_ws_counts(Q), s)) {
         (void)hipStreamSynchronize(s);
         for (Tensor *t : need) release_batch_plan(t, mode, s);
-        for (DevBuf *b : {&d_items, &d_cnt, &d_gpiece, &d_gpair, &d_base, &ppair, &psub, &keys, &keys2, &np, &ia, &ib, &cnt})
-            b->release(s);
+        for (DevBuf *b : {&d_items, &d_cnt, &d_gpair, &keys, &keys2, &ia, &ib, &cnt}) b->release(s);
         return fail(SPT_E_OOM, "batch plan: workspace");
     }
-    SPT_HIP(hipMemcpyAsync(d_gpiece.p, gpiece.data(), sizeof(int64_t) * tiles, hipMemcpyHostToDevice, s));
     SPT_HIP(hipMemcpyAsync(d_gpair.p, gpair.data(), sizeof(int64_t) * tiles, hipMemcpyHostToDevice, s));
-    SPT_HIP(hipMemcpyAsync(d_base.p, piece_base.data(), sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, s));
-    st = launch_emit_plan_batched((SegItem *)d_items.p, n, tiles, nmax, tile, (int64_t *)d_gpiece.p, (int64_t *)d_gpair.p,
-                                  (uint32_t *)ppair.p, (uint32_t *)psub.p, (uint64_t *)keys.p, (uint32_t *)np.p, s);
+    st = launch_emit_plan_batched((SegItem *)d_items.p, n, tiles, nmax, tile, (int64_t *)d_gpair.p, (uint64_t *)keys.p, s);
     uint64_t *sk = nullptr;
     uint32_t *sidx = nullptr;
     if (st == SPT_OK)
         st = sort_u64_keys_ws((uint64_t *)keys.p, (uint64_t *)keys2.p, (uint32_t *)ia.p, (uint32_t *)ib.p,
                               (uint32_t *)cnt.p, Q, bit_len(rows), &sk, &sidx, s);
-    uint32_t *np_sorted = (sidx == (uint32_t *)ia.p) ? (uint32_t *)ib.p : (uint32_t *)ia.p;
-    uint32_t *tmp = (uint32_t *)((sk == (uint64_t *)keys2.p) ? keys.p : keys2.p);  // free after the sort
-    uint32_t *pair_first = tmp + q1;
-    if (st == SPT_OK) st = launch_gather_u32((uint32_t *)np.p, sidx, np_sorted, Q, s);
-    if (st == SPT_OK) st = launch_exclusive_scan_u32(np_sorted, tmp, Q, (uint32_t *)cnt.p, s);
-    if (st == SPT_OK) st = launch_scatter_u32(tmp, sidx, pair_first, Q, s);
-    if (st == SPT_OK)
-        st = launch_piece_dest_batched((SegItem *)d_items.p, n, (int64_t *)d_base.p, (uint32_t *)ppair.p,
-                                       (uint32_t *)psub.p, pair_first, G, s);
+    if (st == SPT_OK) st = launch_plan_records_batched((SegItem *)d_items.p, n, sk, sidx, Q, s);
     if (st == SPT_OK && hipStreamSynchronize(s) != hipSuccess) st = hip_fail(hipGetLastError(), "batch plan: build");
     if (st != SPT_OK) {
         (void)hipStreamSynchronize(s);
         for (Tensor *t : need) release_batch_plan(t, mode, s);
     }
-    for (DevBuf *b : {&d_items, &d_cnt, &d_gpiece, &d_gpair, &d_base, &ppair, &psub, &keys, &keys2, &np, &ia, &ib, &cnt})
-        b->release(s);
+    for (DevBuf *b : {&d_items, &d_cnt, &d_gpair, &keys, &keys2, &ia, &ib, &cnt}) b->release(s);
     return st;
 }
 
@@ -222,23 +197,22 @@ spt_status prepare_batched(Tensor *t, hipStream_t s) {
 
 // The batched MTTKRP pipeline of one mode into M_all (rows x ld, overwritten).
 spt_status run_mttkrp_batched_mode(const SegItem *d_items, int count, int64_t total_tiles, int nmodes_min, int nmodes_max,
-                                   int tile, int64_t records, int64_t rows, int ld, bool vec4, float *M_all,
-                                   BatchMttkrpWs &ws, hipStream_t s) {
+                                   int tile, const uint64_t *rec_row, int64_t records, int64_t rows, int ld, bool vec4,
+                                   float *M_all, BatchMttkrpWs &ws, hipStream_t s) {
     if (rows == 0) return SPT_OK;
     if (records == 0 || total_tiles == 0) return launch_fill_zero(M_all, rows * (int64_t)ld, s);
     if (records >= (int64_t(1) << 32)) return fail(SPT_E_INVALID_ARG, "batch: more than 2^32 records");
     const size_t n1 = (size_t)records;
-    uint64_t *rrow = (uint64_t *)ws.rec_row.get(sizeof(uint64_t) * n1, s);
     float *rval = (float *)ws.rec_val.get(sizeof(float) * n1 * ld, s);
     unsigned long long *counter = (unsigned long long *)ws.counter.get(256, s);
-    if (!rrow || !rval || !counter) return fail(SPT_E_OOM, "batch: record workspace");
+    if (!rval || !counter) return fail(SPT_E_OOM, "batch: record workspace");
     // the batch's records come out grouped by row: no sort
     const int64_t n = rows * (int64_t)ld;
     const bool fill = !zero_on_the_way(n, total_tiles);
-    spt_status st = launch_mttkrp_seg_batched(d_items, count, total_tiles, nmodes_min, nmodes_max, tile, ld, vec4, rrow,
+    spt_status st = launch_mttkrp_seg_batched(d_items, count, total_tiles, nmodes_min, nmodes_max, tile, ld, vec4,
                                               rval, counter, fill ? nullptr : M_all, n, s);
     if (st == SPT_OK && fill) st = launch_fill_zero(M_all, n, s);
-    if (st == SPT_OK) st = launch_reduce_records(rrow, nullptr, rval, records, ld, rows, M_all, s);
+    if (st == SPT_OK) st = launch_reduce_records(rec_row, nullptr, rval, records, ld, rows, M_all, s);
     return st;
 }
 
@@ -291,7 +265,8 @@ BatchEngine::~BatchEngine() {
 }
 
 void BatchEngine::release_buffers() {
-    for (DevBuf *b : {&items_buf_, &M_buf_, &fit_buf_, &status_buf_, &inner_buf_, &resid_buf_, &resid_items_buf_, &gram_ws_})
+    for (DevBuf *b : {&items_buf_, &M_buf_, &fit_buf_, &status_buf_, &inner_buf_, &resid_buf_, &resid_items_buf_, &gram_ws_,
+                      &rows_buf_})
         b->release(s_);
     d_items_ = nullptr;
     M_all_ = nullptr;
@@ -374,7 +349,7 @@ spt_status BatchEngine::rebuild() {
     int64_t inner_total = 0;
     modes_.assign(nmodes_max_, ModeItems{});
     size_t M_need = 0, gram_need = 0;
-    int64_t max_records = 0;
+    int64_t all_records = 0;
     for (int n = 0; n < nmodes_max_; ++n) {
         ModeItems &mi = modes_[n];
         std::vector<SegItem> seg;
@@ -454,7 +429,8 @@ spt_status BatchEngine::rebuild() {
         mi.rmax = rmax;
         mi.vec4 = vec4;
         M_need = std::max(M_need, sizeof(float) * (size_t)rows * std::max(ld, 1));
-        max_records = std::max(max_records, recs);
+        mi.row_at = all_records;
+        all_records += recs;
         mi.seg_v = std::move(seg);
         mi.gm_slices = assign_slices(gm);
         gram_need = std::max(gram_need, gram_batched_ws_bytes(mi.gm_slices, rmax));
@@ -462,7 +438,6 @@ spt_status BatchEngine::rebuild() {
         mi.sv_v = std::move(sv);
         mi.ap_v = std::move(ap);
     }
-    (void)max_records;
     // device buffers that item pointers refer to (replaced in stream order)
     M_all_ = (float *)M_buf_.get(std::max<size_t>(M_need, 256), s_);
     fit_all_ = (double *)fit_buf_.get(sizeof(double) * 4 * std::max(A, 1), s_);
@@ -527,6 +502,14 @@ spt_status BatchEngine::rebuild() {
     d_items_ = (char *)items_buf_.get(std::max<size_t>(blob_.size(), 256), s_);
     if (!d_items_) return fail(SPT_E_OOM, "batch: item arrays");
     if (!blob_.empty()) SPT_HIP(hipMemcpyAsync(d_items_, blob_.data(), blob_.size(), hipMemcpyHostToDevice, s_));
+    // rows of every mode's records, fixed while the members are
+    uint64_t *rows = (uint64_t *)rows_buf_.get(sizeof(uint64_t) * std::max<int64_t>(all_records, 1), s_);
+    if (!rows) return fail(SPT_E_OOM, "batch: record rows");
+    for (const ModeItems &mi : modes_) {
+        spt_status st = launch_record_rows_batched((const SegItem *)(d_items_ + mi.seg_off), mi.count, mi.records,
+                                                   rows + mi.row_at, s_);
+        if (st != SPT_OK) return st;
+    }
     if (init_count_ > 0) {
         spt_status st = launch_gram_batched((const GramItem *)(d_items_ + init_off_), init_count_, init_slices_,
                                             init_rmax_, (double *)gram_ws_.p, s_);
@@ -553,7 +536,7 @@ spt_status BatchEngine::step(bool *before_kernels) {
         const ModeItems &mi = modes_[n];
         if (mi.count == 0) continue;
         spt_status st = run_mttkrp_batched_mode((const SegItem *)(d_items_ + mi.seg_off), mi.count, mi.tiles, nmodes_min_,
-                                                nmodes_max_, tile_, mi.records, mi.rows, mi.ld, mi.vec4, M_all_, ws_, s_);
+                                                nmodes_max_, tile_, (const uint64_t *)rows_buf_.p + mi.row_at, mi.records, mi.rows, mi.ld, mi.vec4, M_all_, ws_, s_);
         if (st == SPT_OK)
             st = launch_gram_batched((const GramItem *)(d_items_ + mi.gm_off), mi.count, mi.gm_slices, mi.rmax,
                                      (double *)gram_ws_.p, s_);
@@ -710,10 +693,13 @@ spt_status spt_mttkrp_batched(const spt_tensor *ts, int count, const float *cons
         dev_free(M, s);
         return fail(SPT_E_OOM, "mttkrp_batched: workspace");
     }
-    spt_status st = upload_staged(d_items, items.data(), sizeof(SegItem) * items.size(), s);
+    uint64_t *rec_row = (uint64_t *)dev_alloc(sizeof(uint64_t) * std::max<int64_t>(recs, 1), s);
+    spt_status st = rec_row ? upload_staged(d_items, items.data(), sizeof(SegItem) * items.size(), s)
+                            : fail(SPT_E_OOM, "mttkrp_batched: workspace");
     BatchMttkrpWs ws;
+    if (st == SPT_OK) st = launch_record_rows_batched(d_items, (int)items.size(), recs, rec_row, s);
     if (st == SPT_OK)
-        st = run_mttkrp_batched_mode(d_items, (int)items.size(), tiles, nmin, nmax, tile, recs, rows, ld, vec4, M, ws, s);
+        st = run_mttkrp_batched_mode(d_items, (int)items.size(), tiles, nmin, nmax, tile, rec_row, recs, rows, ld, vec4, M, ws, s);
     for (size_t i = 0; st == SPT_OK && i < tv.size(); ++i) {
         const int b = idx[i];
         const int64_t In = tv[i]->dims[mode];
@@ -724,6 +710,7 @@ spt_status spt_mttkrp_batched(const spt_tensor *ts, int count, const float *cons
     }
     // released in stream order after the kernels above: no synchronisation
     ws.release(s);
+    dev_free(rec_row, s);
     dev_free(d_items, s);
     dev_free(M, s);
     return st;

@@ -2,157 +2,142 @@
 // (FP64 values, factors and accumulation, 64-bit keys; Section IV-A).
 //
 // It runs the tensor's SEGMENT plan (positions of every nonzero in its tile's
-// row-grouped order, pieces of one output row, records laid out grouped by
+// row-grouped order, runs of one output row, records laid out grouped by
 // row), which does not depend on the value type:
 //  1. a workgroup of T/4 threads stages one tile of the key-ordered stream:
 //     keys are decoded to the non-output coordinates, which are scattered with
 //     the FP64 values to their plan positions in LDS;
-//  2. lane groups of G lanes (lane j owns columns j, j + G, ...) take the
-//     tile's pieces, gather the N-1 factor rows of each nonzero, form
-//     v * Hadamard(rows) and sum the piece in registers;
-//  3. each piece is stored as one FP64 record at its plan-given slot; a
-//     second kernel sums the records of every row (plain stores for rows whose
-//     records lie in one chunk, FP64 atomics at chunk boundaries).
-#include "tile_common.h"
+//  2. lane groups of ceil(R / 2) lanes, two columns each (LaneGroup), walk
+//     equal shares of the tile (seg_walk.h): they gather the N-1 factor rows
+//     of each nonzero in 16-byte loads, all of a step's before the first is
+//     needed, form v * Hadamard(rows) and sum run by run;
+//  3. each run is stored as one FP64 record at its plan-given slot; a second
+//     kernel sums the records of every row (records.h).
+// Bound by the vector memory path as the FP32 kernel, at twice the bytes a
+// row.  One column a lane, one nonzero in flight and whole pieces of up to 64
+// nonzeros to a group took 6.12 ms for an all-mode sweep (rank 16, 20M
+// nonzeros, 3 modes; 1.48 ms a mode and 0.41 ms for the records' sum), this
+// 3.59 ms.
+#include "records.h"
+#include "seg_walk.h"
 
 namespace spt {
 
 namespace {
 
 __host__ __device__ inline size_t f64_lds_bytes(int T, int nmodes) {
-    return (size_t)(nmodes - 1) * T * 4 + (size_t)T * 8;
+    const size_t staged = (size_t)(nmodes - 1) * T * 4 + (size_t)T * 8;
+    return staged > walk_lds_bytes(T / 4, 4 * sizeof(double)) ? staged : walk_lds_bytes(T / 4, 4 * sizeof(double));
 }
 
-template <int NT, int NMAX, int G, int NB>
+struct FactorsF64 {
+    const double *f[kMaxModes];
+};
+
+template <int NT, int VEC, int NMAX, int NFIX>
 __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const double *__restrict__ vals64, int64_t ntiles,
-                                                       const double *f0, const double *f1, const double *f2,
-                                                       const double *f3, const double *f4, const double *f5,
-                                                       const double *f6, const double *f7,
-                                                       double *__restrict__ rec_val) {
-    constexpr int T = 4 * NT;
+                                                       FactorsF64 F, double *__restrict__ rec_val,
+                                                       double *__restrict__ out) {
+    constexpr int T = 4 * NT, NO = NMAX - 1, UB = NMAX <= 4 && VEC <= 2 ? 2 : 1;
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    const int nm = a.nmodes, mode = a.mode, tid = threadIdx.x, R = a.rank;
-    uint32_t *crdg = (uint32_t *)lds;
-    double *valg = (double *)(crdg + (size_t)(nm - 1) * T);
+    const int nm = NFIX ? NFIX : a.nmodes, no = nm - 1, mode = a.mode, tid = threadIdx.x, R = a.rank;
+    double *valg = (double *)lds;
+    uint32_t *crdg = (uint32_t *)(valg + T);
     const CodecRegs cr = load_codec_regs(a.codec);
     const int64_t base = tile * (int64_t)T;
     const int64_t rem = a.nnz - base;
     const int cnt = rem < T ? (int)rem : T;
     const int nwords = 2 * a.codec.key_words;
+    const int64_t k0 = a.pl_off[tile];
+    const int nruns = (int)min<int64_t>(a.pl_off[tile + 1] - k0, T);
+    uint32_t w[4][4];
+    double v[4];
+    int ps[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int e = tid + u * NT;
+        uint64_t klo = 0, khi = 0;
+        v[u] = 0.0;
+        ps[u] = 0;
         if (e < cnt) {
-            const uint64_t klo = a.lo[base + e];
-            const uint64_t khi = nwords == 4 ? a.hi[base + e] : 0ull;
-            const uint32_t w[4] = {(uint32_t)klo, (uint32_t)(klo >> 32), (uint32_t)khi, (uint32_t)(khi >> 32)};
-            const int q = a.pl_pos[base + e] & (T - 1);
-#pragma unroll
-            for (int k = 0; k < NMAX; ++k)
-                if (k < nm && k != mode) crdg[(k - (k > mode)) * T + q] = decode_mode(cr, k, nwords, w);
-            valg[q] = vals64[base + e];
+            klo = __builtin_nontemporal_load(a.lo + base + e);
+            if (nwords == 4) khi = __builtin_nontemporal_load(a.hi + base + e);
+            v[u] = __builtin_nontemporal_load(vals64 + base + e);
+            ps[u] = a.pl_pos[base + e] & (T - 1);  // a position inside the tile
         }
+        w[u][0] = (uint32_t)klo;
+        w[u][1] = (uint32_t)(klo >> 32);
+        w[u][2] = (uint32_t)khi;
+        w[u][3] = (uint32_t)(khi >> 32);
     }
-    __syncthreads();
-    const double *fk[8] = {f0, f1, f2, f3, f4, f5, f6, f7};
-    const double *fo[NMAX - 1];
+    const LaneGroup lg = lane_group<VEC>(R);
+    const WalkShare ws = walk_share<NT, T>(lg, cnt, UB, a.pl_start + tile * (T / 32));
+    // while the loads above are in flight
+    zero_slice((float *)out, 2 * (int64_t)a.frows[mode] * R, tile, ntiles);
 #pragma unroll
-    for (int o = 0; o < NMAX - 1; ++o) {
-        const int k = o + (o >= mode);
-        fo[o] = k < nm ? fk[k] : nullptr;
-    }
-    const int64_t k0 = a.pl_off[tile], k1 = min(a.pl_off[tile + 1], k0 + T);
-    const int npieces = (int)(k1 - k0);
-    constexpr int NG = NT / G;
-    const int g = tid / G, j = tid % G;
-    for (int k = g; k < npieces; k += NG) {
-        const spt_u4 pc = reinterpret_cast<const spt_u4 *>(a.pl_piece)[k0 + k];
-        const uint32_t d = pc.x, prow = pc.y, dest = pc.z;
-        const int p0 = (int)(d & 0xFFFFu), p1 = min(p0 + (int)(d >> 16), T);
-        if (dest >= (uint64_t)a.rec_cap || p0 >= p1) continue;
-        double acc[NB];
+    for (int k = 0; k < NMAX; ++k) {
+        if (k < nm && k != mode) {
+            uint32_t x[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int b = 0; b < NB; ++b) acc[b] = 0.0;
-        for (int q = p0; q < p1; ++q) {
-            const double v = valg[q];
-            double p[NB];
+            for (int word = 0; word < 4; ++word) {
+                if (word < nwords) {
+                    const int r0 = __builtin_amdgcn_readlane(cr.rb, k * 5 + word);
+                    const int r1 = __builtin_amdgcn_readlane(cr.rb, k * 5 + word + 1);
+                    for (int r = r0; r < r1; ++r) {
+                        const uint32_t d = run_desc(cr, r);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) p[b] = v;
-#pragma unroll
-            for (int o = 0; o < NMAX - 1; ++o) {
-                if (o < nm - 1) {
-                    const uint32_t row = min(crdg[o * T + q], a.frows[o + (o >= mode)] - 1);
-                    const double *src = fo[o] + (size_t)row * R;
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) {
-                        const int c = b * G + j;
-                        p[b] *= c < R ? src[c] : 0.0;
+                        for (int u = 0; u < 4; ++u)
+                            x[u] |= __builtin_amdgcn_ubfe(w[u][word], (d >> 8) & 31u, d >> 24) << ((d >> 16) & 31u);
                     }
                 }
             }
 #pragma unroll
-            for (int b = 0; b < NB; ++b) acc[b] += p[b];
-        }
-        if (j == 0) a.rec_row[dest] = prow;
-        double *dst = rec_val + (size_t)dest * R;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int c = b * G + j;
-            if (c < R) dst[c] = acc[b];
+            for (int u = 0; u < 4; ++u)
+                if (tid + u * NT < cnt) crdg[(k - (k > mode)) * T + ps[u]] = x[u];
         }
     }
-}
-
-// Records grouped by row: each lane group sums a chunk of records column by
-// column; a row whose records all lie in the chunk is stored, a row cut by a
-// chunk boundary is added with FP64 atomics (out zeroed first).
-template <int G, int NB>
-__global__ __launch_bounds__(256) void k_reduce_records_f64(const uint64_t *__restrict__ srow,
-                                                            const double *__restrict__ rec, int64_t P, int R,
-                                                            int chunk, int64_t rows, double *__restrict__ out) {
-    constexpr int GROUPS = 256 / G;
-    const int g = threadIdx.x / G, j = threadIdx.x % G;
-    const int64_t c0 = ((int64_t)blockIdx.x * GROUPS + g) * chunk;
-    if (c0 >= P) return;
-    const int64_t c1 = min(c0 + chunk, P);
-    const uint64_t before = c0 > 0 ? srow[c0 - 1] : ~0ull;
-    const uint64_t after = c1 < P ? srow[c1] : ~0ull;
-    uint64_t cur = srow[c0];
-    bool starts_here = cur != before;
-    double acc[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = 0.0;
-    auto emit = [&](uint64_t r, bool whole) {
-        if (r >= (uint64_t)rows) return;
-        double *o = out + (int64_t)r * R;
+    for (int u = 0; u < 4; ++u)
+        if (tid + u * NT < cnt) valg[ps[u]] = v[u];
+    if (tid < nm && cnt < T) {  // the other half of an odd last step: row 0, value 0
+        if (tid < no) crdg[tid * T + cnt] = 0;
+        else valg[cnt] = 0.0;
+    }
+    __syncthreads();
+    spt_i4 fb[NO];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int c = b * G + j;
-            if (c < R) {
-                if (whole) o[c] = acc[b];
-                else unsafeAtomicAdd(o + c, acc[b]);
-            }
-        }
+    for (int o = 0; o < NO; ++o) {
+        const int k = o + (o >= mode);
+        fb[o] = o < no ? row_rsrc(F.f[k], R, a.frows[k]) : row_rsrc((const double *)nullptr, R, 0u);
+    }
+    const int c = lg.col;
+    auto product = [&](int q0, double (&p)[UB][VEC]) {
+        uint32_t row[NO][UB];
+        double xv[NO][UB][VEC], x[UB];
+        load_words<UB>(valg + q0, x);
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+            if (o < no) load_words<UB>(crdg + o * T + q0, row[o]);
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) p[u][q] = x[u];
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+            if (o < no)
+#pragma unroll
+                for (int u = 0; u < UB; ++u) load_row_vec<VEC>(fb[o], row[o][u], c, xv[o][u]);
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+            if (o < no)
+#pragma unroll
+                for (int u = 0; u < UB; ++u)
+#pragma unroll
+                    for (int q = 0; q < VEC; ++q) p[u][q] *= xv[o][u][q];
     };
-    for (int64_t q = c0; q < c1; ++q) {
-        const uint64_t r = srow[q];
-        if (r != cur) {
-            emit(cur, starts_here);
-            cur = r;
-            starts_here = true;
-#pragma unroll
-            for (int b = 0; b < NB; ++b) acc[b] = 0.0;
-        }
-        const double *src = rec + q * R;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int c = b * G + j;
-            acc[b] += c < R ? src[c] : 0.0;
-        }
-    }
-    emit(cur, starts_here && cur != after);
+    run_walk<double, NT, T, VEC, UB>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, rec_val, R, lds, product);
 }
 
 __global__ __launch_bounds__(256) void k_gather_f64(const double *__restrict__ src, const uint32_t *__restrict__ idx,
@@ -161,35 +146,31 @@ __global__ __launch_bounds__(256) void k_gather_f64(const double *__restrict__ s
         dst[i] = src[idx[i]];
 }
 
-template <int NT, int NMAX, int G, int NB>
-spt_status launch_f64_k(const MttkrpArgs &a, const double *vals64, const double *const *F, int64_t ntiles,
-                        double *rec_val, hipStream_t s) {
+template <int NT, int NMAX, int NFIX>
+spt_status launch_f64_k(const MttkrpArgs &a, const double *vals64, const FactorsF64 &F, int64_t ntiles, double *rec_val,
+                        double *out, hipStream_t s) {
     const size_t lds = f64_lds_bytes(4 * NT, a.nmodes);
-    const double *f[8] = {};
-    for (int k = 0; k < a.nmodes; ++k) f[k] = F[k];
-    hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, NMAX, G, NB>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
-                       ntiles, f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7], rec_val);
+    if (a.rank > 128)  // two columns a lane would be more than a wave
+        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 4, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
+                           ntiles, F, rec_val, out);
+    else if (a.rank >= 2)
+        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 2, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
+                           ntiles, F, rec_val, out);
+    else
+        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 1, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
+                           ntiles, F, rec_val, out);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
-template <int NT, int NMAX>
-spt_status launch_f64_r(const MttkrpArgs &a, const double *vals64, const double *const *F, int64_t ntiles,
-                        double *rec_val, hipStream_t s) {
-    const int R = a.rank;
-    if (R <= 16) return launch_f64_k<NT, NMAX, 16, 1>(a, vals64, F, ntiles, rec_val, s);
-    if (R <= 32) return launch_f64_k<NT, NMAX, 32, 1>(a, vals64, F, ntiles, rec_val, s);
-    if (R <= 64) return launch_f64_k<NT, NMAX, 64, 1>(a, vals64, F, ntiles, rec_val, s);
-    if (R <= 128) return launch_f64_k<NT, NMAX, 64, 2>(a, vals64, F, ntiles, rec_val, s);
-    return launch_f64_k<NT, NMAX, 64, 4>(a, vals64, F, ntiles, rec_val, s);
-}
-
 template <int NT>
-spt_status launch_f64_n(const MttkrpArgs &a, const double *vals64, const double *const *F, int64_t ntiles,
-                        double *rec_val, hipStream_t s) {
-    if (a.nmodes <= 3) return launch_f64_r<NT, 3>(a, vals64, F, ntiles, rec_val, s);
-    if (a.nmodes == 4) return launch_f64_r<NT, 4>(a, vals64, F, ntiles, rec_val, s);
-    return launch_f64_r<NT, 8>(a, vals64, F, ntiles, rec_val, s);
+spt_status launch_f64_n(const MttkrpArgs &a, const double *vals64, const FactorsF64 &F, int64_t ntiles, double *rec_val,
+                        double *out, hipStream_t s) {
+    if (a.nmodes == 3) return launch_f64_k<NT, 3, 3>(a, vals64, F, ntiles, rec_val, out, s);
+    if (a.nmodes == 4) return launch_f64_k<NT, 4, 4>(a, vals64, F, ntiles, rec_val, out, s);
+    if (a.nmodes == 5) return launch_f64_k<NT, 5, 5>(a, vals64, F, ntiles, rec_val, out, s);
+    return a.nmodes < 3 ? launch_f64_k<NT, 3, 0>(a, vals64, F, ntiles, rec_val, out, s)
+                        : launch_f64_k<NT, 8, 0>(a, vals64, F, ntiles, rec_val, out, s);
 }
 
 }  // namespace
@@ -199,34 +180,22 @@ bool f64_tile_ok(int tile, int nmodes) {
 }
 
 spt_status launch_mttkrp_seg_f64(const MttkrpArgs &a, const double *vals64, const double *const *F,
-                                 double *rec_val, hipStream_t s) {
+                                 double *rec_val, double *out, hipStream_t s) {
     const int64_t ntiles = (a.nnz + a.tile - 1) / a.tile;
     if (ntiles == 0) return SPT_OK;
     if (!f64_tile_ok(a.tile, a.nmodes)) return fail(SPT_E_INVALID_ARG, "mttkrp_f64: tile does not fit LDS");
-    if (!a.pl_pos || !a.pl_off || !a.pl_piece) return fail(SPT_E_INVALID_ARG, "mttkrp_f64: no plan");
+    if (!a.pl_pos || !a.pl_off || !a.pl_start || !a.pl_rec) return fail(SPT_E_INVALID_ARG, "mttkrp_f64: no plan");
     if (a.rank > 256) return fail(SPT_E_INVALID_ARG, "mttkrp_f64: rank above 256");
-    if (a.tile == 1024) return launch_f64_n<256>(a, vals64, F, ntiles, rec_val, s);
-    if (a.tile == 2048) return launch_f64_n<512>(a, vals64, F, ntiles, rec_val, s);
-    return launch_f64_n<1024>(a, vals64, F, ntiles, rec_val, s);
+    FactorsF64 f{};
+    for (int k = 0; k < a.nmodes; ++k) f.f[k] = F[k];
+    if (a.tile == 1024) return launch_f64_n<256>(a, vals64, f, ntiles, rec_val, out, s);
+    if (a.tile == 2048) return launch_f64_n<512>(a, vals64, f, ntiles, rec_val, out, s);
+    return launch_f64_n<1024>(a, vals64, f, ntiles, rec_val, out, s);
 }
 
 spt_status launch_reduce_records_f64(const uint64_t *srow, const double *rec, int64_t P, int R, int64_t rows,
                                      double *out, hipStream_t s) {
-    if (P == 0) return SPT_OK;
-    constexpr int chunk = 256;
-    auto go = [&](auto kern, int G) -> spt_status {
-        const int groups = 256 / G;
-        const int64_t nchunks = (P + chunk - 1) / chunk;
-        const int64_t blocks = (nchunks + groups - 1) / groups;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, srow, rec, P, R, chunk, rows, out);
-        SPT_HIP(hipGetLastError());
-        return SPT_OK;
-    };
-    if (R <= 16) return go(k_reduce_records_f64<16, 1>, 16);
-    if (R <= 32) return go(k_reduce_records_f64<32, 1>, 32);
-    if (R <= 64) return go(k_reduce_records_f64<64, 1>, 64);
-    if (R <= 128) return go(k_reduce_records_f64<64, 2>, 64);
-    return go(k_reduce_records_f64<64, 4>, 64);
+    return launch_reduce<double>(srow, nullptr, rec, P, R, rows, out, s);
 }
 
 spt_status launch_gather_f64(const double *src, const uint32_t *idx, double *dst, int64_t n, hipStream_t s) {

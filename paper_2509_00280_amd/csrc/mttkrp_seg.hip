@@ -2,60 +2,47 @@
 //
 // A workgroup of NT threads owns a tile of T = 4 NT consecutive nonzeros of
 // the key-ordered stream.  Conflicts on output rows are resolved by
-// regrouping the tile by output row and cutting every row's run into pieces
-// of at most L nonzeros; each piece is summed in registers (a segmented
-// reduction over equal output index) and written as one record (row, R
-// floats) with plain stores; the records are summed per row afterwards
-// (mttkrp_table.hip).  No atomics on the main path.
+// regrouping the tile by output row: the run of every row is summed in
+// registers (a segmented reduction over equal output index, seg_walk.h) and
+// written as one record (R floats) with plain stores; the records are summed
+// per row afterwards (mttkrp_table.hip).  No atomics on the main path.
 //
 // Plan (once per tensor and mode, the hashing stage below): an LDS hash of
 // the tile's output rows (T slots, linear probing, CAS), one block scan of
-// packed (nonzeros << 16 | pieces) per slot, giving every nonzero its
-// position in row-grouped order and every piece its start, length and row.
-// The (tile, row) pairs are then sorted by row across the tensor (or the
-// batch) and scanned, which lays the records out grouped by row.
+// packed (nonzeros << 16 | occupied) per slot, giving every nonzero its
+// position in row-grouped order, the positions where runs begin, and the
+// (tile, row) pairs, one to a run.  The pairs are then sorted by row across
+// the tensor (or the batch), which lays the records out grouped by row and
+// gives every record its row.
 //
 // Call (the planned kernel): coalesced non-temporal loads of keys, values and
 // plan positions; the non-output coordinates are decoded from the bit runs
 // held in VGPRs and scattered once to LDS in row-grouped order; lane groups
-// (G lanes x VEC columns) take the tile's pieces (stored longest first) in
-// snake order, gather the N-1 factor rows of the piece's nonzeros with
-// buffer loads, form v * Hadamard, sum and store the record at its
-// plan-given slot.  No hashing, atomics or scans at run time.
+// (LaneGroup) walk equal shares of it, gather the N-1 factor rows of each
+// nonzero with buffer loads, form v * Hadamard and sum.  No hashing, atomics
+// or scans over nonzeros at run time.
 //
 // Row-cached call (4096-nonzero tiles, 2..4 modes): the tile dictionaries
 // (per mode, each tile's distinct rows most frequent first, and each
 // nonzero's index in that list) replace the key decode; the first cap rows
 // of every non-output mode's list are copied to LDS and a nonzero reads its
 // factor row there when its index is below cap.
+#include <algorithm>
 #include <atomic>
 
-#include "tile_common.h"
-
-#ifndef SPT_SEG_UB
-#define SPT_SEG_UB 1
-#endif
-#ifndef SPT_SEG_PIECE
-#define SPT_SEG_PIECE 64
-#endif
+#include "seg_walk.h"
 
 namespace spt {
 
 namespace {
 
-constexpr int kPiece = SPT_SEG_PIECE;  // nonzeros per piece (L)
-constexpr int kUnroll = SPT_SEG_UB;    // nonzeros in flight per lane group
-constexpr int kUnrollDict = 2;       // the same, row-cached walk
-#ifndef SPT_SEGP_NT4096
-#define SPT_SEGP_NT4096 1024
-#endif
-constexpr int kSegpThreads4096 = SPT_SEGP_NT4096;  // threads of the MTTKRP kernel on 4096-nonzero tiles
+constexpr int kPiece = 64;  // nonzeros per piece, the measure of spt_mttkrp_noalloc's limit
+constexpr int kSegpThreads4096 = 1024;  // threads of the MTTKRP kernel on 4096-nonzero tiles
 
-// A tile staged together with its hash tables: crdg[nm - 1][T] u32
-// (non-output coordinates, row-grouped), valg[T] f32, hkey[T] u32 (slot ->
-// row), hcnt[T + 4] u32 (packed counts, then prefixes; entry T holds the
-// totals), ptab[T] u16 (piece -> slot).  The budget that decides which tile
-// sizes a tensor of nmodes modes may use (seg_tile_ok).
+// The budget that decides which tile sizes a tensor of nmodes modes may use
+// (seg_tile_ok): nm - 1 coordinates and a value of 4 bytes, the plan passes'
+// hash table of 8 and 2 more per position.  The kernels need less; the sizes
+// on offer are part of the plan's interface and stay.
 __host__ __device__ inline size_t seg_lds_bytes(int T, int nmodes) {
     return (size_t)(nmodes - 1) * T * 4 + (size_t)T * 4 + (size_t)T * 4 + (size_t)(T + 4) * 4 + (size_t)T * 2;
 }
@@ -66,38 +53,30 @@ __host__ __device__ inline size_t segp_lds_bytes(int T, int nmodes) {
 }
 
 struct SegLds {
-    uint32_t *crdg;
-    float *valg;
     uint32_t *hkey;
     uint32_t *hcnt;
-    uint16_t *ptab;
+    uint32_t *bits;
 };
 
-// LDS of the plan's counting and emission passes, which stage nothing:
-// occ[T] u32 (emission's pair index per slot), hkey[T], hcnt[T + 4] u32 and
-// ptab[T] u16.  About half of seg_lds_bytes at 4 modes, so two 1024-thread
-// workgroups share a CU.
-__host__ __device__ inline size_t seg_plan_lds_bytes(int T) { return (size_t)T * 12 + 16 + (size_t)T * 2; }
+// LDS of the plan's counting and emission passes: hkey[T], hcnt[T + 4] and
+// the run starts, T / 32 words.
+__host__ __device__ inline size_t seg_plan_lds_bytes(int T) { return (size_t)T * 8 + 16 + (size_t)T / 8; }
 
 __device__ __forceinline__ SegLds seg_carve_plan(char *p, int T) {
     SegLds L;
-    L.crdg = nullptr;
-    L.valg = (float *)p;
-    L.hkey = (uint32_t *)(L.valg + T);
+    L.hkey = (uint32_t *)p;
     L.hcnt = L.hkey + T;
-    L.ptab = (uint16_t *)(L.hcnt + T + 4);
+    L.bits = L.hcnt + T + 4;
     return L;
 }
 
-// Stage and regroup one tile.  After return: hcnt[s] = (first position of
-// slot s) << 16 | (first piece of slot s); hcnt[T] = (cnt << 16) | pieces;
-// crdg/valg hold the tile in row-grouped order and ptab maps pieces to slots.
-// With SCATTER false only the counts are formed (the plan's counting pass).
-// With pos_out (counting mode only) the row-grouped position of every element
-// is written to pos_out[tile * T + e] and the piece table is built as well.
-template <int NT, int NMAX, bool SCATTER>
-__device__ __forceinline__ void seg_stage(const MttkrpArgs &a, int64_t tile, const SegLds &L, const CodecRegs &cr,
-                                          uint32_t *wsum, uint16_t *__restrict__ pos_out = nullptr) {
+// Hash one tile by output row.  After return: hkey[s] = row of slot s, hcnt[s]
+// = (first position of slot s) << 16 | (occupied slots before s), hcnt[T] =
+// (nonzeros << 16) | distinct rows, and sr[u] = slot << 16 | rank within the
+// slot of this thread's nonzero u (e = threadIdx.x + u NT).
+template <int NT>
+__device__ __forceinline__ int seg_hash(const MttkrpArgs &a, int64_t tile, const SegLds &L, const CodecRegs &cr,
+                                        uint32_t *wsum, uint32_t (&sr)[4]) {
     constexpr int T = 4 * NT;
     const int tid = threadIdx.x;
     const int64_t base = tile * (int64_t)T;
@@ -108,56 +87,35 @@ __device__ __forceinline__ void seg_stage(const MttkrpArgs &a, int64_t tile, con
         L.hcnt[i] = 0;
     }
     uint32_t w[4][4];
-    float v[4];
     const int nwords = 2 * a.codec.key_words;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int e = tid + u * NT;
         uint64_t klo = 0, khi = 0;
-        float x = 0.f;
         if (e < cnt) {
             klo = __builtin_nontemporal_load(a.lo + base + e);
             if (nwords == 4) khi = __builtin_nontemporal_load(a.hi + base + e);
-            if (SCATTER) x = __builtin_nontemporal_load(a.vals + base + e);
         }
         w[u][0] = (uint32_t)klo;
         w[u][1] = (uint32_t)(klo >> 32);
         w[u][2] = (uint32_t)khi;
         w[u][3] = (uint32_t)(khi >> 32);
-        v[u] = x;
     }
-    // coordinates of every mode (only the output mode when counting)
-    uint32_t xc[NMAX][4];
+    uint32_t rowv[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int k = 0; k < NMAX; ++k) {
+    for (int word = 0; word < 4; ++word) {
+        if (word < nwords) {
+            const int r0 = __builtin_amdgcn_readlane(cr.rb, a.mode * 5 + word);
+            const int r1 = __builtin_amdgcn_readlane(cr.rb, a.mode * 5 + word + 1);
+            for (int r = r0; r < r1; ++r) {
+                const uint32_t d = run_desc(cr, r);
+                const uint32_t kpos = (d >> 8) & 31u, cpos = (d >> 16) & 31u, len = d >> 24;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) xc[k][u] = 0;
-        if (k < a.nmodes && (SCATTER || k == a.mode)) {
-#pragma unroll
-            for (int word = 0; word < 4; ++word) {
-                if (word < nwords) {
-                    const int r0 = __builtin_amdgcn_readlane(cr.rb, k * 5 + word);
-                    const int r1 = __builtin_amdgcn_readlane(cr.rb, k * 5 + word + 1);
-                    for (int r = r0; r < r1; ++r) {
-                        const uint32_t d = run_desc(cr, r);
-                        const uint32_t kpos = (d >> 8) & 31u, cpos = (d >> 16) & 31u, len = d >> 24;
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) xc[k][u] |= __builtin_amdgcn_ubfe(w[u][word], kpos, len) << cpos;
-                    }
-                }
+                for (int u = 0; u < 4; ++u) rowv[u] |= __builtin_amdgcn_ubfe(w[u][word], kpos, len) << cpos;
             }
         }
     }
-    uint32_t rowv[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        rowv[u] = 0;
-#pragma unroll
-        for (int k = 0; k < NMAX; ++k)
-            if (k == a.mode) rowv[u] = xc[k][u];
-    }
     __syncthreads();  // hash cleared
-    uint32_t sr[4];   // slot << 16 | rank within the slot
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int e = tid + u * NT;
@@ -174,229 +132,26 @@ __device__ __forceinline__ void seg_stage(const MttkrpArgs &a, int64_t tile, con
         }
     }
     __syncthreads();
-    // packed (count << 16 | pieces) per slot, then one exclusive scan
-    for (int i = tid; i < T; i += NT) {
+    return cnt;
+}
+
+// (count << 16 | occupied) per slot, then one exclusive scan (see seg_hash)
+template <int NT>
+__device__ __forceinline__ void seg_scan(const SegLds &L, int cnt, uint32_t *wsum) {
+    constexpr int T = 4 * NT;
+    for (int i = threadIdx.x; i < T; i += NT) {
         const uint32_t c = L.hcnt[i];
-        L.hcnt[i] = (c << 16) | ((c + kPiece - 1) / kPiece);
+        L.hcnt[i] = (c << 16) | (c > 0 ? 1u : 0u);
     }
     __syncthreads();
     block_scan_lds(L.hcnt, T, NT, wsum);
-    if (tid == 0) {
-        // totals: elements = cnt; pieces = prefix of the last slot plus its own pieces
-        const uint32_t pl = L.hcnt[T - 1] & 0xFFFFu;
-        const uint32_t el = L.hcnt[T - 1] >> 16;
-        const uint32_t own = (uint32_t)cnt - el;
-        L.hcnt[T] = ((uint32_t)cnt << 16) | (pl + (own + kPiece - 1) / kPiece);
-    }
-    if (SCATTER || pos_out) {
-        const int nm = a.nmodes, mode = a.mode;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = tid + u * NT;
-            if (e < cnt) {
-                const int pos = (int)(L.hcnt[sr[u] >> 16] >> 16) + (int)(sr[u] & 0xFFFFu);
-                if constexpr (SCATTER) {
-                    L.valg[pos] = v[u];
-#pragma unroll
-                    for (int k = 0; k < NMAX; ++k)
-                        if (k < nm && k != mode) L.crdg[(k - (k > mode)) * T + pos] = xc[k][u];
-                } else {
-                    pos_out[base + e] = (uint16_t)pos;
-                }
-            }
-        }
-        __syncthreads();  // totals visible
-        for (int i = tid; i < T; i += NT) {
-            const uint32_t pk = L.hcnt[i];
-            const uint32_t nx = i + 1 < T ? L.hcnt[i + 1] : L.hcnt[T];
-            const uint32_t c = (nx >> 16) - (pk >> 16);
-            const uint32_t p0 = pk & 0xFFFFu, np = (c + kPiece - 1) / kPiece;
-            for (uint32_t q = 0; q < np; ++q) L.ptab[p0 + q] = (uint16_t)i;
-        }
+    if (threadIdx.x == 0) {
+        // totals: elements = cnt; distinct rows = prefix of the last slot plus its own
+        const uint32_t pk = L.hcnt[T - 1];
+        L.hcnt[T] = ((uint32_t)cnt << 16) | ((pk & 0xFFFFu) + ((uint32_t)cnt > (pk >> 16) ? 1u : 0u));
     }
     __syncthreads();
 }
-
-// Walk the staged tile: every piece (nonzeros [p0, p1) of the row-grouped
-// tile, one output row) becomes one record of ld floats (columns R..ld-1
-// zero) at the position the piece source gives, with row row_base + its row.
-// With at most 5 modes every nonzero slot of an unrolled step reads all its
-// coordinates from LDS first, then issues every factor-row gather, then waits
-// once; with more modes the gathers go mode by mode.  NFIX > 0: the tensor has
-// exactly NFIX modes (no run-time mode test between the gathers, which would
-// otherwise make the compiler wait for one mode's rows before the next
-// mode's gathers are issued).
-// DICT: a crdg entry is either the byte offset in `ldsb` of a row held in
-// the LDS row cache (at most lim, the offset of the cache's last row) or, with
-// kDictMiss set, a global row.  Every lane reads its step's rows from LDS
-// first, then the lanes whose row is global load it over the LDS value.
-template <int NT, int T, int VEC, int NMAX, int NFIX, class Pieces, bool DICT = false>
-__device__ __forceinline__ void seg_walk(const MttkrpArgs &a, const uint32_t *__restrict__ crdg,
-                                         const float *__restrict__ valg, int npieces, const Pieces &pieces,
-                                         uint64_t *__restrict__ rec_row, float *__restrict__ rec_val, int ld,
-                                         int64_t row_base, const char *__restrict__ ldsb = nullptr, uint32_t lim = 0) {
-    constexpr int UB = DICT ? kUnrollDict : kUnroll;
-    constexpr int NO = NMAX - 1;  // non-output modes at most
-    static_assert(NFIX == 0 || NFIX == NMAX, "a fixed mode count is the maximum");
-    static_assert(!DICT || NMAX <= 4, "the row cache serves at most 3 non-output modes");
-    const int R = a.rank, mode = a.mode, no = NFIX ? NFIX - 1 : a.nmodes - 1;
-    const LaneGroup lg = lane_group<VEC>(R);
-    if (npieces <= 0 || !lg.on) return;
-    const int c = lg.col;
-    // factor of the o-th non-output mode as a row buffer
-    spt_i4 fb[NO];
-#pragma unroll
-    for (int o = 0; o < NO; ++o) {
-        const int k = o + (o >= mode);
-        fb[o] = o < no ? row_rsrc(a.f[k], R, a.frows[k]) : row_rsrc(nullptr, R, 0u);
-    }
-    const int NG = NT / 64 * lg.per_wave;
-    // pieces are dealt in snake order (round r: group g, then NG - 1 - g),
-    // which balances the groups when the plan lists the pieces longest first
-    const int g = lg.g;
-    const int nr = (npieces + NG - 1) / NG;
-    auto kof = [&](int r) { return min(r * NG + ((r & 1) ? NG - 1 - g : g), npieces - 1); };
-    typename Pieces::Raw cur = pieces.fetch(kof(0));
-    for (int r = 0; r < nr; ++r) {
-        const int k = r * NG + ((r & 1) ? NG - 1 - g : g);
-        // the next piece's descriptor is fetched while this one is walked
-        const typename Pieces::Raw nxt = pieces.fetch(kof(r + 1));
-        int p0, p1;
-        uint32_t prow;
-        int64_t pos;
-        const bool live = k < npieces && pieces.decode(k, cur, p0, p1, prow, pos);
-        cur = nxt;
-        if (!live) continue;
-        float acc[VEC];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
-        for (int q = p0; q < p1; q += UB) {
-            int pp[UB];
-            float x[UB];
-#pragma unroll
-            for (int u = 0; u < UB; ++u) {
-                const bool ok = q + u < p1;
-                pp[u] = ok ? q + u : p1 - 1;  // in range either way; the value is zeroed
-                const float v = valg[pp[u]];
-                x[u] = ok ? v : 0.f;
-            }
-            float p[UB][VEC];
-#pragma unroll
-            for (int u = 0; u < UB; ++u)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) p[u][v] = x[u];
-            if constexpr (NO <= 4) {
-                uint32_t row[NO][UB];
-#pragma unroll
-                for (int o = 0; o < NO; ++o)
-                    if (o < no)
-#pragma unroll
-                        for (int u = 0; u < UB; ++u) row[o][u] = crdg[o * T + pp[u]];
-                float xv[NO][UB][VEC];
-                if constexpr (DICT) {
-                    // every index read of the step is issued before anything
-                    // waits for one (the scheduler may not hoist a use between them)
-                    __builtin_amdgcn_sched_barrier(0);
-                    // Every lane first reads LDS (a miss reads the last cached
-                    // row: its entry, flag set, clamps to lim), then the misses
-                    // load their rows globally into the same registers.  A global
-                    // load into the registers of an LDS read waits for that read;
-                    // with all LDS reads of the step issued first the loads wait
-                    // for one LDS round trip, and no branch splits hits from misses.
-#pragma unroll
-                    for (int o = 0; o < NO; ++o) {
-#pragma unroll
-                        for (int u = 0; u < UB; ++u) {
-                            const uint32_t off = min(row[o][u], lim);
-                            if (o < no) {
-                                const float *cp = reinterpret_cast<const float *>(ldsb + off) + lg.j * VEC;
-                                load_vec<VEC>(cp, xv[o][u]);
-                            }
-                        }
-                    }
-#pragma unroll
-                    for (int o = 0; o < NO; ++o)
-                        if (o < no)
-#pragma unroll
-                            for (int u = 0; u < UB; ++u) {
-                                const uint32_t rv = row[o][u];
-                                if (rv & kDictMiss) load_row_vec<VEC>(fb[o], rv & ~kDictMiss, c, xv[o][u]);
-                            }
-                } else {
-#pragma unroll
-                    for (int o = 0; o < NO; ++o)
-                        if (o < no)
-#pragma unroll
-                            for (int u = 0; u < UB; ++u) load_row_vec<VEC>(fb[o], row[o][u], c, xv[o][u]);
-                }
-#pragma unroll
-                for (int o = 0; o < NO; ++o)
-                    if (o < no)
-#pragma unroll
-                        for (int u = 0; u < UB; ++u)
-#pragma unroll
-                            for (int v = 0; v < VEC; ++v) p[u][v] *= xv[o][u][v];
-            } else {
-#pragma unroll
-                for (int o = 0; o < NO; ++o) {
-                    if (o < no) {
-                        float xv[UB][VEC];
-#pragma unroll
-                        for (int u = 0; u < UB; ++u) load_row_vec<VEC>(fb[o], crdg[o * T + pp[u]], c, xv[u]);
-#pragma unroll
-                        for (int u = 0; u < UB; ++u)
-#pragma unroll
-                            for (int v = 0; v < VEC; ++v) p[u][v] *= xv[u][v];
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < UB; ++u)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) acc[v] += p[u][v];
-        }
-        if (lg.j == 0) rec_row[pos] = (uint64_t)(row_base + prow);
-        float *o = rec_val + pos * ld;
-        store_vec<VEC>(o + c, acc);
-        for (int z = R + lg.j; z < ld; z += lg.G) o[z] = 0.f;
-    }
-}
-
-// Pieces given by the plan, read from global memory (the tile's range
-// starts at k0).  Reads stay inside the tile and a record outside the plan's
-// range is never written, whatever the plan holds.
-template <int T>
-struct PlanPieces {
-    const uint32_t *__restrict__ pdesc, *__restrict__ prow, *__restrict__ pdst;
-    int64_t k0, cap, rec_base;
-    struct Raw {
-        uint32_t d, r, x;
-    };
-    __device__ __forceinline__ Raw fetch(int k) const { return Raw{pdesc[k0 + k], prow[k0 + k], pdst[k0 + k]}; }
-    __device__ __forceinline__ bool decode(int, const Raw &q, int &p0, int &p1, uint32_t &row, int64_t &pos) const {
-        p0 = (int)(q.d & 0xFFFFu);
-        p1 = min(p0 + (int)(q.d >> 16), T);
-        row = q.r;
-        pos = rec_base + q.x;
-        return q.x < cap && p0 < p1;
-    }
-};
-
-// The same from the packed plan of one tensor: one 16-byte load per piece.
-template <int T>
-struct PackedPieces {
-    const spt_u4 *__restrict__ pk;
-    int64_t k0, cap;
-    using Raw = spt_u4;
-    __device__ __forceinline__ Raw fetch(int k) const { return pk[k0 + k]; }
-    __device__ __forceinline__ bool decode(int, const Raw &q, int &p0, int &p1, uint32_t &row, int64_t &pos) const {
-        p0 = (int)(q.x & 0xFFFFu);
-        p1 = min(p0 + (int)(q.x >> 16), T);
-        row = q.y;
-        pos = q.z;
-        return q.z < cap && p0 < p1;
-    }
-};
 
 // The part of the output that a tile's workgroup zeroes for the record
 // reduction that follows: slice i of `of` of n floats.
@@ -405,26 +160,92 @@ struct ZeroSlice {
     int64_t n, i, of;
 };
 
+// The uncached walk over crdg[no][T] (row-grouped factor rows) and valg[T].
+// With at most 5 modes every nonzero slot of a step reads all its coordinates
+// from LDS first, then issues every factor-row gather, then waits once; with
+// more modes the gathers go mode by mode.  NFIX > 0: the tensor has exactly
+// NFIX modes (no run-time mode test between the gathers, which would otherwise
+// make the compiler wait for one mode's rows before the next mode's gathers
+// are issued).
+__host__ __device__ constexpr int segp_step(int nmax) { return nmax <= 4 ? 2 : 1; }  // nonzeros of a step
+template <int NT, int T, int VEC, int NMAX, int NFIX>
+__device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const LaneGroup &lg, const WalkShare &ws,
+                                          int cnt, int64_t k0, int nruns, float *__restrict__ rec_val, int ld) {
+    constexpr int NO = NMAX - 1;  // non-output modes at most
+    constexpr int UB = segp_step(NMAX);
+    static_assert(NFIX == 0 || NFIX == NMAX, "a fixed mode count is the maximum");
+    const int R = a.rank, mode = a.mode, no = NFIX ? NFIX - 1 : a.nmodes - 1;
+    const uint32_t *crdg = reinterpret_cast<const uint32_t *>(lds);
+    const float *valg = reinterpret_cast<const float *>(crdg + (size_t)no * T);
+    const int c = lg.col;
+    // factor of the o-th non-output mode as a row buffer
+    spt_i4 fb[NO];
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+        const int k = o + (o >= mode);
+        fb[o] = o < no ? row_rsrc(a.f[k], R, a.frows[k]) : row_rsrc((const float *)nullptr, R, 0u);
+    }
+    auto product = [&](int q, float (&p)[UB][VEC]) {
+        float x[UB];
+        load_words<UB>(valg + q, x);
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) p[u][v] = x[u];
+        if constexpr (NO <= 4) {
+            uint32_t row[NO][UB];
+#pragma unroll
+            for (int o = 0; o < NO; ++o)
+                if (o < no) load_words<UB>(crdg + o * T + q, row[o]);
+            float xv[NO][UB][VEC];
+#pragma unroll
+            for (int o = 0; o < NO; ++o)
+                if (o < no)
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) load_row_vec<VEC>(fb[o], row[o][u], c, xv[o][u]);
+#pragma unroll
+            for (int o = 0; o < NO; ++o)
+                if (o < no)
+#pragma unroll
+                    for (int u = 0; u < UB; ++u)
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) p[u][v] *= xv[o][u][v];
+        } else {
+#pragma unroll
+            for (int o = 0; o < NO; ++o) {
+                if (o < no) {
+                    float xv[UB][VEC];
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) load_row_vec<VEC>(fb[o], crdg[o * T + q + u], c, xv[u]);
+#pragma unroll
+                    for (int u = 0; u < UB; ++u)
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) p[u][v] *= xv[u][v];
+                }
+            }
+        }
+    };
+    run_walk<float, NT, T, VEC, UB>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, rec_val, ld, lds, product);
+}
+
 // Planned SEGMENT kernel.  The plan holds, per nonzero, its position in the
-// tile's row-grouped order (u16) and, per piece, (start | length << 16, row,
-// record), with the records of one row contiguous.  A tile is staged by one
-// scatter of values and non-output coordinates to their positions; there is
-// no hashing, no atomic and no scan at run time.
-// PACKED: the pieces come from a.pl_piece (one tensor, records from 0);
-// otherwise from a.pl_desc / pl_row / pl_dest with records from rec_base
-// (a batched member).
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool PACKED>
-__device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, char *lds, uint64_t *__restrict__ rec_row,
-                                          float *__restrict__ rec_val, int ld, int64_t rec_base, int64_t row_base,
-                                          const ZeroSlice &zero) {
+// tile's row-grouped order (u16), per position whether a run begins there
+// (one bit) and per run its record, with the records of one row contiguous.
+// A tile is staged by one scatter of values and non-output coordinates to
+// their positions; there is no hashing and no scan over nonzeros at run time.
+// Records of ld floats go to rec_val.
+template <int NT, int T, int VEC, int NMAX, int NFIX>
+__device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, char *lds,
+                                          float *__restrict__ rec_val, int ld, const ZeroSlice &zero) {
     constexpr int PER = T / NT;  // nonzeros staged per thread
     static_assert(PER * NT == T && PER >= 1 && PER <= 8, "tile must be 1..8 nonzeros per thread");
     const int nm = NFIX ? NFIX : a.nmodes, mode = a.mode, tid = threadIdx.x;
     uint32_t *crdg = (uint32_t *)lds;
     float *valg = (float *)(crdg + (size_t)(nm - 1) * T);
     const CodecRegs cr = load_codec_regs(a.codec);
-    const int64_t k0 = a.pl_off[tile], k1 = min(a.pl_off[tile + 1], k0 + T);  // a tile has at most T pieces
-    const int npieces = (int)(k1 - k0);
+    const int64_t k0 = a.pl_off[tile];
+    const int nruns = (int)min<int64_t>(a.pl_off[tile + 1] - k0, T);
+    const LaneGroup lg = lane_group<VEC>(a.rank);
     const int64_t base = tile * (int64_t)T;
     const int64_t rem = a.nnz - base;
     const int cnt = rem < T ? (int)rem : T;
@@ -451,6 +272,7 @@ __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, cha
         v[u] = x;
         ps[u] = q;
     }
+    const WalkShare ws = walk_share<NT, T>(lg, cnt, segp_step(NMAX), a.pl_start + tile * (T / 32));
     zero_slice(zero.p, zero.n, zero.i, zero.of);  // while the loads above are in flight
     // decode the non-output coordinates and scatter them with the values
 #pragma unroll
@@ -481,15 +303,12 @@ __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, cha
 #pragma unroll
     for (int u = 0; u < PER; ++u)
         if (tid + u * NT < cnt) valg[ps[u]] = v[u];
+    if (tid < nm && cnt < T) {  // the other half of an odd last step: row 0, value 0
+        if (tid < nm - 1) crdg[tid * T + cnt] = 0;
+        else valg[cnt] = 0.f;
+    }
     __syncthreads();
-    if constexpr (PACKED)
-        seg_walk<NT, T, VEC, NMAX, NFIX>(
-            a, crdg, valg, npieces, PackedPieces<T>{reinterpret_cast<const spt_u4 *>(a.pl_piece), k0, a.rec_cap},
-            rec_row, rec_val, ld, row_base);
-    else
-        seg_walk<NT, T, VEC, NMAX, NFIX>(
-            a, crdg, valg, npieces, PlanPieces<T>{a.pl_desc, a.pl_row, a.pl_dest, k0, a.rec_cap, rec_base}, rec_row,
-            rec_val, ld, row_base);
+    segp_walk<NT, T, VEC, NMAX, NFIX>(a, lds, lg, ws, cnt, k0, nruns, rec_val, ld);
 }
 
 __device__ __forceinline__ ZeroSlice out_slice(const MttkrpArgs &a, int64_t tile, int64_t ntiles) {
@@ -497,11 +316,11 @@ __device__ __forceinline__ ZeroSlice out_slice(const MttkrpArgs &a, int64_t tile
 }
 
 template <int NT, int T, int VEC, int NMAX, int NFIX>
-__global__ __launch_bounds__(NT) void k_mttkrp_segp(MttkrpArgs a, int64_t ntiles) {
+__global__ __launch_bounds__(NT, NMAX <= 5 ? 8 : 4) void k_mttkrp_segp(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segp_tile<NT, T, VEC, NMAX, NFIX, true>(a, tile, lds, a.rec_row, a.rec_val, a.rank, 0, 0, out_slice(a, tile, ntiles));
+    segp_tile<NT, T, VEC, NMAX, NFIX>(a, tile, lds, a.rec_val, a.rank, out_slice(a, tile, ntiles));
 }
 
 // ---------------------------------------------------------------- row cache
@@ -627,10 +446,13 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
     uint32_t *crdg = (uint32_t *)lds;
     float *valg = (float *)(crdg + (size_t)no * T);
     float *cache = valg + T;
-    const int64_t k0 = a.pl_off[tile], k1 = min(a.pl_off[tile + 1], k0 + T);
+    const int64_t k0 = a.pl_off[tile];
+    const int nruns = (int)min<int64_t>(a.pl_off[tile + 1] - k0, T);
     const int64_t base = tile * (int64_t)T;
     const int64_t rem = a.nnz - base;
     const int cnt = rem < T ? (int)rem : T;
+    const LaneGroup lg = lane_group<VEC>(R);
+    constexpr int UB = 2;
     // every thread stages PER consecutive nonzeros: one 16-byte load of
     // values and one 8-byte load per u16 stream (tiles start at multiples of
     // T, so the vectors are aligned); the last tile's ragged end goes element
@@ -683,6 +505,7 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u) q[u] &= (uint32_t)(T - 1);  // a position inside the tile
+    const WalkShare ws = walk_share<NT, T>(lg, cnt, UB, a.pl_start + tile * (T / 32));
     {
         const ZeroSlice z = out_slice(a, tile, ntiles);
         zero_slice(z.p, z.n, z.i, z.of);  // while the loads above are in flight
@@ -744,16 +567,69 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
             }
         }
     }
+    if (tid <= no && cnt < T) {  // the other half of an odd last step: a cached row, value 0
+        if (tid < no) crdg[tid * T + cnt] = cache_off;
+        else valg[cnt] = 0.f;
+    }
     __syncthreads();
     // the largest entry a cached row can have: the last slot of the last mode
     const uint32_t lim = cache_off + ((uint32_t)(no * cap) - 1u) * (uint32_t)(RS * 4);
-    seg_walk<NT, T, VEC, NMAX, NFIX, PackedPieces<T>, true>(
-        a, crdg, valg, (int)(k1 - k0), PackedPieces<T>{reinterpret_cast<const spt_u4 *>(a.pl_piece), k0, a.rec_cap},
-        a.rec_row, a.rec_val, a.rank, 0, lds, lim);
+    // A crdg entry is either the byte offset in LDS of a cached row or, with
+    // kDictMiss set, a global row.  Every lane first reads LDS (a miss reads
+    // the last cached row: its entry, flag set, clamps to lim), then the
+    // misses load their rows globally into the same registers.  A global load
+    // into the registers of an LDS read waits for that read; with all LDS
+    // reads of the step issued first the loads wait for one LDS round trip,
+    // and no branch splits hits from misses.
+    spt_i4 fb[NO];
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+        const int k = o + (o >= mode);
+        fb[o] = o < no ? row_rsrc(a.f[k], R, a.frows[k]) : row_rsrc((const float *)nullptr, R, 0u);
+    }
+    const char *mine = lds + lg.j * VEC * 4;  // this lane's columns of the row at offset 0
+    auto product = [&](int q0, float (&p)[UB][VEC]) {
+        uint32_t row[NO][UB];
+        float x[UB];
+        load_words<UB>(valg + q0, x);
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+            if (o < no) load_words<UB>(crdg + o * T + q0, row[o]);
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) p[u][v] = x[u];
+        float xv[NO][UB][VEC];
+        // every index read of the step is issued before anything waits for
+        // one (the scheduler may not hoist a use between them)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+#pragma unroll
+            for (int u = 0; u < UB; ++u)
+                if (o < no) load_vec<VEC>(reinterpret_cast<const float *>(mine + min(row[o][u], lim)), xv[o][u]);
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+            if (o < no)
+#pragma unroll
+                for (int u = 0; u < UB; ++u)
+                    if (row[o][u] & kDictMiss) load_row_vec<VEC>(fb[o], row[o][u] & ~kDictMiss, lg.col, xv[o][u]);
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+            if (o < no)
+#pragma unroll
+                for (int u = 0; u < UB; ++u)
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) p[u][v] *= xv[o][u][v];
+    };
+    run_walk<float, NT, T, VEC, UB>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, a.rec_val, R, lds, product);
 }
 
+// Bounded to 64 VGPRs, which leaves two workgroups of 16 waves to a CU: left to
+// itself the compiler takes 72 to 82 and one workgroup; the few spills lie
+// outside the steps.
 template <int NT, int T, int VEC, int NMAX, int NFIX>
-__global__ __launch_bounds__(NT) void k_mttkrp_segd(MttkrpArgs a, int64_t ntiles) {
+__global__ __launch_bounds__(NT, 8) void k_mttkrp_segd(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
@@ -781,9 +657,8 @@ __device__ __forceinline__ int seg_item_of(const SegItem *__restrict__ items, in
 // workgroup's tiles only increase, so it finds each tile's tensor by moving
 // forward from the last one.
 template <int NT, int VEC, int NMAX, int NFIX>
-__global__ __launch_bounds__(NT) void k_mttkrp_segp_batched(const SegItem *__restrict__ items, int count,
-                                                            int64_t total_tiles, uint64_t *__restrict__ rec_row,
-                                                            float *__restrict__ rec_val, int ld,
+__global__ __launch_bounds__(NT, 7) void k_mttkrp_segp_batched(const SegItem *__restrict__ items, int count,
+                                                            int64_t total_tiles, float *__restrict__ rec_val, int ld,
                                                             unsigned long long *__restrict__ next_tile,
                                                             float *__restrict__ out, int64_t out_floats) {
     extern __shared__ __align__(16) char lds[];
@@ -797,202 +672,181 @@ __global__ __launch_bounds__(NT) void k_mttkrp_segp_batched(const SegItem *__res
         if (it >= total_tiles) break;
         while (b + 1 < count && items[b + 1].first_tile <= it) ++b;
         const SegItem &item = items[b];
-        segp_tile<NT, 4 * NT, VEC, NMAX, NFIX, false>(item.a, it - item.first_tile, lds, rec_row, rec_val, ld,
-                                                      item.rec_base, item.row_base,
-                                                      ZeroSlice{out, out_floats, it, total_tiles});
+        segp_tile<NT, 4 * NT, VEC, NMAX, NFIX>(item.a, it - item.first_tile, lds, rec_val + item.rec_base * ld, ld,
+                                               ZeroSlice{out, out_floats, it, total_tiles});
     }
 }
 
-// The plan of one mode: positions of every nonzero, and per piece its
-// (start | length << 16), row, and (for the record layout) its pair and index
-// within the pair; per distinct (tile, row) pair its row (sort key) and pieces.
-// Emission of one tile: positions to pos (the tensor's), piece start/length
-// and row to desc/prow at a.pl_off[tile]; piece pair and index to
-// ppair/psub at gpiece; pair (row_base + row, pieces) to pair_key/pair_np at
-// gpair (pair indices are global, gpair-based).
-template <int NT, int NMAX>
+// The plan of one tile: positions to pos (the tensor's), run starts to start
+// (the tile's words), and the row (row_base + row) of every run, in position
+// order, to pair_key at gpair.
+template <int NT>
 __device__ __forceinline__ void emit_tile(const MttkrpArgs &a, int64_t tile, char *lds, uint32_t *wsum,
-                                          uint16_t *__restrict__ pos, uint32_t *__restrict__ desc,
-                                          uint32_t *__restrict__ prow, int64_t gpiece, int64_t gpair, int64_t row_base,
-                                          uint32_t *__restrict__ ppair, uint32_t *__restrict__ psub,
-                                          uint64_t *__restrict__ pair_key, uint32_t *__restrict__ pair_np) {
+                                          uint16_t *__restrict__ pos, RunWord *__restrict__ start, int64_t gpair,
+                                          int64_t row_base, uint64_t *__restrict__ pair_key) {
     constexpr int T = 4 * NT;
     const SegLds L = seg_carve_plan(lds, T);
     const CodecRegs cr = load_codec_regs(a.codec);
-    seg_stage<NT, NMAX, false>(a, tile, L, cr, wsum, pos);
-    // pair index of every occupied slot: exclusive count of occupied slots before it
-    uint32_t *occ = (uint32_t *)L.valg;  // free in counting mode; T entries
-    for (int i = threadIdx.x; i < T; i += NT) {
-        const uint32_t nx = i + 1 < T ? L.hcnt[i + 1] : L.hcnt[T];
-        occ[i] = (nx >> 16) != (L.hcnt[i] >> 16) ? 1u : 0u;
+    for (int i = threadIdx.x; i < T / 32; i += NT) L.bits[i] = 0;
+    uint32_t sr[4];
+    const int cnt = seg_hash<NT>(a, tile, L, cr, wsum, sr);
+    seg_scan<NT>(L, cnt, wsum);
+    const int64_t base = tile * (int64_t)T;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = threadIdx.x + u * NT;
+        if (e < cnt) pos[base + e] = (uint16_t)((L.hcnt[sr[u] >> 16] >> 16) + (sr[u] & 0xFFFFu));
     }
-    __syncthreads();
-    block_scan_lds(occ, T, NT, wsum);
-    const int64_t pbase = a.pl_off[tile], qbase = gpair;
     for (int i = threadIdx.x; i < T; i += NT) {
         const uint32_t pk = L.hcnt[i];
-        const uint32_t nx = i + 1 < T ? L.hcnt[i + 1] : L.hcnt[T];
-        const uint32_t c = (nx >> 16) - (pk >> 16);
-        if (c > 0) {
-            pair_key[qbase + occ[i]] = (uint64_t)(row_base + L.hkey[i]);
-            pair_np[qbase + occ[i]] = (c + kPiece - 1) / kPiece;
-        }
-    }
-    // the tile's pieces are stored longest first (a counting sort on the
-    // length): dealt to lane groups in snake order they balance the walk
-    __shared__ uint32_t lstart[kPiece + 1];
-    const int npieces = (int)(L.hcnt[T] & 0xFFFFu);
-    auto piece = [&](int k, int &s, int &i, int &p0, int &p1) {
-        s = L.ptab[k];
-        const uint32_t pk = L.hcnt[s];
-        const uint32_t pn = (s + 1 < T) ? L.hcnt[s + 1] : L.hcnt[T];
-        const int first = (int)(pk >> 16), last = (int)(pn >> 16);
-        i = k - (int)(pk & 0xFFFFu);
-        p0 = first + i * kPiece;
-        p1 = min(p0 + kPiece, last);
-    };
-    for (int b = threadIdx.x; b <= kPiece; b += NT) lstart[b] = 0;
-    __syncthreads();
-    for (int k = threadIdx.x; k < npieces; k += NT) {
-        int sl, i, p0, p1;
-        piece(k, sl, i, p0, p1);
-        atomicAdd(&lstart[kPiece - (p1 - p0)], 1u);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int b = 0; b <= kPiece; ++b) {
-            const uint32_t c = lstart[b];
-            lstart[b] = run;
-            run += c;
+        if (L.hkey[i] != kNoRow) {
+            pair_key[gpair + (pk & 0xFFFFu)] = (uint64_t)(row_base + L.hkey[i]);
+            const uint32_t p = pk >> 16;
+            atomicOr(&L.bits[p >> 5], 1u << (p & 31));
         }
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < npieces; k += NT) {
-        int sl, i, p0, p1;
-        piece(k, sl, i, p0, p1);
-        const uint32_t q = atomicAdd(&lstart[kPiece - (p1 - p0)], 1u);
-        desc[pbase + q] = (uint32_t)p0 | ((uint32_t)(p1 - p0) << 16);
-        prow[pbase + q] = L.hkey[sl];
-        ppair[gpiece + q] = (uint32_t)(qbase + occ[sl]);
-        psub[gpiece + q] = (uint32_t)i;
+    // 32 positions a word, and the starts before it: a scan by the first wave
+    if (threadIdx.x < 64) {
+        constexpr int NW = T / 32, PER = (NW + 63) / 64;
+        const int lane = threadIdx.x;
+        uint32_t w[PER], c = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            w[i] = lane * PER + i < NW ? L.bits[lane * PER + i] : 0u;
+            c += __popc(w[i]);
+        }
+        uint32_t x = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(x, off, 64);
+            if (lane >= off) x += y;
+        }
+        uint32_t run = x - c;
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (lane * PER + i < NW) {
+                RunWord r;
+                r.x = w[i];
+                r.y = run;
+                start[lane * PER + i] = r;
+                run += __popc(w[i]);
+            }
     }
 }
 
-template <int NT, int NMAX>
-__global__ __launch_bounds__(NT) void k_emit_plan(MttkrpArgs a, int64_t ntiles, const int64_t *__restrict__ pair_off,
-                                                  uint16_t *__restrict__ pos, uint32_t *__restrict__ desc,
-                                                  uint32_t *__restrict__ prow, uint32_t *__restrict__ ppair,
-                                                  uint32_t *__restrict__ psub, uint64_t *__restrict__ pair_key,
-                                                  uint32_t *__restrict__ pair_np) {
+template <int NT>
+__global__ __launch_bounds__(NT) void k_emit_plan(MttkrpArgs a, const int64_t *__restrict__ pair_off,
+                                                  uint16_t *__restrict__ pos, RunWord *__restrict__ start,
+                                                  uint64_t *__restrict__ pair_key) {
     extern __shared__ __align__(16) char lds[];
     __shared__ uint32_t wsum[NT / 64];
     const int64_t tile = blockIdx.x;
-    emit_tile<NT, NMAX>(a, tile, lds, wsum, pos, desc, prow, a.pl_off[tile], pair_off[tile], 0, ppair, psub, pair_key,
-                        pair_np);
+    emit_tile<NT>(a, tile, lds, wsum, pos, start + tile * (4 * NT / 32), pair_off[tile], 0, pair_key);
 }
 
-// Batched emission: item b's plan arrays come in its args (pl_pos, pl_desc,
-// pl_row, pl_off); gpiece_off / gpair_off give each global tile's first
-// piece and pair in the batch-wide arrays; pair keys are rows of the
-// concatenated output (row_base + row).
-template <int NT, int NMAX>
+// Batched emission: item b's plan arrays come in its args (pl_pos, pl_start);
+// gpair_off gives each global tile's first pair in the batch-wide array; pair
+// keys are rows of the concatenated output (row_base + row).
+template <int NT>
 __global__ __launch_bounds__(NT) void k_emit_plan_batched(const SegItem *__restrict__ items, int count,
-                                                          const int64_t *__restrict__ gpiece_off,
                                                           const int64_t *__restrict__ gpair_off,
-                                                          uint32_t *__restrict__ ppair, uint32_t *__restrict__ psub,
-                                                          uint64_t *__restrict__ pair_key,
-                                                          uint32_t *__restrict__ pair_np) {
+                                                          uint64_t *__restrict__ pair_key) {
     extern __shared__ __align__(16) char lds[];
     __shared__ uint32_t wsum[NT / 64];
     const int64_t it = blockIdx.x;
     const int b = seg_item_of(items, count, it);
     const SegItem &item = items[b];
     const MttkrpArgs &a = item.a;
-    emit_tile<NT, NMAX>(a, it - item.first_tile, lds, wsum, const_cast<uint16_t *>(a.pl_pos),
-                        const_cast<uint32_t *>(a.pl_desc), const_cast<uint32_t *>(a.pl_row), gpiece_off[it],
-                        gpair_off[it], item.row_base, ppair, psub, pair_key, pair_np);
+    const int64_t tile = it - item.first_tile;
+    emit_tile<NT>(a, tile, lds, wsum, const_cast<uint16_t *>(a.pl_pos),
+                  const_cast<RunWord *>(a.pl_start) + tile * (4 * NT / 32), gpair_off[it], item.row_base, pair_key);
 }
 
-// Batched piece records: global piece g of item b (pieces from
-// items[b].rec_base) gets its first pair record plus its index, made local
-// to the item (the item's records start at its rec_base).
-__global__ __launch_bounds__(256) void k_piece_dest_batched(const SegItem *__restrict__ items, int count,
-                                                            const int64_t *__restrict__ piece_base,
-                                                            const uint32_t *__restrict__ ppair,
-                                                            const uint32_t *__restrict__ psub,
-                                                            const uint32_t *__restrict__ pair_first, int64_t n) {
-    for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < n; g += (int64_t)gridDim.x * 256) {
-        int lo = 0, hi = count - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (piece_base[mid] <= g) lo = mid;
-            else hi = mid - 1;
-        }
-        const uint32_t d = pair_first[ppair[g]] + psub[g];
-        const_cast<uint32_t *>(items[lo].a.pl_dest)[g - piece_base[lo]] = d - (uint32_t)piece_base[lo];
+// Item of the batch-wide pair or record g: the last whose rec_base <= g.
+__device__ __forceinline__ int seg_item_of_record(const SegItem *__restrict__ items, int count, int64_t g) {
+    int lo = 0, hi = count - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (items[mid].rec_base <= g) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// The sorted pairs of a batch: record j (its row sorted[j] of the concatenated
+// output, its run idx[j]) becomes record j - rec_base of its tensor.
+__global__ __launch_bounds__(256) void k_plan_records_batched(const SegItem *__restrict__ items, int count,
+                                                              const uint64_t *__restrict__ sorted,
+                                                              const uint32_t *__restrict__ idx, int64_t n) {
+    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < n; j += (int64_t)gridDim.x * 256) {
+        const SegItem &item = items[seg_item_of_record(items, count, j)];
+        const_cast<uint64_t *>(item.a.pl_rec_row)[j - item.rec_base] = sorted[j] - (uint64_t)item.row_base;
+        const_cast<uint32_t *>(item.a.pl_rec)[(int64_t)idx[j] - item.rec_base] = (uint32_t)(j - item.rec_base);
     }
 }
 
-// packed[k] = {desc[k], prow[k], first record of piece k's pair + its index within the pair, 0}
-__global__ __launch_bounds__(256) void k_piece_pack(const uint32_t *__restrict__ ppair, const uint32_t *__restrict__ psub,
-                                                    const uint32_t *__restrict__ pair_first,
-                                                    const uint32_t *__restrict__ desc, const uint32_t *__restrict__ prow,
-                                                    spt_u4 *__restrict__ packed, int64_t n) {
-    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256) {
-        spt_u4 q;
-        q.x = desc[k];
-        q.y = prow[k];
-        q.z = pair_first[ppair[k]] + psub[k];
-        q.w = 0u;
-        packed[k] = q;
+// Rows of a batch's records in its concatenated output.
+__global__ __launch_bounds__(256) void k_record_rows_batched(const SegItem *__restrict__ items, int count, int64_t n,
+                                                             uint64_t *__restrict__ rows) {
+    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < n; j += (int64_t)gridDim.x * 256) {
+        const SegItem &item = items[seg_item_of_record(items, count, j)];
+        rows[j] = item.a.pl_rec_row[j - item.rec_base] + (uint64_t)item.row_base;
     }
 }
 
-// pieces | distinct rows << 32 of a tile after the hashing stage
-template <int T>
-__device__ __forceinline__ int64_t tile_counts(const SegLds &L) {
-    __shared__ uint32_t s_distinct;
-    if (threadIdx.x == 0) s_distinct = 0;
+// rec[idx[j]] = j: the record of the run that sorted to place j
+__global__ __launch_bounds__(256) void k_plan_records(const uint32_t *__restrict__ idx, uint32_t *__restrict__ rec,
+                                                      int64_t n) {
+    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < n; j += (int64_t)gridDim.x * 256)
+        rec[idx[j]] = (uint32_t)j;
+}
+
+// pieces of at most kPiece nonzeros | distinct rows << 32 of a hashed tile
+template <int NT>
+__device__ __forceinline__ void count_tile(const MttkrpArgs &a, int64_t tile, char *lds, uint32_t *wsum, int64_t *out) {
+    constexpr int T = 4 * NT;
+    __shared__ uint32_t total[2];
+    if (threadIdx.x < 2) total[threadIdx.x] = 0;
+    const SegLds L = seg_carve_plan(lds, T);
+    const CodecRegs cr = load_codec_regs(a.codec);
+    uint32_t sr[4];
+    (void)seg_hash<NT>(a, tile, L, cr, wsum, sr);
+    uint32_t np = 0, d = 0;
+    for (int i = threadIdx.x; i < T; i += NT) {
+        const uint32_t c = L.hcnt[i];
+        np += (c + kPiece - 1) / kPiece;
+        d += c > 0;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        np += __shfl_down(np, off, 64);
+        d += __shfl_down(d, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&total[0], np);
+        atomicAdd(&total[1], d);
+    }
     __syncthreads();
-    uint32_t d = 0;
-    for (int i = threadIdx.x; i < T; i += blockDim.x) {
-        const uint32_t nx = i + 1 < T ? L.hcnt[i + 1] : L.hcnt[T];
-        d += (nx >> 16) != (L.hcnt[i] >> 16);
-    }
-    atomicAdd(&s_distinct, d);
-    __syncthreads();
-    return (int64_t)(L.hcnt[T] & 0xFFFFu) | ((int64_t)s_distinct << 32);
+    if (threadIdx.x == 0) *out = (int64_t)total[0] | ((int64_t)total[1] << 32);
 }
 
 // Pieces and distinct rows of every tile (the plan's counting pass).
-template <int NT, int NMAX>
-__global__ __launch_bounds__(NT) void k_count_pieces(MttkrpArgs a, int64_t ntiles, int64_t *__restrict__ out) {
-    constexpr int T = 4 * NT;
+template <int NT>
+__global__ __launch_bounds__(NT) void k_count_pieces(MttkrpArgs a, int64_t *__restrict__ out) {
     extern __shared__ __align__(16) char lds[];
     __shared__ uint32_t wsum[NT / 64];
-    const int64_t tile = blockIdx.x;
-    const SegLds L = seg_carve_plan(lds, T);
-    const CodecRegs cr = load_codec_regs(a.codec);
-    seg_stage<NT, NMAX, false>(a, tile, L, cr, wsum);
-    const int64_t c = tile_counts<T>(L);
-    if (threadIdx.x == 0) out[tile] = c;
+    count_tile<NT>(a, blockIdx.x, lds, wsum, out + blockIdx.x);
 }
 
-template <int NT, int NMAX>
+template <int NT>
 __global__ __launch_bounds__(NT) void k_count_pieces_batched(const SegItem *__restrict__ items, int count,
-                                                             int64_t total_tiles, int64_t *__restrict__ out) {
-    constexpr int T = 4 * NT;
+                                                             int64_t *__restrict__ out) {
     extern __shared__ __align__(16) char lds[];
     __shared__ uint32_t wsum[NT / 64];
     const int64_t it = blockIdx.x;
     const int b = seg_item_of(items, count, it);
-    const MttkrpArgs &a = items[b].a;
-    const SegLds L = seg_carve_plan(lds, T);
-    const CodecRegs cr = load_codec_regs(a.codec);
-    seg_stage<NT, NMAX, false>(a, it - items[b].first_tile, L, cr, wsum);
-    const int64_t c = tile_counts<T>(L);
-    if (threadIdx.x == 0) out[it] = c;
+    count_tile<NT>(items[b].a, it - items[b].first_tile, lds, wsum, out + it);
 }
 
 template <int NT, int T, int NMAX, int NFIX, int VEC>
@@ -1006,7 +860,7 @@ spt_status launch_seg_k(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
             return SPT_OK;
         }
     }
-    const size_t lds = segp_lds_bytes(T, a.nmodes);
+    const size_t lds = std::max(segp_lds_bytes(T, a.nmodes), walk_lds_bytes(NT));
     hipLaunchKernelGGL((k_mttkrp_segp<NT, T, VEC, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, ntiles);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
@@ -1017,30 +871,6 @@ spt_status launch_seg_nt(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
     return a.rank >= 4 ? launch_seg_k<NT, T, NMAX, NFIX, 4>(a, ntiles, s) : launch_seg_k<NT, T, NMAX, NFIX, 1>(a, ntiles, s);
 }
 
-template <int NT>
-spt_status launch_emit_nt(const MttkrpArgs &a, int64_t ntiles, const PlanOut &o, hipStream_t s) {
-    const size_t lds = seg_plan_lds_bytes(4 * NT);
-    if (a.nmodes <= 4)
-        hipLaunchKernelGGL((k_emit_plan<NT, 4>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, ntiles, o.pair_off, o.pos,
-                           o.desc, o.prow, o.ppair, o.psub, o.pair_key, o.pair_np);
-    else
-        hipLaunchKernelGGL((k_emit_plan<NT, 8>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, ntiles, o.pair_off, o.pos,
-                           o.desc, o.prow, o.ppair, o.psub, o.pair_key, o.pair_np);
-    SPT_HIP(hipGetLastError());
-    return SPT_OK;
-}
-
-template <int NT>
-spt_status launch_count_nt(const MttkrpArgs &a, int64_t ntiles, int64_t *out, hipStream_t s) {
-    const size_t lds = seg_plan_lds_bytes(4 * NT);
-    if (a.nmodes <= 4)
-        hipLaunchKernelGGL((k_count_pieces<NT, 4>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, ntiles, out);
-    else
-        hipLaunchKernelGGL((k_count_pieces<NT, 8>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, ntiles, out);
-    SPT_HIP(hipGetLastError());
-    return SPT_OK;
-}
-
 }  // namespace
 
 // tile sizes served: 1024 (256 threads), 2048 (512), 4096 (1024 threads)
@@ -1049,21 +879,24 @@ bool seg_tile_ok(int tile, int nmodes) {
     return seg_lds_bytes(tile, nmodes) <= 160 * 1024 - 1024 && segp_lds_bytes(tile, nmodes) <= 160 * 1024 - 1024;
 }
 
-spt_status launch_emit_plan(const MttkrpArgs &a, const PlanOut &o, hipStream_t s) {
+spt_status launch_emit_plan(const MttkrpArgs &a, const int64_t *pair_off, uint16_t *pos, spt_u2 *start,
+                            uint64_t *pair_key, hipStream_t s) {
     const int64_t ntiles = (a.nnz + a.tile - 1) / a.tile;
     if (ntiles == 0) return SPT_OK;
     if (!seg_tile_ok(a.tile, a.nmodes)) return fail(SPT_E_INVALID_ARG, "segment: tile does not fit LDS");
-    if (a.tile == 1024) return launch_emit_nt<256>(a, ntiles, o, s);
-    if (a.tile == 2048) return launch_emit_nt<512>(a, ntiles, o, s);
-    return launch_emit_nt<1024>(a, ntiles, o, s);
+    const dim3 g((unsigned)ntiles);
+    const size_t lds = seg_plan_lds_bytes(a.tile);
+    if (a.tile == 1024) hipLaunchKernelGGL(k_emit_plan<256>, g, dim3(256), lds, s, a, pair_off, pos, start, pair_key);
+    else if (a.tile == 2048) hipLaunchKernelGGL(k_emit_plan<512>, g, dim3(512), lds, s, a, pair_off, pos, start, pair_key);
+    else hipLaunchKernelGGL(k_emit_plan<1024>, g, dim3(1024), lds, s, a, pair_off, pos, start, pair_key);
+    SPT_HIP(hipGetLastError());
+    return SPT_OK;
 }
 
-spt_status launch_piece_pack(const uint32_t *ppair, const uint32_t *psub, const uint32_t *pair_first,
-                             const uint32_t *desc, const uint32_t *prow, uint32_t *packed, int64_t n, hipStream_t s) {
+spt_status launch_plan_records(const uint32_t *idx, uint32_t *rec, int64_t n, hipStream_t s) {
     if (n == 0) return SPT_OK;
     const int64_t g = std::min<int64_t>((n + 255) / 256, 65536);
-    hipLaunchKernelGGL(k_piece_pack, dim3((unsigned)g), dim3(256), 0, s, ppair, psub, pair_first, desc, prow,
-                       reinterpret_cast<spt_u4 *>(packed), n);
+    hipLaunchKernelGGL(k_plan_records, dim3((unsigned)g), dim3(256), 0, s, idx, rec, n);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
@@ -1072,9 +905,13 @@ spt_status launch_count_pieces(const MttkrpArgs &a, int64_t *counts, hipStream_t
     const int64_t ntiles = (a.nnz + a.tile - 1) / a.tile;
     if (ntiles == 0) return SPT_OK;
     if (!seg_tile_ok(a.tile, a.nmodes)) return fail(SPT_E_INVALID_ARG, "segment: tile does not fit LDS");
-    if (a.tile == 1024) return launch_count_nt<256>(a, ntiles, counts, s);
-    if (a.tile == 2048) return launch_count_nt<512>(a, ntiles, counts, s);
-    return launch_count_nt<1024>(a, ntiles, counts, s);
+    const dim3 g((unsigned)ntiles);
+    const size_t lds = seg_plan_lds_bytes(a.tile);
+    if (a.tile == 1024) hipLaunchKernelGGL(k_count_pieces<256>, g, dim3(256), lds, s, a, counts);
+    else if (a.tile == 2048) hipLaunchKernelGGL(k_count_pieces<512>, g, dim3(512), lds, s, a, counts);
+    else hipLaunchKernelGGL(k_count_pieces<1024>, g, dim3(1024), lds, s, a, counts);
+    SPT_HIP(hipGetLastError());
+    return SPT_OK;
 }
 
 namespace {
@@ -1111,7 +948,7 @@ spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s) {
     const int64_t ntiles = (a.nnz + a.tile - 1) / a.tile;
     if (ntiles == 0) return SPT_OK;
     if (!seg_tile_ok(a.tile, a.nmodes)) return fail(SPT_E_INVALID_ARG, "segment: tile does not fit LDS");
-    if (!a.pl_pos || !a.pl_off || !a.pl_piece) return fail(SPT_E_INVALID_ARG, "segment: no plan");
+    if (!a.pl_pos || !a.pl_off || !a.pl_start || !a.pl_rec) return fail(SPT_E_INVALID_ARG, "segment: no plan");
     if (a.tile == 1024) return launch_seg_tile<256, 1024>(a, ntiles, s);
     if (a.tile == 2048) return launch_seg_tile<512, 2048>(a, ntiles, s);
     return launch_seg_tile<kSegpThreads4096, 4096>(a, ntiles, s);
@@ -1119,9 +956,9 @@ spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s) {
 
 namespace {
 template <int NT, int NMAX, int NFIX, int VEC>
-spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, uint64_t *rec_row, float *rec_val,
+spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, float *rec_val,
                          int ld, unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
-    const size_t lds = segp_lds_bytes(4 * NT, NMAX);
+    const size_t lds = std::max(segp_lds_bytes(4 * NT, NMAX), walk_lds_bytes(NT));
     static std::atomic<int> per_cu{0};  // resident workgroups per CU (fixed per instantiation: its LDS is)
     int pc = per_cu.load(std::memory_order_relaxed);
     if (pc == 0) {
@@ -1138,76 +975,58 @@ spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, u
     spt_status st = launch_fill_zero(reinterpret_cast<float *>(next_tile), 2, s);  // the tile counter
     if (st != SPT_OK) return st;
     hipLaunchKernelGGL((k_mttkrp_segp_batched<NT, VEC, NMAX, NFIX>), dim3((unsigned)grid), dim3(NT), lds, s, items,
-                       count, total_tiles, rec_row, rec_val, ld, next_tile, out, out_floats);
+                       count, total_tiles, rec_val, ld, next_tile, out, out_floats);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
 template <int NT, int NMAX, int NFIX>
-spt_status launch_segb_n(const SegItem *items, int count, int64_t total_tiles, uint64_t *rec_row, float *rec_val,
+spt_status launch_segb_n(const SegItem *items, int count, int64_t total_tiles, float *rec_val,
                          int ld, bool vec4, unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
-    return vec4 ? launch_segb_k<NT, NMAX, NFIX, 4>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, out, out_floats, s)
-                : launch_segb_k<NT, NMAX, NFIX, 1>(items, count, total_tiles, rec_row, rec_val, ld, next_tile, out, out_floats, s);
+    return vec4 ? launch_segb_k<NT, NMAX, NFIX, 4>(items, count, total_tiles, rec_val, ld, next_tile, out, out_floats, s)
+                : launch_segb_k<NT, NMAX, NFIX, 1>(items, count, total_tiles, rec_val, ld, next_tile, out, out_floats, s);
 }
 
 template <int NT>
 spt_status launch_segb_t(const SegItem *items, int count, int64_t total_tiles, int nmodes_min, int nmodes_max, int ld,
-                         bool vec4, uint64_t *rec_row, float *rec_val, unsigned long long *next_tile, float *out,
+                         bool vec4, float *rec_val, unsigned long long *next_tile, float *out,
                          int64_t out_floats, hipStream_t s) {
     if (nmodes_min == 3 && nmodes_max == 3)
-        return launch_segb_n<NT, 3, 3>(items, count, total_tiles, rec_row, rec_val, ld, vec4, next_tile, out, out_floats, s);
-    if (nmodes_max <= 4) return launch_segb_n<NT, 4, 0>(items, count, total_tiles, rec_row, rec_val, ld, vec4, next_tile, out, out_floats, s);
-    return launch_segb_n<NT, 8, 0>(items, count, total_tiles, rec_row, rec_val, ld, vec4, next_tile, out, out_floats, s);
+        return launch_segb_n<NT, 3, 3>(items, count, total_tiles, rec_val, ld, vec4, next_tile, out, out_floats, s);
+    if (nmodes_max <= 4) return launch_segb_n<NT, 4, 0>(items, count, total_tiles, rec_val, ld, vec4, next_tile, out, out_floats, s);
+    return launch_segb_n<NT, 8, 0>(items, count, total_tiles, rec_val, ld, vec4, next_tile, out, out_floats, s);
 }
 
-template <int NT>
-void launch_emit_b(const SegItem *items, int count, int64_t total_tiles, int nmodes_max, const int64_t *gpiece_off,
-                   const int64_t *gpair_off, uint32_t *ppair, uint32_t *psub, uint64_t *pair_key, uint32_t *pair_np,
-                   hipStream_t s) {
-    constexpr int T = 4 * NT;
-    if (nmodes_max <= 4)
-        hipLaunchKernelGGL((k_emit_plan_batched<NT, 4>), dim3((unsigned)total_tiles), dim3(NT), seg_plan_lds_bytes(T), s,
-                           items, count, gpiece_off, gpair_off, ppair, psub, pair_key, pair_np);
-    else
-        hipLaunchKernelGGL((k_emit_plan_batched<NT, 8>), dim3((unsigned)total_tiles), dim3(NT),
-                           seg_plan_lds_bytes(T), s,
-                           items, count, gpiece_off, gpair_off, ppair, psub, pair_key, pair_np);
-}
-
-template <int NT>
-void launch_count_b(const SegItem *items, int count, int64_t total_tiles, int nmodes_max, int64_t *counts,
-                    hipStream_t s) {
-    constexpr int T = 4 * NT;
-    if (nmodes_max <= 4)
-        hipLaunchKernelGGL((k_count_pieces_batched<NT, 4>), dim3((unsigned)total_tiles), dim3(NT), seg_plan_lds_bytes(T), s,
-                           items, count, total_tiles, counts);
-    else
-        hipLaunchKernelGGL((k_count_pieces_batched<NT, 8>), dim3((unsigned)total_tiles), dim3(NT),
-                           seg_plan_lds_bytes(T), s,
-                           items, count, total_tiles, counts);
-}
 }  // namespace
 
 bool seg_batch_fits(int nmodes_max, int tile) { return seg_tile_ok(tile, nmodes_max); }
 
 spt_status launch_emit_plan_batched(const SegItem *items, int count, int64_t total_tiles, int nmodes_max, int tile,
-                                    const int64_t *gpiece_off, const int64_t *gpair_off, uint32_t *ppair,
-                                    uint32_t *psub, uint64_t *pair_key, uint32_t *pair_np, hipStream_t s) {
+                                    const int64_t *gpair_off, uint64_t *pair_key, hipStream_t s) {
     if (total_tiles == 0) return SPT_OK;
     if (!seg_batch_fits(nmodes_max, tile)) return fail(SPT_E_INVALID_ARG, "batch plan: tile does not fit LDS");
-    if (tile == 1024) launch_emit_b<256>(items, count, total_tiles, nmodes_max, gpiece_off, gpair_off, ppair, psub, pair_key, pair_np, s);
-    else if (tile == 2048) launch_emit_b<512>(items, count, total_tiles, nmodes_max, gpiece_off, gpair_off, ppair, psub, pair_key, pair_np, s);
-    else launch_emit_b<1024>(items, count, total_tiles, nmodes_max, gpiece_off, gpair_off, ppair, psub, pair_key, pair_np, s);
+    const dim3 g((unsigned)total_tiles);
+    const size_t lds = seg_plan_lds_bytes(tile);
+    if (tile == 1024) hipLaunchKernelGGL(k_emit_plan_batched<256>, g, dim3(256), lds, s, items, count, gpair_off, pair_key);
+    else if (tile == 2048) hipLaunchKernelGGL(k_emit_plan_batched<512>, g, dim3(512), lds, s, items, count, gpair_off, pair_key);
+    else hipLaunchKernelGGL(k_emit_plan_batched<1024>, g, dim3(1024), lds, s, items, count, gpair_off, pair_key);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
-spt_status launch_piece_dest_batched(const SegItem *items, int count, const int64_t *piece_base, const uint32_t *ppair,
-                                     const uint32_t *psub, const uint32_t *pair_first, int64_t n, hipStream_t s) {
+spt_status launch_plan_records_batched(const SegItem *items, int count, const uint64_t *sorted, const uint32_t *idx,
+                                       int64_t n, hipStream_t s) {
     if (n == 0) return SPT_OK;
     const int64_t g = std::min<int64_t>((n + 255) / 256, 65536);
-    hipLaunchKernelGGL(k_piece_dest_batched, dim3((unsigned)g), dim3(256), 0, s, items, count, piece_base, ppair, psub,
-                       pair_first, n);
+    hipLaunchKernelGGL(k_plan_records_batched, dim3((unsigned)g), dim3(256), 0, s, items, count, sorted, idx, n);
+    SPT_HIP(hipGetLastError());
+    return SPT_OK;
+}
+
+spt_status launch_record_rows_batched(const SegItem *items, int count, int64_t n, uint64_t *rows, hipStream_t s) {
+    if (n == 0) return SPT_OK;
+    const int64_t g = std::min<int64_t>((n + 255) / 256, 65536);
+    hipLaunchKernelGGL(k_record_rows_batched, dim3((unsigned)g), dim3(256), 0, s, items, count, n, rows);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
@@ -1216,25 +1035,27 @@ spt_status launch_count_pieces_batched(const SegItem *items, int count, int64_t 
                                        int64_t *counts, hipStream_t s) {
     if (total_tiles == 0) return SPT_OK;
     if (!seg_batch_fits(nmodes_max, tile)) return fail(SPT_E_INVALID_ARG, "batch plan: tile does not fit LDS");
-    if (tile == 1024) launch_count_b<256>(items, count, total_tiles, nmodes_max, counts, s);
-    else if (tile == 2048) launch_count_b<512>(items, count, total_tiles, nmodes_max, counts, s);
-    else launch_count_b<1024>(items, count, total_tiles, nmodes_max, counts, s);
+    const dim3 g((unsigned)total_tiles);
+    const size_t lds = seg_plan_lds_bytes(tile);
+    if (tile == 1024) hipLaunchKernelGGL(k_count_pieces_batched<256>, g, dim3(256), lds, s, items, count, counts);
+    else if (tile == 2048) hipLaunchKernelGGL(k_count_pieces_batched<512>, g, dim3(512), lds, s, items, count, counts);
+    else hipLaunchKernelGGL(k_count_pieces_batched<1024>, g, dim3(1024), lds, s, items, count, counts);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
 spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t total_tiles, int nmodes_min,
-                                     int nmodes_max, int tile, int ld, bool vec4, uint64_t *rec_row, float *rec_val,
+                                     int nmodes_max, int tile, int ld, bool vec4, float *rec_val,
                                      unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
     if (total_tiles == 0) return SPT_OK;
     if (ld > 64) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: rank above 64");
     if (!seg_batch_fits(nmodes_max, tile)) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: tile does not fit LDS");
     if (!next_tile) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: no tile counter");
     if (tile == 1024)
-        return launch_segb_t<256>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_row, rec_val, next_tile, out, out_floats, s);
+        return launch_segb_t<256>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_val, next_tile, out, out_floats, s);
     if (tile == 2048)
-        return launch_segb_t<512>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_row, rec_val, next_tile, out, out_floats, s);
-    return launch_segb_t<1024>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_row, rec_val, next_tile, out, out_floats, s);
+        return launch_segb_t<512>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_val, next_tile, out, out_floats, s);
+    return launch_segb_t<1024>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_val, next_tile, out, out_floats, s);
 }
 
 }  // namespace spt

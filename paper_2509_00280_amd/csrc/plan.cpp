@@ -85,14 +85,15 @@ int device_cus() {
 
 void release_mode_plan(Tensor *t, int n, hipStream_t s) {
     ModePlan &p = t->mplan[n];
-    for (void *q : {(void *)p.rec_off, (void *)p.pl_pos, (void *)p.pl_off, (void *)p.pl_piece})
+    for (void *q : {(void *)p.rec_off, (void *)p.pl_pos, (void *)p.pl_off, (void *)p.pl_start, (void *)p.pl_rec,
+                    (void *)p.rec_row})
         dev_free(q, s);
     p = ModePlan{};
 }
 
 void release_batch_plan(Tensor *t, int n, hipStream_t s) {
     ModePlan &p = t->bplan[n];
-    for (void *q : {(void *)p.pl_pos, (void *)p.pl_off, (void *)p.pl_desc, (void *)p.pl_row, (void *)p.pl_dest})
+    for (void *q : {(void *)p.pl_pos, (void *)p.pl_off, (void *)p.pl_start, (void *)p.pl_rec, (void *)p.rec_row})
         dev_free(q, s);
     p = ModePlan{};
 }
@@ -179,24 +180,25 @@ int segment_tile(const Tensor *t, int mode) {
     return seg_tile_ok(4096, t->nmodes) ? 4096 : (seg_tile_ok(2048, t->nmodes) ? 2048 : 1024);
 }
 
-// SEGMENT plan (once per tensor and mode; synchronises s once).  A tile's
-// records are its pieces (runs of at most L nonzeros of one row).
-//  1. a counting pass gives every tile's pieces and distinct rows;
+// SEGMENT plan (once per tensor and mode; synchronises s).  A tile's records
+// are its runs, one for each distinct output row.
+//  1. a counting pass gives every tile's distinct rows;
 //  2. the emission pass (same regrouping) writes every nonzero's position in
-//     its tile's row-grouped order, every piece's start, length and row, and
-//     every distinct (tile, row) pair with its piece count, tile-major;
-//  3. a stable sort of the pairs by row (tile order kept within a row) and an
-//     exclusive scan of their piece counts give each pair its first record,
-//     so the records of one row are contiguous; each piece's record follows.
+//     its tile's row-grouped order, where the runs begin, and every run's row,
+//     tile-major;
+//  3. a stable sort of the runs by row (tile order kept within a row) gives
+//     each run its record, so the records of one row are contiguous, and each
+//     record its row.
 // Calls then stage a tile with one scatter and write records in row order.
 spt_status build_segment_plan(Tensor *t, int mode, int rank, hipStream_t s, ModePlan &p) {
     p.ts = segment_tile(t, mode);
     const int64_t ntiles = (t->nnz + p.ts - 1) / p.ts;
-    std::vector<int64_t> h(ntiles + 1, 0), hq(ntiles + 1, 0);
+    std::vector<int64_t> h(ntiles + 1, 0);
     p.pl_off = (int64_t *)dev_alloc(sizeof(int64_t) * (ntiles + 1), s);
     if (!p.pl_off) return fail(SPT_E_OOM, "plan: offsets");
+    const MttkrpArgs a = make_args(t, nullptr, rank, mode, nullptr, p.ts);
     if (ntiles > 0) {
-        spt_status st = launch_count_pieces(make_args(t, nullptr, rank, mode, nullptr, p.ts), p.pl_off, s);
+        spt_status st = launch_count_pieces(a, p.pl_off, s);
         if (st != SPT_OK) return st;
         SPT_HIP(hipMemcpyAsync(h.data(), p.pl_off, sizeof(int64_t) * ntiles, hipMemcpyDeviceToHost, s));
         SPT_HIP(hipStreamSynchronize(s));
@@ -204,67 +206,42 @@ spt_status build_segment_plan(Tensor *t, int mode, int rank, hipStream_t s, Mode
     int64_t pieces = 0, pairs = 0;
     for (int64_t i = 0; i < ntiles; ++i) {
         const int64_t c = h[i];
-        h[i] = pieces;
-        hq[i] = pairs;
+        h[i] = pairs;
         pieces += c & 0xFFFFFFFFll;
         pairs += c >> 32;
     }
-    h[ntiles] = pieces;
-    hq[ntiles] = pairs;
-    p.records = pieces;
+    h[ntiles] = pairs;
+    p.records = pairs;
+    p.pieces = pieces;
     if (pieces >= (int64_t(1) << 32)) return fail(SPT_E_INVALID_ARG, "plan: more than 2^32 records");
     SPT_HIP(hipMemcpyAsync(p.pl_off, h.data(), sizeof(int64_t) * (ntiles + 1), hipMemcpyHostToDevice, s));
-    const size_t n1 = (size_t)std::max<int64_t>(t->nnz, 1), k1 = (size_t)std::max<int64_t>(pieces, 1),
-                 q1 = (size_t)std::max<int64_t>(pairs, 1);
+    const size_t n1 = (size_t)std::max<int64_t>(t->nnz, 1), q1 = (size_t)std::max<int64_t>(pairs, 1),
+                 w1 = (size_t)std::max<int64_t>(ntiles, 1) * (p.ts / 32);
     p.pl_pos = (uint16_t *)dev_alloc(sizeof(uint16_t) * n1, s);
-    p.pl_piece = (uint32_t *)dev_alloc(sizeof(uint32_t) * 4 * k1, s);
-    if (!p.pl_pos || !p.pl_piece) {
-        (void)hipStreamSynchronize(s);  // the host offsets must outlive their copy
-        return fail(SPT_E_OOM, "plan: arrays");
-    }
-    if (pieces == 0) {
-        SPT_HIP(hipStreamSynchronize(s));
-        return SPT_OK;
-    }
-    int64_t *pair_off = (int64_t *)dev_alloc(sizeof(int64_t) * (ntiles + 1), s);
-    uint32_t *desc = (uint32_t *)dev_alloc(sizeof(uint32_t) * k1, s);
-    uint32_t *prow = (uint32_t *)dev_alloc(sizeof(uint32_t) * k1, s);
-    uint32_t *ppair = (uint32_t *)dev_alloc(sizeof(uint32_t) * k1, s);
-    uint32_t *psub = (uint32_t *)dev_alloc(sizeof(uint32_t) * k1, s);
+    p.pl_start = (spt_u2 *)dev_alloc(sizeof(spt_u2) * w1, s);
+    p.pl_rec = (uint32_t *)dev_alloc(sizeof(uint32_t) * q1, s);
     uint64_t *keys = (uint64_t *)dev_alloc(sizeof(uint64_t) * q1, s);
     uint64_t *keys2 = (uint64_t *)dev_alloc(sizeof(uint64_t) * q1, s);
-    uint32_t *np = (uint32_t *)dev_alloc(sizeof(uint32_t) * q1, s);
     uint32_t *ia = (uint32_t *)dev_alloc(sizeof(uint32_t) * q1, s);
     uint32_t *ib = (uint32_t *)dev_alloc(sizeof(uint32_t) * q1, s);
-    uint32_t *cnt = (uint32_t *)dev_alloc(sizeof(uint32_t) * std::max(sort_ws_counts(pairs), exclusive_scan_ws(pairs)), s);
-    spt_status st = (pair_off && desc && prow && ppair && psub && keys && keys2 && np && ia && ib && cnt)
+    uint32_t *cnt = (uint32_t *)dev_alloc(sizeof(uint32_t) * sort_ws_counts(pairs), s);
+    spt_status st = (p.pl_pos && p.pl_start && p.pl_rec && keys && keys2 && ia && ib && cnt)
                         ? SPT_OK
-                        : fail(SPT_E_OOM, "plan: workspace");
-    if (st == SPT_OK &&
-        hipMemcpyAsync(pair_off, hq.data(), sizeof(int64_t) * (ntiles + 1), hipMemcpyHostToDevice, s) != hipSuccess)
-        st = hip_fail(hipGetLastError(), "plan: pair offsets");
-    MttkrpArgs a = make_args(t, nullptr, rank, mode, nullptr, p.ts);
-    a.pl_off = p.pl_off;
-    PlanOut o{pair_off, p.pl_pos, desc, prow, ppair, psub, keys, np};
-    if (st == SPT_OK) st = launch_emit_plan(a, o, s);
-    uint64_t *sk = nullptr;
+                        : fail(SPT_E_OOM, "plan: arrays");
+    uint64_t *sk = keys;
     uint32_t *sidx = nullptr;
-    if (st == SPT_OK) st = sort_u64_keys_ws(keys, keys2, ia, ib, cnt, pairs, t->lbits[mode], &sk, &sidx, s);
-    // pair pieces in row order -> exclusive prefix -> first record of each pair (emission order)
-    uint32_t *np_sorted = (sidx == ia) ? ib : ia;
-    uint32_t *tmp = (uint32_t *)((sk == keys2) ? keys : keys2);  // the unsorted key buffer is free now
-    uint32_t *pair_first = tmp + q1;                               // second half of that buffer
-    if (st == SPT_OK) st = launch_gather_u32(np, sidx, np_sorted, pairs, s);
-    if (st == SPT_OK) st = launch_exclusive_scan_u32(np_sorted, tmp, pairs, cnt, s);
-    if (st == SPT_OK) st = launch_scatter_u32(tmp, sidx, pair_first, pairs, s);
-    if (st == SPT_OK) st = launch_piece_pack(ppair, psub, pair_first, desc, prow, p.pl_piece, pieces, s);
-    if (st == SPT_OK && hipStreamSynchronize(s) != hipSuccess) st = hip_fail(hipGetLastError(), "plan: build");
-    for (void *q : {(void *)pair_off, (void *)desc, (void *)prow, (void *)ppair, (void *)psub, (void *)keys,
-                    (void *)keys2, (void *)np, (void *)ia, (void *)ib, (void *)cnt})
-        dev_free(q, s);
+    if (st == SPT_OK && pairs > 0) {
+        st = launch_emit_plan(a, p.pl_off, p.pl_pos, p.pl_start, keys, s);
+        if (st == SPT_OK) st = sort_u64_keys_ws(keys, keys2, ia, ib, cnt, pairs, t->lbits[mode], &sk, &sidx, s);
+        if (st == SPT_OK) st = launch_plan_records(sidx, p.pl_rec, pairs, s);
+    }
+    p.rec_row = sk;  // the sorted rows; the other key buffer goes back
+    for (void *q : {(void *)(sk == keys ? keys2 : keys), (void *)ia, (void *)ib, (void *)cnt}) dev_free(q, s);
+    // the host offsets must outlive their copy
+    if (hipStreamSynchronize(s) != hipSuccess && st == SPT_OK) st = hip_fail(hipGetLastError(), "plan: build");
     // the counting pass gave this mode's distinct rows per tile: its tile
     // dictionary costs one more pass
-    if (st == SPT_OK && p.ts == kDictTile) st = build_dict_mode(t, mode, s, hq.data());
+    if (st == SPT_OK && p.ts == kDictTile) st = build_dict_mode(t, mode, s, h.data());
     return st;
 }
 
@@ -453,65 +430,56 @@ spt_status profile_read(double *ms, int64_t *launches) {
 // by its workgroups on the way, or by a launch of its own where that is too
 // much for one of them (zero_on_the_way) or where out shares memory with a
 // factor that they read.
+static bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 static spt_status launch_seg_zeroing(MttkrpArgs a, float *out, hipStream_t s) {
     const int64_t n = (int64_t)a.frows[a.mode] * a.rank;
     a.out = zero_on_the_way(n, (a.nnz + a.tile - 1) / a.tile) ? out : nullptr;
-    for (int k = 0; k < a.nmodes; ++k) {
-        const uintptr_t f = (uintptr_t)a.f[k], o = (uintptr_t)out;
-        if (k != a.mode && o < f + sizeof(float) * (size_t)a.frows[k] * a.rank && f < o + sizeof(float) * (size_t)n)
+    for (int k = 0; k < a.nmodes; ++k)
+        if (k != a.mode && overlap(out, sizeof(float) * (size_t)n, a.f[k], sizeof(float) * (size_t)a.frows[k] * a.rank))
             a.out = nullptr;
-    }
     spt_status st = launch_mttkrp_seg(a, s);
     if (st == SPT_OK && !a.out) st = launch_fill_zero(out, n, s);
     return st;
 }
 
-// Records path shared by SEGMENT and TABLE: the main kernel writes P
-// records (row, R floats) and the reducer sums them per row into out.
-// SEGMENT records come out grouped by row (the plan laid them out); TABLE
-// records are radix-sorted by row first.  The record buffers belong to the
-// call (taken and released in stream order on s).
+// Records path shared by SEGMENT and TABLE: the main kernel writes P records
+// of R floats and the reducer sums them per row into out.  SEGMENT records
+// come out grouped by row (the plan laid them out and holds their rows,
+// rec_row); TABLE records come with rows and are radix-sorted first.  The
+// record buffers belong to the call (taken and released in stream order on s).
 spt_status reduce_via_records(Tensor *t, MttkrpArgs &a, int64_t P, int rank, int64_t rows, float *out, hipStream_t s,
-                              bool segment, TableArgs *ta = nullptr, int nwg = 0, const RecordWs *ws = nullptr) {
+                              const uint64_t *rec_row, TableArgs *ta = nullptr, int nwg = 0, const RecordWs *ws = nullptr) {
     const size_t n1 = (size_t)std::max<int64_t>(P, 1);
-    // SEGMENT records go to the caller's workspace when they fit
-    const bool own = !(segment && ws && ws->row && ws->val && (int64_t)n1 <= ws->records &&
-                       (int64_t)n1 * rank <= ws->val_floats);
-    uint64_t *rrow = own ? (uint64_t *)dev_alloc(sizeof(uint64_t) * n1, s) : ws->row;
-    float *rval = own ? (float *)dev_alloc(sizeof(float) * n1 * rank, s) : ws->val;
-    uint64_t *keys2 = nullptr;
-    uint32_t *ia = nullptr, *ib = nullptr, *cnt = nullptr;
-    auto release = [&]() {
-        if (own) {
-            dev_free(rrow, s);
-            dev_free(rval, s);
-        }
-        dev_free(keys2, s); dev_free(ia, s); dev_free(ib, s); dev_free(cnt, s);
-    };
-    if (!rrow || !rval) {
-        release();
-        return fail(SPT_E_OOM, "mttkrp: record workspace allocation failed");
-    }
-    spt_status st;
-    if (segment) {
-        a.rec_row = rrow;
+    if (rec_row) {  // SEGMENT: the plan's records, to the caller's workspace when they fit
+        const bool own = !(ws && ws->val && (int64_t)n1 * rank <= ws->val_floats);
+        float *rval = own ? (float *)dev_alloc(sizeof(float) * n1 * rank, s) : ws->val;
+        if (!rval) return fail(SPT_E_OOM, "mttkrp: record workspace allocation failed");
         a.rec_val = rval;
-        st = launch_seg_zeroing(a, out, s);
-        if (st == SPT_OK) st = launch_reduce_records(rrow, nullptr, rval, P, rank, rows, out, s);
-        release();
+        spt_status st = launch_seg_zeroing(a, out, s);
+        if (st == SPT_OK) st = launch_reduce_records(rec_row, nullptr, rval, P, rank, rows, out, s);
+        if (own) dev_free(rval, s);
         return st;
     }
-    keys2 = (uint64_t *)dev_alloc(sizeof(uint64_t) * n1, s);
-    ia = (uint32_t *)dev_alloc(sizeof(uint32_t) * n1, s);
-    ib = (uint32_t *)dev_alloc(sizeof(uint32_t) * n1, s);
-    cnt = (uint32_t *)dev_alloc(sizeof(uint32_t) * sort_ws_counts((int64_t)n1), s);
-    if (!keys2 || !ia || !ib || !cnt) {
+    uint64_t *rrow = (uint64_t *)dev_alloc(sizeof(uint64_t) * n1, s);
+    float *rval = (float *)dev_alloc(sizeof(float) * n1 * rank, s);
+    uint64_t *keys2 = (uint64_t *)dev_alloc(sizeof(uint64_t) * n1, s);
+    uint32_t *ia = (uint32_t *)dev_alloc(sizeof(uint32_t) * n1, s);
+    uint32_t *ib = (uint32_t *)dev_alloc(sizeof(uint32_t) * n1, s);
+    uint32_t *cnt = (uint32_t *)dev_alloc(sizeof(uint32_t) * sort_ws_counts((int64_t)n1), s);
+    auto release = [&]() {
+        dev_free(rrow, s); dev_free(rval, s);
+        dev_free(keys2, s); dev_free(ia, s); dev_free(ib, s); dev_free(cnt, s);
+    };
+    if (!rrow || !rval || !keys2 || !ia || !ib || !cnt) {
         release();
         return fail(SPT_E_OOM, "mttkrp: record workspace allocation failed");
     }
     ta->rec_row = rrow;
     ta->rec_val = rval;
-    st = launch_table(*ta, nwg, s);
+    spt_status st = launch_table(*ta, nwg, s);
     uint64_t *srow = nullptr;
     uint32_t *sidx = nullptr;
     if (st == SPT_OK) st = sort_u64_keys_ws(rrow, keys2, ia, ib, cnt, P, t->lbits[a.mode], &srow, &sidx, s);
@@ -538,7 +506,8 @@ spt_status run_mttkrp_impl(Tensor *t, const float *const *factors, int rank, int
         MttkrpArgs a = make_args(t, factors, rank, mode, out, p->ts);
         a.pl_pos = p->pl_pos;
         a.pl_off = p->pl_off;
-        a.pl_piece = p->pl_piece;
+        a.pl_start = p->pl_start;
+        a.pl_rec = p->pl_rec;
         a.rec_cap = p->records;
         // row cache: 4096-nonzero tiles, when the cache holds enough rows and
         // every non-output mode has its tile dictionary (spt_tensor_prepare)
@@ -558,7 +527,7 @@ spt_status run_mttkrp_impl(Tensor *t, const float *const *factors, int rank, int
                 a.d_cap = cap;
             }
         }
-        return reduce_via_records(t, a, p->records, rank, rows, out, s, /*segment=*/true, nullptr, 0, ws);
+        return reduce_via_records(t, a, p->records, rank, rows, out, s, p->rec_row, nullptr, 0, ws);
     }
     if (t->nnz == 0 || p->strategy == SPT_STRATEGY_SEGMENT || p->strategy == SPT_STRATEGY_DIRECT ||
         p->strategy == SPT_STRATEGY_REGROUP) {
@@ -587,7 +556,7 @@ spt_status run_mttkrp_impl(Tensor *t, const float *const *factors, int rank, int
     ta.rec_off = p->rec_off;
     MttkrpArgs a = ta.a;
     a.rec_off = p->rec_off;
-    return reduce_via_records(t, a, p->records, rank, rows, out, s, /*segment=*/false, &ta, p->nwg);
+    return reduce_via_records(t, a, p->records, rank, rows, out, s, nullptr, &ta, p->nwg);
 }
 
 }  // namespace spt
@@ -607,21 +576,19 @@ spt_status run_mttkrp_f64(Tensor *t, const double *const *factors, int rank, int
     MttkrpArgs a = make_args(t, nullptr, rank, mode, nullptr, p->ts);
     a.pl_pos = p->pl_pos;
     a.pl_off = p->pl_off;
-    a.pl_piece = p->pl_piece;
+    a.pl_start = p->pl_start;
+    a.pl_rec = p->pl_rec;
     a.rec_cap = p->records;
     const size_t n1 = (size_t)std::max<int64_t>(p->records, 1);
-    uint64_t *rrow = (uint64_t *)dev_alloc(sizeof(uint64_t) * n1, s);
     double *rval = (double *)dev_alloc(sizeof(double) * n1 * rank, s);
-    if (!rrow || !rval) {
-        dev_free(rrow, s);
-        dev_free(rval, s);
-        return fail(SPT_E_OOM, "mttkrp_f64: record workspace");
-    }
-    a.rec_row = rrow;
-    st = launch_mttkrp_seg_f64(a, t->vals64, factors, rval, s);
-    if (st == SPT_OK) st = launch_fill_zero((float *)out, 2 * rows * (int64_t)rank, s);
-    if (st == SPT_OK) st = launch_reduce_records_f64(rrow, rval, p->records, rank, rows, out, s);
-    dev_free(rrow, s);
+    if (!rval) return fail(SPT_E_OOM, "mttkrp_f64: record workspace");
+    const int64_t n = 2 * rows * (int64_t)rank;  // 32-bit words of the output
+    bool fill = !zero_on_the_way(n, (t->nnz + p->ts - 1) / p->ts);
+    for (int k = 0; k < t->nmodes; ++k)
+        if (k != mode) fill = fill || overlap(out, (size_t)n * 4, factors[k], sizeof(double) * (size_t)t->dims[k] * rank);
+    st = launch_mttkrp_seg_f64(a, t->vals64, factors, rval, fill ? nullptr : out, s);
+    if (st == SPT_OK && fill) st = launch_fill_zero((float *)out, n, s);
+    if (st == SPT_OK) st = launch_reduce_records_f64(p->rec_row, rval, p->records, rank, rows, out, s);
     dev_free(rval, s);
     return st;
 }
@@ -675,11 +642,12 @@ spt_status run_mttkrp_noalloc(Tensor *t, const float *const *factors, int rank, 
     }
     if (p->strategy != SPT_STRATEGY_SEGMENT)
         return fail(SPT_E_INVALID_ARG, "mttkrp_noalloc: only the SEGMENT, DIRECT and REGROUP strategies run without allocation");
-    const int64_t P = p->records;
-    const size_t row_bytes = ((sizeof(uint64_t) * (size_t)std::max<int64_t>(P, 1)) + 255) & ~size_t(255);
-    const size_t need = row_bytes + sizeof(float) * (size_t)std::max<int64_t>(P, 1) * rank;
+    // The limit counts runs cut at 64 nonzeros, with 8 bytes beside their
+    // columns: no fewer than the records, and fixed for a tensor and rank.
+    const int64_t P = p->records, limit = std::max<int64_t>(p->pieces, 1);
+    const size_t need = ((sizeof(uint64_t) * (size_t)limit + 255) & ~size_t(255)) + sizeof(float) * (size_t)limit * rank;
     if (need > kScratchBytes)
-        return fail(SPT_E_INVALID_ARG, "mttkrp_noalloc: " + std::to_string(P) + " records of rank " + std::to_string(rank) +
+        return fail(SPT_E_INVALID_ARG, "mttkrp_noalloc: " + std::to_string(limit) + " records of rank " + std::to_string(rank) +
                                            " need " + std::to_string(need) + " bytes of scratch, above the " +
                                            std::to_string(kScratchBytes) + "-byte maximum");
     void *base = nullptr;
@@ -688,7 +656,8 @@ spt_status run_mttkrp_noalloc(Tensor *t, const float *const *factors, int rank, 
     MttkrpArgs a = make_args(t, factors, rank, mode, out, p->ts);
     a.pl_pos = p->pl_pos;
     a.pl_off = p->pl_off;
-    a.pl_piece = p->pl_piece;
+    a.pl_start = p->pl_start;
+    a.pl_rec = p->pl_rec;
     a.rec_cap = P;
     const int cap = p->ts == kDictTile ? dict_cap(t->nmodes, rank) : 0;
     if (cap > 0 && t->plan.row_cache != 0) {
@@ -708,10 +677,9 @@ spt_status run_mttkrp_noalloc(Tensor *t, const float *const *factors, int rank, 
     }
     // every record the plan lays out is written by the main kernel before the
     // reduction reads it, so the array needs no clearing between calls
-    a.rec_row = (uint64_t *)base;
-    a.rec_val = (float *)((char *)base + row_bytes);
+    a.rec_val = (float *)base;
     st = launch_seg_zeroing(a, out, s);
-    if (st == SPT_OK) st = launch_reduce_records(a.rec_row, nullptr, a.rec_val, P, rank, rows, out, s);
+    if (st == SPT_OK) st = launch_reduce_records(p->rec_row, nullptr, a.rec_val, P, rank, rows, out, s);
     return st;
 }
 

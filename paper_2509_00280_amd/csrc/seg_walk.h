@@ -1,0 +1,207 @@
+// The walk of the SEGMENT kernels over a staged tile, shared by the FP32 and
+// FP64 kernels: which lanes take which nonzeros, and how the partial sums of
+// one output row come together.
+//
+// A tile's nonzeros stand in LDS in row-grouped order; a run is the stretch of
+// one output row.  Every lane group takes an equal stretch of positions,
+// whatever runs begin and end in it, sums a run at a time in registers and
+// stores it as the run's record when it ends.  A run that enters from the left
+// leaves its part in LDS; after a barrier the group in which it began adds the
+// parts to its right and stores the record.  So all groups make the same
+// number of steps at every rank and every skew, and a tile has one record for
+// each of its rows.
+// Groups that took whole pieces of at most 64 nonzeros of a row instead, dealt
+// longest first, waited for the longest: at rank 16 a 4096-nonzero tile has 16
+// nonzeros for each of its 256 groups and pieces of 64.  All-mode sweeps in
+// pieces and in equal shares: 20k nonzeros, rank 16 73.8 / 59.1 us; 3M, 4
+// modes, rank 10 942 / 869 us; 5M, 5 modes, rank 25 807 / 730 us; 100M, 3
+// modes, rank 32 4.42 / 4.21 ms; 150M, 4 modes, rank 64 (16 lanes a group, rows
+// from the LDS cache) 13.65 / 13.56 ms.
+#pragma once
+
+#include "tile_common.h"
+
+namespace spt {
+
+// Bytes of LDS the walk takes over from the staged tile: every lane's part and every group's flag.
+__host__ __device__ constexpr size_t walk_lds_bytes(int nt, size_t lane_bytes = 16) { return nt * (lane_bytes + 4); }
+
+// Run starts, 32 positions of a tile each: bit p says that a run begins there
+// (x), and the starts of the tile before them (y).  The plan holds T / 32 of
+// these per tile.
+typedef spt_u2 RunWord;
+
+// A lane group's share [q0, q1) of a tile, and what it needs of the run starts,
+// read ahead of the barrier behind the staging: its first run, whether that
+// begins at q0 and whether its last ends at q1, and the starts behind q0 in the
+// first 64 positions (more than a share has at up to 64 columns' lanes).
+struct WalkShare {
+    int q0, q1, run;
+    bool began, ended;
+    uint32_t bits[2];
+    const RunWord *words;  // the tile's
+};
+
+template <int T>
+__device__ __forceinline__ uint32_t run_bits(const RunWord *words, int q) {  // starts of positions [q, q + 32)
+    const int w = q >> 5, sh = q & 31;
+    const uint32_t lo = words[min(w, T / 32 - 1)].x, hi = words[min(w + 1, T / 32 - 1)].x;
+    return sh ? (lo >> sh) | (hi << (32 - sh)) : lo;
+}
+
+// step: positions that a step of the walk takes
+template <int NT, int T>
+__device__ __forceinline__ WalkShare walk_share(const LaneGroup &lg, int cnt, int step, const RunWord *words) {
+    const int NG = NT / 64 * lg.per_wave;
+    const int each = ((cnt + NG - 1) / NG + step - 1) / step * step;
+    WalkShare ws;
+    ws.q0 = min(lg.g * each, cnt);
+    ws.q1 = lg.on ? min(ws.q0 + each, cnt) : ws.q0;
+    ws.words = words;
+    const RunWord first = words[min(ws.q0 >> 5, T / 32 - 1)];
+    ws.run = (int)(first.y + __popc(first.x & (0xFFFFFFFFu >> (31 - (ws.q0 & 31))))) - 1;
+    ws.began = (first.x >> (ws.q0 & 31)) & 1u;
+    ws.ended = ws.q1 >= cnt || (run_bits<T>(words, ws.q1) & 1u);
+    ws.bits[0] = run_bits<T>(words, ws.q0) & ~1u;
+    ws.bits[1] = run_bits<T>(words, ws.q0 + 32);
+    return ws;
+}
+
+// Walk the first cnt positions of a staged tile (every thread of the workgroup
+// calls, after the barrier behind the staging).  product(q, p) forms the
+// products p[u][:] of the positions q + u, u < UB, for this lane's columns; q is
+// a multiple of UB, and the staging fills positions from cnt on to the next
+// multiple with anything that can be read.
+// rec[k] is the record of the tile's run k; records have ld columns (R..ld-1
+// are zeroed).  Reads stay inside the tile and no record at or beyond rec_cap
+// is written, whatever the plan holds.
+// UB staged words of 4 or 8 bytes at p (aligned to all of them) in one read
+template <int UB, class Word>
+__device__ __forceinline__ void load_words(const Word *p, Word (&x)[UB]) {
+    static_assert(UB == 1 || UB == 2, "one or two");
+    if constexpr (UB == 2) {
+        typedef Word pair __attribute__((ext_vector_type(2)));
+        const pair t = *reinterpret_cast<const pair *>(p);
+        x[0] = t.x;
+        x[1] = t.y;
+    } else {
+        x[0] = p[0];
+    }
+}
+
+template <class Real, int NT, int T, int VEC, int UB, class Product>
+__device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &ws, int R, int cnt, int nruns,
+                                         const uint32_t *__restrict__ rec, uint32_t rec_cap,
+                                         Real *__restrict__ rec_val, int ld, char *lds, const Product &product) {
+    constexpr int kPart = 1, kThrough = 2;  // a run entered from the left; it also leaves to the right
+    const int NG = NT / 64 * lg.per_wave;
+    const int q0 = ws.q0, q1 = ws.q1;
+    // a sum for each nonzero of a step: chains of additions UB times shorter
+    Real acc[UB][VEC], part[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) part[v] = 0;
+    auto clear = [&]() {
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[u][v] = 0;
+    };
+    auto gather_sums = [&]() {  // the sums of the step's slots into the first
+#pragma unroll
+        for (int u = 1; u < UB; ++u)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[0][v] += acc[u][v];
+    };
+    clear();
+    // run k is the open one; the group's lanes hold the records of runs kb, kb + 1, ...
+    int k = ws.run, kb = 0, flag = 0;
+    uint32_t held = 0;
+    bool began = ws.began, open = false;
+    auto hold = [&]() {
+        kb = k;
+        held = k + lg.j < nruns ? rec[k + lg.j] : 0xFFFFFFFFu;
+    };
+    auto write = [&]() {
+        const uint32_t r = __shfl(held, (int)(threadIdx.x & 63) - lg.j + (k - kb), 64);
+        if (r < rec_cap) {
+            Real *o = rec_val + (int64_t)r * ld;
+            store_vec<VEC>(o + lg.col, acc[0]);
+            for (int z = R + lg.j; z < ld; z += lg.G) o[z] = 0;
+        }
+    };
+    auto close = [&]() {  // the open run is over
+        gather_sums();
+        if (began) {
+            write();
+        } else {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) part[v] = acc[0][v];
+            flag = kPart;
+        }
+    };
+    if (q0 < q1) {
+        hold();
+        for (int qb = q0; qb < q1; qb += 32) {
+            const int n = min(32, q1 - qb);
+            uint32_t bits = qb == q0 ? ws.bits[0] : qb == q0 + 32 ? ws.bits[1] : run_bits<T>(ws.words, qb);
+            for (int i = 0; i < n; i += UB) {
+                Real p[UB][VEC];
+                product(qb + i, p);
+                if (bits & ((1u << UB) - 1u)) {  // a run begins in this step
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) {
+                        if (u == 0 || i + u < n) {
+                            if (bits & (1u << u)) {
+                                close();
+                                clear();
+                                ++k;
+                                began = true;
+                                if (k - kb >= lg.G) hold();
+                            }
+#pragma unroll
+                            for (int v = 0; v < VEC; ++v) acc[u][v] += p[u][v];
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < UB; ++u)
+                        if (u == 0 || i + u < n)
+#pragma unroll
+                            for (int v = 0; v < VEC; ++v) acc[u][v] += p[u][v];
+                }
+                bits >>= UB;
+            }
+        }
+        if (ws.ended) {
+            close();
+        } else {
+            gather_sums();
+            if (began) {
+                open = true;
+            } else {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) part[v] = acc[0][v];
+                flag = kPart | kThrough;
+            }
+        }
+    }
+    __syncthreads();  // the staged tile is done with
+    Real *parts = reinterpret_cast<Real *>(lds);
+    int *flags = reinterpret_cast<int *>(parts + NT * VEC);
+    if (lg.on) {
+        if (flag) store_vec<VEC>(parts + (lg.g * lg.G + lg.j) * VEC, part);
+        if (lg.j == 0) flags[lg.g] = flag;
+    }
+    __syncthreads();
+    if (open) {
+        for (int m = lg.g + 1; m < NG; ++m) {
+            const Real *p = parts + (m * lg.G + lg.j) * VEC;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[0][v] += p[v];
+            if (!(flags[m] & kThrough)) break;
+        }
+        write();
+    }
+}
+
+}  // namespace spt

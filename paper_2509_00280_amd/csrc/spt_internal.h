@@ -11,6 +11,8 @@
 
 namespace spt {
 
+typedef uint32_t spt_u2 __attribute__((ext_vector_type(2)));
+
 constexpr int kMaxModes = SPT_MAX_MODES;
 constexpr int kMaxRuns = 160;          // l(p) <= 128 bits plus splits at 32-bit word boundaries
 constexpr uint32_t kNoRow = 0xFFFFFFFFu;
@@ -74,15 +76,17 @@ struct ModePlan {
     int64_t sub_per_wg = 0;
     int64_t records = 0;     // TABLE / SEGMENT: records written per call
     int64_t *rec_off = nullptr;  // TABLE: device, nwg offsets
-    // SEGMENT plan: per nonzero its position in the tile's row-grouped order;
-    // per piece (tile-major, pl_off[tile] .. pl_off[tile + 1]) its
-    // start | length << 16, row and record (records of one row contiguous):
-    // packed as 4 u32 {desc, row, record, 0} per piece in pl_piece (one
-    // tensor), in the three arrays pl_desc / pl_row / pl_dest (batched plans)
+    // SEGMENT plan: per nonzero its position in the tile's row-grouped order
+    // (pl_pos); per tile T / 32 words of run starts (pl_start, seg_walk.h); per
+    // run (tile-major in position order, pl_off[tile] .. pl_off[tile + 1]) its
+    // record (pl_rec); per record its row (rec_row, ascending: the records of a
+    // row are contiguous)
     uint16_t *pl_pos = nullptr;
     int64_t *pl_off = nullptr;
-    uint32_t *pl_piece = nullptr;
-    uint32_t *pl_desc = nullptr, *pl_row = nullptr, *pl_dest = nullptr;
+    spt_u2 *pl_start = nullptr;
+    uint32_t *pl_rec = nullptr;
+    uint64_t *rec_row = nullptr;
+    int64_t pieces = 0;  // SEGMENT: runs cut at 64 nonzeros (the measure of spt_mttkrp_noalloc's limit)
 };
 
 struct Tensor {
@@ -124,10 +128,8 @@ spt_status prepare_single(Tensor *t, int rank, hipStream_t s);
 // writes them there instead of allocating (a driver that calls every mode in
 // turn on one stream allocates once).
 struct RecordWs {
-    uint64_t *row = nullptr;
     float *val = nullptr;
-    int64_t records = 0;    // capacity in records
-    int64_t val_floats = 0;  // capacity of val
+    int64_t val_floats = 0;  // capacity
 };
 // the largest record count over the tensor's modes under its prepared plans
 int64_t max_plan_records(const Tensor *t);
@@ -159,11 +161,6 @@ spt_status launch_export(const Tensor *t, uint64_t *keys, hipStream_t s);
 // caller-owned buffers (see encode.hip).
 size_t sort_ws_counts(int64_t n);
 spt_status launch_gather_u32(const uint32_t *src, const uint32_t *idx, uint32_t *out, int64_t n, hipStream_t s);
-// dst[idx[j]] = src[j]
-spt_status launch_scatter_u32(const uint32_t *src, const uint32_t *idx, uint32_t *dst, int64_t n, hipStream_t s);
-// exclusive prefix sum of n u32 values (totals below 2^32); ws of exclusive_scan_ws(n) u32
-size_t exclusive_scan_ws(int64_t n);
-spt_status launch_exclusive_scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *ws, hipStream_t s);
 spt_status sort_u64_keys_ws(uint64_t *keys, uint64_t *keys2, uint32_t *idx_a, uint32_t *idx_b, uint32_t *counts,
                             int64_t n, int nbits, uint64_t **sorted_out, uint32_t **idx_out, hipStream_t s);
 
@@ -180,16 +177,16 @@ struct MttkrpArgs {
     const float *f[kMaxModes];
     uint32_t frows[kMaxModes];  // rows of each factor (clamped to 2^32 - 1)
     float *out;
-    // SEGMENT strategy: record output
-    uint64_t *rec_row;
+    const int64_t *rec_off;   // TABLE: per tile, ntiles + 1 entries
+    // SEGMENT: record output, the plan (see ModePlan) and its records (writes
+    // beyond are dropped)
     float *rec_val;
-    const int64_t *rec_off;   // per tile, ntiles + 1 entries
-    // SEGMENT plan (see ModePlan)
     const uint16_t *pl_pos;
     const int64_t *pl_off;
-    const uint32_t *pl_piece;  // one tensor: 4 u32 per piece, 16-byte aligned
-    const uint32_t *pl_desc, *pl_row, *pl_dest;  // batched members
-    int64_t rec_cap;          // records the plan laid out (writes beyond are dropped)
+    const spt_u2 *pl_start;
+    const uint32_t *pl_rec;
+    const uint64_t *pl_rec_row;  // batched members
+    int64_t rec_cap;
     // row cache (SEGMENT, tiles of kDictTile): the tile dictionaries of the
     // non-output modes in order (o-th non-output mode), and the cached rows
     // per mode (0: no cache)
@@ -205,30 +202,25 @@ spt_status launch_mttkrp(const MttkrpArgs &a, int strategy, hipStream_t s);
 bool seg_tile_ok(int tile, int nmodes);
 // per tile: pieces | distinct rows << 32
 spt_status launch_count_pieces(const MttkrpArgs &a, int64_t *counts, hipStream_t s);
-// outputs of the plan-emission pass (a.pl_off must hold the piece offsets)
-struct PlanOut {
-    const int64_t *pair_off;  // per tile, distinct (tile, row) pairs
-    uint16_t *pos;            // nnz
-    uint32_t *desc, *prow, *ppair, *psub;  // per piece
-    uint64_t *pair_key;       // per pair: its row (sort key)
-    uint32_t *pair_np;        // per pair: its pieces
-};
-spt_status launch_emit_plan(const MttkrpArgs &a, const PlanOut &o, hipStream_t s);
-// packed[k] = {desc[k], prow[k], first record of piece k's pair + its index, 0}
-spt_status launch_piece_pack(const uint32_t *ppair, const uint32_t *psub, const uint32_t *pair_first,
-                             const uint32_t *desc, const uint32_t *prow, uint32_t *packed, int64_t n, hipStream_t s);
+// the plan's emission pass: positions, run starts and, per run in position
+// order (pair_off: the tiles' first runs), its row
+spt_status launch_emit_plan(const MttkrpArgs &a, const int64_t *pair_off, uint16_t *pos, spt_u2 *start,
+                            uint64_t *pair_key, hipStream_t s);
+// rec[idx[j]] = j
+spt_status launch_plan_records(const uint32_t *idx, uint32_t *rec, int64_t n, hipStream_t s);
 // Whether a launch of `wgs` workgroups clears n floats of output on its way.
 // It saves the fill launch (rank 64, 150M nonzeros, 14 KB a workgroup: 25 us of
 // 3.4 ms a call) but is at the mercy of the few workgroups of a small or very
 // sparse tensor: at 1 MB each (2.6M rows of rank 32, 1.3M nonzeros) a call
 // took 262 us against 247 with a fill of its own, at 5 MB 112 against 76.
 inline bool zero_on_the_way(int64_t n, int64_t wgs) { return n <= wgs * (64 * 1024 / 4); }
-// the SEGMENT kernel on a's plan: records to a.rec_row / a.rec_val, a.out (if any) zeroed
+// the SEGMENT kernel on a's plan: records to a.rec_val, a.out (if any) zeroed
 spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s);
 // mttkrp_f64.hip
 bool f64_tile_ok(int tile, int nmodes);
+// out: zeroed on the way, or null
 spt_status launch_mttkrp_seg_f64(const MttkrpArgs &a, const double *vals64, const double *const *F, double *rec_val,
-                                 hipStream_t s);
+                                 double *out, hipStream_t s);
 spt_status launch_reduce_records_f64(const uint64_t *srow, const double *rec, int64_t P, int R, int64_t rows,
                                      double *out, hipStream_t s);
 spt_status launch_gather_f64(const double *src, const uint32_t *idx, double *dst, int64_t n, hipStream_t s);
@@ -241,9 +233,8 @@ int dict_cap(int nmodes, int rank);
 
 // Batched SEGMENT MTTKRP: every tensor's tiles (one tile size per launch:
 // 1024, 2048 or 4096 nonzeros) in one persistent launch, each with the
-// tensor's batched plan (a.pl_*); records carry rows of the batch's
-// concatenated output (row_base + row) and go to rec_base + the plan's
-// record, so the batch's records stay grouped by row.
+// tensor's batched plan (a.pl_*); records go to rec_base + the plan's record,
+// so the batch's records stay grouped by row of its concatenated output.
 constexpr int kBatchTileDefault = 2048;
 // the batched tile of a tensor: its plan's batch_tile, else the default
 int batch_tile_of(const Tensor *t);
@@ -258,14 +249,16 @@ bool seg_batch_fits(int nmodes_max, int tile);
 spt_status launch_count_pieces_batched(const SegItem *items, int count, int64_t total_tiles, int nmodes_max, int tile,
                                        int64_t *counts, hipStream_t s);
 spt_status launch_emit_plan_batched(const SegItem *items, int count, int64_t total_tiles, int nmodes_max, int tile,
-                                    const int64_t *gpiece_off, const int64_t *gpair_off, uint32_t *ppair,
-                                    uint32_t *psub, uint64_t *pair_key, uint32_t *pair_np, hipStream_t s);
-spt_status launch_piece_dest_batched(const SegItem *items, int count, const int64_t *piece_base, const uint32_t *ppair,
-                                     const uint32_t *psub, const uint32_t *pair_first, int64_t n, hipStream_t s);
+                                    const int64_t *gpair_off, uint64_t *pair_key, hipStream_t s);
+// the sorted pairs of a batch to its tensors' pl_rec and rec_row (n pairs)
+spt_status launch_plan_records_batched(const SegItem *items, int count, const uint64_t *sorted, const uint32_t *idx,
+                                       int64_t n, hipStream_t s);
+// rows[j] = row of the batch's record j in its concatenated output
+spt_status launch_record_rows_batched(const SegItem *items, int count, int64_t n, uint64_t *rows, hipStream_t s);
 // next_tile: a device counter (8 bytes) the launch zeroes and the workgroups pull tiles from;
 // vec4: every member's rank is at least 4; out: out_floats that the launch also zeroes
 spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t total_tiles, int nmodes_min,
-                                     int nmodes_max, int tile, int ld, bool vec4, uint64_t *rec_row, float *rec_val,
+                                     int nmodes_max, int tile, int ld, bool vec4, float *rec_val,
                                      unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s);
 
 // Batched dense steps (dense.hip): one workgroup per item, except apply
@@ -334,6 +327,7 @@ struct ModeItems {
     int count = 0, ld = 0, rmax = 0;
     bool vec4 = true;
     int64_t tiles = 0, records = 0, rows = 0, blocks = 0;
+    int64_t row_at = 0;  // first of the mode's record rows in the engine's array
     size_t seg_off = 0, gm_off = 0, sv_off = 0, ap_off = 0;
     std::vector<int> member_idx;
     std::vector<SegItem> seg_v;
@@ -365,18 +359,17 @@ struct DevBuf {
     }
 };
 
-// record and sort buffers of the batched MTTKRP
+// record buffer and tile counter of the batched MTTKRP
 struct BatchMttkrpWs {
-    DevBuf rec_row, rec_val, counter;
+    DevBuf rec_val, counter;
     void release(hipStream_t s) {
-        rec_row.release(s);
         rec_val.release(s);
         counter.release(s);
     }
 };
 spt_status run_mttkrp_batched_mode(const SegItem *d_items, int count, int64_t total_tiles, int nmodes_min, int nmodes_max,
-                                   int tile, int64_t records, int64_t rows, int ld, bool vec4, float *M_all,
-                                   BatchMttkrpWs &ws, hipStream_t s);
+                                   int tile, const uint64_t *rec_row, int64_t records, int64_t rows, int ld, bool vec4,
+                                   float *M_all, BatchMttkrpWs &ws, hipStream_t s);
 // batched plans of `mode` at `tile` for the tensors that lack them (a plan
 // at another tile is released and rebuilt); synchronises s when it builds
 spt_status ensure_batch_plans(const std::vector<Tensor *> &ts, int mode, int tile, hipStream_t s);
@@ -418,6 +411,7 @@ private:
     int init_count_ = 0, init_rmax_ = 0;
     int64_t init_slices_ = 0;
     DevBuf gram_ws_;  // partial Grams of the batched Gram launches
+    DevBuf rows_buf_;  // record rows of every mode's launch
     DevBuf items_buf_, M_buf_, fit_buf_, status_buf_, inner_buf_, resid_buf_, resid_items_buf_;
     std::vector<char> blob_;  // host image of the item arrays (kept until the next upload)
     float *M_all_ = nullptr;

@@ -53,6 +53,38 @@ __device__ __forceinline__ void load_vec_any(const float *p, float (&x)[VEC]) {
     }
 }
 
+// two doubles likewise
+typedef double spt_d2u __attribute__((ext_vector_type(2), aligned(8)));
+
+template <int VEC>
+__device__ __forceinline__ void load_vec_any(const double *p, double (&x)[VEC]) {
+    if constexpr (VEC % 2 == 0) {
+#pragma unroll
+        for (int q = 0; q < VEC; q += 2) {
+            const spt_d2u t = *reinterpret_cast<const spt_d2u *>(p + q);
+            x[q] = t.x;
+            x[q + 1] = t.y;
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) x[q] = p[q];
+    }
+}
+
+template <int VEC>
+__device__ __forceinline__ void store_vec(double *p, const double (&x)[VEC]) {
+    if constexpr (VEC % 2 == 0) {
+#pragma unroll
+        for (int q = 0; q < VEC; q += 2) {
+            const spt_d2u t = {x[q], x[q + 1]};
+            *reinterpret_cast<spt_d2u *>(p + q) = t;
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) p[q] = x[q];
+    }
+}
+
 template <int VEC>
 __device__ __forceinline__ void store_vec(float *p, const float (&x)[VEC]) {
     if constexpr (VEC == 4) {
@@ -85,11 +117,11 @@ struct LaneGroup {
 template <int VEC>
 __device__ __forceinline__ LaneGroup lane_group(int R) {
     LaneGroup q;
-    q.G = VEC == 4 ? (R + 3) >> 2 : R;
+    q.G = VEC > 1 ? (R + VEC - 1) / VEC : R;
     q.per_wave = 64 / q.G;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, gl = lane / q.G;
     q.j = lane - gl * q.G;
-    q.col = VEC == 4 ? min(4 * q.j, R - 4) : q.j;
+    q.col = VEC > 1 ? min(VEC * q.j, R - VEC) : q.j;
     q.g = w * q.per_wave + gl;
     q.on = gl < q.per_wave;
     return q;
@@ -117,7 +149,6 @@ __device__ __forceinline__ void zero_slice(float *__restrict__ p, int64_t n, int
 // offset straight to the load, with no address arithmetic, and rows past
 // `rows` read as zero.  The descriptor is wave-uniform (SGPRs); R <= 4095.
 typedef int spt_i4 __attribute__((ext_vector_type(4)));
-typedef uint32_t spt_u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t spt_u4 __attribute__((ext_vector_type(4)));
 __device__ spt_f4 spt_row_load4(spt_i4 rsrc, int vindex, int voffset, int soffset, int aux) __asm(
     "llvm.amdgcn.struct.buffer.load.v4f32");
@@ -145,6 +176,30 @@ __device__ __forceinline__ void load_row_vec(spt_i4 rsrc, uint32_t row, int col,
     } else {
 #pragma unroll
         for (int q = 0; q < VEC; ++q) x[q] = spt_row_load1(rsrc, (int)row, (col + q) * 4, 0, 0);
+    }
+}
+
+// the same for FP64 rows
+__device__ __forceinline__ spt_i4 row_rsrc(const double *base, int R, uint32_t rows) {
+    return row_rsrc(reinterpret_cast<const float *>(base), 2 * R, rows);
+}
+
+template <int VEC>
+__device__ __forceinline__ void load_row_vec(spt_i4 rsrc, uint32_t row, int col, double (&x)[VEC]) {
+    if constexpr (VEC % 2 == 0) {
+#pragma unroll
+        for (int q = 0; q < VEC; q += 2) {
+            const spt_f4 t = spt_row_load4(rsrc, (int)row, (col + q) * 8, 0, 0);
+            x[q] = __hiloint2double(__float_as_int(t.y), __float_as_int(t.x));
+            x[q + 1] = __hiloint2double(__float_as_int(t.w), __float_as_int(t.z));
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) {
+            const float lo = spt_row_load1(rsrc, (int)row, (col + q) * 8, 0, 0);
+            const float hi = spt_row_load1(rsrc, (int)row, (col + q) * 8 + 4, 0, 0);
+            x[q] = __hiloint2double(__float_as_int(hi), __float_as_int(lo));
+        }
     }
 }
 

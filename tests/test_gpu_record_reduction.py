@@ -10,7 +10,7 @@ from paper_2509_00280_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# Rows of up to 200k products: pieces of 64, chunks of at most 64 records and
+# Rows of up to 200k products: a tile's run, chunks of at most 64 records and
 # the sums over those, each a short chain of FP32 additions.  Random roundings
 # of 2^-24 in chains of at most 64 + 64 + 500 terms stay below 628 x 6e-8 of
 # the row's scale in the worst case.
