@@ -23,6 +23,10 @@ constexpr int kRedThreads = 256;
 // with atomics at every chunk's edge, chunks of 64 to 512 records took 21 us
 // for 1000 records of rank 16 (one serial chain) and sums over short chunks
 // 17 ms instead of 13.6 for the rank-64 sweep.
+// The roundings of an FP32 sum: a round's records are added up before they
+// join the run's sum, and the parts of a run over several groups in FP64.
+// FP64 sums throughout took 4.34 instead of 4.21 ms for an all-mode sweep (rank
+// 32, 3 modes, 100M nonzeros); this takes 4.21 ms and as long as one chain.
 template <class Real, int VEC>
 __global__ __launch_bounds__(kRedThreads) void k_reduce_records(const uint64_t *__restrict__ srow,
                                                                 const uint32_t *__restrict__ sidx,
@@ -40,6 +44,14 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_records(const uint64_t *
     Real acc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = 0;
+    Real few[VEC] = {};  // the open run's records of this round, not yet in acc
+    auto fold = [&]() {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            acc[v] += few[v];
+            few[v] = 0;
+        }
+    };
     uint64_t cur = 0, after = ~0ull;
     bool began = true;  // the open run began in this chunk
     Real *mine = part + (g * lg.G + lg.j) * VEC;
@@ -60,6 +72,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_records(const uint64_t *
     // a run that is over: stored, or handed to the group where it began
     int my_flag = 0;
     auto close = [&]() {
+        fold();
         if (began) {
             emit(cur, true);
         } else if (g == 0) {
@@ -98,13 +111,17 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_records(const uint64_t *
                         cur = r[u];
                         began = true;
 #pragma unroll
-                        for (int v = 0; v < VEC; ++v) acc[v] = x[u][v];
+                        for (int v = 0; v < VEC; ++v) {
+                            acc[v] = 0;
+                            few[v] = x[u][v];
+                        }
                     } else {
 #pragma unroll
-                        for (int v = 0; v < VEC; ++v) acc[v] += x[u][v];
+                        for (int v = 0; v < VEC; ++v) few[v] += x[u][v];
                     }
                 }
             }
+            fold();
         }
         if (cur != after) {
             close();
@@ -119,15 +136,20 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_records(const uint64_t *
     // stands in for what began before it): add the parts to its right
     if (work && cur == after && (began || g == 0)) {
         bool ended = false;
+        double sum[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) sum[v] = (double)acc[v];
         for (int k = g + 1; k < NG; ++k) {
             const Real *p = part + (k * lg.G + lg.j) * VEC;
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[v] += p[v];
+            for (int v = 0; v < VEC; ++v) sum[v] += (double)p[v];
             if (!(flag[k] & kThrough)) {
                 ended = true;
                 break;
             }
         }
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] = (Real)sum[v];
         emit(cur, began && ended);
     }
 }
