@@ -185,7 +185,7 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
         const int k = o + (o >= mode);
         fb[o] = o < no ? row_rsrc(a.f[k], R, a.frows[k]) : row_rsrc((const float *)nullptr, R, 0u);
     }
-    auto product = [&](int q, float (&p)[UB][VEC]) {
+    auto product = [&](int q, float (&p)[UB][VEC], float (&last)[UB][VEC]) {
         float x[UB];
         load_words<UB>(valg + q, x);
 #pragma unroll
@@ -209,7 +209,10 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
 #pragma unroll
                     for (int u = 0; u < UB; ++u)
 #pragma unroll
-                        for (int v = 0; v < VEC; ++v) p[u][v] *= xv[o][u][v];
+                        for (int v = 0; v < VEC; ++v) {
+                            if (o == 0) last[u][v] = xv[0][u][v];
+                            else p[u][v] *= xv[o][u][v];
+                        }
         } else {
 #pragma unroll
             for (int o = 0; o < NO; ++o) {
@@ -220,7 +223,10 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
 #pragma unroll
                     for (int u = 0; u < UB; ++u)
 #pragma unroll
-                        for (int v = 0; v < VEC; ++v) p[u][v] *= xv[u][v];
+                        for (int v = 0; v < VEC; ++v) {
+                            if (o == 0) last[u][v] = xv[u][v];
+                            else p[u][v] *= xv[u][v];
+                        }
                 }
             }
         }
@@ -588,7 +594,7 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
         fb[o] = o < no ? row_rsrc(a.f[k], R, a.frows[k]) : row_rsrc((const float *)nullptr, R, 0u);
     }
     const char *mine = lds + lg.j * VEC * 4;  // this lane's columns of the row at offset 0
-    auto product = [&](int q0, float (&p)[UB][VEC]) {
+    auto product = [&](int q0, float (&p)[UB][VEC], float (&last)[UB][VEC]) {
         uint32_t row[NO][UB];
         float x[UB];
         load_words<UB>(valg + q0, x);
@@ -620,7 +626,10 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
 #pragma unroll
                 for (int u = 0; u < UB; ++u)
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) p[u][v] *= xv[o][u][v];
+                    for (int v = 0; v < VEC; ++v) {
+                        if (o == 0) last[u][v] = xv[0][u][v];
+                        else p[u][v] *= xv[o][u][v];
+                    }
     };
     run_walk<float, NT, T, VEC, UB>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, a.rec_val, R, lds, product);
 }
@@ -656,8 +665,14 @@ __device__ __forceinline__ int seg_item_of(const SegItem *__restrict__ items, in
 // *next_tile, zero at launch, until the counter passes total_tiles.  A
 // workgroup's tiles only increase, so it finds each tile's tensor by moving
 // forward from the last one.
+// 3 and 4 modes take the walk of their mode count, all of whose gathers are in
+// flight together, without a branch round each.  Bounded to 128 VGPRs (two
+// workgroups of 8 waves to a CU): at 64, 72 and 80, with 4, 3 and 3
+// workgroups, the spills cost more than the waves bring (32 members of 10k to
+// 5M nonzeros, ranks 16 and 32, 10 iterations: 40.5, 40.9 and 36.3 ms, here
+// 31.7, and 33.0 with one walk for all mode counts at 72).
 template <int NT, int VEC, int NMAX, int NFIX>
-__global__ __launch_bounds__(NT, 7) void k_mttkrp_segp_batched(const SegItem *__restrict__ items, int count,
+__global__ __launch_bounds__(NT, 4) void k_mttkrp_segp_batched(const SegItem *__restrict__ items, int count,
                                                             int64_t total_tiles, float *__restrict__ rec_val, int ld,
                                                             unsigned long long *__restrict__ next_tile,
                                                             float *__restrict__ out, int64_t out_floats) {
@@ -667,13 +682,21 @@ __global__ __launch_bounds__(NT, 7) void k_mttkrp_segp_batched(const SegItem *__
     for (;;) {
         if (threadIdx.x == 0) s_tile = (int64_t)atomicAdd(next_tile, 1ull);
         __syncthreads();  // also: every wave is done with the previous tile's LDS
-        const int64_t it = s_tile;
+        // the same for all lanes, and known to be: an item's fields stay in scalar registers
+        const int64_t it = (int64_t)__builtin_amdgcn_readfirstlane((int)s_tile) & 0xFFFFFFFFll |
+                           (int64_t)__builtin_amdgcn_readfirstlane((int)(s_tile >> 32)) << 32;
         __syncthreads();  // every thread has read s_tile before it is replaced
         if (it >= total_tiles) break;
         while (b + 1 < count && items[b + 1].first_tile <= it) ++b;
         const SegItem &item = items[b];
-        segp_tile<NT, 4 * NT, VEC, NMAX, NFIX>(item.a, it - item.first_tile, lds, rec_val + item.rec_base * ld, ld,
-                                               ZeroSlice{out, out_floats, it, total_tiles});
+        const ZeroSlice zero{out, out_floats, it, total_tiles};
+        float *rv = rec_val + item.rec_base * ld;
+        if (NMAX == 4 && NFIX == 0 && item.a.nmodes == 4)
+            segp_tile<NT, 4 * NT, VEC, 4, 4>(item.a, it - item.first_tile, lds, rv, ld, zero);
+        else if (NMAX == 4 && NFIX == 0 && item.a.nmodes == 3)
+            segp_tile<NT, 4 * NT, VEC, 3, 3>(item.a, it - item.first_tile, lds, rv, ld, zero);
+        else
+            segp_tile<NT, 4 * NT, VEC, NMAX, NFIX>(item.a, it - item.first_tile, lds, rv, ld, zero);
     }
 }
 

@@ -68,9 +68,9 @@ __device__ __forceinline__ WalkShare walk_share(const LaneGroup &lg, int cnt, in
 }
 
 // Walk the first cnt positions of a staged tile (every thread of the workgroup
-// calls, after the barrier behind the staging).  product(q, p) forms the
-// products p[u][:] of the positions q + u, u < UB, for this lane's columns; q is
-// a multiple of UB, and the staging fills positions from cnt on to the next
+// calls, after the barrier behind the staging).  product(q, p, x) forms the
+// products of the positions q + u, u < UB, for this lane's columns, up to the
+// last factor: p[u][:] * x[u][:], which the sum takes in one fma; q is a multiple of UB, and the staging fills positions from cnt on to the next
 // multiple with anything that can be read.
 // rec[k] is the record of the tile's run k; records have ld columns (R..ld-1
 // are zeroed).  Reads stay inside the tile and no record at or beyond rec_cap
@@ -94,8 +94,10 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
                                          const uint32_t *__restrict__ rec, uint32_t rec_cap,
                                          Real *__restrict__ rec_val, int ld, char *lds, const Product &product) {
     constexpr int kPart = 1, kThrough = 2;  // a run entered from the left; it also leaves to the right
+    constexpr uint32_t kNone = 0xFFFFFFFFu;  // no record: a store to it is dropped
     const int NG = NT / 64 * lg.per_wave;
     const int q0 = ws.q0, q1 = ws.q1;
+    const spt_i4 slots = word_rsrc(rec, (uint32_t)nruns), out = row_rsrc(rec_val, ld, rec_cap);
     // a sum for each nonzero of a step: chains of additions UB times shorter
     Real acc[UB][VEC], part[VEC];
 #pragma unroll
@@ -113,76 +115,81 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
             for (int v = 0; v < VEC; ++v) acc[0][v] += acc[u][v];
     };
     clear();
-    // run k is the open one; the group's lanes hold the records of runs kb, kb + 1, ...
-    int k = ws.run, kb = 0, flag = 0;
-    uint32_t held = 0;
+    // The records of the open run and of the next: the load of a run's record
+    // is one run ahead of its use, and the gathers of a later step are waited
+    // for behind it anyway.  Short runs make nearly every step of a wave end
+    // some group's run, so the end of a run is kept to a dozen instructions: a
+    // lookup of the record among the group's lanes, 64-bit addresses and a
+    // branch around a run's sums took 3.59 instead of 3.04 ms for an all-mode
+    // sweep in FP64 (rank 16, 20M nonzeros), 4.21 instead of 4.12 ms in FP32
+    // (rank 32, 100M), 13.59 instead of 13.38 ms (rank 64, 150M).
+    int flag = 0, next_at = (ws.run + 1) * 4;
+    uint32_t cur = kNone, next = 0;
     bool began = ws.began, open = false;
-    auto hold = [&]() {
-        kb = k;
-        held = k + lg.j < nruns ? rec[k + lg.j] : 0xFFFFFFFFu;
-    };
     auto write = [&]() {
-        const uint32_t r = __shfl(held, (int)(threadIdx.x & 63) - lg.j + (k - kb), 64);
-        if (r < rec_cap) {
-            Real *o = rec_val + (int64_t)r * ld;
-            store_vec<VEC>(o + lg.col, acc[0]);
-            for (int z = R + lg.j; z < ld; z += lg.G) o[z] = 0;
+        store_row_vec<VEC>(out, cur, lg.col, acc[0]);
+        if (ld > R) {  // zeros to the row's end
+            if (VEC == 4 && ld - R >= 4) {
+                const Real z[VEC] = {};
+                for (int c = R + VEC * lg.j; c < ld; c += VEC * lg.G) store_row_vec<VEC>(out, cur, min(c, ld - VEC), z);
+            } else {
+                const Real z[1] = {0};
+                for (int c = R + lg.j; c < ld; c += lg.G) store_row_vec<1>(out, cur, c, z);
+            }
         }
     };
-    auto close = [&]() {  // the open run is over
-        gather_sums();
-        if (began) {
-            write();
-        } else {
+    auto keep_part = [&]() {  // the run that entered from the left
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) part[v] = acc[0][v];
-            flag = kPart;
-        }
+        for (int v = 0; v < VEC; ++v) part[v] = acc[0][v];
     };
     if (q0 < q1) {
-        hold();
+        if (began) cur = spt_word_load(slots, ws.run * 4, 0, 0);
+        next = spt_word_load(slots, next_at, 0, 0);
         for (int qb = q0; qb < q1; qb += 32) {
             const int n = min(32, q1 - qb);
             uint32_t bits = qb == q0 ? ws.bits[0] : qb == q0 + 32 ? ws.bits[1] : run_bits<T>(ws.words, qb);
             for (int i = 0; i < n; i += UB) {
-                Real p[UB][VEC];
-                product(qb + i, p);
-                if (bits & ((1u << UB) - 1u)) {  // a run begins in this step
+                Real p[UB][VEC], x[UB][VEC];
+                product(qb + i, p, x);
+                // One nonzero a step (5 modes): wait for the gathers here.  Left
+                // to itself the compiler waits behind the end of a run, and so
+                // for its store too (765 instead of 744 us at rank 25, 5M
+                // nonzeros); with two a step the registers cost more than that
+                // (rank 64, 4 modes, 150M nonzeros: 13.79 instead of 13.39 ms).
+                if constexpr (UB == 1) {
 #pragma unroll
-                    for (int u = 0; u < UB; ++u) {
-                        if (u == 0 || i + u < n) {
-                            if (bits & (1u << u)) {
-                                close();
-                                clear();
-                                ++k;
-                                began = true;
-                                if (k - kb >= lg.G) hold();
-                            }
+                    for (int v = 0; v < VEC; ++v) asm volatile("" : "+v"(p[0][v]), "+v"(x[0][v]));
+                }
 #pragma unroll
-                            for (int v = 0; v < VEC; ++v) acc[u][v] += p[u][v];
+                for (int u = 0; u < UB; ++u) {
+                    if (bits & (1u << u)) {  // a run begins: the open one is over
+                        gather_sums();
+                        if (!began) {
+                            keep_part();
+                            flag = kPart;
+                            began = true;
                         }
+                        write();
+                        clear();
+                        cur = next;
+                        next_at += 4;
+                        next = spt_word_load(slots, next_at, 0, 0);
                     }
-                } else {
+                    if (u == 0 || i + u < n)
 #pragma unroll
-                    for (int u = 0; u < UB; ++u)
-                        if (u == 0 || i + u < n)
-#pragma unroll
-                            for (int v = 0; v < VEC; ++v) acc[u][v] += p[u][v];
+                        for (int v = 0; v < VEC; ++v) acc[u][v] = fma(p[u][v], x[u][v], acc[u][v]);
                 }
                 bits >>= UB;
             }
         }
-        if (ws.ended) {
-            close();
+        gather_sums();
+        if (!began) {
+            keep_part();
+            flag = ws.ended ? kPart : kPart | kThrough;
+        } else if (ws.ended) {
+            write();
         } else {
-            gather_sums();
-            if (began) {
-                open = true;
-            } else {
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) part[v] = acc[0][v];
-                flag = kPart | kThrough;
-            }
+            open = true;
         }
     }
     __syncthreads();  // the staged tile is done with

@@ -155,6 +155,21 @@ __device__ spt_f4 spt_row_load4(spt_i4 rsrc, int vindex, int voffset, int soffse
 __device__ float spt_row_load1(spt_i4 rsrc, int vindex, int voffset, int soffset, int aux) __asm(
     "llvm.amdgcn.struct.buffer.load.f32");
 
+__device__ uint32_t spt_word_load(spt_i4 rsrc, int voffset, int soffset, int aux) __asm(
+    "llvm.amdgcn.raw.buffer.load.i32");
+__device__ void spt_row_store4(spt_f4 x, spt_i4 rsrc, int vindex, int voffset, int soffset, int aux) __asm(
+    "llvm.amdgcn.struct.buffer.store.v4f32");
+__device__ void spt_row_store1(float x, spt_i4 rsrc, int vindex, int voffset, int soffset, int aux) __asm(
+    "llvm.amdgcn.struct.buffer.store.f32");
+
+// n 32-bit words, the same for all lanes; reads past them give 0
+__device__ __forceinline__ spt_i4 word_rsrc(const uint32_t *base, uint32_t n) {
+    const uint64_t p = (uint64_t)base;
+    return spt_i4{__builtin_amdgcn_readfirstlane((int)(uint32_t)p),
+                  __builtin_amdgcn_readfirstlane((int)((uint32_t)(p >> 32) & 0xFFFFu)),
+                  __builtin_amdgcn_readfirstlane((int)(n * 4)), 0x00020000};
+}
+
 __device__ __forceinline__ spt_i4 row_rsrc(const float *base, int R, uint32_t rows) {
     const uint64_t p = (uint64_t)base;
     spt_i4 r;
@@ -199,6 +214,34 @@ __device__ __forceinline__ void load_row_vec(spt_i4 rsrc, uint32_t row, int col,
             const float lo = spt_row_load1(rsrc, (int)row, (col + q) * 8, 0, 0);
             const float hi = spt_row_load1(rsrc, (int)row, (col + q) * 8 + 4, 0, 0);
             x[q] = __hiloint2double(__float_as_int(hi), __float_as_int(lo));
+        }
+    }
+}
+
+// Rows past the buffer's are not written.
+template <int VEC>
+__device__ __forceinline__ void store_row_vec(spt_i4 rsrc, uint32_t row, int col, const float (&x)[VEC]) {
+    if constexpr (VEC == 4) {
+        spt_row_store4(spt_f4{x[0], x[1], x[2], x[3]}, rsrc, (int)row, col * 4, 0, 0);
+    } else {
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) spt_row_store1(x[q], rsrc, (int)row, (col + q) * 4, 0, 0);
+    }
+}
+
+template <int VEC>
+__device__ __forceinline__ void store_row_vec(spt_i4 rsrc, uint32_t row, int col, const double (&x)[VEC]) {
+    if constexpr (VEC % 2 == 0) {
+#pragma unroll
+        for (int q = 0; q < VEC; q += 2)
+            spt_row_store4(spt_f4{__int_as_float(__double2loint(x[q])), __int_as_float(__double2hiint(x[q])),
+                                  __int_as_float(__double2loint(x[q + 1])), __int_as_float(__double2hiint(x[q + 1]))},
+                           rsrc, (int)row, (col + q) * 8, 0, 0);
+    } else {
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) {
+            spt_row_store1(__int_as_float(__double2loint(x[q])), rsrc, (int)row, (col + q) * 8, 0, 0);
+            spt_row_store1(__int_as_float(__double2hiint(x[q])), rsrc, (int)row, (col + q) * 8 + 4, 0, 0);
         }
     }
 }
