@@ -73,7 +73,7 @@ __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const doubl
         w[u][3] = (uint32_t)(khi >> 32);
     }
     const LaneGroup lg = lane_group<VEC>(R);
-    const WalkShare ws = walk_share<NT, T>(lg, cnt, UB, a.pl_start + tile * (T / 32));
+    const WalkShare ws = walk_share<NT, T, true>(lg, cnt, UB, a.pl_start + tile * (T / 32));
     // while the loads above are in flight
     zero_slice((float *)out, 2 * (int64_t)a.frows[mode] * R, tile, ntiles);
 #pragma unroll

@@ -240,7 +240,7 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
 // A tile is staged by one scatter of values and non-output coordinates to
 // their positions; there is no hashing and no scan over nonzeros at run time.
 // Records of ld floats go to rec_val.
-template <int NT, int T, int VEC, int NMAX, int NFIX>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool AHEAD = true>
 __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, char *lds,
                                           float *__restrict__ rec_val, int ld, const ZeroSlice &zero) {
     constexpr int PER = T / NT;  // nonzeros staged per thread
@@ -278,7 +278,7 @@ __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, cha
         v[u] = x;
         ps[u] = q;
     }
-    const WalkShare ws = walk_share<NT, T>(lg, cnt, segp_step(NMAX), a.pl_start + tile * (T / 32));
+    const WalkShare ws = walk_share<NT, T, AHEAD>(lg, cnt, segp_step(NMAX), a.pl_start + tile * (T / 32));
     zero_slice(zero.p, zero.n, zero.i, zero.of);  // while the loads above are in flight
     // decode the non-output coordinates and scatter them with the values
 #pragma unroll
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(NT, NMAX <= 5 ? 8 : 4) void k_mttkrp_segp(MttkrpArg
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segp_tile<NT, T, VEC, NMAX, NFIX>(a, tile, lds, a.rec_val, a.rank, out_slice(a, tile, ntiles));
+    segp_tile<NT, T, VEC, NMAX, NFIX, NMAX != 4>(a, tile, lds, a.rec_val, a.rank, out_slice(a, tile, ntiles));
 }
 
 // ---------------------------------------------------------------- row cache
@@ -511,7 +511,7 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u) q[u] &= (uint32_t)(T - 1);  // a position inside the tile
-    const WalkShare ws = walk_share<NT, T>(lg, cnt, UB, a.pl_start + tile * (T / 32));
+    const WalkShare ws = walk_share<NT, T, NMAX != 4>(lg, cnt, UB, a.pl_start + tile * (T / 32));
     {
         const ZeroSlice z = out_slice(a, tile, ntiles);
         zero_slice(z.p, z.n, z.i, z.of);  // while the loads above are in flight

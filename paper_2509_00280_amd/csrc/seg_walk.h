@@ -44,13 +44,18 @@ struct WalkShare {
 
 template <int T>
 __device__ __forceinline__ uint32_t run_bits(const RunWord *words, int q) {  // starts of positions [q, q + 32)
-    const int w = q >> 5, sh = q & 31;
-    const uint32_t lo = words[min(w, T / 32 - 1)].x, hi = words[min(w + 1, T / 32 - 1)].x;
-    return sh ? (lo >> sh) | (hi << (32 - sh)) : lo;
+    const int w = q >> 5;
+    return __builtin_amdgcn_alignbit(words[min(w + 1, T / 32 - 1)].x, words[min(w, T / 32 - 1)].x, q & 31);
 }
 
-// step: positions that a step of the walk takes
-template <int NT, int T>
+// step: positions that a step of the walk takes.  AHEAD: all words of the run
+// starts are asked for at once; one after the other, as they are needed, they
+// are four round trips to memory at every tile's start, but cost fewer
+// registers on the way.  All-mode sweeps without and with: 100M nonzeros, 3
+// modes, rank 32 4.12 / 4.07 ms; a batch of 32 decompositions 31.8 / 31.0 ms;
+// the 4-mode kernels held to 64 VGPRs spill more, 13.32 / 13.57 ms (150M
+// nonzeros, rank 64) and 863 / 874 us (3M, rank 10), and go without.
+template <int NT, int T, bool AHEAD>
 __device__ __forceinline__ WalkShare walk_share(const LaneGroup &lg, int cnt, int step, const RunWord *words) {
     const int NG = NT / 64 * lg.per_wave;
     const int each = ((cnt + NG - 1) / NG + step - 1) / step * step;
@@ -58,12 +63,29 @@ __device__ __forceinline__ WalkShare walk_share(const LaneGroup &lg, int cnt, in
     ws.q0 = min(lg.g * each, cnt);
     ws.q1 = lg.on ? min(ws.q0 + each, cnt) : ws.q0;
     ws.words = words;
-    const RunWord first = words[min(ws.q0 >> 5, T / 32 - 1)];
-    ws.run = (int)(first.y + __popc(first.x & (0xFFFFFFFFu >> (31 - (ws.q0 & 31))))) - 1;
-    ws.began = (first.x >> (ws.q0 & 31)) & 1u;
-    ws.ended = ws.q1 >= cnt || (run_bits<T>(words, ws.q1) & 1u);
-    ws.bits[0] = run_bits<T>(words, ws.q0) & ~1u;
-    ws.bits[1] = run_bits<T>(words, ws.q0 + 32);
+    const int w = ws.q0 >> 5;
+    const RunWord first = words[min(w, T / 32 - 1)];
+    if constexpr (AHEAD) {
+        const uint32_t second = words[min(w + 1, T / 32 - 1)].x, third = words[min(w + 2, T / 32 - 1)].x;
+        const uint32_t end = words[min(ws.q1 >> 5, T / 32 - 1)].x;
+        ws.run = (int)(first.y + __popc(first.x & (0xFFFFFFFFu >> (31 - (ws.q0 & 31))))) - 1;
+        ws.began = (first.x >> (ws.q0 & 31)) & 1u;
+        ws.ended = ws.q1 >= cnt || ((end >> (ws.q1 & 31)) & 1u);
+        ws.bits[0] = __builtin_amdgcn_alignbit(second, first.x, ws.q0 & 31) & ~1u;
+        ws.bits[1] = __builtin_amdgcn_alignbit(third, second, ws.q0 & 31);
+        asm volatile("" : "+v"(ws.run), "+v"(ws.bits[0]), "+v"(ws.bits[1]));  // made here, before the words pile up
+    } else {
+        auto at = [&](int q) {  // the second word only where it is needed
+            const int sh = q & 31;
+            const uint32_t lo = words[min(q >> 5, T / 32 - 1)].x, hi = words[min((q >> 5) + 1, T / 32 - 1)].x;
+            return sh ? (lo >> sh) | (hi << (32 - sh)) : lo;
+        };
+        ws.run = (int)(first.y + __popc(first.x & (0xFFFFFFFFu >> (31 - (ws.q0 & 31))))) - 1;
+        ws.began = (first.x >> (ws.q0 & 31)) & 1u;
+        ws.ended = ws.q1 >= cnt || (at(ws.q1) & 1u);
+        ws.bits[0] = at(ws.q0) & ~1u;
+        ws.bits[1] = at(ws.q0 + 32);
+    }
     return ws;
 }
 
