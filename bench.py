@@ -43,7 +43,7 @@ def source_digest() -> str:
     """Digest of the sources of every kernel one MTTKRP call runs (main kernel,
     record sort, record reduction, plan); stored HBM counters are valid only for it."""
     h = hashlib.sha256()
-    for f in ("mttkrp_seg.hip", "mttkrp_table.hip", "encode.hip", "plan.cpp", "tile_common.h"):
+    for f in ("mttkrp_seg.hip", "mttkrp_table.hip", "seg_walk.h", "records.h", "encode.hip", "plan.cpp", "tile_common.h"):
         with open(os.path.join(ROOT, "paper_2509_00280_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -977,7 +977,7 @@ def bench_tensor(args):
     bound_ms = max(alg_avg / (HBM_PEAK_GBS * 1e9), gather_bytes / (lds_peak_gbs * 1e9)) * 1e3
     roofline = {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": "one mode-n MTTKRP call (k_mttkrp_segd, k_fill_zero, k_reduce_records)",
+                "kernel": "one mode-n MTTKRP call (k_mttkrp_segd, k_reduce_records)",
                 "algorithmic_bytes_per_launch": int(alg_avg),
                 "algorithmic_bytes_per_nnz": round(alg_avg / t.nnz, 2),
                 "measured_bytes_per_nnz": None if traffic is None else round(traffic / t.nnz, 2),
