@@ -73,7 +73,7 @@ __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const doubl
         w[u][3] = (uint32_t)(khi >> 32);
     }
     const LaneGroup lg = lane_group<VEC>(R);
-    const WalkShare ws = walk_share<NT, T, true>(lg, cnt, UB, a.pl_start + tile * (T / 32));
+    const WalkShare ws = walk_share<NT, T, false>(lg, cnt, UB, a.pl_start + tile * (T / 32));
     // while the loads above are in flight
     zero_slice((float *)out, 2 * (int64_t)a.frows[mode] * R, tile, ntiles);
 #pragma unroll
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const doubl
                         else p[u][q] *= xv[o][u][q];
                     }
     };
-    run_walk<double, NT, T, VEC, UB>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, rec_val, R, lds, product);
+    run_walk<double, NT, T, VEC, UB, false>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, rec_val, R, lds, product);
 }
 
 __global__ __launch_bounds__(256) void k_gather_f64(const double *__restrict__ src, const uint32_t *__restrict__ idx,

@@ -168,7 +168,7 @@ struct ZeroSlice {
 // make the compiler wait for one mode's rows before the next mode's gathers
 // are issued).
 __host__ __device__ constexpr int segp_step(int nmax) { return nmax <= 4 ? 2 : 1; }  // nonzeros of a step
-template <int NT, int T, int VEC, int NMAX, int NFIX>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT>
 __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const LaneGroup &lg, const WalkShare &ws,
                                           int cnt, int64_t k0, int nruns, float *__restrict__ rec_val, int ld) {
     constexpr int NO = NMAX - 1;  // non-output modes at most
@@ -231,7 +231,7 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
             }
         }
     };
-    run_walk<float, NT, T, VEC, UB>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, rec_val, ld, lds, product);
+    run_walk<float, NT, T, VEC, UB, TIGHT>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, rec_val, ld, lds, product);
 }
 
 // Planned SEGMENT kernel.  The plan holds, per nonzero, its position in the
@@ -240,7 +240,7 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
 // A tile is staged by one scatter of values and non-output coordinates to
 // their positions; there is no hashing and no scan over nonzeros at run time.
 // Records of ld floats go to rec_val.
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool AHEAD = true>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT = false>
 __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, char *lds,
                                           float *__restrict__ rec_val, int ld, const ZeroSlice &zero) {
     constexpr int PER = T / NT;  // nonzeros staged per thread
@@ -278,7 +278,7 @@ __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, cha
         v[u] = x;
         ps[u] = q;
     }
-    const WalkShare ws = walk_share<NT, T, AHEAD>(lg, cnt, segp_step(NMAX), a.pl_start + tile * (T / 32));
+    const WalkShare ws = walk_share<NT, T, TIGHT>(lg, cnt, segp_step(NMAX), a.pl_start + tile * (T / 32));
     zero_slice(zero.p, zero.n, zero.i, zero.of);  // while the loads above are in flight
     // decode the non-output coordinates and scatter them with the values
 #pragma unroll
@@ -314,7 +314,7 @@ __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, cha
         else valg[cnt] = 0.f;
     }
     __syncthreads();
-    segp_walk<NT, T, VEC, NMAX, NFIX>(a, lds, lg, ws, cnt, k0, nruns, rec_val, ld);
+    segp_walk<NT, T, VEC, NMAX, NFIX, TIGHT>(a, lds, lg, ws, cnt, k0, nruns, rec_val, ld);
 }
 
 __device__ __forceinline__ ZeroSlice out_slice(const MttkrpArgs &a, int64_t tile, int64_t ntiles) {
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(NT, NMAX <= 5 ? 8 : 4) void k_mttkrp_segp(MttkrpArg
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segp_tile<NT, T, VEC, NMAX, NFIX, NMAX != 4>(a, tile, lds, a.rec_val, a.rank, out_slice(a, tile, ntiles));
+    segp_tile<NT, T, VEC, NMAX, NFIX, NMAX == 4>(a, tile, lds, a.rec_val, a.rank, out_slice(a, tile, ntiles));
 }
 
 // ---------------------------------------------------------------- row cache
@@ -511,7 +511,7 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u) q[u] &= (uint32_t)(T - 1);  // a position inside the tile
-    const WalkShare ws = walk_share<NT, T, NMAX != 4>(lg, cnt, UB, a.pl_start + tile * (T / 32));
+    const WalkShare ws = walk_share<NT, T, NMAX == 4>(lg, cnt, UB, a.pl_start + tile * (T / 32));
     {
         const ZeroSlice z = out_slice(a, tile, ntiles);
         zero_slice(z.p, z.n, z.i, z.of);  // while the loads above are in flight
@@ -631,7 +631,7 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
                         else p[u][v] *= xv[o][u][v];
                     }
     };
-    run_walk<float, NT, T, VEC, UB>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, a.rec_val, R, lds, product);
+    run_walk<float, NT, T, VEC, UB, NMAX == 4>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, a.rec_val, R, lds, product);
 }
 
 // Bounded to 64 VGPRs, which leaves two workgroups of 16 waves to a CU: left to

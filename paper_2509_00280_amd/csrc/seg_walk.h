@@ -48,14 +48,14 @@ __device__ __forceinline__ uint32_t run_bits(const RunWord *words, int q) {  // 
     return __builtin_amdgcn_alignbit(words[min(w + 1, T / 32 - 1)].x, words[min(w, T / 32 - 1)].x, q & 31);
 }
 
-// step: positions that a step of the walk takes.  AHEAD: all words of the run
-// starts are asked for at once; one after the other, as they are needed, they
-// are four round trips to memory at every tile's start, but cost fewer
+// step: positions that a step of the walk takes.  Unless TIGHT (the 4-mode
+// kernels held to 64 VGPRs), all words of the run starts are asked for at once;
+// one after the other, as they are needed, they are four round trips to memory at every tile's start, but cost fewer
 // registers on the way.  All-mode sweeps without and with: 100M nonzeros, 3
 // modes, rank 32 4.12 / 4.07 ms; a batch of 32 decompositions 31.8 / 31.0 ms;
-// the 4-mode kernels held to 64 VGPRs spill more, 13.32 / 13.57 ms (150M
-// nonzeros, rank 64) and 863 / 874 us (3M, rank 10), and go without.
-template <int NT, int T, bool AHEAD>
+// the 4-mode kernels spill more, 12.89 / 13.28 ms (150M nonzeros, rank 64) and
+// 845 / 857 us (3M, rank 10).
+template <int NT, int T, bool TIGHT>
 __device__ __forceinline__ WalkShare walk_share(const LaneGroup &lg, int cnt, int step, const RunWord *words) {
     const int NG = NT / 64 * lg.per_wave;
     const int each = ((cnt + NG - 1) / NG + step - 1) / step * step;
@@ -65,7 +65,7 @@ __device__ __forceinline__ WalkShare walk_share(const LaneGroup &lg, int cnt, in
     ws.words = words;
     const int w = ws.q0 >> 5;
     const RunWord first = words[min(w, T / 32 - 1)];
-    if constexpr (AHEAD) {
+    if constexpr (!TIGHT) {
         const uint32_t second = words[min(w + 1, T / 32 - 1)].x, third = words[min(w + 2, T / 32 - 1)].x;
         const uint32_t end = words[min(ws.q1 >> 5, T / 32 - 1)].x;
         ws.run = (int)(first.y + __popc(first.x & (0xFFFFFFFFu >> (31 - (ws.q0 & 31))))) - 1;
@@ -111,7 +111,7 @@ __device__ __forceinline__ void load_words(const Word *p, Word (&x)[UB]) {
     }
 }
 
-template <class Real, int NT, int T, int VEC, int UB, class Product>
+template <class Real, int NT, int T, int VEC, int UB, bool TIGHT, class Product>
 __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &ws, int R, int cnt, int nruns,
                                          const uint32_t *__restrict__ rec, uint32_t rec_cap,
                                          Real *__restrict__ rec_val, int ld, char *lds, const Product &product) {
@@ -148,7 +148,7 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
     int flag = 0, next_at = (ws.run + 1) * 4;
     uint32_t cur = kNone, next = 0;
     bool began = ws.began, open = false;
-    auto write = [&]() {
+    auto store_end = [&](const LaneGroup &lg) {
         store_row_vec<VEC>(out, cur, lg.col, acc[0]);
         if (ld > R) {  // zeros to the row's end
             if (VEC == 4 && ld - R >= 4) {
@@ -160,6 +160,7 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
             }
         }
     };
+    auto write = [&]() { store_end(lg); };
     auto keep_part = [&]() {  // the run that entered from the left
 #pragma unroll
         for (int v = 0; v < VEC; ++v) part[v] = acc[0][v];
@@ -214,22 +215,34 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
             open = true;
         }
     }
+    // TIGHT: the lane group worked out anew.  Its numbers, and the addresses made
+    // from them, would otherwise be held across the walk in spills, which reach
+    // HBM (40 bytes a thread were 10 of 18 bytes written per nonzero): 13.38 /
+    // 12.89 ms for an all-mode sweep (rank 64, 4 modes, 150M nonzeros), 868 / 845
+    // us (rank 10, 3M).  Without spills it only costs: 4.07 / 4.09 ms (rank 32,
+    // 3 modes, 100M).
+    LaneGroup tail = lg;
+    if constexpr (TIGHT) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        tail = lane_group<VEC>(R, tid);
+    }
     __syncthreads();  // the staged tile is done with
     Real *parts = reinterpret_cast<Real *>(lds);
     int *flags = reinterpret_cast<int *>(parts + NT * VEC);
-    if (lg.on) {
-        if (flag) store_vec<VEC>(parts + (lg.g * lg.G + lg.j) * VEC, part);
-        if (lg.j == 0) flags[lg.g] = flag;
+    if (tail.on) {
+        if (flag) store_vec<VEC>(parts + (tail.g * tail.G + tail.j) * VEC, part);
+        if (tail.j == 0) flags[tail.g] = flag;
     }
     __syncthreads();
     if (open) {
-        for (int m = lg.g + 1; m < NG; ++m) {
-            const Real *p = parts + (m * lg.G + lg.j) * VEC;
+        for (int m = tail.g + 1; m < NG; ++m) {
+            const Real *p = parts + (m * tail.G + tail.j) * VEC;
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[0][v] += p[v];
             if (!(flags[m] & kThrough)) break;
         }
-        write();
+        store_end(tail);
     }
 }
 

@@ -115,16 +115,20 @@ struct LaneGroup {
     bool on;
 };
 template <int VEC>
-__device__ __forceinline__ LaneGroup lane_group(int R) {
+__device__ __forceinline__ LaneGroup lane_group(int R, int tid) {
     LaneGroup q;
     q.G = VEC > 1 ? (R + VEC - 1) / VEC : R;
     q.per_wave = 64 / q.G;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, gl = lane / q.G;
+    const int lane = tid & 63, w = tid >> 6, gl = lane / q.G;
     q.j = lane - gl * q.G;
     q.col = VEC > 1 ? min(VEC * q.j, R - VEC) : q.j;
     q.g = w * q.per_wave + gl;
     q.on = gl < q.per_wave;
     return q;
+}
+template <int VEC>
+__device__ __forceinline__ LaneGroup lane_group(int R) {
+    return lane_group<VEC>(R, threadIdx.x);
 }
 
 // Zeroes slice `i` of `of` of an array of n floats (16-byte aligned, or null): a kernel
