@@ -191,7 +191,10 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
 #pragma unroll
         for (int u = 0; u < UB; ++u)
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) p[u][v] = x[u];
+            for (int v = 0; v < VEC; ++v) {
+                p[u][v] = x[u];
+                if constexpr (NFIX == 0) last[u][v] = 1.f;  // one mode: the empty product
+            }
         if constexpr (NO <= 4) {
             uint32_t row[NO][UB];
 #pragma unroll
