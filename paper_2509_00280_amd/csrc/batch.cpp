@@ -196,9 +196,10 @@ spt_status prepare_batched(Tensor *t, hipStream_t s) {
 }
 
 // The batched MTTKRP pipeline of one mode into M_all (rows x ld, overwritten).
-spt_status run_mttkrp_batched_mode(const SegItem *d_items, int count, int64_t total_tiles, int nmodes_min, int nmodes_max,
-                                   int tile, const uint64_t *rec_row, int64_t records, int64_t rows, int ld, bool vec4,
-                                   float *M_all, BatchMttkrpWs &ws, hipStream_t s) {
+spt_status run_mttkrp_batched_mode(const SegItem *d_items, int count, int64_t total_tiles, const BatchShape &b,
+                                   const uint64_t *rec_row, int64_t records, int64_t rows, float *M_all,
+                                   BatchMttkrpWs &ws, hipStream_t s) {
+    const int ld = b.ld;
     if (rows == 0) return SPT_OK;
     if (records == 0 || total_tiles == 0) return launch_fill_zero(M_all, rows * (int64_t)ld, s);
     if (records >= (int64_t(1) << 32)) return fail(SPT_E_INVALID_ARG, "batch: more than 2^32 records");
@@ -209,8 +210,7 @@ spt_status run_mttkrp_batched_mode(const SegItem *d_items, int count, int64_t to
     // the batch's records come out grouped by row: no sort
     const int64_t n = rows * (int64_t)ld;
     const bool fill = !zero_on_the_way(n, total_tiles);
-    spt_status st = launch_mttkrp_seg_batched(d_items, count, total_tiles, nmodes_min, nmodes_max, tile, ld, vec4,
-                                              rval, counter, fill ? nullptr : M_all, n, s);
+    spt_status st = launch_mttkrp_seg_batched(d_items, count, total_tiles, b, rval, counter, fill ? nullptr : M_all, n, s);
     if (st == SPT_OK && fill) st = launch_fill_zero(M_all, n, s);
     if (st == SPT_OK) st = launch_reduce_records(rec_row, nullptr, rval, records, ld, rows, M_all, s);
     return st;
@@ -365,6 +365,7 @@ spt_status BatchEngine::rebuild() {
             }
         const int ld = rmax;
         const int rw = apply_batch_rows();
+        bool far = false;
         int64_t tiles = 0, recs = 0, rows = 0, blocks = 0;
         for (int i = 0; i < A; ++i) {
             Member *m = act[i];
@@ -377,6 +378,7 @@ spt_status BatchEngine::rebuild() {
             si.first_tile = tiles;
             si.rec_base = recs;
             si.row_base = rows;
+            far = far || seg_far(si.a, ld, sizeof(float));
             seg.push_back(si);
             const int64_t In = t->dims[n];
             // M_all block of this member: filled in below once M_all exists (offset only here)
@@ -428,6 +430,7 @@ spt_status BatchEngine::rebuild() {
         mi.ld = ld;
         mi.rmax = rmax;
         mi.vec4 = vec4;
+        mi.far = far;
         M_need = std::max(M_need, sizeof(float) * (size_t)rows * std::max(ld, 1));
         mi.row_at = all_records;
         all_records += recs;
@@ -535,8 +538,10 @@ spt_status BatchEngine::step(bool *before_kernels) {
     for (int n = 0; n < nmodes_max_; ++n) {
         const ModeItems &mi = modes_[n];
         if (mi.count == 0) continue;
-        spt_status st = run_mttkrp_batched_mode((const SegItem *)(d_items_ + mi.seg_off), mi.count, mi.tiles, nmodes_min_,
-                                                nmodes_max_, tile_, (const uint64_t *)rows_buf_.p + mi.row_at, mi.records, mi.rows, mi.ld, mi.vec4, M_all_, ws_, s_);
+        const BatchShape shape{nmodes_min_, nmodes_max_, tile_, mi.ld, mi.vec4, mi.far};
+        spt_status st = run_mttkrp_batched_mode((const SegItem *)(d_items_ + mi.seg_off), mi.count, mi.tiles, shape,
+                                                (const uint64_t *)rows_buf_.p + mi.row_at, mi.records, mi.rows, M_all_,
+                                                ws_, s_);
         if (st == SPT_OK)
             st = launch_gram_batched((const GramItem *)(d_items_ + mi.gm_off), mi.count, mi.gm_slices, mi.rmax,
                                      (double *)gram_ws_.p, s_);
@@ -669,6 +674,7 @@ spt_status spt_mttkrp_batched(const spt_tensor *ts, int count, const float *cons
     if (tv.empty()) return SPT_OK;
     if (!seg_batch_fits(nmax, tile)) return fail(SPT_E_INVALID_ARG, "mttkrp_batched: too many modes");
     const int ld = rmax;
+    BatchShape shape{nmin, nmax, tile, ld, vec4, false};
     std::vector<SegItem> items(tv.size());
     int64_t tiles = 0, recs = 0, rows = 0;
     std::vector<int64_t> row_base(tv.size());
@@ -681,6 +687,7 @@ spt_status spt_mttkrp_batched(const spt_tensor *ts, int count, const float *cons
         items[i].first_tile = tiles;
         items[i].rec_base = recs;
         items[i].row_base = rows;
+        shape.far = shape.far || seg_far(items[i].a, ld, sizeof(float));
         row_base[i] = rows;
         tiles += (t->nnz + tile - 1) / tile;
         recs += t->bplan[mode].records;
@@ -699,7 +706,7 @@ spt_status spt_mttkrp_batched(const spt_tensor *ts, int count, const float *cons
     BatchMttkrpWs ws;
     if (st == SPT_OK) st = launch_record_rows_batched(d_items, (int)items.size(), recs, rec_row, s);
     if (st == SPT_OK)
-        st = run_mttkrp_batched_mode(d_items, (int)items.size(), tiles, nmin, nmax, tile, rec_row, recs, rows, ld, vec4, M, ws, s);
+        st = run_mttkrp_batched_mode(d_items, (int)items.size(), tiles, shape, rec_row, recs, rows, M, ws, s);
     for (size_t i = 0; st == SPT_OK && i < tv.size(); ++i) {
         const int b = idx[i];
         const int64_t In = tv[i]->dims[mode];

@@ -34,7 +34,7 @@ struct FactorsF64 {
     const double *f[kMaxModes];
 };
 
-template <int NT, int VEC, int NMAX, int NFIX>
+template <int NT, int VEC, int NMAX, int NFIX, bool FAR>
 __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const double *__restrict__ vals64, int64_t ntiles,
                                                        FactorsF64 F, double *__restrict__ rec_val,
                                                        double *__restrict__ out) {
@@ -106,11 +106,11 @@ __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const doubl
         else valg[cnt] = 0.0;
     }
     __syncthreads();
-    spt_i4 fb[NO];
+    RowView<double, FAR> fb[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int k = o + (o >= mode);
-        fb[o] = o < no ? row_rsrc(F.f[k], R, a.frows[k]) : row_rsrc((const double *)nullptr, R, 0u);
+        fb[o] = o < no ? RowView<double, FAR>(F.f[k], R, a.frows[k]) : RowView<double, FAR>(nullptr, R, 0u);
     }
     const int c = lg.col;
     auto product = [&](int q0, double (&p)[UB][VEC], double (&last)[UB][VEC]) {
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const doubl
         for (int o = 0; o < NO; ++o)
             if (o < no)
 #pragma unroll
-                for (int u = 0; u < UB; ++u) load_row_vec<VEC>(fb[o], row[o][u], c, xv[o][u]);
+                for (int u = 0; u < UB; ++u) fb[o].template load<VEC>(row[o][u], c, xv[o][u]);
 #pragma unroll
         for (int o = 0; o < NO; ++o)
             if (o < no)
@@ -143,7 +143,8 @@ __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const doubl
                         else p[u][q] *= xv[o][u][q];
                     }
     };
-    run_walk<double, NT, T, VEC, UB, false>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, rec_val, R, lds, product);
+    run_walk<double, NT, T, VEC, UB, false, FAR>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, rec_val, R,
+                                                 lds, product);
 }
 
 __global__ __launch_bounds__(256) void k_gather_f64(const double *__restrict__ src, const uint32_t *__restrict__ idx,
@@ -152,18 +153,18 @@ __global__ __launch_bounds__(256) void k_gather_f64(const double *__restrict__ s
         dst[i] = src[idx[i]];
 }
 
-template <int NT, int NMAX, int NFIX>
+template <int NT, int NMAX, int NFIX, bool FAR = false>
 spt_status launch_f64_k(const MttkrpArgs &a, const double *vals64, const FactorsF64 &F, int64_t ntiles, double *rec_val,
                         double *out, hipStream_t s) {
     const size_t lds = f64_lds_bytes(4 * NT, a.nmodes);
     if (a.rank > 128)  // two columns a lane would be more than a wave
-        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 4, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
+        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 4, NMAX, NFIX, FAR>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
                            ntiles, F, rec_val, out);
     else if (a.rank >= 2)
-        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 2, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
+        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 2, NMAX, NFIX, FAR>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
                            ntiles, F, rec_val, out);
     else
-        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 1, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
+        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 1, NMAX, NFIX, FAR>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
                            ntiles, F, rec_val, out);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
@@ -172,6 +173,9 @@ spt_status launch_f64_k(const MttkrpArgs &a, const double *vals64, const Factors
 template <int NT>
 spt_status launch_f64_n(const MttkrpArgs &a, const double *vals64, const FactorsF64 &F, int64_t ntiles, double *rec_val,
                         double *out, hipStream_t s) {
+    if (seg_far(a, a.rank, sizeof(double)))
+        return a.nmodes <= 4 ? launch_f64_k<NT, 4, 0, true>(a, vals64, F, ntiles, rec_val, out, s)
+                             : launch_f64_k<NT, 8, 0, true>(a, vals64, F, ntiles, rec_val, out, s);
     if (a.nmodes == 3) return launch_f64_k<NT, 3, 3>(a, vals64, F, ntiles, rec_val, out, s);
     if (a.nmodes == 4) return launch_f64_k<NT, 4, 4>(a, vals64, F, ntiles, rec_val, out, s);
     if (a.nmodes == 5) return launch_f64_k<NT, 5, 5>(a, vals64, F, ntiles, rec_val, out, s);

@@ -168,7 +168,7 @@ struct ZeroSlice {
 // make the compiler wait for one mode's rows before the next mode's gathers
 // are issued).
 __host__ __device__ constexpr int segp_step(int nmax) { return nmax <= 4 ? 2 : 1; }  // nonzeros of a step
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, bool FAR>
 __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const LaneGroup &lg, const WalkShare &ws,
                                           int cnt, int64_t k0, int nruns, float *__restrict__ rec_val, int ld) {
     constexpr int NO = NMAX - 1;  // non-output modes at most
@@ -179,11 +179,11 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
     const float *valg = reinterpret_cast<const float *>(crdg + (size_t)no * T);
     const int c = lg.col;
     // factor of the o-th non-output mode as a row buffer
-    spt_i4 fb[NO];
+    RowView<float, FAR> fb[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int k = o + (o >= mode);
-        fb[o] = o < no ? row_rsrc(a.f[k], R, a.frows[k]) : row_rsrc((const float *)nullptr, R, 0u);
+        fb[o] = o < no ? RowView<float, FAR>(a.f[k], R, a.frows[k]) : RowView<float, FAR>(nullptr, R, 0u);
     }
     auto product = [&](int q, float (&p)[UB][VEC], float (&last)[UB][VEC]) {
         float x[UB];
@@ -205,7 +205,7 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
             for (int o = 0; o < NO; ++o)
                 if (o < no)
 #pragma unroll
-                    for (int u = 0; u < UB; ++u) load_row_vec<VEC>(fb[o], row[o][u], c, xv[o][u]);
+                    for (int u = 0; u < UB; ++u) fb[o].template load<VEC>(row[o][u], c, xv[o][u]);
 #pragma unroll
             for (int o = 0; o < NO; ++o)
                 if (o < no)
@@ -222,7 +222,7 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
                 if (o < no) {
                     float xv[UB][VEC];
 #pragma unroll
-                    for (int u = 0; u < UB; ++u) load_row_vec<VEC>(fb[o], crdg[o * T + q + u], c, xv[u]);
+                    for (int u = 0; u < UB; ++u) fb[o].template load<VEC>(crdg[o * T + q + u], c, xv[u]);
 #pragma unroll
                     for (int u = 0; u < UB; ++u)
 #pragma unroll
@@ -234,7 +234,8 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
             }
         }
     };
-    run_walk<float, NT, T, VEC, UB, TIGHT>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, rec_val, ld, lds, product);
+    run_walk<float, NT, T, VEC, UB, TIGHT, FAR>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, rec_val, ld,
+                                                lds, product);
 }
 
 // Planned SEGMENT kernel.  The plan holds, per nonzero, its position in the
@@ -243,7 +244,7 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
 // A tile is staged by one scatter of values and non-output coordinates to
 // their positions; there is no hashing and no scan over nonzeros at run time.
 // Records of ld floats go to rec_val.
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT = false>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, bool FAR>
 __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, char *lds,
                                           float *__restrict__ rec_val, int ld, const ZeroSlice &zero) {
     constexpr int PER = T / NT;  // nonzeros staged per thread
@@ -317,19 +318,19 @@ __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, cha
         else valg[cnt] = 0.f;
     }
     __syncthreads();
-    segp_walk<NT, T, VEC, NMAX, NFIX, TIGHT>(a, lds, lg, ws, cnt, k0, nruns, rec_val, ld);
+    segp_walk<NT, T, VEC, NMAX, NFIX, TIGHT, FAR>(a, lds, lg, ws, cnt, k0, nruns, rec_val, ld);
 }
 
 __device__ __forceinline__ ZeroSlice out_slice(const MttkrpArgs &a, int64_t tile, int64_t ntiles) {
     return ZeroSlice{a.out, (int64_t)a.frows[a.mode] * a.rank, tile, ntiles};
 }
 
-template <int NT, int T, int VEC, int NMAX, int NFIX>
-__global__ __launch_bounds__(NT, NMAX <= 5 ? 8 : 4) void k_mttkrp_segp(MttkrpArgs a, int64_t ntiles) {
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool FAR>
+__global__ __launch_bounds__(NT, NMAX <= 5 && !FAR ? 8 : 4) void k_mttkrp_segp(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segp_tile<NT, T, VEC, NMAX, NFIX, NMAX == 4>(a, tile, lds, a.rec_val, a.rank, out_slice(a, tile, ntiles));
+    segp_tile<NT, T, VEC, NMAX, NFIX, NMAX == 4 && !FAR, FAR>(a, tile, lds, a.rec_val, a.rank, out_slice(a, tile, ntiles));
 }
 
 // ---------------------------------------------------------------- row cache
@@ -445,7 +446,7 @@ __host__ __device__ inline size_t segd_lds_bytes(int T, int nmodes, int cap, int
 // tile dictionary are copied to LDS; a nonzero whose index is below cap
 // reads its factor row there, any other reads it from HBM/L2 by its global
 // row.
-template <int NT, int T, int VEC, int NMAX, int NFIX>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, bool FAR>
 __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int64_t ntiles, char *lds) {
     constexpr int PER = T / NT;
     constexpr int NO = NMAX - 1;
@@ -514,7 +515,7 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u) q[u] &= (uint32_t)(T - 1);  // a position inside the tile
-    const WalkShare ws = walk_share<NT, T, NMAX == 4>(lg, cnt, UB, a.pl_start + tile * (T / 32));
+    const WalkShare ws = walk_share<NT, T, TIGHT>(lg, cnt, UB, a.pl_start + tile * (T / 32));
     {
         const ZeroSlice z = out_slice(a, tile, ntiles);
         zero_slice(z.p, z.n, z.i, z.of);  // while the loads above are in flight
@@ -590,11 +591,11 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
     // into the registers of an LDS read waits for that read; with all LDS
     // reads of the step issued first the loads wait for one LDS round trip,
     // and no branch splits hits from misses.
-    spt_i4 fb[NO];
+    RowView<float, FAR> fb[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int k = o + (o >= mode);
-        fb[o] = o < no ? row_rsrc(a.f[k], R, a.frows[k]) : row_rsrc((const float *)nullptr, R, 0u);
+        fb[o] = o < no ? RowView<float, FAR>(a.f[k], R, a.frows[k]) : RowView<float, FAR>(nullptr, R, 0u);
     }
     const char *mine = lds + lg.j * VEC * 4;  // this lane's columns of the row at offset 0
     auto product = [&](int q0, float (&p)[UB][VEC], float (&last)[UB][VEC]) {
@@ -622,7 +623,7 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
             if (o < no)
 #pragma unroll
                 for (int u = 0; u < UB; ++u)
-                    if (row[o][u] & kDictMiss) load_row_vec<VEC>(fb[o], row[o][u] & ~kDictMiss, lg.col, xv[o][u]);
+                    if (row[o][u] & kDictMiss) fb[o].template load<VEC>(row[o][u] & ~kDictMiss, lg.col, xv[o][u]);
 #pragma unroll
         for (int o = 0; o < NO; ++o)
             if (o < no)
@@ -634,18 +635,19 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
                         else p[u][v] *= xv[o][u][v];
                     }
     };
-    run_walk<float, NT, T, VEC, UB, NMAX == 4>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, a.rec_val, R, lds, product);
+    run_walk<float, NT, T, VEC, UB, TIGHT, FAR>(lg, ws, R, cnt, nruns, a.pl_rec + k0, (uint32_t)a.rec_cap, a.rec_val, R,
+                                                lds, product);
 }
 
 // Bounded to 64 VGPRs, which leaves two workgroups of 16 waves to a CU: left to
 // itself the compiler takes 72 to 82 and one workgroup; the few spills lie
 // outside the steps.
-template <int NT, int T, int VEC, int NMAX, int NFIX>
-__global__ __launch_bounds__(NT, 8) void k_mttkrp_segd(MttkrpArgs a, int64_t ntiles) {
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool FAR>
+__global__ __launch_bounds__(NT, FAR ? 4 : 8) void k_mttkrp_segd(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segd_tile<NT, T, VEC, NMAX, NFIX>(a, tile, ntiles, lds);
+    segd_tile<NT, T, VEC, NMAX, NFIX, NMAX == 4 && !FAR, FAR>(a, tile, ntiles, lds);
 }
 
 // Batched: tile `it` of the whole batch belongs to the last item whose
@@ -674,7 +676,7 @@ __device__ __forceinline__ int seg_item_of(const SegItem *__restrict__ items, in
 // workgroups, the spills cost more than the waves bring (32 members of 10k to
 // 5M nonzeros, ranks 16 and 32, 10 iterations: 40.5, 40.9 and 36.3 ms, here
 // 31.7, and 33.0 with one walk for all mode counts at 72).
-template <int NT, int VEC, int NMAX, int NFIX>
+template <int NT, int VEC, int NMAX, int NFIX, bool FAR>
 __global__ __launch_bounds__(NT, 4) void k_mttkrp_segp_batched(const SegItem *__restrict__ items, int count,
                                                             int64_t total_tiles, float *__restrict__ rec_val, int ld,
                                                             unsigned long long *__restrict__ next_tile,
@@ -695,11 +697,11 @@ __global__ __launch_bounds__(NT, 4) void k_mttkrp_segp_batched(const SegItem *__
         const ZeroSlice zero{out, out_floats, it, total_tiles};
         float *rv = rec_val + item.rec_base * ld;
         if (NMAX == 4 && NFIX == 0 && item.a.nmodes == 4)
-            segp_tile<NT, 4 * NT, VEC, 4, 4>(item.a, it - item.first_tile, lds, rv, ld, zero);
+            segp_tile<NT, 4 * NT, VEC, 4, 4, false, FAR>(item.a, it - item.first_tile, lds, rv, ld, zero);
         else if (NMAX == 4 && NFIX == 0 && item.a.nmodes == 3)
-            segp_tile<NT, 4 * NT, VEC, 3, 3>(item.a, it - item.first_tile, lds, rv, ld, zero);
+            segp_tile<NT, 4 * NT, VEC, 3, 3, false, FAR>(item.a, it - item.first_tile, lds, rv, ld, zero);
         else
-            segp_tile<NT, 4 * NT, VEC, NMAX, NFIX>(item.a, it - item.first_tile, lds, rv, ld, zero);
+            segp_tile<NT, 4 * NT, VEC, NMAX, NFIX, false, FAR>(item.a, it - item.first_tile, lds, rv, ld, zero);
     }
 }
 
@@ -875,29 +877,39 @@ __global__ __launch_bounds__(NT) void k_count_pieces_batched(const SegItem *__re
     count_tile<NT>(items[b].a, it - items[b].first_tile, lds, wsum, out + it);
 }
 
-template <int NT, int T, int NMAX, int NFIX, int VEC>
+template <int NT, int T, int NMAX, int NFIX, int VEC, bool FAR>
 spt_status launch_seg_k(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
     if constexpr (T == kDictTile && NMAX <= 4) {
         if (a.d_cap > 0) {
             const size_t lds = segd_lds_bytes(T, a.nmodes, a.d_cap, a.rank);
-            hipLaunchKernelGGL((k_mttkrp_segd<NT, T, VEC, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a,
+            hipLaunchKernelGGL((k_mttkrp_segd<NT, T, VEC, NMAX, NFIX, FAR>), dim3((unsigned)ntiles), dim3(NT), lds, s, a,
                                ntiles);
             SPT_HIP(hipGetLastError());
             return SPT_OK;
         }
     }
     const size_t lds = std::max(segp_lds_bytes(T, a.nmodes), walk_lds_bytes(NT));
-    hipLaunchKernelGGL((k_mttkrp_segp<NT, T, VEC, NMAX, NFIX>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, ntiles);
+    hipLaunchKernelGGL((k_mttkrp_segp<NT, T, VEC, NMAX, NFIX, FAR>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, ntiles);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
-template <int NT, int T, int NMAX, int NFIX>
+template <int NT, int T, int NMAX, int NFIX, bool FAR = false>
 spt_status launch_seg_nt(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
-    return a.rank >= 4 ? launch_seg_k<NT, T, NMAX, NFIX, 4>(a, ntiles, s) : launch_seg_k<NT, T, NMAX, NFIX, 1>(a, ntiles, s);
+    return a.rank >= 4 ? launch_seg_k<NT, T, NMAX, NFIX, 4, FAR>(a, ntiles, s)
+                       : launch_seg_k<NT, T, NMAX, NFIX, 1, FAR>(a, ntiles, s);
 }
 
 }  // namespace
+
+// Whether a call on `a` reads a factor or writes records (ld columns) beyond the
+// 4 GiB that a structured buffer's 32-bit offsets reach (RowView): a row of
+// more than 4 GiB's index would come around to the array's start.
+bool seg_far(const MttkrpArgs &a, int ld, size_t item) {
+    bool far = (uint64_t)a.rec_cap * ld * item > kBufferBytes;
+    for (int k = 0; k < a.nmodes; ++k) far = far || (k != a.mode && (uint64_t)a.frows[k] * a.rank * item > kBufferBytes);
+    return far;
+}
 
 // tile sizes served: 1024 (256 threads), 2048 (512), 4096 (1024 threads)
 bool seg_tile_ok(int tile, int nmodes) {
@@ -941,10 +953,13 @@ spt_status launch_count_pieces(const MttkrpArgs &a, int64_t *counts, hipStream_t
 }
 
 namespace {
-// 3, 4 and 5 modes get a kernel with the mode count fixed; others the general one
+// 3, 4 and 5 modes get a kernel with the mode count fixed; others, and arrays
+// past the reach of a structured buffer, a general one
 template <int NT, int T>
 spt_status launch_seg_tile(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
     const int nm = a.nmodes;
+    if (seg_far(a, a.rank, sizeof(float)))
+        return nm <= 4 ? launch_seg_nt<NT, T, 4, 0, true>(a, ntiles, s) : launch_seg_nt<NT, T, 8, 0, true>(a, ntiles, s);
     if (nm == 3) return launch_seg_nt<NT, T, 3, 3>(a, ntiles, s);
     if (nm == 4) return launch_seg_nt<NT, T, 4, 4>(a, ntiles, s);
     if (nm == 5) return launch_seg_nt<NT, T, 5, 5>(a, ntiles, s);
@@ -981,7 +996,7 @@ spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s) {
 }
 
 namespace {
-template <int NT, int NMAX, int NFIX, int VEC>
+template <int NT, int NMAX, int NFIX, int VEC, bool FAR>
 spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, float *rec_val,
                          int ld, unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
     const size_t lds = std::max(segp_lds_bytes(4 * NT, NMAX), walk_lds_bytes(NT));
@@ -989,7 +1004,7 @@ spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, f
     int pc = per_cu.load(std::memory_order_relaxed);
     if (pc == 0) {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &pc, reinterpret_cast<const void *>(&k_mttkrp_segp_batched<NT, VEC, NMAX, NFIX>), NT, lds) !=
+                &pc, reinterpret_cast<const void *>(&k_mttkrp_segp_batched<NT, VEC, NMAX, NFIX, FAR>), NT, lds) !=
                 hipSuccess ||
             pc < 1) {
             (void)hipGetLastError();  // not a failure of this call: one resident workgroup per CU is assumed
@@ -1000,27 +1015,26 @@ spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, f
     const int64_t grid = std::min<int64_t>(total_tiles, (int64_t)pc * device_cus());
     spt_status st = launch_fill_zero(reinterpret_cast<float *>(next_tile), 2, s);  // the tile counter
     if (st != SPT_OK) return st;
-    hipLaunchKernelGGL((k_mttkrp_segp_batched<NT, VEC, NMAX, NFIX>), dim3((unsigned)grid), dim3(NT), lds, s, items,
+    hipLaunchKernelGGL((k_mttkrp_segp_batched<NT, VEC, NMAX, NFIX, FAR>), dim3((unsigned)grid), dim3(NT), lds, s, items,
                        count, total_tiles, rec_val, ld, next_tile, out, out_floats);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
-template <int NT, int NMAX, int NFIX>
-spt_status launch_segb_n(const SegItem *items, int count, int64_t total_tiles, float *rec_val,
-                         int ld, bool vec4, unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
-    return vec4 ? launch_segb_k<NT, NMAX, NFIX, 4>(items, count, total_tiles, rec_val, ld, next_tile, out, out_floats, s)
-                : launch_segb_k<NT, NMAX, NFIX, 1>(items, count, total_tiles, rec_val, ld, next_tile, out, out_floats, s);
+template <int NT, int NMAX, int NFIX, bool FAR = false>
+spt_status launch_segb_n(const SegItem *items, int count, int64_t total_tiles, int ld, bool vec4, float *rec_val,
+                         unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
+    return vec4 ? launch_segb_k<NT, NMAX, NFIX, 4, FAR>(items, count, total_tiles, rec_val, ld, next_tile, out, out_floats, s)
+                : launch_segb_k<NT, NMAX, NFIX, 1, FAR>(items, count, total_tiles, rec_val, ld, next_tile, out, out_floats, s);
 }
 
 template <int NT>
-spt_status launch_segb_t(const SegItem *items, int count, int64_t total_tiles, int nmodes_min, int nmodes_max, int ld,
-                         bool vec4, float *rec_val, unsigned long long *next_tile, float *out,
-                         int64_t out_floats, hipStream_t s) {
-    if (nmodes_min == 3 && nmodes_max == 3)
-        return launch_segb_n<NT, 3, 3>(items, count, total_tiles, rec_val, ld, vec4, next_tile, out, out_floats, s);
-    if (nmodes_max <= 4) return launch_segb_n<NT, 4, 0>(items, count, total_tiles, rec_val, ld, vec4, next_tile, out, out_floats, s);
-    return launch_segb_n<NT, 8, 0>(items, count, total_tiles, rec_val, ld, vec4, next_tile, out, out_floats, s);
+spt_status launch_segb_t(const SegItem *items, int count, int64_t total_tiles, const BatchShape &b, float *rec_val,
+                         unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
+    auto go = [&](auto launch) { return launch(items, count, total_tiles, b.ld, b.vec4, rec_val, next_tile, out, out_floats, s); };
+    if (b.far) return b.nmodes_max <= 4 ? go(launch_segb_n<NT, 4, 0, true>) : go(launch_segb_n<NT, 8, 0, true>);
+    if (b.nmodes_min == 3 && b.nmodes_max == 3) return go(launch_segb_n<NT, 3, 3>);
+    return b.nmodes_max <= 4 ? go(launch_segb_n<NT, 4, 0>) : go(launch_segb_n<NT, 8, 0>);
 }
 
 }  // namespace
@@ -1070,18 +1084,15 @@ spt_status launch_count_pieces_batched(const SegItem *items, int count, int64_t 
     return SPT_OK;
 }
 
-spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t total_tiles, int nmodes_min,
-                                     int nmodes_max, int tile, int ld, bool vec4, float *rec_val,
-                                     unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
+spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t total_tiles, const BatchShape &b,
+                                     float *rec_val, unsigned long long *next_tile, float *out, int64_t out_floats,
+                                     hipStream_t s) {
     if (total_tiles == 0) return SPT_OK;
-    if (ld > 64) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: rank above 64");
-    if (!seg_batch_fits(nmodes_max, tile)) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: tile does not fit LDS");
+    if (b.ld > 64) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: rank above 64");
+    if (!seg_batch_fits(b.nmodes_max, b.tile)) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: tile does not fit LDS");
     if (!next_tile) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: no tile counter");
-    if (tile == 1024)
-        return launch_segb_t<256>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_val, next_tile, out, out_floats, s);
-    if (tile == 2048)
-        return launch_segb_t<512>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_val, next_tile, out, out_floats, s);
-    return launch_segb_t<1024>(items, count, total_tiles, nmodes_min, nmodes_max, ld, vec4, rec_val, next_tile, out, out_floats, s);
+    auto go = [&](auto launch) { return launch(items, count, total_tiles, b, rec_val, next_tile, out, out_floats, s); };
+    return b.tile == 1024 ? go(launch_segb_t<256>) : b.tile == 2048 ? go(launch_segb_t<512>) : go(launch_segb_t<1024>);
 }
 
 }  // namespace spt

@@ -111,7 +111,7 @@ __device__ __forceinline__ void load_words(const Word *p, Word (&x)[UB]) {
     }
 }
 
-template <class Real, int NT, int T, int VEC, int UB, bool TIGHT, class Product>
+template <class Real, int NT, int T, int VEC, int UB, bool TIGHT, bool FAR, class Product>
 __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &ws, int R, int cnt, int nruns,
                                          const uint32_t *__restrict__ rec, uint32_t rec_cap,
                                          Real *__restrict__ rec_val, int ld, char *lds, const Product &product) {
@@ -119,7 +119,8 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
     constexpr uint32_t kNone = 0xFFFFFFFFu;  // no record: a store to it is dropped
     const int NG = NT / 64 * lg.per_wave;
     const int q0 = ws.q0, q1 = ws.q1;
-    const spt_i4 slots = word_rsrc(rec, (uint32_t)nruns), out = row_rsrc(rec_val, ld, rec_cap);
+    const spt_i4 slots = word_rsrc(rec, (uint32_t)nruns);
+    const RowView<Real, FAR> out(rec_val, ld, rec_cap);
     // a sum for each nonzero of a step: chains of additions UB times shorter
     Real acc[UB][VEC], part[VEC];
 #pragma unroll
@@ -149,14 +150,14 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
     uint32_t cur = kNone, next = 0;
     bool began = ws.began, open = false;
     auto store_end = [&](const LaneGroup &lg) {
-        store_row_vec<VEC>(out, cur, lg.col, acc[0]);
+        out.template store<VEC>(cur, lg.col, acc[0]);
         if (ld > R) {  // zeros to the row's end
             if (VEC == 4 && ld - R >= 4) {
                 const Real z[VEC] = {};
-                for (int c = R + VEC * lg.j; c < ld; c += VEC * lg.G) store_row_vec<VEC>(out, cur, min(c, ld - VEC), z);
+                for (int c = R + VEC * lg.j; c < ld; c += VEC * lg.G) out.template store<VEC>(cur, min(c, ld - VEC), z);
             } else {
                 const Real z[1] = {0};
-                for (int c = R + lg.j; c < ld; c += lg.G) store_row_vec<1>(out, cur, c, z);
+                for (int c = R + lg.j; c < ld; c += lg.G) out.template store<1>(cur, c, z);
             }
         }
     };

@@ -214,6 +214,8 @@ spt_status launch_plan_records(const uint32_t *idx, uint32_t *rec, int64_t n, hi
 // sparse tensor: at 1 MB each (2.6M rows of rank 32, 1.3M nonzeros) a call
 // took 262 us against 247 with a fill of its own, at 5 MB 112 against 76.
 inline bool zero_on_the_way(int64_t n, int64_t wgs) { return n <= wgs * (64 * 1024 / 4); }
+constexpr uint64_t kBufferBytes = uint64_t(1) << 32;
+bool seg_far(const MttkrpArgs &a, int ld, size_t item);
 // the SEGMENT kernel on a's plan: records to a.rec_val, a.out (if any) zeroed
 spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s);
 // mttkrp_f64.hip
@@ -255,11 +257,18 @@ spt_status launch_plan_records_batched(const SegItem *items, int count, const ui
                                        int64_t n, hipStream_t s);
 // rows[j] = row of the batch's record j in its concatenated output
 spt_status launch_record_rows_batched(const SegItem *items, int count, int64_t n, uint64_t *rows, hipStream_t s);
+// A batch as its MTTKRP launches see it.
+struct BatchShape {
+    int nmodes_min, nmodes_max, tile;
+    int ld;     // columns of M and of the records: the largest rank
+    bool vec4;  // every member's rank is at least 4
+    bool far;   // seg_far of any member
+};
 // next_tile: a device counter (8 bytes) the launch zeroes and the workgroups pull tiles from;
-// vec4: every member's rank is at least 4; out: out_floats that the launch also zeroes
-spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t total_tiles, int nmodes_min,
-                                     int nmodes_max, int tile, int ld, bool vec4, float *rec_val,
-                                     unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s);
+// out: out_floats that the launch also zeroes
+spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t total_tiles, const BatchShape &b,
+                                     float *rec_val, unsigned long long *next_tile, float *out, int64_t out_floats,
+                                     hipStream_t s);
 
 // Batched dense steps (dense.hip): one workgroup per item, except apply
 // (a grid over the items' row blocks).
@@ -325,7 +334,7 @@ struct Member {
 
 struct ModeItems {
     int count = 0, ld = 0, rmax = 0;
-    bool vec4 = true;
+    bool vec4 = true, far = false;
     int64_t tiles = 0, records = 0, rows = 0, blocks = 0;
     int64_t row_at = 0;  // first of the mode's record rows in the engine's array
     size_t seg_off = 0, gm_off = 0, sv_off = 0, ap_off = 0;
@@ -367,9 +376,9 @@ struct BatchMttkrpWs {
         counter.release(s);
     }
 };
-spt_status run_mttkrp_batched_mode(const SegItem *d_items, int count, int64_t total_tiles, int nmodes_min, int nmodes_max,
-                                   int tile, const uint64_t *rec_row, int64_t records, int64_t rows, int ld, bool vec4,
-                                   float *M_all, BatchMttkrpWs &ws, hipStream_t s);
+spt_status run_mttkrp_batched_mode(const SegItem *d_items, int count, int64_t total_tiles, const BatchShape &b,
+                                   const uint64_t *rec_row, int64_t records, int64_t rows, float *M_all,
+                                   BatchMttkrpWs &ws, hipStream_t s);
 // batched plans of `mode` at `tile` for the tensors that lack them (a plan
 // at another tile is released and rebuilt); synchronises s when it builds
 spt_status ensure_batch_plans(const std::vector<Tensor *> &ts, int mode, int tile, hipStream_t s);

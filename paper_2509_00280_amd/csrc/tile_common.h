@@ -152,6 +152,8 @@ __device__ __forceinline__ void zero_slice(float *__restrict__ p, int64_t n, int
 // (stride R floats): a gather passes the row index and the column's byte
 // offset straight to the load, with no address arithmetic, and rows past
 // `rows` read as zero.  The descriptor is wave-uniform (SGPRs); R <= 4095.
+// The hardware forms the byte offset of a row in 32 bits: for arrays up to
+// kBufferBytes (RowView has the others).
 typedef int spt_i4 __attribute__((ext_vector_type(4)));
 typedef uint32_t spt_u4 __attribute__((ext_vector_type(4)));
 __device__ spt_f4 spt_row_load4(spt_i4 rsrc, int vindex, int voffset, int soffset, int aux) __asm(
@@ -249,6 +251,41 @@ __device__ __forceinline__ void store_row_vec(spt_i4 rsrc, uint32_t row, int col
         }
     }
 }
+
+// A row-major matrix of `rows` rows of R values as the walk reads or writes it:
+// a structured buffer or, FAR, 64-bit addresses.  Rows past the last read as
+// zeros or as the last row (FAR), and are not written.
+template <class Real, bool FAR>
+struct RowView {
+    spt_i4 r;
+    __device__ __forceinline__ RowView() {}
+    __device__ __forceinline__ RowView(const Real *p, int R, uint32_t rows) : r(row_rsrc(p, R, rows)) {}
+    template <int VEC>
+    __device__ __forceinline__ void load(uint32_t row, int col, Real (&x)[VEC]) const {
+        load_row_vec<VEC>(r, row, col, x);
+    }
+    template <int VEC>
+    __device__ __forceinline__ void store(uint32_t row, int col, const Real (&x)[VEC]) const {
+        store_row_vec<VEC>(r, row, col, x);
+    }
+};
+
+template <class Real>
+struct RowView<Real, true> {
+    const Real *p;
+    int R;
+    uint32_t rows;
+    __device__ __forceinline__ RowView() {}
+    __device__ __forceinline__ RowView(const Real *q, int ld, uint32_t n) : p(q), R(ld), rows(n) {}
+    template <int VEC>
+    __device__ __forceinline__ void load(uint32_t row, int col, Real (&x)[VEC]) const {
+        load_vec_any<VEC>(p + (size_t)min(row, rows - 1) * R + col, x);
+    }
+    template <int VEC>
+    __device__ __forceinline__ void store(uint32_t row, int col, const Real (&x)[VEC]) const {
+        if (row < rows) store_vec<VEC>(const_cast<Real *>(p) + (size_t)row * R + col, x);
+    }
+};
 
 // The codec held in VGPRs: lane l of every wave keeps run descriptors l,
 // l + 64 and l + 128 and the run bound rb[l / 5][l % 5].  Decoding reads them
