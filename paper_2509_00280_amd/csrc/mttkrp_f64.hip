@@ -123,10 +123,12 @@ __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const doubl
 #pragma unroll
         for (int u = 0; u < UB; ++u)
 #pragma unroll
-            for (int q = 0; q < VEC; ++q) {
-                p[u][q] = x[u];
-                if constexpr (NFIX == 0) last[u][q] = 1.0;  // one mode: the empty product
-            }
+            for (int q = 0; q < VEC; ++q) p[u][q] = x[u];
+        if (NFIX == 0 && no == 0)  // one mode: the empty product
+#pragma unroll
+            for (int u = 0; u < UB; ++u)
+#pragma unroll
+                for (int q = 0; q < VEC; ++q) last[u][q] = 1.0;
 #pragma unroll
         for (int o = 0; o < NO; ++o)
             if (o < no)

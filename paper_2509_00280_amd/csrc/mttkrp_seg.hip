@@ -191,10 +191,12 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
 #pragma unroll
         for (int u = 0; u < UB; ++u)
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                p[u][v] = x[u];
-                if constexpr (NFIX == 0) last[u][v] = 1.f;  // one mode: the empty product
-            }
+            for (int v = 0; v < VEC; ++v) p[u][v] = x[u];
+        if (NFIX == 0 && no == 0)  // one mode: the empty product
+#pragma unroll
+            for (int u = 0; u < UB; ++u)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) last[u][v] = 1.f;
         if constexpr (NO <= 4) {
             uint32_t row[NO][UB];
 #pragma unroll

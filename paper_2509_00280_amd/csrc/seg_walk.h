@@ -5,11 +5,11 @@
 // A tile's nonzeros stand in LDS in row-grouped order; a run is the stretch of
 // one output row.  Every lane group takes an equal stretch of positions,
 // whatever runs begin and end in it, sums a run at a time in registers and
-// stores it as the run's record when it ends.  A run that enters from the left
-// leaves its part in LDS; after a barrier the group in which it began adds the
-// parts to its right and stores the record.  So all groups make the same
-// number of steps at every rank and every skew, and a tile has one record for
-// each of its rows.
+// stores it as the run's record when it ends.  The part of a run that entered
+// from the left goes to the group in which it began, through shuffles within a
+// wave and LDS between waves, which stores the record.  So all groups make the
+// same number of steps at every rank and every skew, and a tile has one record
+// for each of its rows.
 // Groups that took whole pieces of at most 64 nonzeros of a row instead, dealt
 // longest first, waited for the longest: at rank 16 a 4096-nonzero tile has 16
 // nonzeros for each of its 256 groups and pieces of 64.  All-mode sweeps in
@@ -115,9 +115,7 @@ template <class Real, int NT, int T, int VEC, int UB, bool TIGHT, bool FAR, clas
 __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &ws, int R, int cnt, int nruns,
                                          const uint32_t *__restrict__ rec, uint32_t rec_cap,
                                          Real *__restrict__ rec_val, int ld, char *lds, const Product &product) {
-    constexpr int kPart = 1, kThrough = 2;  // a run entered from the left; it also leaves to the right
     constexpr uint32_t kNone = 0xFFFFFFFFu;  // no record: a store to it is dropped
-    const int NG = NT / 64 * lg.per_wave;
     const int q0 = ws.q0, q1 = ws.q1;
     const spt_i4 slots = word_rsrc(rec, (uint32_t)nruns);
     const RowView<Real, FAR> out(rec_val, ld, rec_cap);
@@ -146,9 +144,10 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
     // branch around a run's sums took 3.59 instead of 3.04 ms for an all-mode
     // sweep in FP64 (rank 16, 20M nonzeros), 4.21 instead of 4.12 ms in FP32
     // (rank 32, 100M), 13.59 instead of 13.38 ms (rank 64, 150M).
-    int flag = 0, next_at = (ws.run + 1) * 4;
+    int next_at = (ws.run + 1) * 4;
     uint32_t cur = kNone, next = 0;
     bool began = ws.began, open = false;
+    bool through = false;  // a run entered from the left and leaves to the right
     auto store_end = [&](const LaneGroup &lg) {
         out.template store<VEC>(cur, lg.col, acc[0]);
         if (ld > R) {  // zeros to the row's end
@@ -190,7 +189,6 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
                         gather_sums();
                         if (!began) {
                             keep_part();
-                            flag = kPart;
                             began = true;
                         }
                         write();
@@ -209,7 +207,7 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
         gather_sums();
         if (!began) {
             keep_part();
-            flag = ws.ended ? kPart : kPart | kThrough;
+            through = !ws.ended;
         } else if (ws.ended) {
             write();
         } else {
@@ -222,26 +220,49 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
     // 12.89 ms for an all-mode sweep (rank 64, 4 modes, 150M nonzeros), 868 / 845
     // us (rank 10, 3M).  Without spills it only costs: 4.07 / 4.09 ms (rank 32,
     // 3 modes, 100M).
+    int tid = threadIdx.x;
     LaneGroup tail = lg;
     if constexpr (TIGHT) {
-        int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         tail = lane_group<VEC>(R, tid);
+    }
+    // A run over many groups: the parts of a wave's groups are joined by halves,
+    // the waves' then one after the other, so a run over a whole tile takes
+    // log2(groups of a wave) + 16 additions.  One for every group, 1023 of them at
+    // ranks up to 4, lost up to 246 roundings of FP32, and took 331 us for 5M
+    // nonzeros of one row (rank 4, 3 modes) instead of 62; 24 rows 78 / 60 us, an
+    // all-mode sweep of 3M nonzeros at rank 10 (4 modes) 859 / 803 us, of 150M at
+    // rank 64 12.88 / 12.55 ms.  The run's first group takes the joined parts
+    // from LDS: through a shuffle they cost 0.7% of a sweep at rank 32 (100M).
+    const int lane = tid & 63, wave = tid >> 6, groups_end = tail.per_wave * tail.G;
+    for (int d = tail.G; d < groups_end; d *= 2) {
+        const bool in = through && lane + d < groups_end;
+        if (!__any(in)) break;
+        const bool beyond = __shfl((int)through, lane + d, 64);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            const Real y = __shfl(part[v], lane + d, 64);
+            if (in) part[v] += y;
+        }
+        if (in) through = beyond;  // of the groups joined so far
     }
     __syncthreads();  // the staged tile is done with
     Real *parts = reinterpret_cast<Real *>(lds);
     int *flags = reinterpret_cast<int *>(parts + NT * VEC);
     if (tail.on) {
-        if (flag) store_vec<VEC>(parts + (tail.g * tail.G + tail.j) * VEC, part);
-        if (tail.j == 0) flags[tail.g] = flag;
+        store_vec<VEC>(parts + (tail.g * tail.G + tail.j) * VEC, part);
+        if (tail.j == 0) flags[tail.g] = through;
     }
     __syncthreads();
     if (open) {
-        for (int m = tail.g + 1; m < NG; ++m) {
+        int m = tail.g + 1, w = wave + (lane + tail.G < groups_end ? 1 : 2);
+        for (;;) {  // ends at the latest in the last wave, whose last group's run ends with it
             const Real *p = parts + (m * tail.G + tail.j) * VEC;
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[0][v] += p[v];
-            if (!(flags[m] & kThrough)) break;
+            if (!flags[m] || w >= NT / 64) break;
+            m = w * tail.per_wave;
+            ++w;
         }
         store_end(tail);
     }
