@@ -152,7 +152,8 @@ spt_status spt_set_allocator(spt_alloc_fn alloc, spt_release_fn release, void *c
  * Errors: SPT_E_INVALID_ARG (NULL).
  *
  * spt_empty_cache returns every idle block to the driver (waits for the
- * work ordered before each release, then hipFree).  Live buffers stay.
+ * work ordered before each release, then hipFree), and the few pinned host
+ * blocks kept for spt_cp_als.  Live buffers stay.
  * Errors: SPT_E_DEVICE.
  */
 spt_status spt_memory_stats(int64_t *stats);
@@ -309,8 +310,10 @@ spt_status spt_mttkrp_f64(spt_tensor t, const double *const *factors, int rank, 
  *   fit_out, iters_out  host (out).
  * The iterations run on library-owned copies of the factors: factors and
  * lambda are written only when the call returns SPT_OK.  Prepares the
- * tensor for `rank` if needed.  Synchronises `stream` once per iteration
- * (and while preparing).  1 <= rank <= SPT_MAX_ALS_RANK.
+ * tensor for `rank` if needed.  The host waits for every iteration (and while
+ * preparing): with a tolerance before it starts the next one, without one
+ * while the next one runs, so a solve that fails ends the call at most one
+ * iteration later.  1 <= rank <= SPT_MAX_ALS_RANK.
  * Errors: SPT_E_INVALID_ARG (also when |X| = 0), SPT_E_NOT_SPD, SPT_E_OOM, SPT_E_DEVICE.
  */
 spt_status spt_cp_als(spt_tensor t, int rank, int max_iters, double tol, float *const *factors,

@@ -10,6 +10,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -225,6 +226,65 @@ void dev_free(void *p, hipStream_t s) {
     (void)cache_free(p, s);
 }
 
+// ---------------------------------------------------------------- reports
+// Pinned host memory that kernels write their reports to, so that the host can
+// look at one iteration while the stream works on the next.  Allocating it
+// stalls the device, so up to kReportsKept blocks are kept for later calls
+// (spt_empty_cache frees them).  A block is given back once no kernel writes to
+// it any more.
+namespace {
+constexpr int kReportsKept = 8;
+std::mutex g_reports_mu;
+AlsReport *g_reports[kReportsKept];
+int g_nreports = 0;
+
+struct Reports {
+    static constexpr int kSlots = 2;
+    AlsReport *at = nullptr;  // kSlots reports, numbered 0
+    bool get() {
+        {
+            std::lock_guard<std::mutex> lk(g_reports_mu);
+            if (g_nreports > 0) at = g_reports[--g_nreports];
+        }
+        if (!at && hipHostMalloc((void **)&at, sizeof(AlsReport) * kSlots,
+                                 hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+            (void)hipGetLastError();
+            at = nullptr;
+            return false;
+        }
+        for (int i = 0; i < kSlots; ++i) __atomic_store_n(&at[i].number, 0, __ATOMIC_RELEASE);
+        return true;
+    }
+    // Waits for report `number` in its slot.  The stream running empty without
+    // it (a failed launch) ends the wait too.
+    bool wait(int number, hipStream_t s) const {
+        const AlsReport &r = at[number % kSlots];
+        auto here = [&] { return __atomic_load_n(&r.number, __ATOMIC_ACQUIRE) == number; };
+        for (unsigned spin = 1; !here(); ++spin) {
+            std::this_thread::yield();
+            if (spin % 4096 == 0 && hipStreamQuery(s) != hipErrorNotReady) return here();
+        }
+        return true;
+    }
+    ~Reports() {
+        if (!at) return;
+        {
+            std::lock_guard<std::mutex> lk(g_reports_mu);
+            if (g_nreports < kReportsKept) {
+                g_reports[g_nreports++] = at;
+                return;
+            }
+        }
+        (void)hipHostFree(at);
+    }
+};
+
+void release_reports() {
+    std::lock_guard<std::mutex> lk(g_reports_mu);
+    while (g_nreports > 0) (void)hipHostFree(g_reports[--g_nreports]);
+}
+}  // namespace
+
 spt_status memory_stats(int64_t *stats) {
     BlockCache &c = cache();
     std::lock_guard<std::mutex> lk(c.mu);
@@ -236,6 +296,7 @@ spt_status memory_stats(int64_t *stats) {
 }
 
 spt_status empty_cache() {
+    release_reports();
     BlockCache &c = cache();
     std::lock_guard<std::mutex> lk(c.mu);
     int cur = 0;
@@ -617,16 +678,8 @@ spt_status spt_cp_als(spt_tensor t, int rank, int max_iters, double tol, float *
     double *gwork = (double *)dev_alloc(gw, s);
     double *inner = (double *)dev_alloc(sizeof(double) * inner_parts, s);
     double *resid = (double *)dev_alloc(sizeof(double) * 2 * std::max<int64_t>(resid_tiles, 1), s);
-    // Without a tolerance no iteration depends on the one before it having been
-    // looked at: the host reads kAhead iterations' results at once (20k
-    // nonzeros, rank 16, 10 iterations: 1430 us with a readback each, 1015 us
-    // with one).
-    constexpr int kAhead = 32;
-    struct IterOut {
-        double fit[4];
-        int status[kMaxModes];
-    };
-    IterOut *iters = (IterOut *)dev_alloc(sizeof(IterOut) * kAhead, s);
+    double *fitd = (double *)dev_alloc(sizeof(double) * 4 + sizeof(int) * kMaxModes, s);
+    int *status = (int *)(fitd + 4);
     double *lam = (double *)dev_alloc(sizeof(double) * R, s);
     // one record workspace for every mode's MTTKRP (the largest plan's records)
     RecordWs ws;
@@ -639,11 +692,11 @@ spt_status spt_cp_als(spt_tensor t, int rank, int max_iters, double tol, float *
     for (int k = 0; k < N; ++k) fok = fok && (F[k] = (float *)dev_alloc(sizeof(float) * t->dims[k] * R, s)) != nullptr;
     auto cleanup = [&]() {
         dev_free(M, s); dev_free(grams, s); dev_free(gram_m, s); dev_free(S, s); dev_free(gwork, s);
-        dev_free(inner, s); dev_free(resid, s); dev_free(iters, s); dev_free(lam, s);
+        dev_free(inner, s); dev_free(resid, s); dev_free(fitd, s); dev_free(lam, s);
         dev_free(ws.val, s);
         for (int k = 0; k < N; ++k) dev_free(F[k], s);
     };
-    if (!M || !grams || !gram_m || !S || !gwork || !inner || !resid || !iters || !lam || !ws.val || !fok) {
+    if (!M || !grams || !gram_m || !S || !gwork || !inner || !resid || !fitd || !lam || !ws.val || !fok) {
         cleanup();
         return fail(SPT_E_OOM, "cp_als: workspace allocation failed");
     }
@@ -652,57 +705,63 @@ spt_status spt_cp_als(spt_tensor t, int rank, int max_iters, double tol, float *
             cleanup();
             return hip_fail(hipGetLastError(), "cp_als: factor copy");
         }
-#define CK(x)                    \
-    do {                         \
-        spt_status st__ = (x);   \
-        if (st__ != SPT_OK) {    \
-            cleanup();           \
-            return st__;         \
-        }                        \
+#define CK(x)                                                              \
+    do {                                                                   \
+        spt_status st__ = (x);                                             \
+        if (st__ != SPT_OK) {                                              \
+            (void)hipStreamSynchronize(s); /* a report may still be due */ \
+            cleanup();                                                     \
+            return st__;                                                   \
+        }                                                                  \
     } while (0)
+    Reports rep;
+    if (!rep.get()) {
+        cleanup();
+        return fail(SPT_E_OOM, "cp_als: report buffer");
+    }
     for (int k = 0; k < N; ++k) CK(launch_gram(F[k], t->dims[k], R, grams + (size_t)k * R * R, gwork, gw, nullptr, s));
     double fit = 0.0, fit_prev = 0.0;
-    int it = 0, pending = 0;  // iterations launched; those of them not read back
+    int it = 0, seen = 0;  // iterations launched, and looked at
+    // waits for the oldest iteration not looked at yet
+    auto look = [&]() -> spt_status {
+        if (!rep.wait(++seen, s)) return hip_fail(hipGetLastError(), "cp_als: iteration");
+        const AlsReport &r = rep.at[seen % Reports::kSlots];
+        for (int n = 0; n < N; ++n)
+            if (r.status[n] < 0)
+                return fail(SPT_E_NOT_SPD, "cp_als: normal equations of mode " + std::to_string(n) +
+                                               " not positive definite after ridge retries");
+        fit = r.fit;
+        return SPT_OK;
+    };
     while (it < max_iters) {
-        IterOut *io = iters + pending;
         for (int n = 0; n < N; ++n) {
             const int64_t In = t->dims[n];
             CK(run_mttkrp(t, (const float *const *)F, R, n, M, s, &ws));
             GramRef gm{};
             CK(launch_gram(M, In, R, gram_m, gwork, gw, &gm, s));
-            CK(launch_solve_prep(grams, N, n, R, gm, S, lam, io->status + n, grams + (size_t)n * R * R, s));
+            CK(launch_solve_prep(grams, N, n, R, gm, S, lam, status + n, grams + (size_t)n * R * R, s));
             CK(launch_apply(M, In, R, S, F[n], lam, n == N - 1 ? inner : nullptr, s));
         }
-        CK(launch_fit(grams, N, R, lam, inner, inner_parts, t->norm_x2, io->fit, s));
         ++it;
-        ++pending;
-        if (!(tol > 0.0) && it < max_iters && pending < kAhead) continue;
-        IterOut h[kAhead];
-        if (hipMemcpyAsync(h, iters, sizeof(IterOut) * pending, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess) {
-            cleanup();
-            return hip_fail(hipGetLastError(), "cp_als: fit readback");
-        }
-        for (int p = 0; p < pending; ++p)
-            for (int n = 0; n < N; ++n)
-                if (h[p].status[n] < 0) {
-                    cleanup();
-                    return fail(SPT_E_NOT_SPD, "cp_als: normal equations of mode " + std::to_string(n) +
-                                                   " not positive definite after ridge retries");
-                }
-        fit = h[pending - 1].fit[0];
-        pending = 0;
-        if (1.0 - fit < 1e-2 && t->nnz > 0 && (tol > 0.0 || it == max_iters)) {
+        CK(launch_fit(grams, N, R, lam, inner, inner_parts, t->norm_x2, fitd, status, rep.at + it % Reports::kSlots, it, s));
+        // Without a tolerance no iteration depends on the one before it having
+        // been looked at, so one more is under way while the host waits: a
+        // solve that fails is seen at most one iteration late, and the stream does
+        // not wait for the host (20k nonzeros, rank 16, 10 iterations: 964 us, with
+        // a wait for each 1009; 1013 with one readback of all of them at the end,
+        // behind which a failure of the first solve of 100 iterations took 5.1 ms
+        // instead of 0.43).
+        while (seen < it && (tol > 0.0 || it == max_iters || seen + 1 < it)) CK(look());
+        if (!(tol > 0.0) && it < max_iters) continue;
+        if (1.0 - fit < 1e-2 && t->nnz > 0) {
             // near convergence the Gram shortcut loses accuracy (FP32 MTTKRP); take the
             // residual directly over the nonzeros in FP64
             MttkrpArgs a = make_args(t, (const float *const *)F, R, -1, nullptr, 1024);
             CK(launch_resid(a, lam, resid, (int)resid_tiles, s));
-            CK(launch_fit_direct(resid, (int)resid_tiles, t->norm_x2, io->fit, s));  // with this iteration's |Xhat|^2
-            if (hipMemcpyAsync(&fit, io->fit, sizeof(fit), hipMemcpyDeviceToHost, s) != hipSuccess ||
-                hipStreamSynchronize(s) != hipSuccess) {
-                cleanup();
-                return hip_fail(hipGetLastError(), "cp_als: direct fit readback");
-            }
+            CK(launch_fit_direct(resid, (int)resid_tiles, t->norm_x2, fitd, s));  // with this iteration's |Xhat|^2
+            if (hipMemcpyAsync(&fit, fitd, sizeof(fit), hipMemcpyDeviceToHost, s) != hipSuccess ||
+                hipStreamSynchronize(s) != hipSuccess)
+                CK(hip_fail(hipGetLastError(), "cp_als: direct fit readback"));
         }
         if (tol > 0.0 && std::fabs(fit - fit_prev) < tol) break;
         fit_prev = fit;

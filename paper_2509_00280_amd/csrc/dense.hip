@@ -614,8 +614,14 @@ __device__ __forceinline__ void fit_body(const double *__restrict__ grams, int n
 __global__ __launch_bounds__(kFitThreads) void k_fit(const double *__restrict__ grams, int nmodes, int R,
                                                   const double *__restrict__ lambda,
                                                   const double *__restrict__ inner_partials, int nparts,
-                                                  double norm_x2, double *__restrict__ out) {
+                                                  double norm_x2, double *__restrict__ out,
+                                                  const int *__restrict__ status, AlsReport *report, int number) {
     fit_body(grams, nmodes, R, lambda, inner_partials, nparts, norm_x2, out);
+    if (threadIdx.x == 0) {
+        report->fit = out[0];
+        for (int k = 0; k < nmodes; ++k) report->status[k] = status[k];
+        __hip_atomic_store(&report->number, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 __global__ __launch_bounds__(kFitThreads) void k_fit_batched(const FitItem *__restrict__ items) {
@@ -722,9 +728,10 @@ spt_status launch_apply(const float *M, int64_t rows, int rank, const double *S,
 }
 
 spt_status launch_fit(const double *grams, int nmodes, int rank, const double *lambda, const double *inner_partials,
-                      int nparts, double norm_x2, double *out, hipStream_t s) {
+                      int nparts, double norm_x2, double *out, const int *status, AlsReport *report, int number,
+                      hipStream_t s) {
     hipLaunchKernelGGL(k_fit, dim3(1), dim3(kFitThreads), 0, s, grams, nmodes, rank, lambda, inner_partials, nparts, norm_x2,
-                       out);
+                       out, status, report, number);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }

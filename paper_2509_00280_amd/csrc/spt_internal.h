@@ -500,9 +500,18 @@ spt_status launch_solve_prep(const double *grams, int nmodes, int mode, int rank
 spt_status launch_apply(const float *M, int64_t rows, int rank, const double *S, float *C,
                         const double *lambda, double *inner_partials, hipStream_t s);
 int apply_blocks(int64_t rows);  // blocks of launch_apply: one inner-product partial each
-// fit: out[0] = fit (shortcut), out[1] = |Xhat|^2; reads inner partials
+// What the host looks at after an iteration: the fit, the modes' solve status
+// and, written last, the report's number.
+struct AlsReport {
+    double fit;
+    int status[kMaxModes];
+    int number;
+};
+// fit: out[0] = fit (shortcut), out[1] = |Xhat|^2; reads inner partials; the fit and
+// `status` (nmodes entries) also go to *report (coherent host memory) under `number`
 spt_status launch_fit(const double *grams, int nmodes, int rank, const double *lambda,
-                      const double *inner_partials, int nparts, double norm_x2, double *out, hipStream_t s);
+                      const double *inner_partials, int nparts, double norm_x2, double *out, const int *status,
+                      AlsReport *report, int number, hipStream_t s);
 spt_status launch_fit_direct(const double *resid_partials, int nparts, double norm_x2, double *out,
                              hipStream_t s);
 spt_status launch_sum_f64(const double *parts, int n, double *out, hipStream_t s);

@@ -1,5 +1,6 @@
-"""CP-ALS without a tolerance, whose iterations are read back in groups: what it
-returns is the last iteration's, bit for bit that of a run that looks at each."""
+"""CP-ALS without a tolerance, which does not wait for an iteration before it starts
+the next: what it returns is the last iteration's, bit for bit that of a run that
+looks at each, and a solve that fails ends the call soon."""
 import numpy as np
 import pytest
 
@@ -69,3 +70,60 @@ def test_direct_residual_of_the_last_iteration(iters):
     off = np.linalg.norm(model(first["lam"], first["factors"])) ** 2 - (xhat[on] ** 2).sum()
     mistaken = 1.0 - np.sqrt(((dense - xhat)[on] ** 2).sum() + max(off, 0.0)) / norm
     assert abs(mistaken - exact) > 10 * tol
+
+
+@pytest.mark.parametrize("tol", [0.0, 1e-300])
+def test_a_failed_solve_ends_the_call(tol):
+    """The first solve is refused: at most one iteration is under way beyond it, of 100 asked for."""
+    import torch
+    from paper_2509_00280_amd import spt
+    t = synth.distinct_coo(6, (60, 50, 40), 6000, ["uniform"] * 3, "u01")
+    h = spt.encode(t.dims, *to_dev(t))
+    F = factors_dev([np.full((d, 4), np.nan, np.float32) for d in t.dims])
+    F[2] = torch.ones_like(F[2])
+    h.prepare(4)
+    spt.profile_reset(True)
+    with pytest.raises(spt.SptError, match="mode 0 not positive definite"):
+        spt.cp_als(h, F, 100, tol=tol)
+    calls = spt.profile_read()["mttkrp_launches"][:3]
+    spt.lib().spt_profile_enable(0)
+    assert max(calls) <= 2, calls
+    assert torch.equal(F[2], torch.ones_like(F[2])) and torch.isnan(F[0]).all()
+    h.free()
+
+
+def test_calls_of_several_threads():
+    """Each call has its own reports: the same models as one call after the other."""
+    import threading
+    import torch
+    from paper_2509_00280_amd import spt
+    ts = [synth.distinct_coo(20 + i, (60 + i, 50, 40), 5000, ["uniform"] * 3, "u01") for i in range(6)]
+    hs = [spt.encode(t.dims, *to_dev(t)) for t in ts]
+    init = [[(np.abs(f) + 0.1).astype(np.float32) for f in synth.normal_factors(i, t.dims, 4)] for i, t in enumerate(ts)]
+    alone = []
+    for h, f0 in zip(hs, init):
+        F = factors_dev(f0)
+        alone.append((spt.cp_als(h, F, 9)[1], F))
+    got = [None] * len(ts)
+    Fs = [factors_dev(f0) for f0 in init]
+    torch.cuda.synchronize()
+
+    def work(i):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            for _ in range(5):
+                for f, f0 in zip(Fs[i], init[i]):
+                    f.copy_(torch.from_numpy(f0))
+                fit = spt.cp_als(hs[i], Fs[i], 9)[1]
+            s.synchronize()
+        got[i] = fit
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(ts))]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    for i, (fit, F) in enumerate(alone):
+        assert got[i] == fit
+        assert all(torch.equal(a, b) for a, b in zip(Fs[i], F))
+    spt.empty_cache()
