@@ -260,6 +260,7 @@ BatchEngine::BatchEngine(hipStream_t s) : s_(s) {}
 // Every engine buffer is released in stream order on the engine's stream:
 // work already queued keeps its memory until it has run.
 BatchEngine::~BatchEngine() {
+    wait_upload();
     for (Member *m : members_) free_member_state(m);
     release_buffers();
 }
@@ -275,6 +276,12 @@ void BatchEngine::release_buffers() {
     inner_all_ = nullptr;
     resid_ = nullptr;
     ws_.release(s_);
+}
+
+// A step that failed may have left the upload of blob_ without a synchronisation behind it.
+void BatchEngine::wait_upload() {
+    if (uploading_) (void)hipStreamSynchronize(s_);
+    uploading_ = false;
 }
 
 void BatchEngine::free_member_state(Member *m) {
@@ -491,23 +498,22 @@ spt_status BatchEngine::rebuild() {
                 init.push_back(g);
             }
             init_rmax = std::max(init_rmax, m->R);
-            m->fresh = false;
         }
     init_slices_ = assign_slices(init);
     gram_need = std::max(gram_need, gram_batched_ws_bytes(init_slices_, std::max(init_rmax, 1)));
-    if (!gram_ws_.get(gram_need, s_)) return fail(SPT_E_OOM, "batch: Gram workspace");
     init_off_ = put(init.data(), sizeof(GramItem) * init.size());
     init_count_ = (int)init.size();
     init_rmax_ = init_rmax;
-    // the host image lives in the engine until the next rebuild, which comes
-    // after a step's synchronisation: the asynchronous upload has run by then
+    // every buffer is there before the first copy or kernel
+    uint64_t *rows = (uint64_t *)rows_buf_.get(sizeof(uint64_t) * std::max<int64_t>(all_records, 1), s_);
+    d_items_ = (char *)items_buf_.get(std::max<size_t>(blob.size(), 256), s_);
+    if (!gram_ws_.get(gram_need, s_) || !rows || !d_items_) return fail(SPT_E_OOM, "batch: item arrays");
+    // the host image lives in the engine until a synchronisation has followed its asynchronous upload
+    wait_upload();
     blob_.swap(blob);
-    d_items_ = (char *)items_buf_.get(std::max<size_t>(blob_.size(), 256), s_);
-    if (!d_items_) return fail(SPT_E_OOM, "batch: item arrays");
+    uploading_ = true;
     if (!blob_.empty()) SPT_HIP(hipMemcpyAsync(d_items_, blob_.data(), blob_.size(), hipMemcpyHostToDevice, s_));
     // rows of every mode's records, fixed while the members are
-    uint64_t *rows = (uint64_t *)rows_buf_.get(sizeof(uint64_t) * std::max<int64_t>(all_records, 1), s_);
-    if (!rows) return fail(SPT_E_OOM, "batch: record rows");
     for (const ModeItems &mi : modes_) {
         spt_status st = launch_record_rows_batched((const SegItem *)(d_items_ + mi.seg_off), mi.count, mi.records,
                                                    rows + mi.row_at, s_);
@@ -518,6 +524,7 @@ spt_status BatchEngine::rebuild() {
                                             init_rmax_, (double *)gram_ws_.p, s_);
         if (st != SPT_OK) return st;
     }
+    for (Member *m : act) m->fresh = false;
     dirty_ = false;
     return SPT_OK;
 }
@@ -558,6 +565,7 @@ spt_status BatchEngine::step(bool *before_kernels) {
         hipMemcpyAsync(hstat_.data(), status_all_, sizeof(int) * kMaxModes * A, hipMemcpyDeviceToHost, s_) != hipSuccess ||
         hipStreamSynchronize(s_) != hipSuccess)
         return hip_fail(hipGetLastError(), "batch: fit readback");
+    uploading_ = false;
     // direct FP64 residual near convergence, as in the single-tensor driver
     std::vector<int> direct;
     for (int i = 0; i < A; ++i) {

@@ -409,6 +409,7 @@ public:
 private:
     spt_status rebuild();
     void release_buffers();
+    void wait_upload();
     void free_member_state(Member *m);
     hipStream_t s_;
     std::vector<Member *> members_, active_;
@@ -422,7 +423,8 @@ private:
     DevBuf gram_ws_;  // partial Grams of the batched Gram launches
     DevBuf rows_buf_;  // record rows of every mode's launch
     DevBuf items_buf_, M_buf_, fit_buf_, status_buf_, inner_buf_, resid_buf_, resid_items_buf_;
-    std::vector<char> blob_;  // host image of the item arrays (kept until the next upload)
+    std::vector<char> blob_;  // host image of the item arrays (kept until its upload has run)
+    bool uploading_ = false;  // no synchronisation since the upload
     float *M_all_ = nullptr;
     double *fit_all_ = nullptr, *inner_all_ = nullptr, *resid_ = nullptr;
     int *status_all_ = nullptr;
