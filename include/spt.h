@@ -263,9 +263,10 @@ spt_status spt_mttkrp(spt_tensor t, const float *const *factors, int rank, int m
  * tensor must be prepared (SPT_PREPARE_SINGLE) and its plan for `mode` must
  * be SEGMENT (or AUTO), DIRECT or REGROUP; a workspace above the maximum
  * (records x (8 + 4 rank) bytes, counting a record for every 64 nonzeros of a
- * run, about 0.1 records per nonzero) is rejected with SPT_E_INVALID_ARG.  Every call on one GPU shares the array: calls that
- * overlap on one GPU (on different streams or threads) race, so the caller
- * orders them.  Asynchronous, free of synchronisation.
+ * run, about 0.1 records per nonzero) is rejected with SPT_E_INVALID_ARG.
+ * Every call on one GPU shares the array: calls that overlap on one GPU (on
+ * different streams or threads) race, so the caller orders them.
+ * Asynchronous, free of synchronisation.
  */
 #define SPT_NOALLOC_SCRATCH_BYTES (64u << 20)
 spt_status spt_mttkrp_noalloc(spt_tensor t, const float *const *factors, int rank, int mode, float *out,

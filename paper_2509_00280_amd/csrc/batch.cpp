@@ -63,8 +63,8 @@ void set_batch_plan_args(MttkrpArgs &a, const ModePlan &p) {
 // Builds the batched SEGMENT plan of `mode` for every tensor that lacks it,
 // for all of them at once: one counting launch and readback, one emission
 // launch, one sort of all distinct (tile, row) pairs by row of the
-// concatenated output (tensors in order, tile order kept within a row).  Each tensor's records come out grouped by row,
-// numbered from 0 within the tensor.
+// concatenated output (tensors in order, tile order kept within a row).  Each
+// tensor's records come out grouped by row, numbered from 0 within the tensor.
 int batch_tile_of(const Tensor *t) {
     const int b = t->plan.batch_tile;
     return (b == 1024 || b == 2048 || b == 4096) ? b : kBatchTileDefault;

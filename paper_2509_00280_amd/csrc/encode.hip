@@ -670,10 +670,4 @@ spt_status sort_u64_keys_ws(uint64_t *keys, uint64_t *keys2, uint32_t *idx_a, ui
     return SPT_OK;
 }
 
-spt_status launch_sum_f64(const double *parts, int n, double *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_sum_f64, dim3(1), dim3(kThreads), 0, s, parts, n, out);
-    SPT_HIP(hipGetLastError());
-    return SPT_OK;
-}
-
 }  // namespace spt

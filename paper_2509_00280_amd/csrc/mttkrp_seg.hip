@@ -905,8 +905,11 @@ spt_status launch_seg_nt(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
 }  // namespace
 
 // Whether a call on `a` reads a factor or writes records (ld columns) beyond the
-// 4 GiB that a structured buffer's 32-bit offsets reach (RowView): a row of
-// more than 4 GiB's index would come around to the array's start.
+// 4 GiB that a structured buffer's 32-bit offsets reach (RowView): rows past
+// them would come around to the array's start.  The kernels with 64-bit
+// addresses take up to 115 registers, so fewer waves to a CU: FP64, 20M
+// rows of rank 32, 20M nonzeros 1.59 and 1.11 ms for the modes that gather them,
+// 1.41 and 1.01 in the buffer's (there wrong) rows.
 bool seg_far(const MttkrpArgs &a, int ld, size_t item) {
     bool far = (uint64_t)a.rec_cap * ld * item > kBufferBytes;
     for (int k = 0; k < a.nmodes; ++k) far = far || (k != a.mode && (uint64_t)a.frows[k] * a.rank * item > kBufferBytes);
@@ -1026,14 +1029,16 @@ spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, f
 template <int NT, int NMAX, int NFIX, bool FAR = false>
 spt_status launch_segb_n(const SegItem *items, int count, int64_t total_tiles, int ld, bool vec4, float *rec_val,
                          unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
-    return vec4 ? launch_segb_k<NT, NMAX, NFIX, 4, FAR>(items, count, total_tiles, rec_val, ld, next_tile, out, out_floats, s)
-                : launch_segb_k<NT, NMAX, NFIX, 1, FAR>(items, count, total_tiles, rec_val, ld, next_tile, out, out_floats, s);
+    auto go = [&](auto launch) { return launch(items, count, total_tiles, rec_val, ld, next_tile, out, out_floats, s); };
+    return vec4 ? go(launch_segb_k<NT, NMAX, NFIX, 4, FAR>) : go(launch_segb_k<NT, NMAX, NFIX, 1, FAR>);
 }
 
 template <int NT>
 spt_status launch_segb_t(const SegItem *items, int count, int64_t total_tiles, const BatchShape &b, float *rec_val,
                          unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
-    auto go = [&](auto launch) { return launch(items, count, total_tiles, b.ld, b.vec4, rec_val, next_tile, out, out_floats, s); };
+    auto go = [&](auto launch) {
+        return launch(items, count, total_tiles, b.ld, b.vec4, rec_val, next_tile, out, out_floats, s);
+    };
     if (b.far) return b.nmodes_max <= 4 ? go(launch_segb_n<NT, 4, 0, true>) : go(launch_segb_n<NT, 8, 0, true>);
     if (b.nmodes_min == 3 && b.nmodes_max == 3) return go(launch_segb_n<NT, 3, 3>);
     return b.nmodes_max <= 4 ? go(launch_segb_n<NT, 4, 0>) : go(launch_segb_n<NT, 8, 0>);

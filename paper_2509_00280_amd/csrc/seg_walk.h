@@ -48,13 +48,17 @@ __device__ __forceinline__ uint32_t run_bits(const RunWord *words, int q) {  // 
     return __builtin_amdgcn_alignbit(words[min(w + 1, T / 32 - 1)].x, words[min(w, T / 32 - 1)].x, q & 31);
 }
 
-// step: positions that a step of the walk takes.  Unless TIGHT (the 4-mode
-// kernels held to 64 VGPRs), all words of the run starts are asked for at once;
-// one after the other, as they are needed, they are four round trips to memory at every tile's start, but cost fewer
-// registers on the way.  All-mode sweeps without and with: 100M nonzeros, 3
-// modes, rank 32 4.12 / 4.07 ms; a batch of 32 decompositions 31.8 / 31.0 ms;
-// the 4-mode kernels spill more, 12.89 / 13.28 ms (150M nonzeros, rank 64) and
-// 845 / 857 us (3M, rank 10).
+// step: positions that a step of the walk takes.  Unless TIGHT, all words of
+// the run starts are asked for at once; one after the other, as they are
+// needed, they are four round trips to memory at every tile's start, but cost
+// fewer registers on the way.  TIGHT are the 4-mode kernels of one tensor, the
+// widest that are held to 64 VGPRs: all-mode sweeps without and with it, here
+// and at the walk's end, 13.61 / 12.57 ms (150M nonzeros, rank 64) and 837 / 798
+// us (3M, rank 10).  It cost the 3-mode kernel (100M, rank 32: 4.07 / 4.12 ms
+// here, 4.07 / 4.09 at the end) and the batched kernels, which are held to 128
+// VGPRs (32 decompositions 31.0 / 31.8 ms).  The kernel for up to 3 modes, which
+// runs two, spills as well and would gain (10M, rank 16: 201 / 189 us), but
+// shares the 3-mode kernel's form.
 template <int NT, int T, bool TIGHT>
 __device__ __forceinline__ WalkShare walk_share(const LaneGroup &lg, int cnt, int step, const RunWord *words) {
     const int NG = NT / 64 * lg.per_wave;
@@ -89,14 +93,6 @@ __device__ __forceinline__ WalkShare walk_share(const LaneGroup &lg, int cnt, in
     return ws;
 }
 
-// Walk the first cnt positions of a staged tile (every thread of the workgroup
-// calls, after the barrier behind the staging).  product(q, p, x) forms the
-// products of the positions q + u, u < UB, for this lane's columns, up to the
-// last factor: p[u][:] * x[u][:], which the sum takes in one fma; q is a multiple of UB, and the staging fills positions from cnt on to the next
-// multiple with anything that can be read.
-// rec[k] is the record of the tile's run k; records have ld columns (R..ld-1
-// are zeroed).  Reads stay inside the tile and no record at or beyond rec_cap
-// is written, whatever the plan holds.
 // UB staged words of 4 or 8 bytes at p (aligned to all of them) in one read
 template <int UB, class Word>
 __device__ __forceinline__ void load_words(const Word *p, Word (&x)[UB]) {
@@ -111,6 +107,15 @@ __device__ __forceinline__ void load_words(const Word *p, Word (&x)[UB]) {
     }
 }
 
+// Walk the first cnt positions of a staged tile (every thread of the workgroup
+// calls, after the barrier behind the staging).  product(q, p, x) forms the
+// products of the positions q + u, u < UB, for this lane's columns, up to the
+// last factor: p[u][:] * x[u][:], which the sum takes in one fma; q is a
+// multiple of UB, and the staging fills positions from cnt on to the next
+// multiple with anything that can be read.
+// rec[k] is the record of the tile's run k; records have ld columns (R..ld-1
+// are zeroed).  Reads stay inside the tile and no record at or beyond rec_cap
+// is written, whatever the plan holds.
 template <class Real, int NT, int T, int VEC, int UB, bool TIGHT, bool FAR, class Product>
 __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &ws, int R, int cnt, int nruns,
                                          const uint32_t *__restrict__ rec, uint32_t rec_cap,
@@ -216,10 +221,7 @@ __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &w
     }
     // TIGHT: the lane group worked out anew.  Its numbers, and the addresses made
     // from them, would otherwise be held across the walk in spills, which reach
-    // HBM (40 bytes a thread were 10 of 18 bytes written per nonzero): 13.38 /
-    // 12.89 ms for an all-mode sweep (rank 64, 4 modes, 150M nonzeros), 868 / 845
-    // us (rank 10, 3M).  Without spills it only costs: 4.07 / 4.09 ms (rank 32,
-    // 3 modes, 100M).
+    // HBM (40 bytes a thread were 10 of 18 bytes written per nonzero).
     int tid = threadIdx.x;
     LaneGroup tail = lg;
     if constexpr (TIGHT) {

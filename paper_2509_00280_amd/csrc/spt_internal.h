@@ -516,7 +516,6 @@ spt_status launch_fit(const double *grams, int nmodes, int rank, const double *l
                       AlsReport *report, int number, hipStream_t s);
 spt_status launch_fit_direct(const double *resid_partials, int nparts, double norm_x2, double *out,
                              hipStream_t s);
-spt_status launch_sum_f64(const double *parts, int n, double *out, hipStream_t s);
 
 }  // namespace spt
 
