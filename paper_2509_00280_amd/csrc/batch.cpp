@@ -372,7 +372,7 @@ spt_status BatchEngine::rebuild() {
             }
         const int ld = rmax;
         const int rw = apply_batch_rows();
-        bool far = false;
+        SegFar far = kNear;
         int64_t tiles = 0, recs = 0, rows = 0, blocks = 0;
         for (int i = 0; i < A; ++i) {
             Member *m = act[i];
@@ -385,7 +385,7 @@ spt_status BatchEngine::rebuild() {
             si.first_tile = tiles;
             si.rec_base = recs;
             si.row_base = rows;
-            far = far || seg_far(si.a, ld, sizeof(float));
+            far = std::max(far, seg_far(si.a, ld, sizeof(float)));
             seg.push_back(si);
             const int64_t In = t->dims[n];
             // M_all block of this member: filled in below once M_all exists (offset only here)
@@ -682,7 +682,7 @@ spt_status spt_mttkrp_batched(const spt_tensor *ts, int count, const float *cons
     if (tv.empty()) return SPT_OK;
     if (!seg_batch_fits(nmax, tile)) return fail(SPT_E_INVALID_ARG, "mttkrp_batched: too many modes");
     const int ld = rmax;
-    BatchShape shape{nmin, nmax, tile, ld, vec4, false};
+    BatchShape shape{nmin, nmax, tile, ld, vec4, kNear};
     std::vector<SegItem> items(tv.size());
     int64_t tiles = 0, recs = 0, rows = 0;
     std::vector<int64_t> row_base(tv.size());
@@ -695,7 +695,7 @@ spt_status spt_mttkrp_batched(const spt_tensor *ts, int count, const float *cons
         items[i].first_tile = tiles;
         items[i].rec_base = recs;
         items[i].row_base = rows;
-        shape.far = shape.far || seg_far(items[i].a, ld, sizeof(float));
+        shape.far = std::max(shape.far, seg_far(items[i].a, ld, sizeof(float)));
         row_base[i] = rows;
         tiles += (t->nnz + tile - 1) / tile;
         recs += t->bplan[mode].records;

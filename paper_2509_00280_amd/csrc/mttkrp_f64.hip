@@ -34,7 +34,7 @@ struct FactorsF64 {
     const double *f[kMaxModes];
 };
 
-template <int NT, int VEC, int NMAX, int NFIX, bool FAR>
+template <int NT, int VEC, int NMAX, int NFIX, SegFar FAR>
 __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const double *__restrict__ vals64, int64_t ntiles,
                                                        FactorsF64 F, double *__restrict__ rec_val,
                                                        double *__restrict__ out) {
@@ -106,11 +106,12 @@ __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const doubl
         else valg[cnt] = 0.0;
     }
     __syncthreads();
-    RowView<double, FAR> fb[NO];
+    RowView<double, FAR == kFarAll> fb[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int k = o + (o >= mode);
-        fb[o] = o < no ? RowView<double, FAR>(F.f[k], R, a.frows[k]) : RowView<double, FAR>(nullptr, R, 0u);
+        fb[o] = o < no ? RowView<double, FAR == kFarAll>(F.f[k], R, a.frows[k])
+                       : RowView<double, FAR == kFarAll>(nullptr, R, 0u);
     }
     const int c = lg.col;
     auto product = [&](int q0, double (&p)[UB][VEC], double (&last)[UB][VEC]) {
@@ -155,34 +156,41 @@ __global__ __launch_bounds__(256) void k_gather_f64(const double *__restrict__ s
         dst[i] = src[idx[i]];
 }
 
-template <int NT, int NMAX, int NFIX, bool FAR = false>
+template <int NT, int VEC, int NMAX, int NFIX, SegFar FAR>
 spt_status launch_f64_k(const MttkrpArgs &a, const double *vals64, const FactorsF64 &F, int64_t ntiles, double *rec_val,
                         double *out, hipStream_t s) {
-    const size_t lds = f64_lds_bytes(4 * NT, a.nmodes);
-    if (a.rank > 128)  // two columns a lane would be more than a wave
-        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 4, NMAX, NFIX, FAR>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
-                           ntiles, F, rec_val, out);
-    else if (a.rank >= 2)
-        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 2, NMAX, NFIX, FAR>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
-                           ntiles, F, rec_val, out);
-    else
-        hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, 1, NMAX, NFIX, FAR>), dim3((unsigned)ntiles), dim3(NT), lds, s, a, vals64,
-                           ntiles, F, rec_val, out);
+    hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, VEC, NMAX, NFIX, FAR>), dim3((unsigned)ntiles), dim3(NT),
+                       f64_lds_bytes(4 * NT, a.nmodes), s, a, vals64, ntiles, F, rec_val, out);
     SPT_HIP(hipGetLastError());
     return SPT_OK;
 }
 
-template <int NT>
+template <int NT, int VEC, SegFar FAR>
 spt_status launch_f64_n(const MttkrpArgs &a, const double *vals64, const FactorsF64 &F, int64_t ntiles, double *rec_val,
                         double *out, hipStream_t s) {
-    if (seg_far(a, a.rank, sizeof(double)))
-        return a.nmodes <= 4 ? launch_f64_k<NT, 4, 0, true>(a, vals64, F, ntiles, rec_val, out, s)
-                             : launch_f64_k<NT, 8, 0, true>(a, vals64, F, ntiles, rec_val, out, s);
-    if (a.nmodes == 3) return launch_f64_k<NT, 3, 3>(a, vals64, F, ntiles, rec_val, out, s);
-    if (a.nmodes == 4) return launch_f64_k<NT, 4, 4>(a, vals64, F, ntiles, rec_val, out, s);
-    if (a.nmodes == 5) return launch_f64_k<NT, 5, 5>(a, vals64, F, ntiles, rec_val, out, s);
-    return a.nmodes < 3 ? launch_f64_k<NT, 3, 0>(a, vals64, F, ntiles, rec_val, out, s)
-                        : launch_f64_k<NT, 8, 0>(a, vals64, F, ntiles, rec_val, out, s);
+    auto go = [&](auto launch) { return launch(a, vals64, F, ntiles, rec_val, out, s); };
+    if constexpr (FAR == kFarAll) {
+        return a.nmodes <= 4 ? go(launch_f64_k<NT, VEC, 4, 0, FAR>) : go(launch_f64_k<NT, VEC, 8, 0, FAR>);
+    } else {
+        if (a.nmodes == 3) return go(launch_f64_k<NT, VEC, 3, 3, FAR>);
+        if (a.nmodes == 4) return go(launch_f64_k<NT, VEC, 4, 4, FAR>);
+        if (a.nmodes == 5) return go(launch_f64_k<NT, VEC, 5, 5, FAR>);
+        return a.nmodes < 3 ? go(launch_f64_k<NT, VEC, 3, 0, FAR>) : go(launch_f64_k<NT, VEC, 8, 0, FAR>);
+    }
+}
+
+template <int NT>
+spt_status launch_f64_t(const MttkrpArgs &a, const double *vals64, const FactorsF64 &F, int64_t ntiles, double *rec_val,
+                        double *out, hipStream_t s) {
+    auto go = [&](auto launch) { return launch(a, vals64, F, ntiles, rec_val, out, s); };
+    const SegFar far = seg_far(a, a.rank, sizeof(double));
+    if (a.rank < 2) return far == kNear ? go(launch_f64_n<NT, 1, kNear>) : go(launch_f64_n<NT, 1, kFarAll>);
+    if (a.rank <= 128)
+        return far == kNear ? go(launch_f64_n<NT, 2, kNear>)
+                            : far == kFarRecords ? go(launch_f64_n<NT, 2, kFarRecords>) : go(launch_f64_n<NT, 2, kFarAll>);
+    // two columns a lane would be more than a wave
+    return far == kNear ? go(launch_f64_n<NT, 4, kNear>)
+                        : far == kFarRecords ? go(launch_f64_n<NT, 4, kFarRecords>) : go(launch_f64_n<NT, 4, kFarAll>);
 }
 
 }  // namespace
@@ -200,9 +208,9 @@ spt_status launch_mttkrp_seg_f64(const MttkrpArgs &a, const double *vals64, cons
     if (a.rank > 256) return fail(SPT_E_INVALID_ARG, "mttkrp_f64: rank above 256");
     FactorsF64 f{};
     for (int k = 0; k < a.nmodes; ++k) f.f[k] = F[k];
-    if (a.tile == 1024) return launch_f64_n<256>(a, vals64, f, ntiles, rec_val, out, s);
-    if (a.tile == 2048) return launch_f64_n<512>(a, vals64, f, ntiles, rec_val, out, s);
-    return launch_f64_n<1024>(a, vals64, f, ntiles, rec_val, out, s);
+    if (a.tile == 1024) return launch_f64_t<256>(a, vals64, f, ntiles, rec_val, out, s);
+    if (a.tile == 2048) return launch_f64_t<512>(a, vals64, f, ntiles, rec_val, out, s);
+    return launch_f64_t<1024>(a, vals64, f, ntiles, rec_val, out, s);
 }
 
 spt_status launch_reduce_records_f64(const uint64_t *srow, const double *rec, int64_t P, int R, int64_t rows,

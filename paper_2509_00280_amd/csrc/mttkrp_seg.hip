@@ -168,7 +168,7 @@ struct ZeroSlice {
 // make the compiler wait for one mode's rows before the next mode's gathers
 // are issued).
 __host__ __device__ constexpr int segp_step(int nmax) { return nmax <= 4 ? 2 : 1; }  // nonzeros of a step
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, bool FAR>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, SegFar FAR>
 __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const LaneGroup &lg, const WalkShare &ws,
                                           int cnt, int64_t k0, int nruns, float *__restrict__ rec_val, int ld) {
     constexpr int NO = NMAX - 1;  // non-output modes at most
@@ -179,11 +179,12 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
     const float *valg = reinterpret_cast<const float *>(crdg + (size_t)no * T);
     const int c = lg.col;
     // factor of the o-th non-output mode as a row buffer
-    RowView<float, FAR> fb[NO];
+    RowView<float, FAR == kFarAll> fb[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int k = o + (o >= mode);
-        fb[o] = o < no ? RowView<float, FAR>(a.f[k], R, a.frows[k]) : RowView<float, FAR>(nullptr, R, 0u);
+        fb[o] = o < no ? RowView<float, FAR == kFarAll>(a.f[k], R, a.frows[k])
+                       : RowView<float, FAR == kFarAll>(nullptr, R, 0u);
     }
     auto product = [&](int q, float (&p)[UB][VEC], float (&last)[UB][VEC]) {
         float x[UB];
@@ -246,7 +247,7 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
 // A tile is staged by one scatter of values and non-output coordinates to
 // their positions; there is no hashing and no scan over nonzeros at run time.
 // Records of ld floats go to rec_val.
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, bool FAR>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, SegFar FAR>
 __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, char *lds,
                                           float *__restrict__ rec_val, int ld, const ZeroSlice &zero) {
     constexpr int PER = T / NT;  // nonzeros staged per thread
@@ -327,12 +328,13 @@ __device__ __forceinline__ ZeroSlice out_slice(const MttkrpArgs &a, int64_t tile
     return ZeroSlice{a.out, (int64_t)a.frows[a.mode] * a.rank, tile, ntiles};
 }
 
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool FAR>
-__global__ __launch_bounds__(NT, NMAX <= 5 && !FAR ? 8 : 4) void k_mttkrp_segp(MttkrpArgs a, int64_t ntiles) {
+template <int NT, int T, int VEC, int NMAX, int NFIX, SegFar FAR>
+__global__ __launch_bounds__(NT, NMAX <= 5 && FAR != kFarAll ? 8 : 4) void k_mttkrp_segp(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segp_tile<NT, T, VEC, NMAX, NFIX, NMAX == 4 && !FAR, FAR>(a, tile, lds, a.rec_val, a.rank, out_slice(a, tile, ntiles));
+    segp_tile<NT, T, VEC, NMAX, NFIX, NMAX == 4 && FAR != kFarAll, FAR>(a, tile, lds, a.rec_val, a.rank,
+                                                                       out_slice(a, tile, ntiles));
 }
 
 // ---------------------------------------------------------------- row cache
@@ -448,7 +450,7 @@ __host__ __device__ inline size_t segd_lds_bytes(int T, int nmodes, int cap, int
 // tile dictionary are copied to LDS; a nonzero whose index is below cap
 // reads its factor row there, any other reads it from HBM/L2 by its global
 // row.
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, bool FAR>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, SegFar FAR>
 __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int64_t ntiles, char *lds) {
     constexpr int PER = T / NT;
     constexpr int NO = NMAX - 1;
@@ -593,11 +595,12 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
     // into the registers of an LDS read waits for that read; with all LDS
     // reads of the step issued first the loads wait for one LDS round trip,
     // and no branch splits hits from misses.
-    RowView<float, FAR> fb[NO];
+    RowView<float, FAR == kFarAll> fb[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int k = o + (o >= mode);
-        fb[o] = o < no ? RowView<float, FAR>(a.f[k], R, a.frows[k]) : RowView<float, FAR>(nullptr, R, 0u);
+        fb[o] = o < no ? RowView<float, FAR == kFarAll>(a.f[k], R, a.frows[k])
+                       : RowView<float, FAR == kFarAll>(nullptr, R, 0u);
     }
     const char *mine = lds + lg.j * VEC * 4;  // this lane's columns of the row at offset 0
     auto product = [&](int q0, float (&p)[UB][VEC], float (&last)[UB][VEC]) {
@@ -644,12 +647,12 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
 // Bounded to 64 VGPRs, which leaves two workgroups of 16 waves to a CU: left to
 // itself the compiler takes 72 to 82 and one workgroup; the few spills lie
 // outside the steps.
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool FAR>
-__global__ __launch_bounds__(NT, FAR ? 4 : 8) void k_mttkrp_segd(MttkrpArgs a, int64_t ntiles) {
+template <int NT, int T, int VEC, int NMAX, int NFIX, SegFar FAR>
+__global__ __launch_bounds__(NT, FAR == kFarAll ? 4 : 8) void k_mttkrp_segd(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= ntiles) return;
-    segd_tile<NT, T, VEC, NMAX, NFIX, NMAX == 4 && !FAR, FAR>(a, tile, ntiles, lds);
+    segd_tile<NT, T, VEC, NMAX, NFIX, NMAX == 4 && FAR != kFarAll, FAR>(a, tile, ntiles, lds);
 }
 
 // Batched: tile `it` of the whole batch belongs to the last item whose
@@ -678,7 +681,7 @@ __device__ __forceinline__ int seg_item_of(const SegItem *__restrict__ items, in
 // workgroups, the spills cost more than the waves bring (32 members of 10k to
 // 5M nonzeros, ranks 16 and 32, 10 iterations: 40.5, 40.9 and 36.3 ms, here
 // 31.7, and 33.0 with one walk for all mode counts at 72).
-template <int NT, int VEC, int NMAX, int NFIX, bool FAR>
+template <int NT, int VEC, int NMAX, int NFIX, SegFar FAR>
 __global__ __launch_bounds__(NT, 4) void k_mttkrp_segp_batched(const SegItem *__restrict__ items, int count,
                                                             int64_t total_tiles, float *__restrict__ rec_val, int ld,
                                                             unsigned long long *__restrict__ next_tile,
@@ -879,7 +882,7 @@ __global__ __launch_bounds__(NT) void k_count_pieces_batched(const SegItem *__re
     count_tile<NT>(items[b].a, it - items[b].first_tile, lds, wsum, out + it);
 }
 
-template <int NT, int T, int NMAX, int NFIX, int VEC, bool FAR>
+template <int NT, int T, int NMAX, int NFIX, int VEC, SegFar FAR>
 spt_status launch_seg_k(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
     if constexpr (T == kDictTile && NMAX <= 4) {
         if (a.d_cap > 0) {
@@ -896,24 +899,21 @@ spt_status launch_seg_k(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
     return SPT_OK;
 }
 
-template <int NT, int T, int NMAX, int NFIX, bool FAR = false>
-spt_status launch_seg_nt(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
-    return a.rank >= 4 ? launch_seg_k<NT, T, NMAX, NFIX, 4, FAR>(a, ntiles, s)
-                       : launch_seg_k<NT, T, NMAX, NFIX, 1, FAR>(a, ntiles, s);
-}
-
 }  // namespace
 
-// Whether a call on `a` reads a factor or writes records (ld columns) beyond the
-// 4 GiB that a structured buffer's 32-bit offsets reach (RowView): rows past
-// them would come around to the array's start.  The kernels with 64-bit
-// addresses take up to 115 registers, so fewer waves to a CU: FP64, 20M
-// rows of rank 32, 20M nonzeros 1.59 and 1.11 ms for the modes that gather them,
-// 1.41 and 1.01 in the buffer's (there wrong) rows.
-bool seg_far(const MttkrpArgs &a, int ld, size_t item) {
-    bool far = (uint64_t)a.rec_cap * ld * item > kBufferBytes;
-    for (int k = 0; k < a.nmodes; ++k) far = far || (k != a.mode && (uint64_t)a.frows[k] * a.rank * item > kBufferBytes);
-    return far;
+// What a call on `a` reads or writes (records of ld columns) beyond the 4 GiB
+// that a structured buffer's 32-bit offsets reach (RowView): rows past them
+// would come around to the array's start.  Records get there where labels are
+// in no order (150M nonzeros of rank 64, shuffled, modes 1 and 2), so those
+// kernels are the others but for the records' addresses: 5.23 and 5.62 ms a
+// call, 7.65 and 7.97 in the general kernel with 64-bit addresses throughout.
+// Factors that large take that one (FP64, 20M rows of rank 32, 20M nonzeros:
+// 1.58 and 1.11 ms for the modes that gather them; 2.67 and 1.94 with one column
+// a lane and one nonzero in flight).
+SegFar seg_far(const MttkrpArgs &a, int ld, size_t item) {
+    for (int k = 0; k < a.nmodes; ++k)
+        if (k != a.mode && (uint64_t)a.frows[k] * a.rank * item > kBufferBytes) return kFarAll;
+    return (uint64_t)a.rec_cap * ld * item > kBufferBytes ? kFarRecords : kNear;
 }
 
 // tile sizes served: 1024 (256 threads), 2048 (512), 4096 (1024 threads)
@@ -958,17 +958,29 @@ spt_status launch_count_pieces(const MttkrpArgs &a, int64_t *counts, hipStream_t
 }
 
 namespace {
-// 3, 4 and 5 modes get a kernel with the mode count fixed; others, and arrays
+// 3, 4 and 5 modes get a kernel with the mode count fixed; others, and factors
 // past the reach of a structured buffer, a general one
+template <int NT, int T, int VEC, SegFar FAR>
+spt_status launch_seg_nm(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
+    const int nm = a.nmodes;
+    if (nm == 3) return launch_seg_k<NT, T, 3, 3, VEC, FAR>(a, ntiles, s);
+    if (nm == 4) return launch_seg_k<NT, T, 4, 4, VEC, FAR>(a, ntiles, s);
+    if (nm == 5) return launch_seg_k<NT, T, 5, 5, VEC, FAR>(a, ntiles, s);
+    return nm < 3 ? launch_seg_k<NT, T, 3, 0, VEC, FAR>(a, ntiles, s) : launch_seg_k<NT, T, 8, 0, VEC, FAR>(a, ntiles, s);
+}
+
+template <int NT, int T, int VEC>
+spt_status launch_seg_far(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
+    return a.nmodes <= 4 ? launch_seg_k<NT, T, 4, 0, VEC, kFarAll>(a, ntiles, s)
+                         : launch_seg_k<NT, T, 8, 0, VEC, kFarAll>(a, ntiles, s);
+}
+
 template <int NT, int T>
 spt_status launch_seg_tile(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
-    const int nm = a.nmodes;
-    if (seg_far(a, a.rank, sizeof(float)))
-        return nm <= 4 ? launch_seg_nt<NT, T, 4, 0, true>(a, ntiles, s) : launch_seg_nt<NT, T, 8, 0, true>(a, ntiles, s);
-    if (nm == 3) return launch_seg_nt<NT, T, 3, 3>(a, ntiles, s);
-    if (nm == 4) return launch_seg_nt<NT, T, 4, 4>(a, ntiles, s);
-    if (nm == 5) return launch_seg_nt<NT, T, 5, 5>(a, ntiles, s);
-    return nm < 3 ? launch_seg_nt<NT, T, 3, 0>(a, ntiles, s) : launch_seg_nt<NT, T, 8, 0>(a, ntiles, s);
+    const SegFar far = seg_far(a, a.rank, sizeof(float));
+    if (a.rank < 4) return far == kNear ? launch_seg_nm<NT, T, 1, kNear>(a, ntiles, s) : launch_seg_far<NT, T, 1>(a, ntiles, s);
+    if (far == kNear) return launch_seg_nm<NT, T, 4, kNear>(a, ntiles, s);
+    return far == kFarRecords ? launch_seg_nm<NT, T, 4, kFarRecords>(a, ntiles, s) : launch_seg_far<NT, T, 4>(a, ntiles, s);
 }
 }  // namespace
 
@@ -1001,7 +1013,7 @@ spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s) {
 }
 
 namespace {
-template <int NT, int NMAX, int NFIX, int VEC, bool FAR>
+template <int NT, int NMAX, int NFIX, int VEC, SegFar FAR>
 spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, float *rec_val,
                          int ld, unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
     const size_t lds = std::max(segp_lds_bytes(4 * NT, NMAX), walk_lds_bytes(NT));
@@ -1026,22 +1038,21 @@ spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, f
     return SPT_OK;
 }
 
-template <int NT, int NMAX, int NFIX, bool FAR = false>
-spt_status launch_segb_n(const SegItem *items, int count, int64_t total_tiles, int ld, bool vec4, float *rec_val,
+template <int NT, int VEC, SegFar FAR>
+spt_status launch_segb_t(const SegItem *items, int count, int64_t total_tiles, const BatchShape &b, float *rec_val,
                          unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
-    auto go = [&](auto launch) { return launch(items, count, total_tiles, rec_val, ld, next_tile, out, out_floats, s); };
-    return vec4 ? go(launch_segb_k<NT, NMAX, NFIX, 4, FAR>) : go(launch_segb_k<NT, NMAX, NFIX, 1, FAR>);
+    auto go = [&](auto launch) { return launch(items, count, total_tiles, rec_val, b.ld, next_tile, out, out_floats, s); };
+    if (b.nmodes_min == 3 && b.nmodes_max == 3) return go(launch_segb_k<NT, 3, 3, VEC, FAR>);
+    return b.nmodes_max <= 4 ? go(launch_segb_k<NT, 4, 0, VEC, FAR>) : go(launch_segb_k<NT, 8, 0, VEC, FAR>);
 }
 
 template <int NT>
-spt_status launch_segb_t(const SegItem *items, int count, int64_t total_tiles, const BatchShape &b, float *rec_val,
+spt_status launch_segb_n(const SegItem *items, int count, int64_t total_tiles, const BatchShape &b, float *rec_val,
                          unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
-    auto go = [&](auto launch) {
-        return launch(items, count, total_tiles, b.ld, b.vec4, rec_val, next_tile, out, out_floats, s);
-    };
-    if (b.far) return b.nmodes_max <= 4 ? go(launch_segb_n<NT, 4, 0, true>) : go(launch_segb_n<NT, 8, 0, true>);
-    if (b.nmodes_min == 3 && b.nmodes_max == 3) return go(launch_segb_n<NT, 3, 3>);
-    return b.nmodes_max <= 4 ? go(launch_segb_n<NT, 4, 0>) : go(launch_segb_n<NT, 8, 0>);
+    auto go = [&](auto launch) { return launch(items, count, total_tiles, b, rec_val, next_tile, out, out_floats, s); };
+    if (!b.vec4) return b.far == kNear ? go(launch_segb_t<NT, 1, kNear>) : go(launch_segb_t<NT, 1, kFarAll>);
+    if (b.far == kNear) return go(launch_segb_t<NT, 4, kNear>);
+    return b.far == kFarRecords ? go(launch_segb_t<NT, 4, kFarRecords>) : go(launch_segb_t<NT, 4, kFarAll>);
 }
 
 }  // namespace
@@ -1099,7 +1110,7 @@ spt_status launch_mttkrp_seg_batched(const SegItem *items, int count, int64_t to
     if (!seg_batch_fits(b.nmodes_max, b.tile)) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: tile does not fit LDS");
     if (!next_tile) return fail(SPT_E_INVALID_ARG, "batched MTTKRP: no tile counter");
     auto go = [&](auto launch) { return launch(items, count, total_tiles, b, rec_val, next_tile, out, out_floats, s); };
-    return b.tile == 1024 ? go(launch_segb_t<256>) : b.tile == 2048 ? go(launch_segb_t<512>) : go(launch_segb_t<1024>);
+    return b.tile == 1024 ? go(launch_segb_n<256>) : b.tile == 2048 ? go(launch_segb_n<512>) : go(launch_segb_n<1024>);
 }
 
 }  // namespace spt

@@ -215,7 +215,9 @@ spt_status launch_plan_records(const uint32_t *idx, uint32_t *rec, int64_t n, hi
 // took 262 us against 247 with a fill of its own, at 5 MB 112 against 76.
 inline bool zero_on_the_way(int64_t n, int64_t wgs) { return n <= wgs * (64 * 1024 / 4); }
 constexpr uint64_t kBufferBytes = uint64_t(1) << 32;
-bool seg_far(const MttkrpArgs &a, int ld, size_t item);
+// which of a call's arrays pass kBufferBytes: none, the records, or a factor that it reads
+enum SegFar { kNear = 0, kFarRecords = 1, kFarAll = 2 };
+SegFar seg_far(const MttkrpArgs &a, int ld, size_t item);
 // the SEGMENT kernel on a's plan: records to a.rec_val, a.out (if any) zeroed
 spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s);
 // mttkrp_f64.hip
@@ -262,7 +264,7 @@ struct BatchShape {
     int nmodes_min, nmodes_max, tile;
     int ld;     // columns of M and of the records: the largest rank
     bool vec4;  // every member's rank is at least 4
-    bool far;   // seg_far of any member
+    SegFar far; // the farthest member's
 };
 // next_tile: a device counter (8 bytes) the launch zeroes and the workgroups pull tiles from;
 // out: out_floats that the launch also zeroes
@@ -334,7 +336,8 @@ struct Member {
 
 struct ModeItems {
     int count = 0, ld = 0, rmax = 0;
-    bool vec4 = true, far = false;
+    bool vec4 = true;
+    SegFar far = kNear;
     int64_t tiles = 0, records = 0, rows = 0, blocks = 0;
     int64_t row_at = 0;  // first of the mode's record rows in the engine's array
     size_t seg_off = 0, gm_off = 0, sv_off = 0, ap_off = 0;
