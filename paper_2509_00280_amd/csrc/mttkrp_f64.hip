@@ -34,7 +34,7 @@ struct FactorsF64 {
     const double *f[kMaxModes];
 };
 
-template <int NT, int VEC, int NMAX, int NFIX, SegFar FAR>
+template <int NT, int VEC, int NMAX, int NFIX, int FAR>
 __global__ __launch_bounds__(NT) void k_mttkrp_seg_f64(MttkrpArgs a, const double *__restrict__ vals64, int64_t ntiles,
                                                        FactorsF64 F, double *__restrict__ rec_val,
                                                        double *__restrict__ out) {
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void k_gather_f64(const double *__restrict__ s
         dst[i] = src[idx[i]];
 }
 
-template <int NT, int VEC, int NMAX, int NFIX, SegFar FAR>
+template <int NT, int VEC, int NMAX, int NFIX, int FAR>
 spt_status launch_f64_k(const MttkrpArgs &a, const double *vals64, const FactorsF64 &F, int64_t ntiles, double *rec_val,
                         double *out, hipStream_t s) {
     hipLaunchKernelGGL((k_mttkrp_seg_f64<NT, VEC, NMAX, NFIX, FAR>), dim3((unsigned)ntiles), dim3(NT),
@@ -165,7 +165,7 @@ spt_status launch_f64_k(const MttkrpArgs &a, const double *vals64, const Factors
     return SPT_OK;
 }
 
-template <int NT, int VEC, SegFar FAR>
+template <int NT, int VEC, int FAR>
 spt_status launch_f64_n(const MttkrpArgs &a, const double *vals64, const FactorsF64 &F, int64_t ntiles, double *rec_val,
                         double *out, hipStream_t s) {
     auto go = [&](auto launch) { return launch(a, vals64, F, ntiles, rec_val, out, s); };

@@ -168,7 +168,7 @@ struct ZeroSlice {
 // make the compiler wait for one mode's rows before the next mode's gathers
 // are issued).
 __host__ __device__ constexpr int segp_step(int nmax) { return nmax <= 4 ? 2 : 1; }  // nonzeros of a step
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, SegFar FAR>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, int FAR>
 __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const LaneGroup &lg, const WalkShare &ws,
                                           int cnt, int64_t k0, int nruns, float *__restrict__ rec_val, int ld) {
     constexpr int NO = NMAX - 1;  // non-output modes at most
@@ -247,7 +247,7 @@ __device__ __forceinline__ void segp_walk(const MttkrpArgs &a, char *lds, const 
 // A tile is staged by one scatter of values and non-output coordinates to
 // their positions; there is no hashing and no scan over nonzeros at run time.
 // Records of ld floats go to rec_val.
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, SegFar FAR>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, int FAR>
 __device__ __forceinline__ void segp_tile(const MttkrpArgs &a, int64_t tile, char *lds,
                                           float *__restrict__ rec_val, int ld, const ZeroSlice &zero) {
     constexpr int PER = T / NT;  // nonzeros staged per thread
@@ -328,7 +328,7 @@ __device__ __forceinline__ ZeroSlice out_slice(const MttkrpArgs &a, int64_t tile
     return ZeroSlice{a.out, (int64_t)a.frows[a.mode] * a.rank, tile, ntiles};
 }
 
-template <int NT, int T, int VEC, int NMAX, int NFIX, SegFar FAR>
+template <int NT, int T, int VEC, int NMAX, int NFIX, int FAR>
 __global__ __launch_bounds__(NT, NMAX <= 5 && FAR != kFarAll ? 8 : 4) void k_mttkrp_segp(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
@@ -450,7 +450,7 @@ __host__ __device__ inline size_t segd_lds_bytes(int T, int nmodes, int cap, int
 // tile dictionary are copied to LDS; a nonzero whose index is below cap
 // reads its factor row there, any other reads it from HBM/L2 by its global
 // row.
-template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, SegFar FAR>
+template <int NT, int T, int VEC, int NMAX, int NFIX, bool TIGHT, int FAR>
 __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int64_t ntiles, char *lds) {
     constexpr int PER = T / NT;
     constexpr int NO = NMAX - 1;
@@ -647,7 +647,7 @@ __device__ __forceinline__ void segd_tile(const MttkrpArgs &a, int64_t tile, int
 // Bounded to 64 VGPRs, which leaves two workgroups of 16 waves to a CU: left to
 // itself the compiler takes 72 to 82 and one workgroup; the few spills lie
 // outside the steps.
-template <int NT, int T, int VEC, int NMAX, int NFIX, SegFar FAR>
+template <int NT, int T, int VEC, int NMAX, int NFIX, int FAR>
 __global__ __launch_bounds__(NT, FAR == kFarAll ? 4 : 8) void k_mttkrp_segd(MttkrpArgs a, int64_t ntiles) {
     extern __shared__ __align__(16) char lds[];
     const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
@@ -681,7 +681,7 @@ __device__ __forceinline__ int seg_item_of(const SegItem *__restrict__ items, in
 // workgroups, the spills cost more than the waves bring (32 members of 10k to
 // 5M nonzeros, ranks 16 and 32, 10 iterations: 40.5, 40.9 and 36.3 ms, here
 // 31.7, and 33.0 with one walk for all mode counts at 72).
-template <int NT, int VEC, int NMAX, int NFIX, SegFar FAR>
+template <int NT, int VEC, int NMAX, int NFIX, int FAR>
 __global__ __launch_bounds__(NT, 4) void k_mttkrp_segp_batched(const SegItem *__restrict__ items, int count,
                                                             int64_t total_tiles, float *__restrict__ rec_val, int ld,
                                                             unsigned long long *__restrict__ next_tile,
@@ -882,7 +882,7 @@ __global__ __launch_bounds__(NT) void k_count_pieces_batched(const SegItem *__re
     count_tile<NT>(items[b].a, it - items[b].first_tile, lds, wsum, out + it);
 }
 
-template <int NT, int T, int NMAX, int NFIX, int VEC, SegFar FAR>
+template <int NT, int T, int NMAX, int NFIX, int VEC, int FAR>
 spt_status launch_seg_k(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
     if constexpr (T == kDictTile && NMAX <= 4) {
         if (a.d_cap > 0) {
@@ -960,7 +960,7 @@ spt_status launch_count_pieces(const MttkrpArgs &a, int64_t *counts, hipStream_t
 namespace {
 // 3, 4 and 5 modes get a kernel with the mode count fixed; others, and factors
 // past the reach of a structured buffer, a general one
-template <int NT, int T, int VEC, SegFar FAR>
+template <int NT, int T, int VEC, int FAR>
 spt_status launch_seg_nm(const MttkrpArgs &a, int64_t ntiles, hipStream_t s) {
     const int nm = a.nmodes;
     if (nm == 3) return launch_seg_k<NT, T, 3, 3, VEC, FAR>(a, ntiles, s);
@@ -1013,7 +1013,7 @@ spt_status launch_mttkrp_seg(const MttkrpArgs &a, hipStream_t s) {
 }
 
 namespace {
-template <int NT, int NMAX, int NFIX, int VEC, SegFar FAR>
+template <int NT, int NMAX, int NFIX, int VEC, int FAR>
 spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, float *rec_val,
                          int ld, unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
     const size_t lds = std::max(segp_lds_bytes(4 * NT, NMAX), walk_lds_bytes(NT));
@@ -1038,7 +1038,7 @@ spt_status launch_segb_k(const SegItem *items, int count, int64_t total_tiles, f
     return SPT_OK;
 }
 
-template <int NT, int VEC, SegFar FAR>
+template <int NT, int VEC, int FAR>
 spt_status launch_segb_t(const SegItem *items, int count, int64_t total_tiles, const BatchShape &b, float *rec_val,
                          unsigned long long *next_tile, float *out, int64_t out_floats, hipStream_t s) {
     auto go = [&](auto launch) { return launch(items, count, total_tiles, rec_val, b.ld, next_tile, out, out_floats, s); };

@@ -116,7 +116,7 @@ __device__ __forceinline__ void load_words(const Word *p, Word (&x)[UB]) {
 // rec[k] is the record of the tile's run k; records have ld columns (R..ld-1
 // are zeroed).  Reads stay inside the tile and no record at or beyond rec_cap
 // is written, whatever the plan holds.
-template <class Real, int NT, int T, int VEC, int UB, bool TIGHT, SegFar FAR, class Product>
+template <class Real, int NT, int T, int VEC, int UB, bool TIGHT, int FAR, class Product>
 __device__ __forceinline__ void run_walk(const LaneGroup &lg, const WalkShare &ws, int R, int cnt, int nruns,
                                          const uint32_t *__restrict__ rec, uint32_t rec_cap,
                                          Real *__restrict__ rec_val, int ld, char *lds, const Product &product) {
